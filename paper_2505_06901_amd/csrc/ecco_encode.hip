@@ -1,0 +1,367 @@
+// Encoders of the two-chain block format for gfx950: bulk (ecco_encode, ecco_encode_minmax) and appended tokens
+// (ecco_kv_append, ecco_kv_append_minmax).
+//
+// What bounds them.  Rating all S patterns value by value is 24 vector instructions per value and pattern for 16
+// candidates: 48 wavefront instructions per group and pattern, 4 ns per group on the whole chip at S = 64, where reading
+// the group and writing its block takes 0.06 ns.  The search is therefore done in two steps (ecco_search.h): bounds on
+// every pattern's error from a matrix product of the group's histogram with tables of the model, 16 groups x 16 patterns at
+// a time on the matrix cores, and the exact FP32 error only for the patterns whose bounds overlap the best (1.3 to 2 of 64 on
+// weights, keys and values).  The chosen pattern, the indices and the block are those of the plain search, bit for bit.
+// A workgroup of four wavefronts takes 16 groups at a time, one group per row of 16 lanes (ecco_rows.h).
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "ecco_launch.h"
+#include "ecco_rows.h"
+
+using namespace ecco;
+using namespace ecco_rows;
+
+namespace {
+
+constexpr int kHalf = kGroup / 2;
+
+// where a kernel finds group i and where its block goes
+struct BulkIo {
+    const uint32_t* src;
+    uint32_t* blocks;
+    uint32_t* meta;
+    size_t n;
+    __device__ __forceinline__ size_t groups() const { return n; }
+    __device__ __forceinline__ const uint32_t* values() const { return src; }
+    __device__ __forceinline__ bool place(size_t i, size_t& at) const {
+        at = i;
+        return i < n;
+    }
+};
+// one new token per sequence and head: group (b, h) goes to the slot seq_len[b] of its cache, if there is one
+struct AppendIo {
+    const uint32_t* src;
+    uint32_t* blocks;
+    uint32_t* meta;
+    const int32_t* seq_len;
+    int n, heads, t_max;
+    __device__ __forceinline__ size_t groups() const { return (size_t)n; }
+    __device__ __forceinline__ const uint32_t* values() const { return src; }
+    __device__ __forceinline__ bool place(size_t i, size_t& at) const {
+        if (i >= (size_t)n) return false;
+        const int t = seq_len[(uint32_t)i / (uint32_t)heads];
+        at = i * t_max + t;
+        return t >= 0 && t < t_max;
+    }
+};
+template <class Io>
+struct Job {  // one model and the groups it encodes; blockIdx.y picks one of two (keys and values)
+    const uint32_t* dev;
+    int S;
+    Io io;
+};
+
+// tables of a model in LDS, in words: near [S][64], pair [S][16], codes [S][16] as code << 8 | length: the word serves as a
+// shift count as it is (its low five bits), and the lengths of up to 16 words can be summed with the codes still on top
+struct EncTables {
+    const uint8_t* near;
+    uint32_t pair;         // LDS address, a multiple of 64
+    const uint32_t* enc;
+};
+constexpr int kTableWords = kSearchBins / 4 + 16 + kK;  // per pattern
+__device__ __forceinline__ EncTables stage_enc_tables(uint32_t* lds, const uint32_t* __restrict__ dev, int S) {
+    const DevLayout D{S};
+    const uint4* a = reinterpret_cast<const uint4*>(dev + D.near());  // near and pair follow each other
+    uint4* d = reinterpret_cast<uint4*>(lds);
+    const int n0 = S * (kSearchBins / 4 + 16) / 4, n1 = S * kK / 4;
+    for (int i = threadIdx.x; i < n0; i += kEncThreads) d[i] = a[i];
+    const uint4* e = reinterpret_cast<const uint4*>(dev + D.enc());
+    const auto code = [](uint32_t w) { return ((w & 0xFFFFu) << 8) | (w >> 16); };
+    for (int i = threadIdx.x; i < n1; i += kEncThreads) {
+        const uint4 w = e[i];
+        d[n0 + i] = make_uint4(code(w.x), code(w.y), code(w.z), code(w.w));
+    }
+    EncTables t;
+    t.near = reinterpret_cast<const uint8_t*>(lds);
+    t.pair = lds_address(lds + S * (kSearchBins / 4));
+    t.enc = lds + S * (kSearchBins / 4 + 16);
+    return t;
+}
+
+// the values of group `local` of batch b (the last group's beyond the end)
+__device__ __forceinline__ void load_values(RowValues& v, const uint32_t* src, size_t groups, size_t b, int local, int l) {
+    const size_t first = min(b * kBatch, groups - 1);  // uniform
+    const int last = (int)min(groups - 1 - first, (size_t)(kBatch - 1));
+    const u32x4_dword t = *reinterpret_cast<const u32x4_dword*>(src + first * (kGroup / 2) + (min(local, last) * kRowLanes + l) * 4);
+    v.x[0] = t.x; v.x[1] = t.y; v.x[2] = t.z; v.x[3] = t.w;
+}
+
+// Packs the row's group with the codes `enc` of its pattern: lane l returns payload word l and the meta word.  idx: the
+// lane's eight indices as nibbles, which is also the lane's payload word in raw mode.  image: 18 words of LDS of the row.
+template <bool kLong>
+__device__ __forceinline__ uint32_t pack_row(const uint32_t* enc, uint32_t* image, uint32_t idx, int l, uint32_t smax, uint32_t pattern, uint32_t& meta) {
+    image[l] = 0u;
+    if (l < 2) image[kRowLanes + l] = 0u;
+    uint32_t e[kRowValues];
+#pragma unroll
+    for (int i = 0; i < kRowValues; ++i) e[i] = enc[(idx >> (28 - 4 * i)) & 15u];
+    constexpr int kRun = kLong ? 2 : 4;  // values whose codes always fit 32 bits together
+    constexpr int kRuns = kRowValues / kRun;
+    uint32_t bits[kRuns], n[kRuns], lane_bits = 0;
+#pragma unroll
+    for (int r = 0; r < kRuns; ++r) {
+        bits[r] = e[r * kRun] >> 8;
+        n[r] = e[r * kRun];
+#pragma unroll
+        for (int i = 1; i < kRun; ++i) {
+            bits[r] = (bits[r] << (e[r * kRun + i] & 31u)) | (e[r * kRun + i] >> 8);
+            n[r] += e[r * kRun + i];
+        }
+        n[r] &= 0xFFu;
+        lane_bits += n[r];
+    }
+    const uint32_t end = row_scan(lane_bits);
+    const uint32_t total = row_lane<15>(end), mid = row_lane<7>(end);  // bits of all values, of values 0..63
+    const bool raw = total > 8u * ECCO_BLOCK_BYTES;
+    wave_fence();
+    if (!raw) {
+        uint32_t at = end - lane_bits;
+#pragma unroll
+        for (int r = 0; r < kRuns; ++r) {
+            const uint64_t v = (uint64_t)bits[r] << (64u - n[r] - (at & 31u));  // left-aligned at stream bit `at`
+            atomicOr(&image[at >> 5], (uint32_t)(v >> 32));
+            if ((uint32_t)v != 0u) atomicOr(&image[(at >> 5) + 1], (uint32_t)v);
+            at += n[r];
+        }
+    }
+    wave_fence();
+    meta = smax | (pattern << 16) | (raw ? 1u << 22 : 0u) | ((raw ? 4u * kHalf : mid) << 23);
+    const uint32_t word = raw ? idx : image[l];
+    wave_fence();
+    return word;
+}
+
+// ---- the full search ---------------------------------------------------------------------------------------------------
+constexpr size_t search_lds_bytes(int S) { return ((size_t)S * kTableWords + search_lds_words(search_tiles(S))) * 4; }
+
+template <int kTiles, bool kLong, class Io>
+__global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2))) void encode_search_kernel(Job<Io> j0, Job<Io> j1) {
+    extern __shared__ __align__(16) uint32_t smem[];
+    const Job<Io>& job = blockIdx.y ? j1 : j0;
+    const int S = job.S, tiles = search_tiles(S);
+    const Io io = job.io;
+    const int lane = threadIdx.x & 63, l = lane & 15, row = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const SearchLds L = search_lds(smem + S * kTableWords, kTiles);
+    uint32_t* hist = L.hist + (wave * kWaveRows + row) * kHistStride;
+    const size_t batches = (io.groups() + kBatch - 1) / kBatch;
+    RowValues v, next;
+    load_values(v, io.values(), io.groups(), blockIdx.x, wave * kWaveRows + row, l);
+    Coefs<kTiles> C;
+    C.load(job.dev + DevLayout{S}.coef(), wave, tiles, lane);
+    const EncTables T = stage_enc_tables(smem, job.dev, S);
+    for (size_t b = blockIdx.x; b < batches; b += gridDim.x) {
+        const size_t g = b * kBatch + wave * kWaveRows + row;
+        load_values(next, io.values(), io.groups(), b + gridDim.x, wave * kWaveRows + row, l);
+        const uint32_t smax = row_max(lane_absmax(v));
+        const float s = half_bits_f(smax);
+        const half2_t s2 = splat_half(smax);
+        clear_hist(L.hist + wave * kWaveRows * kHistStride, lane);
+        wave_fence();
+        set_bins<true>(v, kSearchStep * __builtin_amdgcn_rcpf(s), hist, -1);
+        wave_fence();
+        convert_hist(L.hist + wave * kWaveRows * kHistStride, lane);
+        uint64_t left = patterns_left<kTiles>(L, C, tiles, wave, lane);
+        const bool plain = !(s >= kSearchLeastScale);  // all patterns, value by value
+        if (plain) left = S == 64 ? ~0ull : (1ull << S) - 1ull;
+        uint32_t pattern = 0, idx = 0;
+        float best = 0.0f;
+        bool first = true;
+        do {  // the patterns left, ascending; a row that has none left repeats its last one
+            const bool more = left != 0ull;
+            const uint32_t p = more ? (uint32_t)__builtin_ctzll(left) : pattern;
+            left &= left - 1ull;
+            float sse;
+            uint32_t id;
+            rate_pattern<kK, true>(T.near + p * kSearchBins, T.pair + p * 64u, s2, v, plain, -1, sse, id);
+            if (first || (more && sse < best)) {  // strict <: the lowest pattern wins a tie
+                best = sse;
+                pattern = p;
+                idx = id;
+            }
+            first = false;
+        } while (__builtin_amdgcn_ballot_w64(left != 0ull) != 0ull);
+        uint32_t mw;
+        const uint32_t word = pack_row<kLong>(T.enc + pattern * kK, hist, idx, l, smax, pattern, mw);
+        size_t at;
+        if (io.place(g, at)) {
+            io.blocks[at * kBlockWords + l] = word;
+            if (l == 0) io.meta[at] = mw;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v.x[i] = next.x[i];
+    }
+}
+
+// ---- the min/max selector ------------------------------------------------------------------------------------------------
+// Pattern selector of the online compressor (Section 3.2 "KV Cache Compression", pattern selector of Section 4.3): only the
+// group's least and greatest value are compared with each pattern's ends, taken in the group's scale as fp16(centroid * s):
+// fitness = (min - first)^2 + (max - last)^2, every operation rounded to FP32 on its own.  The lanes of a row rate the
+// patterns l, l + 16, ...; the least fitness wins, the lowest pattern on a tie (pattern 0 if the input held a NaN, against
+// the contract).
+// (the wait states belong to the cross-lane moves that may follow: the compiler does not see into the instruction)
+__device__ __forceinline__ half2_t pk_min(half2_t a, half2_t b) {
+    half2_t r;
+    asm("v_pk_min_f16 %0, %1, %2\n\ts_nop 1" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ half2_t pk_max(half2_t a, half2_t b) {
+    half2_t r;
+    asm("v_pk_max_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ uint32_t select_minmax(const uint32_t* ends, int S, half2_t s2, const RowValues& v, int l) {
+    // (least value, least negated value) of the row
+    half2_t lo2 = as_half2(v.x[0]), hi2 = lo2;
+#pragma unroll
+    for (int i = 1; i < 4; ++i) {
+        lo2 = pk_min(lo2, as_half2(v.x[i]));
+        hi2 = pk_max(hi2, as_half2(v.x[i]));
+    }
+    half2_t ends2 = pk_min(as_half2(__builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, -hi2), __builtin_bit_cast(uint32_t, lo2), 0x05040100u)),
+                           as_half2(__builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, -hi2), __builtin_bit_cast(uint32_t, lo2), 0x07060302u)));
+    ends2 = row_all(ends2, [](half2_t a, half2_t b) { return pk_min(a, b); });
+    const float lo = (float)ends2[0], hi = -(float)ends2[1];
+    float least = __builtin_inff();
+    uint32_t at = 0xFFFFu;
+    for (int p = l; p < S; p += kRowLanes) {
+        const half2_t e = as_half2(ends[p]) * s2;
+        const float dlo = __fsub_rn(lo, (float)e[0]), dhi = __fsub_rn(hi, (float)e[1]);
+        const float f = __fadd_rn(__fmul_rn(dlo, dlo), __fmul_rn(dhi, dhi));
+        if (f < least) {
+            least = f;
+            at = (uint32_t)p;
+        }
+    }
+    const float all = row_min_pos(least);
+    const uint32_t p = row_min(least == all ? at : 0xFFFFu);
+    return p < (uint32_t)S ? p : 0u;
+}
+
+constexpr int kImageStride = 20;  // words per group of the payload being assembled
+constexpr size_t minmax_lds_bytes(int S) { return ((size_t)S * (kTableWords + 1) + kBatch * kImageStride + 3) * 4; }
+
+template <bool kLong, class Io>
+__global__ __launch_bounds__(kEncThreads) void encode_minmax_kernel(Job<Io> j0, Job<Io> j1) {
+    extern __shared__ __align__(16) uint32_t smem[];
+    const Job<Io>& job = blockIdx.y ? j1 : j0;
+    const int S = job.S;
+    const Io io = job.io;
+    const int lane = threadIdx.x & 63, l = lane & 15, row = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint32_t* ends = smem + S * kTableWords;
+    uint32_t* image = ends + S + (wave * kWaveRows + row) * kImageStride;
+    const size_t batches = (io.groups() + kBatch - 1) / kBatch;
+    RowValues v, next;
+    load_values(v, io.values(), io.groups(), blockIdx.x, wave * kWaveRows + row, l);
+    const EncTables T = stage_enc_tables(smem, job.dev, S);
+    if ((int)threadIdx.x < S) {
+        const uint32_t* pair = job.dev + DevLayout{S}.pair() + threadIdx.x * 16;
+        ends[threadIdx.x] = __builtin_amdgcn_perm(pair[kK - 1], pair[0], 0x05040100u);  // first and last centroid
+    }
+    __syncthreads();
+    for (size_t b = blockIdx.x; b < batches; b += gridDim.x) {
+        const size_t g = b * kBatch + wave * kWaveRows + row;
+        load_values(next, io.values(), io.groups(), b + gridDim.x, wave * kWaveRows + row, l);
+        const uint32_t smax = row_max(lane_absmax(v));
+        const float s = half_bits_f(smax);
+        const half2_t s2 = splat_half(smax);
+        const uint32_t pattern = select_minmax(ends, S, s2, v, l);
+        set_bins<false>(v, kSearchStep * __builtin_amdgcn_rcpf(s), nullptr, -1);
+        float sse;
+        uint32_t idx;
+        rate_pattern<kK, false>(T.near + pattern * kSearchBins, T.pair + pattern * 64u, s2, v, !(s >= kSearchLeastScale), -1, sse, idx);
+        uint32_t mw;
+        const uint32_t word = pack_row<kLong>(T.enc + pattern * kK, image, idx, l, smax, pattern, mw);
+        size_t at;
+        if (io.place(g, at)) {
+            io.blocks[at * kBlockWords + l] = word;
+            if (l == 0) io.meta[at] = mw;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v.x[i] = next.x[i];
+    }
+}
+
+// ---- host side -----------------------------------------------------------------------------------------------------------
+template <class Io>
+int launch_encode(bool minmax, const ecco_model* m0, const Io& io0, const ecco_model* m1, const Io& io1, size_t groups, int jobs, void* stream) {
+    const Job<Io> j0{m0->dev, m0->S, io0}, j1{m1->dev, m1->S, io1};
+    const int S = std::max(m0->S, m1->S);
+    const bool lng = std::max(m0->max_len, m1->max_len) > 8;
+    const size_t wgs = (groups + kBatch - 1) / kBatch;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const auto run = [&](auto kernel, size_t lds, int per_cu) {
+        const dim3 grid((unsigned)std::min<size_t>(wgs, (size_t)cu_count(m0->device) * per_cu), jobs);
+        hipLaunchKernelGGL(kernel, grid, dim3(kEncThreads), lds, st, j0, j1);
+    };
+    if (minmax) {
+        const size_t lds = minmax_lds_bytes(S);
+        if (lng) run(encode_minmax_kernel<true, Io>, lds, 4);
+        else run(encode_minmax_kernel<false, Io>, lds, 4);
+    } else {
+        const size_t lds = search_lds_bytes(S);
+        switch (search_tiles(S)) {
+            case 1: lng ? run(encode_search_kernel<1, true, Io>, lds, 2) : run(encode_search_kernel<1, false, Io>, lds, 2); break;
+            case 2: lng ? run(encode_search_kernel<2, true, Io>, lds, 2) : run(encode_search_kernel<2, false, Io>, lds, 2); break;
+            default: lng ? run(encode_search_kernel<4, true, Io>, lds, 2) : run(encode_search_kernel<4, false, Io>, lds, 2);
+        }
+    }
+    ECCO_HIP_CHECK(hipGetLastError());
+    return ECCO_OK;
+}
+
+int encode_common(bool minmax, const ecco_model* m, const uint16_t* src, size_t n_groups, void* blocks, uint32_t* meta, void* stream) {
+    if (!m) return ECCO_EINVAL;
+    if (n_groups == 0) return model_ready(m);  // nothing to do; pointers may be null
+    if (!src || !blocks || !meta) return ECCO_EINVAL;
+    if (!aligned(blocks, 64) || !aligned(src, 4) || !aligned(meta, 4)) return ECCO_EALIGN;
+    if (model_ready(m) != ECCO_OK) return ECCO_EINVAL;
+    const BulkIo io{reinterpret_cast<const uint32_t*>(src), static_cast<uint32_t*>(blocks), meta, n_groups};
+    return launch_encode(minmax, m, io, m, io, n_groups, 1, stream);
+}
+
+int kv_append_common(bool minmax, const ecco_model* mk, const ecco_model* mv, const uint16_t* k_new, const uint16_t* v_new,
+                     void* k_blocks, uint32_t* k_meta, void* v_blocks, uint32_t* v_meta,
+                     const int32_t* seq_len, int B, int H, int T_max, void* stream) {
+    if (!mk || !mv || !k_new || !v_new || !k_blocks || !k_meta || !v_blocks || !v_meta || !seq_len) return ECCO_EINVAL;
+    if (B <= 0 || H <= 0 || T_max <= 0 || (long long)B * H > 0x7FFFFFFF) return ECCO_ESHAPE;
+    if (!aligned(k_blocks, 64) || !aligned(v_blocks, 64) || !aligned(k_new, 4) || !aligned(v_new, 4)) return ECCO_EALIGN;
+    if (model_ready(mk) != ECCO_OK || model_ready(mv) != ECCO_OK || mk->device != mv->device) return ECCO_EINVAL;
+    const AppendIo k{reinterpret_cast<const uint32_t*>(k_new), static_cast<uint32_t*>(k_blocks), k_meta, seq_len, B * H, H, T_max};
+    const AppendIo v{reinterpret_cast<const uint32_t*>(v_new), static_cast<uint32_t*>(v_blocks), v_meta, seq_len, B * H, H, T_max};
+    return launch_encode(minmax, mk, k, mv, v, (size_t)B * H, 2, stream);
+}
+
+}  // namespace
+
+extern "C" {
+
+int ecco_encode(const ecco_model* m, const uint16_t* src, size_t n_groups, void* blocks, uint32_t* meta, void* stream) {
+    return encode_common(false, m, src, n_groups, blocks, meta, stream);
+}
+
+int ecco_encode_minmax(const ecco_model* m, const uint16_t* src, size_t n_groups, void* blocks, uint32_t* meta, void* stream) {
+    return encode_common(true, m, src, n_groups, blocks, meta, stream);
+}
+
+int ecco_kv_append(const ecco_model* mk, const ecco_model* mv, const uint16_t* k_new, const uint16_t* v_new,
+                   void* k_blocks, uint32_t* k_meta, void* v_blocks, uint32_t* v_meta,
+                   const int32_t* seq_len, int B, int H, int T_max, void* stream) {
+    return kv_append_common(false, mk, mv, k_new, v_new, k_blocks, k_meta, v_blocks, v_meta, seq_len, B, H, T_max, stream);
+}
+
+int ecco_kv_append_minmax(const ecco_model* mk, const ecco_model* mv, const uint16_t* k_new, const uint16_t* v_new,
+                          void* k_blocks, uint32_t* k_meta, void* v_blocks, uint32_t* v_meta,
+                          const int32_t* seq_len, int B, int H, int T_max, void* stream) {
+    return kv_append_common(true, mk, mv, k_new, v_new, k_blocks, k_meta, v_blocks, v_meta, seq_len, B, H, T_max, stream);
+}
+
+}  // extern "C"

@@ -5,6 +5,7 @@
 #include <cstdint>
 
 #include "ecco.h"
+#include "ecco_search.h"
 
 namespace ecco {
 
@@ -25,7 +26,8 @@ constexpr int kPeekBits = 8;
 constexpr int kPeekEntries = 1 << kPeekBits;
 
 // Device memory of a model, one allocation, in 32-bit words:
-//   compact tables  [enc S x 16][centroids S x 8][longtab S x 16]   (a few KB; kernels expand them in LDS)
+//   decode and codes [enc S x 16][centroids S x 8][longtab S x 16]   (a few KB; the decoders expand them in LDS)
+//   encoder search   [near][pair][coef]                              (ecco_search.h; 118 KB for S = 64)
 // The decode table itself (S x 256 entries) is never stored in global memory: every workgroup
 // builds it in LDS from `enc` and the centroids, which costs less than fetching 64 KB per workgroup.
 struct DevLayout {
@@ -34,9 +36,14 @@ struct DevLayout {
     constexpr size_t cent() const { return (size_t)S * kK; }
     constexpr size_t longtab() const { return cent() + (size_t)S * kK / 2; }
     constexpr size_t table_words() const { return longtab() + (size_t)S * kK; }
-    constexpr size_t image_words() const { return table_words(); }
+    constexpr size_t near() const { return table_words(); }
+    constexpr size_t pair() const { return near() + search_near_words(S); }
+    constexpr size_t coef() const { return pair() + search_pair_words(S); }
+    constexpr size_t image_words() const { return coef() + search_coef_words(S); }
     constexpr size_t total_bytes() const { return image_words() * 4; }
 };
+
+constexpr float kSearchStep = 32700.0f;  // axis units of the encoder search per u = 1: |x| <= scale here (ecco_search.h)
 
 // longtab entry j (canonical position j): bits 11:0 the code left-aligned in 12 bits,
 // bits 15:12 the index, bits 20:16 the code length.

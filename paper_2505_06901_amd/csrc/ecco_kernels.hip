@@ -22,7 +22,7 @@
 #include <utility>
 #include <vector>
 
-#include "ecco_internal.h"
+#include "ecco_launch.h"
 
 using namespace ecco;
 
@@ -33,8 +33,6 @@ constexpr int kHalf = kGroup / 2;         // values per chain
 
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
-
-#define ECCO_HIP_CHECK(expr) do { if ((expr) != hipSuccess) return ECCO_EHIP; } while (0)
 
 __device__ __forceinline__ float half_bits_f(uint32_t bits) { return __half2float(__ushort_as_half((unsigned short)bits)); }
 // dequantisation: one exact FP32 product, one rounding to FP16
@@ -713,305 +711,6 @@ __global__ __launch_bounds__(kGemvThreads) void gemm_kernel(const uint32_t* __re
     }
 }
 
-// ---- encoder ---------------------------------------------------------------------------------------
-// One wavefront per group; lane l holds values 2l and 2l+1.
-constexpr int kEncThreads = 256;
-constexpr int kEncWaves = kEncThreads / 64;
-
-
-struct EncLds {
-    const __half* cent;     // [S][16]
-    const uint32_t* enc;    // [S][16]
-    float* recon;           // per wave [S][16]
-    uint32_t* bits;         // per wave 16 words
-};
-
-// The group's scale: the largest magnitude among the 128 values (two per lane), as an FP16 bit pattern.
-__device__ inline uint32_t group_scale_bits(uint32_t hx0, uint32_t hx1) {
-    return wave_all(max(hx0 & 0x7FFFu, hx1 & 0x7FFFu), [](uint32_t a, uint32_t b) { return max(a, b); });
-}
-
-// Sixteen sums over the 64 lanes at once, each in the balanced tree (lanes l and l ^ 1, then ^ 2, ^ 4, ... ^ 32):
-// at every one of the first four levels a lane keeps the half of its entries that matches its own lane bit and
-// sends the other half to its partner, so the work halves per level instead of being done sixteen times over.
-// Lane l returns the total of entry l & 15.  (Addition is commutative, so own + received is the tree's sum.)
-__device__ __forceinline__ float wave_sum16(const float (&q)[16], int lane) {
-    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4, b3 = lane & 8;
-    float a[8], b[4], c[2];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) a[i] = (b0 ? q[2 * i + 1] : q[2 * i]) + dpp_mov<0xB1>(b0 ? q[2 * i] : q[2 * i + 1]);    // entry 2i + b0
-#pragma unroll
-    for (int i = 0; i < 4; ++i) b[i] = (b1 ? a[2 * i + 1] : a[2 * i]) + dpp_mov<0x4E>(b1 ? a[2 * i] : a[2 * i + 1]);    // entry 4i + (l & 3)
-#pragma unroll
-    for (int i = 0; i < 2; ++i) c[i] = (b2 ? b[2 * i + 1] : b[2 * i]) + __shfl_xor(b2 ? b[2 * i] : b[2 * i + 1], 4);    // entry 8i + (l & 7)
-    float t = (b3 ? c[1] : c[0]) + __shfl_xor(b3 ? c[0] : c[1], 8);                                                    // entry l & 15
-    t += __shfl_xor(t, 16);
-    t += __shfl_xor(t, 32);
-    return t;
-}
-
-struct EncChoice {
-    float sse;         // squared error of the best pattern so far (uniform over the wavefront)
-    int pattern;
-    uint32_t idx;      // this lane's two indices: value 2l in bits 3:0, value 2l+1 in bits 7:4
-};
-
-// Pattern search over patterns [p0, p1) for the group whose two values of this lane are (x0, x1):
-// reconstructed values fp16(centroid * s) of those patterns into E.recon, nearest value per element
-// (strict <: the lowest index wins a tie), squared errors summed by the balanced tree, least sum
-// wins (strict <: the lowest pattern wins a tie).  p0 < p1.
-// Choosing the pattern needs the least distance of every element, not the index that attains it: the squared
-// error of an element is that distance squared, whichever of several equally near values is taken.  So the
-// patterns are rated with a subtraction per candidate and a three-way minimum per two candidates, and the
-// index scan (a subtraction, a compare and a select per candidate) runs once, for the winner.
-__device__ inline EncChoice search_patterns(const EncLds& E, int p0, int p1, float s, float x0, float x1) {
-    const int lane = threadIdx.x & 63;
-    for (int i = p0 * kK + lane; i < p1 * kK; i += 64) E.recon[i] = half_bits_f(dequant_bits(__half_as_ushort(E.cent[i]), s));
-    wave_lds_fence();
-    EncChoice best{0.0f, p0, 0u};
-    if (p1 - p0 > 1) {
-        // Sixteen patterns at a time: q[e] is this lane's part (two elements) of the squared error of pattern pb + e.
-        // The sixteen sums over the wavefront are formed together (wave_sum16): lane l ends up with the total of
-        // pattern pb + (l & 15), keeps the least it has seen over the batches, and the lanes are compared at the end.
-        float mine = __builtin_inff();
-        int mine_p = p0;
-        for (int pb = p0; pb < p1; pb += 16) {
-            float q[16];
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                q[e] = __builtin_inff();
-                if (pb + e < p1) {  // uniform
-                    const float* r = E.recon + (pb + e) * kK;
-                    float d0 = fabsf(__fsub_rn(x0, r[0])), d1 = fabsf(__fsub_rn(x1, r[0]));
-                    static_assert(kK % 2 == 0, "candidates 1 .. kK - 2 in pairs, the last one alone");
-#pragma unroll
-                    for (int k = 1; k + 1 < kK; k += 2) {
-                        const float ra = r[k], rb = r[k + 1];
-                        d0 = fminf(fminf(d0, fabsf(__fsub_rn(x0, ra))), fabsf(__fsub_rn(x0, rb)));
-                        d1 = fminf(fminf(d1, fabsf(__fsub_rn(x1, ra))), fabsf(__fsub_rn(x1, rb)));
-                    }
-                    d0 = fminf(d0, fabsf(__fsub_rn(x0, r[kK - 1])));
-                    d1 = fminf(d1, fabsf(__fsub_rn(x1, r[kK - 1])));
-                    q[e] = __fadd_rn(__fmul_rn(d0, d0), __fmul_rn(d1, d1));  // tree level 0: values 2l and 2l+1
-                }
-            }
-            const float t = wave_sum16(q, lane);
-            const int tp = pb + (lane & 15);
-            if (t < mine) {  // strict <: an earlier batch keeps a tie
-                mine = t;
-                mine_p = tp;
-            }
-        }
-        // least sum over the lanes, and the lowest pattern among the lanes that hold it (a pattern past p1 holds +inf;
-        // if every sum is +inf or the input held a NaN, against the contract, p0 stays)
-        best.sse = wave_all(mine, [](float a, float b) { return fminf(a, b); });
-        const int cand = (mine == best.sse && mine_p < p1) ? mine_p : 0x7FFFFFFF;
-        const int win = wave_all(cand, [](int a, int b) { return min(a, b); });
-        best.pattern = win < p1 ? win : p0;
-    }
-    // The indices of the chosen pattern.  The reconstructed values ascend with k, and FP32 rounding is monotone, so
-    // |x - r[k]| falls (weakly) up to its least value and rises (weakly) after it: the first index of the least
-    // distance -- what a scan with a strict < finds -- is the last k at which the distance strictly drops.
-    const float* r = E.recon + best.pattern * kK;
-    float d0 = fabsf(__fsub_rn(x0, r[0])), d1 = fabsf(__fsub_rn(x1, r[0]));
-    uint32_t k0 = 0, k1 = 0;
-#pragma unroll
-    for (int k = 1; k < kK; ++k) {
-        const float rk = r[k];
-        const float a = fabsf(__fsub_rn(x0, rk)), b = fabsf(__fsub_rn(x1, rk));
-        k0 = a < d0 ? (uint32_t)k : k0;
-        k1 = b < d1 ? (uint32_t)k : k1;
-        d0 = a;
-        d1 = b;
-    }
-    best.idx = k0 | (k1 << 4);
-    if (p1 - p0 == 1) {
-        const float e0 = __fsub_rn(x0, r[k0]), e1 = __fsub_rn(x1, r[k1]);
-        best.sse = wave_sum(__fadd_rn(__fmul_rn(e0, e0), __fmul_rn(e1, e1)));
-    }
-    return best;
-}
-
-// Packs the group with the chosen pattern and indices: lanes 0..15 return one payload word each in
-// *word, every lane the meta word in *meta.
-__device__ inline void pack_group(const EncLds& E, uint32_t smax, int best_p, uint32_t best_idx, uint32_t* word, uint32_t* meta) {
-    const int lane = threadIdx.x & 63;
-    if (lane < kBlockWords) E.bits[lane] = 0;
-    wave_lds_fence();
-    // codes of the chosen pattern, bit positions by an inclusive scan over lanes
-    const uint32_t c0 = E.enc[best_p * kK + (best_idx & 15u)], c1 = E.enc[best_p * kK + (best_idx >> 4)];
-    const uint32_t l0 = c0 >> 16, l1 = c1 >> 16;
-    uint32_t incl = l0 + l1;
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t o = (uint32_t)__shfl_up((int)incl, d);
-        if (lane >= d) incl += o;
-    }
-    const uint32_t total = (uint32_t)__shfl((int)incl, 63);
-    const uint32_t mid = (uint32_t)__shfl((int)incl, 31);  // bits used by values 0..63
-    const bool raw = total > 8u * ECCO_BLOCK_BYTES;
-    if (raw) {
-        // value i in stream bits 4i..4i+3, top bit first: lane l owns the byte at stream bits 8l..8l+7
-        atomicOr(&E.bits[lane >> 2], (((best_idx & 15u) << 4) | (best_idx >> 4)) << (24 - 8 * (lane & 3)));
-    } else {
-        const uint32_t pos = incl - (l0 + l1);
-        const uint32_t both = ((c0 & 0xFFFFu) << l1) | (c1 & 0xFFFFu);       // l0 + l1 <= 24 bits
-        const uint64_t v = (uint64_t)both << (64 - (l0 + l1) - (pos & 31u));  // left-aligned at stream bit pos
-        atomicOr(&E.bits[pos >> 5], (uint32_t)(v >> 32));
-        if ((uint32_t)v != 0u) atomicOr(&E.bits[(pos >> 5) + 1], (uint32_t)v);
-    }
-    wave_lds_fence();
-    *word = lane < kBlockWords ? E.bits[lane] : 0u;
-    *meta = smax | ((uint32_t)best_p << 16) | (raw ? (1u << 22) : 0u) | ((raw ? 4u * kHalf : mid) << 23);
-    wave_lds_fence();
-}
-
-// Pattern selector of the online compressor (Section 3.2 "KV Cache Compression", pattern selector of Section 4.3):
-// only the group's least and greatest value are compared with each pattern's ends, taken in the group's scale as
-// fp16(centroid * s):  fitness = (min - first)^2 + (max - last)^2, every operation rounded to FP32 on its own.
-// Lane p rates pattern p (S <= 64); the least fitness wins, the lowest pattern on a tie.  Uniform result.
-__device__ inline int select_minmax(const EncLds& E, int S, float s, float x0, float x1) {
-    const int lane = threadIdx.x & 63;
-    const float lo = wave_all(fminf(x0, x1), [](float a, float b) { return fminf(a, b); });
-    const float hi = wave_all(fmaxf(x0, x1), [](float a, float b) { return fmaxf(a, b); });
-    float f = __builtin_inff();
-    if (lane < S) {
-        const float first = half_bits_f(dequant_bits(__half_as_ushort(E.cent[lane * kK]), s));
-        const float last = half_bits_f(dequant_bits(__half_as_ushort(E.cent[lane * kK + kK - 1]), s));
-        const float dlo = __fsub_rn(lo, first), dhi = __fsub_rn(hi, last);
-        f = __fadd_rn(__fmul_rn(dlo, dlo), __fmul_rn(dhi, dhi));
-    }
-    const float least = wave_all(f, [](float a, float b) { return fminf(a, b); });
-    // lowest lane holding the least fitness (no lane does if the input held a NaN, against the contract: pattern 0 then)
-    return max(__ffsll((long long)__ballot(f == least)) - 1, 0);
-}
-
-// One wavefront encodes one group (hx0, hx1: this lane's two values as FP16 bits).  kMinMax: the pattern comes
-// from the min/max selector and only that pattern's value mapping is done; otherwise every pattern is tried
-// and the least squared error wins.
-template <bool kMinMax>
-__device__ inline void encode_group(const EncLds& E, int S, uint32_t hx0, uint32_t hx1, uint32_t* word, uint32_t* meta) {
-    const uint32_t smax = group_scale_bits(hx0, hx1);
-    const float s = half_bits_f(smax), x0 = half_bits_f(hx0), x1 = half_bits_f(hx1);
-    int p0 = 0, p1 = S;
-    if (kMinMax) {
-        p0 = select_minmax(E, S, s, x0, x1);
-        p1 = p0 + 1;
-    }
-    const EncChoice c = search_patterns(E, p0, p1, s, x0, x1);
-    pack_group(E, smax, c.pattern, c.idx, word, meta);
-}
-
-constexpr size_t enc_lds_bytes(int S) { return (size_t)S * kK * 2 + (size_t)S * kK * 4 + (size_t)kEncWaves * ((size_t)S * kK * 4 + kBlockWords * 4); }
-
-__device__ inline EncLds setup_enc_lds(unsigned char* smem, const uint32_t* dev, int S) {
-    const DevLayout D{S};
-    uint32_t* cent = reinterpret_cast<uint32_t*>(smem);
-    uint32_t* enc = cent + S * kK / 2;
-    float* recon = reinterpret_cast<float*>(enc + S * kK);
-    uint32_t* bits = reinterpret_cast<uint32_t*>(recon + kEncWaves * S * kK);
-    stage_vec(cent, dev + D.cent(), S * kK / 2);
-    stage_vec(enc, dev + D.enc(), S * kK);
-    __syncthreads();
-    const int wave = threadIdx.x >> 6;
-    EncLds E;
-    E.cent = reinterpret_cast<const __half*>(cent);
-    E.enc = enc;
-    E.recon = recon + wave * S * kK;
-    E.bits = bits + wave * kBlockWords;
-    return E;
-}
-
-template <bool kMinMax>
-__global__ __launch_bounds__(kEncThreads) void encode_kernel(const uint32_t* __restrict__ dev, int S,
-                                                             const uint32_t* __restrict__ src, size_t n_groups,
-                                                             uint32_t* __restrict__ blocks, uint32_t* __restrict__ meta) {
-    extern __shared__ __align__(16) unsigned char smem_enc[];
-    EncLds E = setup_enc_lds(smem_enc, dev, S);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (size_t g = (size_t)blockIdx.x * kEncWaves + wave; g < n_groups; g += (size_t)gridDim.x * kEncWaves) {
-        const uint32_t pair = src[g * (kGroup / 2) + lane];
-        uint32_t word, mw;
-        encode_group<kMinMax>(E, S, pair & 0xFFFFu, pair >> 16, &word, &mw);
-        if (lane < kBlockWords) blocks[g * kBlockWords + lane] = word;
-        if (lane == 0) meta[g] = mw;
-    }
-}
-
-// grid: (B*H, 2); y = 0 encodes K, y = 1 encodes V.  One workgroup per new group: the append is a
-// latency problem (B*H*2 groups, far fewer than the chip has wavefront slots), so the four wavefronts
-// of the workgroup split the pattern search, a quarter of the patterns each, and wavefront 0 packs
-// the winner (ascending pattern ranges, strict <: the lowest pattern still wins a tie).
-__global__ __launch_bounds__(kEncThreads) void kv_append_kernel(const uint32_t* __restrict__ dev_k, int Sk,
-                                                                const uint32_t* __restrict__ dev_v, int Sv,
-                                                                const uint32_t* __restrict__ k_new, const uint32_t* __restrict__ v_new,
-                                                                uint32_t* __restrict__ k_blocks, uint32_t* __restrict__ k_meta,
-                                                                uint32_t* __restrict__ v_blocks, uint32_t* __restrict__ v_meta,
-                                                                const int32_t* __restrict__ seq_len, int B, int H, int T_max) {
-    extern __shared__ __align__(16) unsigned char smem_enc[];
-    __shared__ float cand_sse[kEncWaves];
-    __shared__ int cand_pattern[kEncWaves];
-    __shared__ uint32_t cand_idx[kEncWaves][64];
-    const bool is_v = blockIdx.y != 0;  // uniform per workgroup, so each workgroup stages one model
-    const int S = is_v ? Sv : Sk;
-    EncLds E = setup_enc_lds(smem_enc, is_v ? dev_v : dev_k, S);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int bh = blockIdx.x;
-    const int t = seq_len[bh / H];
-    if (t < 0 || t >= T_max) return;  // uniform over the workgroup
-    const uint32_t* src = (is_v ? v_new : k_new) + (size_t)bh * (kGroup / 2);
-    const uint32_t pair = src[lane];
-    const uint32_t smax = group_scale_bits(pair & 0xFFFFu, pair >> 16);
-    const int per = (S + kEncWaves - 1) / kEncWaves;
-    const int p0 = wave * per, p1 = min(S, p0 + per);
-    if (p0 < p1) {
-        const EncChoice c = search_patterns(E, p0, p1, half_bits_f(smax), half_bits_f(pair & 0xFFFFu), half_bits_f(pair >> 16));
-        cand_idx[wave][lane] = c.idx;
-        if (lane == 0) {
-            cand_sse[wave] = c.sse;
-            cand_pattern[wave] = c.pattern;
-        }
-    }
-    __syncthreads();
-    if (wave != 0) return;
-    int win = 0;
-    for (int w = 1; w < kEncWaves; ++w)
-        if (w * per < S && cand_sse[w] < cand_sse[win]) win = w;
-    uint32_t word, mw;
-    pack_group(E, smax, cand_pattern[win], cand_idx[win][lane], &word, &mw);
-    const size_t g = (size_t)bh * T_max + t;
-    uint32_t* blocks = is_v ? v_blocks : k_blocks;
-    uint32_t* meta = is_v ? v_meta : k_meta;
-    if (lane < kBlockWords) blocks[g * kBlockWords + lane] = word;
-    if (lane == 0) meta[g] = mw;
-}
-
-// The append with the min/max selector: grid (ceil(B*H / 4), 2); one wavefront per new group, since the
-// selector leaves a single pattern to map and nothing to split.
-__global__ __launch_bounds__(kEncThreads) void kv_append_minmax_kernel(const uint32_t* __restrict__ dev_k, int Sk,
-                                                                       const uint32_t* __restrict__ dev_v, int Sv,
-                                                                       const uint32_t* __restrict__ k_new, const uint32_t* __restrict__ v_new,
-                                                                       uint32_t* __restrict__ k_blocks, uint32_t* __restrict__ k_meta,
-                                                                       uint32_t* __restrict__ v_blocks, uint32_t* __restrict__ v_meta,
-                                                                       const int32_t* __restrict__ seq_len, int B, int H, int T_max) {
-    extern __shared__ __align__(16) unsigned char smem_enc[];
-    const bool is_v = blockIdx.y != 0;
-    const int S = is_v ? Sv : Sk;
-    EncLds E = setup_enc_lds(smem_enc, is_v ? dev_v : dev_k, S);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int bh = blockIdx.x * kEncWaves + wave;
-    if (bh >= B * H) return;  // no workgroup barrier below
-    const int t = seq_len[bh / H];
-    if (t < 0 || t >= T_max) return;
-    const uint32_t pair = ((is_v ? v_new : k_new) + (size_t)bh * (kGroup / 2))[lane];
-    uint32_t word, mw;
-    encode_group<true>(E, S, pair & 0xFFFFu, pair >> 16, &word, &mw);
-    const size_t g = (size_t)bh * T_max + t;
-    uint32_t* blocks = is_v ? v_blocks : k_blocks;
-    uint32_t* meta = is_v ? v_meta : k_meta;
-    if (lane < kBlockWords) blocks[g * kBlockWords + lane] = word;
-    if (lane == 0) meta[g] = mw;
-}
-
 // ---- single-query attention over compressed K / V ----------------------------------------------------
 // One workgroup of 12 wavefronts per (sequence, head): three per SIMD, which leaves each lane the
 // registers for 64 private accumulators next to the decoder state (8 wavefronts when the V model has
@@ -1529,16 +1228,6 @@ float* scratch_on_current_device(int device) {
 }
 
 // ---- host side -----------------------------------------------------------------------------------------
-inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
-
-// a model can be used once it is on a device, and only while that device is the calling thread's current one: the
-// kernels are launched on the current device and read the model's tables through device pointers
-inline int model_ready(const ecco_model* m) {
-    if (!m || !m->dev || m->device < 0) return ECCO_EINVAL;
-    int cur = -1;
-    return (hipGetDevice(&cur) == hipSuccess && cur == m->device) ? ECCO_OK : ECCO_EINVAL;
-}
-
 // A kernel that needs more than 64 KB of LDS has to be told so; the attribute belongs to the kernel (on the
 // current device), not to a launch, so it is set the first time a kernel is launched on a device -- to the most
 // any launch can ask for -- and remembered (a short list under a mutex: host threads may enter together).
@@ -1556,6 +1245,9 @@ int allow_lds_once(const void* kernel, int device, size_t bytes) {
 template <class K>
 int allow_lds(K kernel, int device, size_t bytes) { return allow_lds_once(reinterpret_cast<const void*>(kernel), device, bytes); }
 
+}  // namespace
+
+namespace ecco {
 // compute units of a device, asked once per device (atomics: host threads may race to fill the cache, with the same value)
 int cu_count(int device) {
     static std::atomic<int> cached[16];
@@ -1568,37 +1260,12 @@ int cu_count(int device) {
     return n;
 }
 
-}  // namespace
-
-namespace ecco {
 // Called by ecco_model_to_device with `device` current: asks for the scratch array's address on that device, so that
 // the entry point that allocates nothing finds it ready (also under stream capture).
 int init_device_scratch(int device) { return scratch_on_current_device(device) ? ECCO_OK : ECCO_EHIP; }
 }  // namespace ecco
 
 extern "C" {
-
-static int encode_common(bool minmax, const ecco_model* m, const uint16_t* src, size_t n_groups, void* blocks, uint32_t* meta, void* stream) {
-    if (!m) return ECCO_EINVAL;
-    if (n_groups == 0) return model_ready(m);  // nothing to do; pointers may be null
-    if (!src || !blocks || !meta) return ECCO_EINVAL;
-    if (!aligned(blocks, 64) || !aligned(src, 4) || !aligned(meta, 4)) return ECCO_EALIGN;
-    if (model_ready(m) != ECCO_OK) return ECCO_EINVAL;
-    const size_t wgs = (n_groups + kEncWaves - 1) / kEncWaves;
-    const int grid = (int)std::min<size_t>(wgs, (size_t)cu_count(m->device) * 16);
-    hipLaunchKernelGGL(minmax ? encode_kernel<true> : encode_kernel<false>, dim3(grid), dim3(kEncThreads), enc_lds_bytes(m->S), static_cast<hipStream_t>(stream), m->dev,
-                       m->S, reinterpret_cast<const uint32_t*>(src), n_groups, static_cast<uint32_t*>(blocks), meta);
-    ECCO_HIP_CHECK(hipGetLastError());
-    return ECCO_OK;
-}
-
-int ecco_encode(const ecco_model* m, const uint16_t* src, size_t n_groups, void* blocks, uint32_t* meta, void* stream) {
-    return encode_common(false, m, src, n_groups, blocks, meta, stream);
-}
-
-int ecco_encode_minmax(const ecco_model* m, const uint16_t* src, size_t n_groups, void* blocks, uint32_t* meta, void* stream) {
-    return encode_common(true, m, src, n_groups, blocks, meta, stream);
-}
 
 static int decode_common(const ecco_model* m, const void* blocks, const uint32_t* meta, size_t n_groups, void* dst,
                          void* stream, bool indices) {
@@ -1676,35 +1343,6 @@ int ecco_decode_gemv(const ecco_model* m, const void* blocks, const uint32_t* me
     }
     ECCO_HIP_CHECK(hipGetLastError());
     return ECCO_OK;
-}
-
-static int kv_append_common(bool minmax, const ecco_model* mk, const ecco_model* mv, const uint16_t* k_new, const uint16_t* v_new,
-                            void* k_blocks, uint32_t* k_meta, void* v_blocks, uint32_t* v_meta,
-                            const int32_t* seq_len, int B, int H, int T_max, void* stream) {
-    if (!mk || !mv || !k_new || !v_new || !k_blocks || !k_meta || !v_blocks || !v_meta || !seq_len) return ECCO_EINVAL;
-    if (B <= 0 || H <= 0 || T_max <= 0 || (long long)B * H > 0x7FFFFFFF) return ECCO_ESHAPE;
-    if (!aligned(k_blocks, 64) || !aligned(v_blocks, 64) || !aligned(k_new, 4) || !aligned(v_new, 4)) return ECCO_EALIGN;
-    if (model_ready(mk) != ECCO_OK || model_ready(mv) != ECCO_OK || mk->device != mv->device) return ECCO_EINVAL;
-    const dim3 grid(minmax ? (B * H + kEncWaves - 1) / kEncWaves : B * H, 2);
-    hipLaunchKernelGGL(minmax ? kv_append_minmax_kernel : kv_append_kernel, grid, dim3(kEncThreads),
-                       enc_lds_bytes(std::max(mk->S, mv->S)),
-                       static_cast<hipStream_t>(stream), mk->dev, mk->S, mv->dev, mv->S,
-                       reinterpret_cast<const uint32_t*>(k_new), reinterpret_cast<const uint32_t*>(v_new),
-                       static_cast<uint32_t*>(k_blocks), k_meta, static_cast<uint32_t*>(v_blocks), v_meta, seq_len, B, H, T_max);
-    ECCO_HIP_CHECK(hipGetLastError());
-    return ECCO_OK;
-}
-
-int ecco_kv_append(const ecco_model* mk, const ecco_model* mv, const uint16_t* k_new, const uint16_t* v_new,
-                   void* k_blocks, uint32_t* k_meta, void* v_blocks, uint32_t* v_meta,
-                   const int32_t* seq_len, int B, int H, int T_max, void* stream) {
-    return kv_append_common(false, mk, mv, k_new, v_new, k_blocks, k_meta, v_blocks, v_meta, seq_len, B, H, T_max, stream);
-}
-
-int ecco_kv_append_minmax(const ecco_model* mk, const ecco_model* mv, const uint16_t* k_new, const uint16_t* v_new,
-                          void* k_blocks, uint32_t* k_meta, void* v_blocks, uint32_t* v_meta,
-                          const int32_t* seq_len, int B, int H, int T_max, void* stream) {
-    return kv_append_common(true, mk, mv, k_new, v_new, k_blocks, k_meta, v_blocks, v_meta, seq_len, B, H, T_max, stream);
 }
 
 int ecco_kv_attend_gqa_splits(int device, int B, int Hkv, int tokens) {

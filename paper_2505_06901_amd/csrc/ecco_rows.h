@@ -1,0 +1,330 @@
+// Device side shared by the encoders of both block formats: a group of 128 values lies in one row of 16 lanes, eight
+// consecutive values per lane, so a wavefront holds four groups and everything that is done once per group (extremes,
+// scans, sums) is done four groups at a time with cross-lane moves that stay inside a row.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "ecco_search.h"
+
+namespace ecco_rows {
+
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
+typedef float float4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4_dword __attribute__((ext_vector_type(4), aligned(4)));  // sixteen bytes on a 4-byte boundary
+
+constexpr int kRowLanes = 16;   // lanes of a group
+constexpr int kRowValues = 8;   // values per lane
+constexpr int kWaveRows = 4;    // groups per wavefront
+constexpr int kEncThreads = 256;
+constexpr int kEncWaves = kEncThreads / 64;
+constexpr int kBatch = kEncWaves * kWaveRows;                 // groups a workgroup encodes at a time = rows of a matrix-core tile
+constexpr int kHistStride = ecco::kSearchBins + 4;            // words per group of the histogram (skewed over the banks)
+
+template <int kCtrl>
+__device__ __forceinline__ uint32_t dpp(uint32_t v) { return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kCtrl, 0xF, 0xF, true); }
+template <int kCtrl>
+__device__ __forceinline__ float dpp(float v) { return __builtin_bit_cast(float, dpp<kCtrl>(__builtin_bit_cast(uint32_t, v))); }
+
+template <int kCtrl>
+__device__ __forceinline__ half2_t dpp(half2_t v) { return __builtin_bit_cast(half2_t, dpp<kCtrl>(__builtin_bit_cast(uint32_t, v))); }
+
+// a commutative operation over the 16 lanes of a row; every lane of the row returns the result.  As a sum this is the
+// balanced tree over lanes l and l ^ 1, then ^ 2, ^ 4, ^ 8: once the quads agree, mirroring is the same as the xor.
+template <class T, class Op>
+__device__ __forceinline__ T row_all(T t, Op op) {
+    t = op(t, dpp<0xB1>(t));   // quad_perm [1,0,3,2]
+    t = op(t, dpp<0x4E>(t));   // quad_perm [2,3,0,1]
+    t = op(t, dpp<0x141>(t));  // row_half_mirror
+    t = op(t, dpp<0x140>(t));  // row_mirror
+    return t;
+}
+__device__ __forceinline__ uint32_t row_max(uint32_t v) { return row_all(v, [](uint32_t a, uint32_t b) { return max(a, b); }); }
+__device__ __forceinline__ uint32_t row_min(uint32_t v) { return row_all(v, [](uint32_t a, uint32_t b) { return min(a, b); }); }
+// least of non-negative FP32 values (their bits are ordered like whole numbers, and those fuse with the cross-lane moves)
+__device__ __forceinline__ float row_min_pos(float v) { return __builtin_bit_cast(float, row_min(__builtin_bit_cast(uint32_t, v))); }
+// sum over the lanes of the row up to and including this one
+__device__ __forceinline__ uint32_t row_scan(uint32_t v) {
+    v += dpp<0x111>(v);  // row_shr 1, 2, 4, 8; zeros come in
+    v += dpp<0x112>(v);
+    v += dpp<0x114>(v);
+    v += dpp<0x118>(v);
+    return v;
+}
+template <int kLane>
+__device__ __forceinline__ uint32_t row_lane(uint32_t v) { return dpp<0x150 + kLane>(v); }  // row_newbcast
+
+__device__ __forceinline__ void wave_fence() {  // orders the LDS accesses of one wavefront
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__device__ __forceinline__ half2_t as_half2(uint32_t v) { return __builtin_bit_cast(half2_t, v); }
+__device__ __forceinline__ float half_bits_f(uint32_t bits) { return (float)__builtin_bit_cast(_Float16, (unsigned short)bits); }
+__device__ __forceinline__ half2_t splat_half(uint32_t bits) { return as_half2(bits | (bits << 16)); }
+
+// the eight values of a lane (FP16 pairs) and the bins they fall in
+struct RowValues {
+    uint32_t x[4];
+    uint32_t bin[kRowValues];
+};
+__device__ __forceinline__ _Float16 value(const RowValues& v, int i) { return as_half2(v.x[i >> 1])[i & 1]; }
+// the largest magnitude of the lane's values, as FP16 bits
+__device__ __forceinline__ uint32_t lane_absmax(const RowValues& v) {
+    ushort2_t m = __builtin_bit_cast(ushort2_t, v.x[0] & 0x7FFF7FFFu);
+#pragma unroll
+    for (int i = 1; i < 4; ++i) m = __builtin_elementwise_max(m, __builtin_bit_cast(ushort2_t, v.x[i] & 0x7FFF7FFFu));
+    return max((uint32_t)m.x, (uint32_t)m.y);
+}
+// Bins of the lane's values for axis units `per` = step / scale per unit of x.  Adding 2^23 + 32768 leaves
+// rint(x * per) + 32768 in the low 16 bits (q).  hist (if not null): this group's row of the histogram; a word counts the
+// bin's values in its upper half and sums their places q & 255 in its lower half.
+template <bool kHist>
+__device__ __forceinline__ void set_bins(RowValues& v, float per, uint32_t* hist, int skip) {
+#pragma unroll
+    for (int i = 0; i < kRowValues; ++i) {
+        const uint32_t q = __builtin_bit_cast(uint32_t, fmaf((float)value(v, i), per, 8421376.0f));
+        v.bin[i] = (q >> 8) & 255u;
+        if (kHist) {
+            const uint32_t one = 65536u | (q & 255u);
+            atomicAdd(&hist[v.bin[i]], i == skip ? 0u : one);
+        }
+    }
+}
+
+// x - r in FP32, rounded once, of the kX-th half of x and the kR-th half of r: one mixed-precision instruction (written
+// out, the compiler turns the product with 1 into two conversions and a subtraction)
+template <int kX, int kR>
+__device__ __forceinline__ float half_diff(uint32_t x, uint32_t r) {
+    float d;
+    if (kX == 0 && kR == 0) asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[0,0,0] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(x), "v"(r));
+    if (kX == 1 && kR == 0) asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,0] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(x), "v"(r));
+    if (kX == 0 && kR == 1) asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[0,0,1] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(x), "v"(r));
+    if (kX == 1 && kR == 1) asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,1] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(x), "v"(r));
+    return d;
+}
+// distance of the lane's i-th value to the kR-th half of r
+template <int kR>
+__device__ __forceinline__ float distance(const RowValues& v, int i, half2_t r) {
+    const uint32_t x = v.x[i >> 1], rb = __builtin_bit_cast(uint32_t, r);
+    return fabsf((i & 1) ? half_diff<1, kR>(x, rb) : half_diff<0, kR>(x, rb));
+}
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+typedef __attribute__((address_space(3))) uint8_t lds_u8;
+__device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(size_t)(const lds_u8*)p; }
+__device__ __forceinline__ uint32_t lds_word(uint32_t address) { return *(const lds_u32*)(size_t)address; }
+
+// The row's values under one pattern: every value's index (the lowest of the nearest reconstructed centroids
+// fp16(c * s)), eight nibbles per lane, first value on top; and the group's squared error, in FP32 by the balanced tree
+// over value pairs (i, i ^ 1), (.., i ^ 2), ... (kSse).  near, pair: the pattern's rows of the tables in LDS (pair as an LDS
+// address, a multiple of 64); plain rows compare every value with all kCent centroids.  A value whose place is `skip` counts as without error, with index 15.
+// The distance falls (weakly) with k up to its least value and rises (weakly) after it, so the lowest nearest index is
+// the last k at which it strictly drops.
+template <int kCent, bool kSse>
+__device__ __forceinline__ void rate_pattern(const uint8_t* near, uint32_t pair, half2_t s2, const RowValues& v, bool plain, int skip,
+                                             float& sse, uint32_t& idx) {
+    uint32_t nb[kRowValues], k[kRowValues], marks = 0;
+    float d[kRowValues];
+#pragma unroll
+    for (int i = 0; i < kRowValues; ++i) nb[i] = near[v.bin[i]];
+#pragma unroll
+    for (int i = 0; i < kRowValues; ++i) {
+        const half2_t r = as_half2(lds_word((nb[i] & 0x3Cu) | pair)) * s2;
+        const float d0 = distance<0>(v, i, r), d1 = distance<1>(v, i, r);
+        const bool up = d1 < d0;
+        k[i] = (nb[i] >> 2) + (up ? 1u : 0u);
+        d[i] = up ? d1 : d0;
+        marks |= nb[i];
+    }
+    if (__builtin_amdgcn_ballot_w64((marks & ecco::kNearTwo) != 0u) != 0ull) {
+#pragma unroll
+        for (int i = 0; i < kRowValues; ++i) {
+            if (nb[i] & ecco::kNearTwo) {
+                const half2_t r = as_half2(lds_word(((nb[i] & 0x3Cu) | pair) + 4u)) * s2;
+                const float d1 = distance<0>(v, i, r), d2 = distance<1>(v, i, r);
+                if (d2 < d1) {
+                    k[i] = (nb[i] >> 2) + 2u;
+                    d[i] = d2;
+                }
+            }
+        }
+    }
+    const bool all = plain || (marks & ecco::kNearWide) != 0u;
+    if (__builtin_amdgcn_ballot_w64(all) != 0ull) {
+        float e[kRowValues];
+#pragma unroll
+        for (int i = 0; i < kRowValues; ++i) e[i] = __builtin_inff();
+#pragma unroll 1
+        for (int c = 0; c < kCent; ++c) {
+            const half2_t r = as_half2(lds_word(pair + 4u * c)) * s2;
+#pragma unroll
+            for (int i = 0; i < kRowValues; ++i) {
+                const float dc = distance<0>(v, i, r);
+                if (all && dc < e[i]) {  // strict: the lowest index wins a tie
+                    e[i] = dc;
+                    k[i] = (uint32_t)c;
+                    d[i] = dc;
+                }
+            }
+        }
+    }
+    idx = 0;
+#pragma unroll
+    for (int i = 0; i < kRowValues; ++i) idx = (idx << 4) | (i == skip ? 15u : k[i]);
+    if (kSse) {
+        float q[kRowValues / 2];
+#pragma unroll
+        for (int i = 0; i < kRowValues / 2; ++i) {
+            const float a = __fmul_rn(d[2 * i], d[2 * i]), b = __fmul_rn(d[2 * i + 1], d[2 * i + 1]);
+            q[i] = __fadd_rn(2 * i == skip ? 0.0f : a, 2 * i + 1 == skip ? 0.0f : b);
+        }
+        sse = row_all(__fadd_rn(__fadd_rn(q[0], q[1]), __fadd_rn(q[2], q[3])), [](float a, float b) { return __fadd_rn(a, b); });
+    }
+}
+
+// ---- bounds on every pattern's error, and the patterns that can be the best ------------------------------------------
+// Workgroup-wide LDS of the bounds: histogram, partial sums of the matrix product, the wavefronts' least upper bounds,
+// the patterns left per group.
+struct SearchLds {
+    uint32_t* hist;   // [kBatch][kHistStride]
+    float* part;      // [kEncWaves][8][64], only where several wavefronts share a tile of patterns
+    float* least;     // [kEncWaves][kBatch]
+    uint16_t* left;   // [kBatch][4]
+};
+constexpr int kPartWords = kEncWaves * 8 * 64;
+constexpr int search_lds_words(int tiles) { return kBatch * kHistStride + (tiles <= 2 ? kPartWords : 0) + kEncWaves * kBatch + kBatch * 2; }
+__device__ __forceinline__ SearchLds search_lds(uint32_t* base, int tiles) {
+    SearchLds s;
+    s.hist = base;
+    s.part = reinterpret_cast<float*>(base + kBatch * kHistStride);
+    s.least = s.part + (tiles <= 2 ? kPartWords : 0);
+    s.left = reinterpret_cast<uint16_t*>(s.least + kEncWaves * kBatch);
+    return s;
+}
+
+// A wavefront's share of the matrix product: with kTiles tiles of 16 patterns, kParts wavefronts share a tile, each over
+// its own part of the bins.  The operands stay in registers for as long as the workgroup lives.
+template <int kTiles>
+struct Coefs {
+    static constexpr int kParts = kTiles == 1 ? 4 : kTiles == 2 ? 2 : 1;
+    static constexpr int kBlocks = ecco::kSearchBlocks / kParts;
+    uint4 w[kBlocks * 3];
+    __device__ __forceinline__ void load(const uint32_t* __restrict__ coef, int wave, int tiles, int lane) {
+        const int tile = min(wave / kParts, tiles - 1);
+        const uint4* src = reinterpret_cast<const uint4*>(coef) + ((size_t)(tile * ecco::kSearchBlocks + (wave % kParts) * kBlocks) * 3) * 64 + lane;
+#pragma unroll
+        for (int i = 0; i < kBlocks * 3; ++i) w[i] = src[i * 64];
+    }
+};
+
+// this wavefront's four rows of the histogram, to "no values"
+__device__ __forceinline__ void clear_hist(uint32_t* rows, int lane) {
+    const uint4 none = make_uint4(0u, 0u, 0u, 0u);
+    constexpr int kPieces = kWaveRows * kHistStride / 4;
+#pragma unroll
+    for (int i = 0; i < kPieces / 64; ++i) reinterpret_cast<uint4*>(rows)[i * 64 + lane] = none;
+    if (lane < kPieces % 64) reinterpret_cast<uint4*>(rows)[kPieces / 64 * 64 + lane] = none;
+}
+// sums and counts to FP16 (m, n) pairs, in place
+__device__ __forceinline__ void convert_hist(uint32_t* rows, int lane) {
+#pragma unroll
+    for (int r = 0; r < kWaveRows; ++r) {
+        uint4* at = reinterpret_cast<uint4*>(rows + r * kHistStride) + lane;
+        uint4 v = *at;
+        uint32_t* w = reinterpret_cast<uint32_t*>(&v);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            uint32_t m, n;
+            asm("v_cvt_f16_u16_e32 %0, %1" : "=v"(m) : "v"(w[i]));
+            asm("v_cvt_f16_u16_sdwa %0, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_1" : "=v"(n) : "v"(w[i]));
+            w[i] = m | (n << 16);
+        }
+        *at = v;
+    }
+}
+
+// For the batch's converted histogram: the patterns of this wavefront's group (wave, row) that can have the least error,
+// one bit each.  Called by all wavefronts of the workgroup together (barriers inside); the histogram is free afterwards.
+template <int kTiles>
+__device__ __forceinline__ uint64_t patterns_left(const SearchLds& L, const Coefs<kTiles>& C, int tiles, int wave, int lane) {
+    constexpr int kParts = Coefs<kTiles>::kParts, kBlocks = Coefs<kTiles>::kBlocks;
+    const int tile = wave / kParts;
+    float4_t sum = {0.0f, 0.0f, 0.0f, 0.0f}, err = {0.0f, 0.0f, 0.0f, 0.0f};
+    __syncthreads();
+    if (tile < tiles) {
+        // row l % 16 of the A operand; bins 4 (l / 16) .. + 3 of each 16
+        const uint4* a = reinterpret_cast<const uint4*>(L.hist + (lane & 15) * kHistStride + (wave % kParts) * kBlocks * 32 + 4 * (lane >> 4));
+#pragma unroll
+        for (int j = 0; j < kBlocks; ++j) {
+            const uint4 a0 = a[j * 8], a1 = a[j * 8 + 4];
+            // the counts alone: the upper halves of the eight words
+            const uint4 n = make_uint4(__builtin_amdgcn_perm(a0.y, a0.x, 0x07060302u), __builtin_amdgcn_perm(a0.w, a0.z, 0x07060302u),
+                                       __builtin_amdgcn_perm(a1.y, a1.x, 0x07060302u), __builtin_amdgcn_perm(a1.w, a1.z, 0x07060302u));
+            sum = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a0), __builtin_bit_cast(half8_t, C.w[3 * j]), sum, 0, 0, 0);
+            err = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, n), __builtin_bit_cast(half8_t, C.w[3 * j + 2]), err, 0, 0, 0);
+            sum = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a1), __builtin_bit_cast(half8_t, C.w[3 * j + 1]), sum, 0, 0, 0);
+        }
+    }
+    if (kParts > 1) {
+        float* mine = L.part + wave * 512 + lane;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            mine[j * 64] = sum[j];
+            mine[(4 + j) * 64] = err[j];
+        }
+        __syncthreads();
+        const float* first = L.part + tile * kParts * 512 + lane;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            sum[j] = first[j * 64];
+            err[j] = first[(4 + j) * 64];
+#pragma unroll
+            for (int p = 1; p < kParts; ++p) {
+                sum[j] += first[p * 512 + j * 64];
+                err[j] += first[p * 512 + (4 + j) * 64];
+            }
+        }
+    }
+    // lane l, register j: group 4 (l / 16) + j of the batch, pattern 16 tile + l % 16
+    float least[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        // the FP32 sums that decide differ from the true ones by less than 2^-18 of the error, what all patterns share included
+        err[j] += fabsf(sum[j]) * 0x1p-16f + 0x1p-12f;
+        sum[j] += 16.0f;  // the bound with what is shared left out can be below zero, by less than 3
+        least[j] = row_min_pos(sum[j] + err[j]);
+    }
+    if (kTiles > 1) {
+        if ((lane & 15) == 0)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) L.least[wave * kBatch + 4 * (lane >> 4) + j] = tile < tiles ? least[j] : __builtin_inff();
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float* at = L.least + 4 * (lane >> 4) + j;
+            least[j] = fminf(fminf(at[0], at[kBatch]), fminf(at[2 * kBatch], at[3 * kBatch]));
+        }
+    }
+    uint64_t left[4];  // register j: 16 bits for each of the groups j, 4 + j, 8 + j, 12 + j
+#pragma unroll
+    for (int j = 0; j < 4; ++j) left[j] = __builtin_amdgcn_ballot_w64(sum[j] - err[j] <= least[j]);
+    const int row = lane >> 4;
+    if (kTiles == 1) {  // every wavefront has all of it: group 4 wave + row
+        const uint64_t m = row == 0 ? left[0] : row == 1 ? left[1] : row == 2 ? left[2] : left[3];
+        return (m >> (16 * wave)) & 0xFFFFull;
+    }
+    if (lane < kBatch && wave % kParts == 0) {  // lane g writes group g = 4 r + j
+        const int j = lane & 3;
+        const uint64_t m = j == 0 ? left[0] : j == 1 ? left[1] : j == 2 ? left[2] : left[3];
+        L.left[lane * 4 + tile] = tile < tiles ? (uint16_t)(m >> (16 * (lane >> 2))) : (uint16_t)0;
+    }
+    __syncthreads();
+    uint64_t m = *reinterpret_cast<const uint64_t*>(L.left + (wave * kWaveRows + row) * 4);
+    if (kParts == 2) m &= 0xFFFFFFFFull;  // tiles 2 and 3 do not exist
+    return m;
+}
+
+}  // namespace ecco_rows
