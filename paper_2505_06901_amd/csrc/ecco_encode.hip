@@ -7,7 +7,7 @@
 // every pattern's error from a matrix product of the group's histogram with tables of the model, 16 groups x 16 patterns at
 // a time on the matrix cores, and the exact FP32 error only for the patterns whose bounds overlap the best (1.3 to 2 of 64 on
 // weights, keys and values).  The chosen pattern, the indices and the block are those of the plain search, bit for bit.
-// A workgroup of four wavefronts takes 16 groups at a time, one group per row of 16 lanes (ecco_rows.h).
+// A group lies in a row of 16 lanes (ecco_rows.h).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -21,6 +21,8 @@ using namespace ecco_rows;
 namespace {
 
 constexpr int kHalf = kGroup / 2;
+constexpr int kMinmaxThreads = 256;                                    // workgroup of the min/max encoder: 16 groups at a time
+constexpr int kMinmaxBatch = kMinmaxThreads / 64 * kWaveRows;
 
 // where a kernel finds group i and where its block goes
 struct BulkIo {
@@ -66,15 +68,16 @@ struct EncTables {
     const uint32_t* enc;
 };
 constexpr int kTableWords = kSearchBins / 4 + 16 + kK;  // per pattern
+template <int kThreads>
 __device__ __forceinline__ EncTables stage_enc_tables(uint32_t* lds, const uint32_t* __restrict__ dev, int S) {
     const DevLayout D{S};
     const uint4* a = reinterpret_cast<const uint4*>(dev + D.near());  // near and pair follow each other
     uint4* d = reinterpret_cast<uint4*>(lds);
     const int n0 = S * (kSearchBins / 4 + 16) / 4, n1 = S * kK / 4;
-    for (int i = threadIdx.x; i < n0; i += kEncThreads) d[i] = a[i];
+    for (int i = threadIdx.x; i < n0; i += kThreads) d[i] = a[i];
     const uint4* e = reinterpret_cast<const uint4*>(dev + D.enc());
     const auto code = [](uint32_t w) { return ((w & 0xFFFFu) << 8) | (w >> 16); };
-    for (int i = threadIdx.x; i < n1; i += kEncThreads) {
+    for (int i = threadIdx.x; i < n1; i += kThreads) {
         const uint4 w = e[i];
         d[n0 + i] = make_uint4(code(w.x), code(w.y), code(w.z), code(w.w));
     }
@@ -86,6 +89,7 @@ __device__ __forceinline__ EncTables stage_enc_tables(uint32_t* lds, const uint3
 }
 
 // the values of group `local` of batch b (the last group's beyond the end)
+template <int kBatch>
 __device__ __forceinline__ void load_values(RowValues& v, const uint32_t* src, size_t groups, size_t b, int local, int l) {
     const size_t first = min(b * kBatch, groups - 1);  // uniform
     const int last = (int)min(groups - 1 - first, (size_t)(kBatch - 1));
@@ -142,7 +146,7 @@ __device__ __forceinline__ uint32_t pack_row(const uint32_t* enc, uint32_t* imag
 constexpr size_t search_lds_bytes(int S) { return ((size_t)S * kTableWords + search_lds_words(search_tiles(S))) * 4; }
 
 template <int kTiles, bool kLong, class Io>
-__global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2))) void encode_search_kernel(Job<Io> j0, Job<Io> j1) {
+__global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(4))) void encode_search_kernel(Job<Io> j0, Job<Io> j1) {
     extern __shared__ __align__(16) uint32_t smem[];
     const Job<Io>& job = blockIdx.y ? j1 : j0;
     const int S = job.S, tiles = search_tiles(S);
@@ -151,15 +155,14 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2))
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const SearchLds L = search_lds(smem + S * kTableWords, kTiles);
     uint32_t* hist = L.hist + (wave * kWaveRows + row) * kHistStride;
-    const size_t batches = (io.groups() + kBatch - 1) / kBatch;
-    RowValues v, next;
-    load_values(v, io.values(), io.groups(), blockIdx.x, wave * kWaveRows + row, l);
+    const size_t batches = (io.groups() + kSearchBatch - 1) / kSearchBatch;
+    RowValues v;
+    load_values<kSearchBatch>(v, io.values(), io.groups(), blockIdx.x, wave * kWaveRows + row, l);
     Coefs<kTiles> C;
     C.load(job.dev + DevLayout{S}.coef(), wave, tiles, lane);
-    const EncTables T = stage_enc_tables(smem, job.dev, S);
+    const EncTables T = stage_enc_tables<kSearchThreads>(smem, job.dev, S);
     for (size_t b = blockIdx.x; b < batches; b += gridDim.x) {
-        const size_t g = b * kBatch + wave * kWaveRows + row;
-        load_values(next, io.values(), io.groups(), b + gridDim.x, wave * kWaveRows + row, l);
+        const size_t g = b * kSearchBatch + wave * kWaveRows + row;
         const uint32_t smax = row_max(lane_absmax(v));
         const float s = half_bits_f(smax);
         const half2_t s2 = splat_half(smax);
@@ -188,6 +191,8 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2))
             }
             first = false;
         } while (__builtin_amdgcn_ballot_w64(left != 0ull) != 0ull);
+        // the next group is requested here, when the search has given its registers back
+        load_values<kSearchBatch>(v, io.values(), io.groups(), b + gridDim.x, wave * kWaveRows + row, l);
         uint32_t mw;
         const uint32_t word = pack_row<kLong>(T.enc + pattern * kK, hist, idx, l, smax, pattern, mw);
         size_t at;
@@ -195,8 +200,6 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(2))
             io.blocks[at * kBlockWords + l] = word;
             if (l == 0) io.meta[at] = mw;
         }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v.x[i] = next.x[i];
     }
 }
 
@@ -246,10 +249,10 @@ __device__ __forceinline__ uint32_t select_minmax(const uint32_t* ends, int S, h
 }
 
 constexpr int kImageStride = 20;  // words per group of the payload being assembled
-constexpr size_t minmax_lds_bytes(int S) { return ((size_t)S * (kTableWords + 1) + kBatch * kImageStride + 3) * 4; }
+constexpr size_t minmax_lds_bytes(int S) { return ((size_t)S * (kTableWords + 1) + kMinmaxBatch * kImageStride + 3) * 4; }
 
 template <bool kLong, class Io>
-__global__ __launch_bounds__(kEncThreads) void encode_minmax_kernel(Job<Io> j0, Job<Io> j1) {
+__global__ __launch_bounds__(kMinmaxThreads) void encode_minmax_kernel(Job<Io> j0, Job<Io> j1) {
     extern __shared__ __align__(16) uint32_t smem[];
     const Job<Io>& job = blockIdx.y ? j1 : j0;
     const int S = job.S;
@@ -258,18 +261,18 @@ __global__ __launch_bounds__(kEncThreads) void encode_minmax_kernel(Job<Io> j0, 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint32_t* ends = smem + S * kTableWords;
     uint32_t* image = ends + S + (wave * kWaveRows + row) * kImageStride;
-    const size_t batches = (io.groups() + kBatch - 1) / kBatch;
+    const size_t batches = (io.groups() + kMinmaxBatch - 1) / kMinmaxBatch;
     RowValues v, next;
-    load_values(v, io.values(), io.groups(), blockIdx.x, wave * kWaveRows + row, l);
-    const EncTables T = stage_enc_tables(smem, job.dev, S);
+    load_values<kMinmaxBatch>(v, io.values(), io.groups(), blockIdx.x, wave * kWaveRows + row, l);
+    const EncTables T = stage_enc_tables<kMinmaxThreads>(smem, job.dev, S);
     if ((int)threadIdx.x < S) {
         const uint32_t* pair = job.dev + DevLayout{S}.pair() + threadIdx.x * 16;
         ends[threadIdx.x] = __builtin_amdgcn_perm(pair[kK - 1], pair[0], 0x05040100u);  // first and last centroid
     }
     __syncthreads();
     for (size_t b = blockIdx.x; b < batches; b += gridDim.x) {
-        const size_t g = b * kBatch + wave * kWaveRows + row;
-        load_values(next, io.values(), io.groups(), b + gridDim.x, wave * kWaveRows + row, l);
+        const size_t g = b * kMinmaxBatch + wave * kWaveRows + row;
+        load_values<kMinmaxBatch>(next, io.values(), io.groups(), b + gridDim.x, wave * kWaveRows + row, l);
         const uint32_t smax = row_max(lane_absmax(v));
         const float s = half_bits_f(smax);
         const half2_t s2 = splat_half(smax);
@@ -296,22 +299,22 @@ int launch_encode(bool minmax, const ecco_model* m0, const Io& io0, const ecco_m
     const Job<Io> j0{m0->dev, m0->S, io0}, j1{m1->dev, m1->S, io1};
     const int S = std::max(m0->S, m1->S);
     const bool lng = std::max(m0->max_len, m1->max_len) > 8;
-    const size_t wgs = (groups + kBatch - 1) / kBatch;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const auto run = [&](auto kernel, size_t lds, int per_cu) {
+    const auto run = [&](auto kernel, size_t lds, int batch, int threads, int per_cu) {
+        const size_t wgs = (groups + batch - 1) / batch;
         const dim3 grid((unsigned)std::min<size_t>(wgs, (size_t)cu_count(m0->device) * per_cu), jobs);
-        hipLaunchKernelGGL(kernel, grid, dim3(kEncThreads), lds, st, j0, j1);
+        hipLaunchKernelGGL(kernel, grid, dim3(threads), lds, st, j0, j1);
     };
     if (minmax) {
         const size_t lds = minmax_lds_bytes(S);
-        if (lng) run(encode_minmax_kernel<true, Io>, lds, 4);
-        else run(encode_minmax_kernel<false, Io>, lds, 4);
+        if (lng) run(encode_minmax_kernel<true, Io>, lds, kMinmaxBatch, kMinmaxThreads, 6);
+        else run(encode_minmax_kernel<false, Io>, lds, kMinmaxBatch, kMinmaxThreads, 6);
     } else {
         const size_t lds = search_lds_bytes(S);
         switch (search_tiles(S)) {
-            case 1: lng ? run(encode_search_kernel<1, true, Io>, lds, 2) : run(encode_search_kernel<1, false, Io>, lds, 2); break;
-            case 2: lng ? run(encode_search_kernel<2, true, Io>, lds, 2) : run(encode_search_kernel<2, false, Io>, lds, 2); break;
-            default: lng ? run(encode_search_kernel<4, true, Io>, lds, 2) : run(encode_search_kernel<4, false, Io>, lds, 2);
+            case 1: lng ? run(encode_search_kernel<1, true, Io>, lds, kSearchBatch, kSearchThreads, 2) : run(encode_search_kernel<1, false, Io>, lds, kSearchBatch, kSearchThreads, 2); break;
+            case 2: lng ? run(encode_search_kernel<2, true, Io>, lds, kSearchBatch, kSearchThreads, 2) : run(encode_search_kernel<2, false, Io>, lds, kSearchBatch, kSearchThreads, 2); break;
+            default: lng ? run(encode_search_kernel<4, true, Io>, lds, kSearchBatch, kSearchThreads, 2) : run(encode_search_kernel<4, false, Io>, lds, kSearchBatch, kSearchThreads, 2);
         }
     }
     ECCO_HIP_CHECK(hipGetLastError());

@@ -18,9 +18,12 @@ typedef uint32_t u32x4_dword __attribute__((ext_vector_type(4), aligned(4)));  /
 constexpr int kRowLanes = 16;   // lanes of a group
 constexpr int kRowValues = 8;   // values per lane
 constexpr int kWaveRows = 4;    // groups per wavefront
-constexpr int kEncThreads = 256;
-constexpr int kEncWaves = kEncThreads / 64;
-constexpr int kBatch = kEncWaves * kWaveRows;                 // groups a workgroup encodes at a time = rows of a matrix-core tile
+// Workgroup of the full search: eight wavefronts, 32 groups at a time, two matrix-core tiles of 16.  (Four wavefronts with
+// a pattern tile's whole operands each, 96 registers, ran two workgroups per compute unit, two wavefronts per SIMD, and
+// were bound by latency: 79 us for 131072 groups.)
+constexpr int kSearchThreads = 512;
+constexpr int kSearchWaves = kSearchThreads / 64;
+constexpr int kSearchBatch = kSearchWaves * kWaveRows;
 constexpr int kHistStride = ecco::kSearchBins + 4;            // words per group of the histogram (skewed over the banks)
 
 template <int kCtrl>
@@ -66,10 +69,11 @@ __device__ __forceinline__ half2_t as_half2(uint32_t v) { return __builtin_bit_c
 __device__ __forceinline__ float half_bits_f(uint32_t bits) { return (float)__builtin_bit_cast(_Float16, (unsigned short)bits); }
 __device__ __forceinline__ half2_t splat_half(uint32_t bits) { return as_half2(bits | (bits << 16)); }
 
-// the eight values of a lane (FP16 pairs) and the bins they fall in
+// the eight values of a lane (FP16 pairs) and the bins they fall in, a byte each
 struct RowValues {
     uint32_t x[4];
-    uint32_t bin[kRowValues];
+    uint32_t bins[2];
+    __device__ __forceinline__ uint32_t bin(int i) const { return (bins[i >> 2] >> (8 * (i & 3))) & 255u; }
 };
 __device__ __forceinline__ _Float16 value(const RowValues& v, int i) { return as_half2(v.x[i >> 1])[i & 1]; }
 // the largest magnitude of the lane's values, as FP16 bits
@@ -85,12 +89,17 @@ __device__ __forceinline__ uint32_t lane_absmax(const RowValues& v) {
 template <bool kHist>
 __device__ __forceinline__ void set_bins(RowValues& v, float per, uint32_t* hist, int skip) {
 #pragma unroll
-    for (int i = 0; i < kRowValues; ++i) {
-        const uint32_t q = __builtin_bit_cast(uint32_t, fmaf((float)value(v, i), per, 8421376.0f));
-        v.bin[i] = (q >> 8) & 255u;
+    for (int h = 0; h < 2; ++h) {
+        uint32_t q[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) q[i] = __builtin_bit_cast(uint32_t, fmaf((float)value(v, 4 * h + i), per, 8421376.0f));
+        v.bins[h] = __builtin_amdgcn_perm(q[1], q[0], 0x0C0C0501u) | __builtin_amdgcn_perm(q[3], q[2], 0x05010C0Cu);  // byte 1 of each
         if (kHist) {
-            const uint32_t one = 65536u | (q & 255u);
-            atomicAdd(&hist[v.bin[i]], i == skip ? 0u : one);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t one = 65536u | (q[i] & 255u);
+                atomicAdd(&hist[(q[i] >> 8) & 255u], 4 * h + i == skip ? 0u : one);
+            }
         }
     }
 }
@@ -126,27 +135,34 @@ __device__ __forceinline__ uint32_t lds_word(uint32_t address) { return *(const 
 template <int kCent, bool kSse>
 __device__ __forceinline__ void rate_pattern(const uint8_t* near, uint32_t pair, half2_t s2, const RowValues& v, bool plain, int skip,
                                              float& sse, uint32_t& idx) {
-    uint32_t nb[kRowValues], k[kRowValues], marks = 0;
+    uint32_t k[kRowValues], marks = 0;
     float d[kRowValues];
+    // four values at a time: all eight in flight need 24 more registers than three workgroups per compute unit leave
 #pragma unroll
-    for (int i = 0; i < kRowValues; ++i) nb[i] = near[v.bin[i]];
+    for (int h = 0; h < kRowValues; h += 4) {
+        uint32_t nb[4];
 #pragma unroll
-    for (int i = 0; i < kRowValues; ++i) {
-        const half2_t r = as_half2(lds_word((nb[i] & 0x3Cu) | pair)) * s2;
-        const float d0 = distance<0>(v, i, r), d1 = distance<1>(v, i, r);
-        const bool up = d1 < d0;
-        k[i] = (nb[i] >> 2) + (up ? 1u : 0u);
-        d[i] = up ? d1 : d0;
-        marks |= nb[i];
+        for (int i = 0; i < 4; ++i) nb[i] = near[v.bin(h + i)];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const half2_t r = as_half2(lds_word((nb[i] & 0x3Cu) | pair)) * s2;
+            const float d0 = distance<0>(v, h + i, r), d1 = distance<1>(v, h + i, r);
+            const bool up = d1 < d0;
+            k[h + i] = (nb[i] >> 2) + (up ? 1u : 0u);
+            d[h + i] = up ? d1 : d0;
+            marks |= nb[i];
+        }
+        __builtin_amdgcn_sched_barrier(0);
     }
     if (__builtin_amdgcn_ballot_w64((marks & ecco::kNearTwo) != 0u) != 0ull) {
 #pragma unroll
         for (int i = 0; i < kRowValues; ++i) {
-            if (nb[i] & ecco::kNearTwo) {
-                const half2_t r = as_half2(lds_word(((nb[i] & 0x3Cu) | pair) + 4u)) * s2;
+            const uint32_t nb = near[v.bin(i)];
+            if (nb & ecco::kNearTwo) {
+                const half2_t r = as_half2(lds_word(((nb & 0x3Cu) | pair) + 4u)) * s2;
                 const float d1 = distance<0>(v, i, r), d2 = distance<1>(v, i, r);
                 if (d2 < d1) {
-                    k[i] = (nb[i] >> 2) + 2u;
+                    k[i] = (nb >> 2) + 2u;
                     d[i] = d2;
                 }
             }
@@ -154,17 +170,15 @@ __device__ __forceinline__ void rate_pattern(const uint8_t* near, uint32_t pair,
     }
     const bool all = plain || (marks & ecco::kNearWide) != 0u;
     if (__builtin_amdgcn_ballot_w64(all) != 0ull) {
-        float e[kRowValues];
 #pragma unroll
-        for (int i = 0; i < kRowValues; ++i) e[i] = __builtin_inff();
+        for (int i = 0; i < kRowValues; ++i) d[i] = all ? __builtin_inff() : d[i];
 #pragma unroll 1
         for (int c = 0; c < kCent; ++c) {
             const half2_t r = as_half2(lds_word(pair + 4u * c)) * s2;
 #pragma unroll
             for (int i = 0; i < kRowValues; ++i) {
                 const float dc = distance<0>(v, i, r);
-                if (all && dc < e[i]) {  // strict: the lowest index wins a tie
-                    e[i] = dc;
+                if (all && dc < d[i]) {  // strict: the lowest index wins a tie
                     k[i] = (uint32_t)c;
                     d[i] = dc;
                 }
@@ -186,30 +200,31 @@ __device__ __forceinline__ void rate_pattern(const uint8_t* near, uint32_t pair,
 }
 
 // ---- bounds on every pattern's error, and the patterns that can be the best ------------------------------------------
-// Workgroup-wide LDS of the bounds: histogram, partial sums of the matrix product, the wavefronts' least upper bounds,
+// Workgroup-wide LDS of the bounds: histogram, partial sums of the matrix product, the pattern tiles' least upper bounds,
 // the patterns left per group.
 struct SearchLds {
-    uint32_t* hist;   // [kBatch][kHistStride]
-    float* part;      // [kEncWaves][8][64], only where several wavefronts share a tile of patterns
-    float* least;     // [kEncWaves][kBatch]
-    uint16_t* left;   // [kBatch][4]
+    uint32_t* hist;   // [kSearchBatch][kHistStride]
+    float4_t* part;   // [wavefront (and tile of groups)][sum, error][64]
+    float* least;     // [4][kSearchBatch]
+    uint16_t* left;   // [kSearchBatch][4]
 };
-constexpr int kPartWords = kEncWaves * 8 * 64;
-constexpr int search_lds_words(int tiles) { return kBatch * kHistStride + (tiles <= 2 ? kPartWords : 0) + kEncWaves * kBatch + kBatch * 2; }
+// one tile of patterns per 16; the wavefronts share the tiles evenly, each over its own part of the bins
+constexpr int search_parts(int tiles) { return tiles == 1 ? 8 : tiles == 2 ? 4 : 2; }
+constexpr int search_part_words(int tiles) { return kSearchWaves * (search_parts(tiles) == 2 ? 1 : 2) * 2 * 64 * 4; }
+constexpr int search_lds_words(int tiles) { return kSearchBatch * kHistStride + search_part_words(tiles) + 4 * kSearchBatch + kSearchBatch * 2; }
 __device__ __forceinline__ SearchLds search_lds(uint32_t* base, int tiles) {
     SearchLds s;
     s.hist = base;
-    s.part = reinterpret_cast<float*>(base + kBatch * kHistStride);
-    s.least = s.part + (tiles <= 2 ? kPartWords : 0);
-    s.left = reinterpret_cast<uint16_t*>(s.least + kEncWaves * kBatch);
+    s.part = reinterpret_cast<float4_t*>(base + kSearchBatch * kHistStride);
+    s.least = reinterpret_cast<float*>(base + kSearchBatch * kHistStride + search_part_words(tiles));
+    s.left = reinterpret_cast<uint16_t*>(s.least + 4 * kSearchBatch);
     return s;
 }
 
-// A wavefront's share of the matrix product: with kTiles tiles of 16 patterns, kParts wavefronts share a tile, each over
-// its own part of the bins.  The operands stay in registers for as long as the workgroup lives.
+// A wavefront's operands of the matrix product; they stay in registers for as long as the workgroup lives.
 template <int kTiles>
 struct Coefs {
-    static constexpr int kParts = kTiles == 1 ? 4 : kTiles == 2 ? 2 : 1;
+    static constexpr int kParts = search_parts(kTiles);
     static constexpr int kBlocks = ecco::kSearchBlocks / kParts;
     uint4 w[kBlocks * 3];
     __device__ __forceinline__ void load(const uint32_t* __restrict__ coef, int wave, int tiles, int lane) {
@@ -251,80 +266,83 @@ __device__ __forceinline__ void convert_hist(uint32_t* rows, int lane) {
 template <int kTiles>
 __device__ __forceinline__ uint64_t patterns_left(const SearchLds& L, const Coefs<kTiles>& C, int tiles, int wave, int lane) {
     constexpr int kParts = Coefs<kTiles>::kParts, kBlocks = Coefs<kTiles>::kBlocks;
-    const int tile = wave / kParts;
-    float4_t sum = {0.0f, 0.0f, 0.0f, 0.0f}, err = {0.0f, 0.0f, 0.0f, 0.0f};
+    const int tile = wave / kParts, part = wave % kParts;
+    float4_t sum[2], err[2];  // of groups 0..15 and 16..31
     __syncthreads();
-    if (tile < tiles) {
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        sum[m] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        err[m] = sum[m];
         // row l % 16 of the A operand; bins 4 (l / 16) .. + 3 of each 16
-        const uint4* a = reinterpret_cast<const uint4*>(L.hist + (lane & 15) * kHistStride + (wave % kParts) * kBlocks * 32 + 4 * (lane >> 4));
+        const uint4* a = reinterpret_cast<const uint4*>(L.hist + (16 * m + (lane & 15)) * kHistStride + part * kBlocks * 32 + 4 * (lane >> 4));
 #pragma unroll
         for (int j = 0; j < kBlocks; ++j) {
             const uint4 a0 = a[j * 8], a1 = a[j * 8 + 4];
             // the counts alone: the upper halves of the eight words
             const uint4 n = make_uint4(__builtin_amdgcn_perm(a0.y, a0.x, 0x07060302u), __builtin_amdgcn_perm(a0.w, a0.z, 0x07060302u),
                                        __builtin_amdgcn_perm(a1.y, a1.x, 0x07060302u), __builtin_amdgcn_perm(a1.w, a1.z, 0x07060302u));
-            sum = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a0), __builtin_bit_cast(half8_t, C.w[3 * j]), sum, 0, 0, 0);
-            err = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, n), __builtin_bit_cast(half8_t, C.w[3 * j + 2]), err, 0, 0, 0);
-            sum = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a1), __builtin_bit_cast(half8_t, C.w[3 * j + 1]), sum, 0, 0, 0);
+            sum[m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a0), __builtin_bit_cast(half8_t, C.w[3 * j]), sum[m], 0, 0, 0);
+            err[m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, n), __builtin_bit_cast(half8_t, C.w[3 * j + 2]), err[m], 0, 0, 0);
+            sum[m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a1), __builtin_bit_cast(half8_t, C.w[3 * j + 1]), sum[m], 0, 0, 0);
         }
     }
-    if (kParts > 1) {
-        float* mine = L.part + wave * 512 + lane;
+    // parts 0 and 1 of a tile of patterns add up the parts for groups 0..15 and 16..31
+    float4_t s, e;
+    if (kParts == 2) {
+        L.part[(wave * 2) * 64 + lane] = part ? sum[0] : sum[1];
+        L.part[(wave * 2 + 1) * 64 + lane] = part ? err[0] : err[1];
+        __syncthreads();
+        s = (part ? sum[1] : sum[0]) + L.part[((wave ^ 1) * 2) * 64 + lane];
+        e = (part ? err[1] : err[0]) + L.part[((wave ^ 1) * 2 + 1) * 64 + lane];
+    } else {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            mine[j * 64] = sum[j];
-            mine[(4 + j) * 64] = err[j];
+        for (int m = 0; m < 2; ++m) {
+            L.part[((wave * 2 + m) * 2) * 64 + lane] = sum[m];
+            L.part[((wave * 2 + m) * 2 + 1) * 64 + lane] = err[m];
         }
         __syncthreads();
-        const float* first = L.part + tile * kParts * 512 + lane;
+        const float4_t* at = L.part + (tile * kParts * 4 + min(part, 1) * 2) * 64 + lane;
+        s = at[0];
+        e = at[64];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            sum[j] = first[j * 64];
-            err[j] = first[(4 + j) * 64];
-#pragma unroll
-            for (int p = 1; p < kParts; ++p) {
-                sum[j] += first[p * 512 + j * 64];
-                err[j] += first[p * 512 + (4 + j) * 64];
-            }
+        for (int q = 1; q < kParts; ++q) {
+            s += at[q * 256];
+            e += at[q * 256 + 64];
         }
     }
-    // lane l, register j: group 4 (l / 16) + j of the batch, pattern 16 tile + l % 16
+    // lane l, register j: group 16 part + 4 (l / 16) + j of the batch, pattern 16 tile + l % 16
+    const bool mine = part < 2;
     float least[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         // the FP32 sums that decide differ from the true ones by less than 2^-18 of the error, what all patterns share included
-        err[j] += fabsf(sum[j]) * 0x1p-16f + 0x1p-12f;
-        sum[j] += 16.0f;  // the bound with what is shared left out can be below zero, by less than 3
-        least[j] = row_min_pos(sum[j] + err[j]);
+        e[j] += fabsf(s[j]) * 0x1p-16f + 0x1p-12f;
+        s[j] += 16.0f;  // the bound with what is shared left out can be below zero, by less than 3
+        least[j] = row_min_pos(s[j] + e[j]);
     }
     if (kTiles > 1) {
-        if ((lane & 15) == 0)
+        if (mine && (lane & 15) == 0)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) L.least[wave * kBatch + 4 * (lane >> 4) + j] = tile < tiles ? least[j] : __builtin_inff();
+            for (int j = 0; j < 4; ++j) L.least[tile * kSearchBatch + 16 * part + 4 * (lane >> 4) + j] = tile < tiles ? least[j] : __builtin_inff();
         __syncthreads();
+        const float* at = L.least + 16 * min(part, 1) + 4 * (lane >> 4);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const float* at = L.least + 4 * (lane >> 4) + j;
-            least[j] = fminf(fminf(at[0], at[kBatch]), fminf(at[2 * kBatch], at[3 * kBatch]));
+            least[j] = fminf(at[j], at[kSearchBatch + j]);
+            if (kTiles > 2) least[j] = fminf(least[j], fminf(at[2 * kSearchBatch + j], at[3 * kSearchBatch + j]));
         }
     }
     uint64_t left[4];  // register j: 16 bits for each of the groups j, 4 + j, 8 + j, 12 + j
 #pragma unroll
-    for (int j = 0; j < 4; ++j) left[j] = __builtin_amdgcn_ballot_w64(sum[j] - err[j] <= least[j]);
-    const int row = lane >> 4;
-    if (kTiles == 1) {  // every wavefront has all of it: group 4 wave + row
-        const uint64_t m = row == 0 ? left[0] : row == 1 ? left[1] : row == 2 ? left[2] : left[3];
-        return (m >> (16 * wave)) & 0xFFFFull;
-    }
-    if (lane < kBatch && wave % kParts == 0) {  // lane g writes group g = 4 r + j
+    for (int j = 0; j < 4; ++j) left[j] = __builtin_amdgcn_ballot_w64(s[j] - e[j] <= least[j]);
+    if (mine && lane < 16) {  // lane g writes group g = 4 r + j
         const int j = lane & 3;
         const uint64_t m = j == 0 ? left[0] : j == 1 ? left[1] : j == 2 ? left[2] : left[3];
-        L.left[lane * 4 + tile] = tile < tiles ? (uint16_t)(m >> (16 * (lane >> 2))) : (uint16_t)0;
+        L.left[(16 * part + lane) * 4 + tile] = tile < tiles ? (uint16_t)(m >> (16 * (lane >> 2))) : (uint16_t)0;
     }
     __syncthreads();
-    uint64_t m = *reinterpret_cast<const uint64_t*>(L.left + (wave * kWaveRows + row) * 4);
-    if (kParts == 2) m &= 0xFFFFFFFFull;  // tiles 2 and 3 do not exist
-    return m;
+    const uint64_t m = *reinterpret_cast<const uint64_t*>(L.left + (wave * kWaveRows + (lane >> 4)) * 4);
+    return kTiles == 1 ? m & 0xFFFFull : kTiles == 2 ? m & 0xFFFFFFFFull : m;  // tiles that do not exist are not written
 }
 
 }  // namespace ecco_rows
