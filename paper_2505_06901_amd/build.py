@@ -10,7 +10,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libecco.so")
 PROBES = ["probe_lds", "probe_last_vgpr"]  # stand-alone measurement programs (csrc/<name>.hip), not part of the library
-SOURCES = ["ecco_fit.cpp", "ecco_model.cpp", "ecco_pb_model.cpp", "ecco_kernels.hip", "ecco_encode.hip", "ecco_act.hip", "ecco_pb_kernels.hip"]
+SOURCES = ["ecco_fit.cpp", "ecco_model.cpp", "ecco_pb_model.cpp", "ecco_kernels.hip", "ecco_encode.hip", "ecco_act.hip", "ecco_pb_kernels.hip", "ecco_pb_encode.hip"]
 
 
 def _hipcc() -> str:

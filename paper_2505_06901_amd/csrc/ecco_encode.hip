@@ -88,15 +88,6 @@ __device__ __forceinline__ EncTables stage_enc_tables(uint32_t* lds, const uint3
     return t;
 }
 
-// the values of group `local` of batch b (the last group's beyond the end)
-template <int kBatch>
-__device__ __forceinline__ void load_values(RowValues& v, const uint32_t* src, size_t groups, size_t b, int local, int l) {
-    const size_t first = min(b * kBatch, groups - 1);  // uniform
-    const int last = (int)min(groups - 1 - first, (size_t)(kBatch - 1));
-    const u32x4_dword t = *reinterpret_cast<const u32x4_dword*>(src + first * (kGroup / 2) + (min(local, last) * kRowLanes + l) * 4);
-    v.x[0] = t.x; v.x[1] = t.y; v.x[2] = t.z; v.x[3] = t.w;
-}
-
 // Packs the row's group with the codes `enc` of its pattern: lane l returns payload word l and the meta word.  idx: the
 // lane's eight indices as nibbles, which is also the lane's payload word in raw mode.  image: 18 words of LDS of the row.
 template <bool kLong>
@@ -143,7 +134,7 @@ __device__ __forceinline__ uint32_t pack_row(const uint32_t* enc, uint32_t* imag
 }
 
 // ---- the full search ---------------------------------------------------------------------------------------------------
-constexpr size_t search_lds_bytes(int S) { return ((size_t)S * kTableWords + search_lds_words(search_tiles(S))) * 4; }
+constexpr size_t search_lds_bytes(int S) { return ((size_t)S * kTableWords + search_lds_words<false>(search_tiles(S))) * 4; }
 
 template <int kTiles, bool kLong, class Io>
 __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(4))) void encode_search_kernel(Job<Io> j0, Job<Io> j1) {
@@ -153,7 +144,7 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
     const Io io = job.io;
     const int lane = threadIdx.x & 63, l = lane & 15, row = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const SearchLds L = search_lds(smem + S * kTableWords, kTiles);
+    const SearchLds L = search_lds<false>(smem + S * kTableWords, kTiles);
     uint32_t* hist = L.hist + (wave * kWaveRows + row) * kHistStride;
     const size_t batches = (io.groups() + kSearchBatch - 1) / kSearchBatch;
     RowValues v;
@@ -171,7 +162,7 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
         set_bins<true>(v, kSearchStep * __builtin_amdgcn_rcpf(s), hist, -1);
         wave_fence();
         convert_hist(L.hist + wave * kWaveRows * kHistStride, lane);
-        uint64_t left = patterns_left<kTiles>(L, C, tiles, wave, lane);
+        uint64_t left = patterns_left<kTiles, false>(L, C, tiles, wave, lane);
         const bool plain = !(s >= kSearchLeastScale);  // all patterns, value by value
         if (plain) left = S == 64 ? ~0ull : (1ull << S) - 1ull;
         uint32_t pattern = 0, idx = 0;
@@ -300,25 +291,28 @@ int launch_encode(bool minmax, const ecco_model* m0, const Io& io0, const ecco_m
     const int S = std::max(m0->S, m1->S);
     const bool lng = std::max(m0->max_len, m1->max_len) > 8;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const auto run = [&](auto kernel, size_t lds, int batch, int threads, int per_cu) {
+    const auto run = [&](auto kernel, size_t lds, int batch, int threads, int per_cu) -> int {
+        const int rc = allow_lds(kernel, m0->device, lds);
+        if (rc != ECCO_OK) return rc;
         const size_t wgs = (groups + batch - 1) / batch;
         const dim3 grid((unsigned)std::min<size_t>(wgs, (size_t)cu_count(m0->device) * per_cu), jobs);
         hipLaunchKernelGGL(kernel, grid, dim3(threads), lds, st, j0, j1);
+        ECCO_HIP_CHECK(hipGetLastError());
+        return ECCO_OK;
     };
+    int rc;
     if (minmax) {
         const size_t lds = minmax_lds_bytes(S);
-        if (lng) run(encode_minmax_kernel<true, Io>, lds, kMinmaxBatch, kMinmaxThreads, 6);
-        else run(encode_minmax_kernel<false, Io>, lds, kMinmaxBatch, kMinmaxThreads, 6);
+        rc = lng ? run(encode_minmax_kernel<true, Io>, lds, kMinmaxBatch, kMinmaxThreads, 6) : run(encode_minmax_kernel<false, Io>, lds, kMinmaxBatch, kMinmaxThreads, 6);
     } else {
         const size_t lds = search_lds_bytes(S);
         switch (search_tiles(S)) {
-            case 1: lng ? run(encode_search_kernel<1, true, Io>, lds, kSearchBatch, kSearchThreads, 2) : run(encode_search_kernel<1, false, Io>, lds, kSearchBatch, kSearchThreads, 2); break;
-            case 2: lng ? run(encode_search_kernel<2, true, Io>, lds, kSearchBatch, kSearchThreads, 2) : run(encode_search_kernel<2, false, Io>, lds, kSearchBatch, kSearchThreads, 2); break;
-            default: lng ? run(encode_search_kernel<4, true, Io>, lds, kSearchBatch, kSearchThreads, 2) : run(encode_search_kernel<4, false, Io>, lds, kSearchBatch, kSearchThreads, 2);
+            case 1: rc = lng ? run(encode_search_kernel<1, true, Io>, lds, kSearchBatch, kSearchThreads, 2) : run(encode_search_kernel<1, false, Io>, lds, kSearchBatch, kSearchThreads, 2); break;
+            case 2: rc = lng ? run(encode_search_kernel<2, true, Io>, lds, kSearchBatch, kSearchThreads, 2) : run(encode_search_kernel<2, false, Io>, lds, kSearchBatch, kSearchThreads, 2); break;
+            default: rc = lng ? run(encode_search_kernel<4, true, Io>, lds, kSearchBatch, kSearchThreads, 2) : run(encode_search_kernel<4, false, Io>, lds, kSearchBatch, kSearchThreads, 2);
         }
     }
-    ECCO_HIP_CHECK(hipGetLastError());
-    return ECCO_OK;
+    return rc;
 }
 
 int encode_common(bool minmax, const ecco_model* m, const uint16_t* src, size_t n_groups, void* blocks, uint32_t* meta, void* stream) {

@@ -1228,23 +1228,6 @@ float* scratch_on_current_device(int device) {
 }
 
 // ---- host side -----------------------------------------------------------------------------------------
-// A kernel that needs more than 64 KB of LDS has to be told so; the attribute belongs to the kernel (on the
-// current device), not to a launch, so it is set the first time a kernel is launched on a device -- to the most
-// any launch can ask for -- and remembered (a short list under a mutex: host threads may enter together).
-int allow_lds_once(const void* kernel, int device, size_t bytes) {
-    if (bytes <= 64 * 1024) return ECCO_OK;
-    static std::mutex lock;
-    static std::vector<std::pair<const void*, int>> done;
-    std::lock_guard<std::mutex> hold(lock);
-    for (const auto& d : done)
-        if (d.first == kernel && d.second == device) return ECCO_OK;
-    ECCO_HIP_CHECK(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
-    done.emplace_back(kernel, device);
-    return ECCO_OK;
-}
-template <class K>
-int allow_lds(K kernel, int device, size_t bytes) { return allow_lds_once(reinterpret_cast<const void*>(kernel), device, bytes); }
-
 }  // namespace
 
 namespace ecco {
@@ -1258,6 +1241,21 @@ int cu_count(int device) {
         cached[device].store(n, std::memory_order_relaxed);
     }
     return n;
+}
+
+// A kernel that needs more than 64 KB of LDS has to be told so; the attribute belongs to the kernel (on the
+// current device), not to a launch, so it is set the first time a kernel is launched on a device -- to the most
+// any launch can ask for -- and remembered (a short list under a mutex: host threads may enter together).
+int allow_lds_once(const void* kernel, int device, size_t bytes) {
+    if (bytes <= 64 * 1024) return ECCO_OK;
+    static std::mutex lock;
+    static std::vector<std::pair<const void*, int>> done;
+    std::lock_guard<std::mutex> hold(lock);
+    for (const auto& d : done)
+        if (d.first == kernel && d.second == device) return ECCO_OK;
+    ECCO_HIP_CHECK(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+    done.emplace_back(kernel, device);
+    return ECCO_OK;
 }
 
 // Called by ecco_model_to_device with `device` current: asks for the scratch array's address on that device, so that

@@ -25,4 +25,9 @@ inline int model_ready(const ecco_model* m) {
 // compute units of a device, asked once per device (defined in ecco_kernels.hip)
 int cu_count(int device);
 
+// tells the runtime, once per kernel and device, that the kernel may use more than 64 KB of LDS (defined in ecco_kernels.hip)
+int allow_lds_once(const void* kernel, int device, size_t bytes);
+template <class K>
+int allow_lds(K kernel, int device, size_t bytes) { return allow_lds_once(reinterpret_cast<const void*>(kernel), device, bytes); }
+
 }  // namespace ecco

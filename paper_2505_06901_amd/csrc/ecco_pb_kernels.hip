@@ -1,4 +1,4 @@
-// Decoder and encoder of the self-contained 4x block (include/ecco_paper_block.h) for gfx950.
+// Decoder of the self-contained 4x block (include/ecco_paper_block.h) for gfx950.
 //
 // Decoder: the block has one code stream of 128 values behind a variable-length header, so a lane owns a whole
 // block: 64 blocks (4 KB) per wavefront pass, loaded with 16-byte pieces on consecutive addresses into a private
@@ -9,13 +9,6 @@
 // lane at a time, as 64-byte pieces (four lanes per block).  The padded entries are only known when the stream
 // has been walked to its end: the lane then overwrites those positions in global memory, after the wavefront's
 // earlier stores have completed.
-//
-// Encoder: one wavefront per group, two values per lane, the same search and packing scheme as the other
-// format's encoder (reconstructed centroids in LDS, nearest value by a strict-< scan, balanced FP32 error tree,
-// bit positions by a wavefront scan, payload assembled with LDS atomic OR), plus: the element of largest
-// magnitude takes index 15 and no error; the codebook is the one of least total length; the stream is cut at
-// bit 512; if it ends before, the largest remaining magnitudes are found one by one (a wavefront maximum over a
-// key of magnitude and position) and appended as 15-bit entries.
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 
@@ -23,15 +16,13 @@
 #include <cstdint>
 #include <type_traits>
 
-#include "ecco_pb_internal.h"
+#include "ecco_pb_launch.h"
 
 namespace {
 
 using namespace ecco_pb;
 
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
-
-#define ECCO_HIP_CHECK(expr) do { if ((expr) != hipSuccess) return ECCO_EHIP; } while (0)
 
 constexpr int kSlot = kBlockWords + 1;    // LDS words per staged block; the last one is a zero pad
 constexpr int kUnit = 64;                 // blocks per wavefront pass, one per lane
@@ -205,25 +196,6 @@ __device__ __forceinline__ float wave_tree_sum(float t) {
     return __fadd_rn(__fadd_rn(g(lane_u32(f(t), 0)), g(lane_u32(f(t), 16))), __fadd_rn(g(lane_u32(f(t), 32)), g(lane_u32(f(t), 48))));
 }
 
-// Sixteen such sums at once: at each of the first four levels a lane keeps the half of its entries that matches its
-// own lane bit and sends the other half to its partner (lanes l and l ^ 1, ^ 2, ^ 4, ^ 8), then the two remaining
-// levels (^ 16, ^ 32) on the one entry left: lane l returns the total of entry l & 15, summed in the same tree.
-__device__ __forceinline__ float wave_tree_sum16(const float (&q)[16], int lane) {
-    const auto x1 = [](float v) { return __uint_as_float(dpp_u32<0xB1>(__float_as_uint(v))); };
-    const auto x2 = [](float v) { return __uint_as_float(dpp_u32<0x4E>(__float_as_uint(v))); };
-    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4, b3 = lane & 8;
-    float a[8], b[4], c[2];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) a[i] = __fadd_rn(b0 ? q[2 * i + 1] : q[2 * i], x1(b0 ? q[2 * i] : q[2 * i + 1]));
-#pragma unroll
-    for (int i = 0; i < 4; ++i) b[i] = __fadd_rn(b1 ? a[2 * i + 1] : a[2 * i], x2(b1 ? a[2 * i] : a[2 * i + 1]));
-#pragma unroll
-    for (int i = 0; i < 2; ++i) c[i] = __fadd_rn(b2 ? b[2 * i + 1] : b[2 * i], __shfl_xor(b2 ? b[2 * i] : b[2 * i + 1], 4));
-    float t = __fadd_rn(b3 ? c[1] : c[0], __shfl_xor(b3 ? c[0] : c[1], 8));
-    t = __fadd_rn(t, __shfl_xor(t, 16));
-    return __fadd_rn(t, __shfl_xor(t, 32));
-}
-
 // ---- decode fused into the matrix-vector product --------------------------------------------------------------------
 // y = W x without writing W: a workgroup owns a band of rows (its blocks are consecutive in memory); a wavefront
 // takes 64 consecutive blocks of the band at a time, one per lane, exactly as the decoder does.  The lane keeps the
@@ -377,217 +349,9 @@ __global__ __launch_bounds__(kGvThreads) void pb_gemv_kernel(const uint32_t* __r
     }
 }
 
-// ---- encoder ---------------------------------------------------------------------------------------------------
-constexpr int kEncThreads = 256;
-constexpr int kEncWaves = kEncThreads / 64;
-constexpr int kBitWords = kBlockWords + 2;
-
-__device__ __forceinline__ float half_bits_f(uint32_t bits) { return __half2float(__ushort_as_half((unsigned short)bits)); }
-
-// v to the format's 8-bit float: nearest, ties to the even code, saturating at +-480
-__device__ __forceinline__ uint32_t fp8_round_dev(float v) {
-    const uint32_t sign = (__float_as_uint(v) >> 24) & 0x80u;
-    const float a = fabsf(v);
-    uint32_t code;
-    if (a < 0.015625f) {
-        code = (uint32_t)rintf(a * 512.0f);  // below 2^-6 the values are multiples of 2^-9; 8 is the smallest normal number
-    } else {
-        const uint32_t b = __float_as_uint(a);
-        const uint32_t r = b + 0x7FFFFu + ((b >> 20) & 1u);  // to three mantissa bits, ties to even
-        const int e = (int)(r >> 23) - 120;
-        code = e > 15 ? 127u : (((uint32_t)e << 3) | ((r >> 20) & 7u));
-    }
-    return sign | code;
-}
-
-inline size_t enc_lds_bytes(int S) { return (DevLayout{S}.encode_words() + (size_t)kEncWaves * ((size_t)S * 16 + kBitWords)) * 4; }
-
-// ORs the low `nbits` of `value` into the block image at stream bit `at`, most significant bit first; bits at or
-// beyond 512 are dropped (the cut)
-__device__ __forceinline__ void put_bits(uint32_t* bits, uint32_t at, uint32_t value, uint32_t nbits) {
-    const uint64_t v = (uint64_t)value << (64u - nbits - (at & 31u));
-    const uint32_t wi = at >> 5;
-    if (wi < (uint32_t)kBlockWords && (uint32_t)(v >> 32) != 0u) atomicOr(&bits[wi], (uint32_t)(v >> 32));
-    if (wi + 1 < (uint32_t)kBlockWords && (uint32_t)v != 0u) atomicOr(&bits[wi + 1], (uint32_t)v);
-}
-
-__global__ __launch_bounds__(kEncThreads) void pb_encode_kernel(const uint32_t* __restrict__ dev, int S, float inv_tscale,
-                                                               const uint32_t* __restrict__ src, size_t n_groups,
-                                                               uint32_t* __restrict__ blocks) {
-    extern __shared__ __align__(16) uint32_t smem[];
-    const DevLayout D{S};
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    stage_words(smem, dev + D.cent(), (int)D.encode_words());
-    __syncthreads();
-    const uint16_t* cent = reinterpret_cast<const uint16_t*>(smem);                                   // [S][16]
-    const uint16_t* fp8 = reinterpret_cast<const uint16_t*>(smem + (D.fp8() - D.cent()));             // [256]
-    const uint32_t* enc = smem + (D.enc() - D.cent());                                                // [S * 4][16]
-    const uint32_t* kpenc = smem + (D.kpenc() - D.cent());                                            // [S]
-    float* recon = reinterpret_cast<float*>(smem + D.encode_words()) + wave * (S * 16 + kBitWords);   // [S][16], this wavefront's
-    uint32_t* bits = reinterpret_cast<uint32_t*>(recon + S * 16);                                     // [18]
-    const auto umax = [](uint32_t a, uint32_t b) { return max(a, b); };
-    const auto uadd = [](uint32_t a, uint32_t b) { return a + b; };
-
-    for (size_t g = (size_t)blockIdx.x * kEncWaves + wave; g < n_groups; g += (size_t)gridDim.x * kEncWaves) {
-        const uint32_t pair = src[g * (kGroup / 2) + lane];
-        const uint32_t hx0 = pair & 0xFFFFu, hx1 = pair >> 16;                   // values 2l and 2l + 1
-        // the element of largest magnitude, first position on ties: largest key of (magnitude, 127 - position)
-        const uint32_t pos0 = 2u * lane, pos1 = pos0 + 1u;
-        uint32_t key0 = ((hx0 & 0x7FFFu) << 7) | (127u - pos0), key1 = ((hx1 & 0x7FFFu) << 7) | (127u - pos1);
-        const uint32_t top = wave_all_u32(max(key0, key1), umax);
-        const uint32_t a = 127u - (top & 127u);
-        const uint32_t xa = lane_u32((a & 1u) ? hx1 : hx0, (int)(a >> 1));
-        const uint32_t s8 = fp8_round_dev(half_bits_f(xa) * inv_tscale);
-        const uint32_t sv = fp8[s8];
-        const float s = half_bits_f(sv & 0x7FFFu);
-        const float x0 = half_bits_f(hx0), x1 = half_bits_f(hx1);
-        const bool is0 = pos0 == a, is1 = pos1 == a;
-        // reconstructed centroids of every pattern
-        for (int i = lane; i < S * 16; i += 64) recon[i] = half_bits_f((uint32_t)__half_as_ushort(__float2half_rn(half_bits_f(cent[i]) * s)));
-        if (lane < kBitWords) bits[lane] = 0u;
-        wave_lds_fence();
-        // pattern of least squared error over the other 127 elements
-        // Rating a pattern needs every element's least distance, not the index that attains it (the squared error is
-        // that distance squared): a subtraction per candidate and a three-way minimum per two candidates.  The index
-        // scan runs once, for the winner.
-        // Sixteen patterns at a time: q[e] is this lane's part of the squared error of pattern pb + e; the sixteen sums
-        // over the wavefront are formed together (wave_tree_sum16: lane l ends up with the total of pattern
-        // pb + (l & 15)), every lane keeps the least it has seen, and the lanes are compared at the end.
-        float mine = __builtin_inff();
-        int mine_p = 0;
-        for (int pb = 0; pb < S; pb += 16) {
-            float q[16];
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                q[e] = __builtin_inff();
-                if (pb + e < S) {  // uniform
-                    const float* r = recon + (pb + e) * 16;
-                    float d0 = fabsf(__fsub_rn(x0, r[0])), d1 = fabsf(__fsub_rn(x1, r[0]));
-                    static_assert(kCent % 2 == 1, "candidates 1 .. kCent - 1 in pairs");
-#pragma unroll
-                    for (int k = 1; k < kCent; k += 2) {
-                        const float ra = r[k], rb = r[k + 1];
-                        d0 = fminf(fminf(d0, fabsf(__fsub_rn(x0, ra))), fabsf(__fsub_rn(x0, rb)));
-                        d1 = fminf(fminf(d1, fabsf(__fsub_rn(x1, ra))), fabsf(__fsub_rn(x1, rb)));
-                    }
-                    const float q0 = is0 ? 0.0f : __fmul_rn(d0, d0), q1 = is1 ? 0.0f : __fmul_rn(d1, d1);
-                    q[e] = __fadd_rn(q0, q1);
-                }
-            }
-            const float t = wave_tree_sum16(q, lane);
-            if (t < mine) {  // strict <: an earlier batch keeps a tie
-                mine = t;
-                mine_p = pb + (lane & 15);
-            }
-        }
-        // least sum over the lanes, and the lowest pattern among the lanes that hold it
-        const float least = __uint_as_float(wave_all_u32(__float_as_uint(mine), [](uint32_t a, uint32_t b) { return __float_as_uint(fminf(__uint_as_float(a), __uint_as_float(b))); }));
-        const uint32_t cand = (mine == least && mine_p < S) ? (uint32_t)mine_p : 0x7FFFFFFFu;
-        const uint32_t win = wave_all_u32(cand, [](uint32_t a, uint32_t b) { return min(a, b); });
-        const int best_p = win < (uint32_t)S ? (int)win : 0;
-        uint32_t best_idx;
-        {
-            // the reconstructed values ascend with k and FP32 rounding is monotone, so the distance falls (weakly) to its
-            // least value and rises (weakly) after it: the first index of the least distance -- what a scan with a strict <
-            // finds -- is the last k at which the distance strictly drops
-            const float* r = recon + best_p * 16;
-            float d0 = fabsf(__fsub_rn(x0, r[0])), d1 = fabsf(__fsub_rn(x1, r[0]));
-            uint32_t k0 = 0, k1 = 0;
-#pragma unroll
-            for (int k = 1; k < kCent; ++k) {
-                const float rk = r[k];
-                const float u = fabsf(__fsub_rn(x0, rk)), v = fabsf(__fsub_rn(x1, rk));
-                k0 = u < d0 ? (uint32_t)k : k0;
-                k1 = v < d1 ? (uint32_t)k : k1;
-                d0 = u;
-                d1 = v;
-            }
-            best_idx = k0 | (k1 << 4);
-        }
-        const uint32_t i0 = is0 ? 15u : (best_idx & 15u), i1 = is1 ? 15u : (best_idx >> 4);
-        // the codebook of least total length
-        uint32_t c0 = 0, c1 = 0, best_total = 0;
-        int best_h = 0;
-        for (int h = 0; h < kBooks; ++h) {
-            const uint32_t* t = enc + (best_p * kBooks + h) * kSym;
-            const uint32_t a0 = t[i0], a1 = t[i1];
-            const uint32_t total = wave_all_u32((a0 >> 16) + (a1 >> 16), uadd);
-            if (h == 0 || total < best_total) {
-                best_total = total;
-                best_h = h;
-                c0 = a0;
-                c1 = a1;
-            }
-        }
-        // header, then the codes at their positions (inclusive scan of the lengths over the lanes)
-        const uint32_t kp = kpenc[best_p], base = 10u + (kp >> 16);
-        if (lane == 0) bits[0] = (s8 << 24) | ((uint32_t)best_h << 22) | ((kp & 0xFFFFu) << (22u - (kp >> 16)));
-        wave_lds_fence();
-        const uint32_t l0 = c0 >> 16, l1 = c1 >> 16;
-        uint32_t incl = l0 + l1;
-        for (int d = 1; d < 64; d <<= 1) {
-            const uint32_t o = (uint32_t)__shfl_up((int)incl, d);
-            if (lane >= d) incl += o;
-        }
-        put_bits(bits, base + incl - (l0 + l1), ((c0 & 0xFFFFu) << l1) | (c1 & 0xFFFFu), l0 + l1);
-        const uint32_t end = base + best_total;
-        if (end <= (uint32_t)kBlockBits) {
-            // room left: the largest remaining magnitudes, one per round, as (position, 8-bit float) entries
-            const uint32_t slots = ((uint32_t)kBlockBits - end) / kOutlierBits;
-            key0 = is0 ? 0u : key0 + 1u;
-            key1 = is1 ? 0u : key1 + 1u;
-            for (uint32_t j = 0; j < slots; ++j) {
-                const uint32_t best = wave_all_u32(max(key0, key1), umax);
-                if (best == 0u) break;
-                if (key0 == best || key1 == best) {
-                    const bool first = key0 == best;
-                    const uint32_t v8 = fp8_round_dev((first ? x0 : x1) * inv_tscale);
-                    put_bits(bits, end + j * kOutlierBits, ((first ? pos0 : pos1) << 8) | v8, kOutlierBits);
-                    if (first) key0 = 0u; else key1 = 0u;
-                }
-            }
-        }
-        wave_lds_fence();
-        if (lane < kBlockWords) blocks[g * kBlockWords + lane] = bits[lane];
-        wave_lds_fence();
-    }
-}
-
-inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
-// a model can be used once it is on a device, and only while that device is the calling thread's current one: the
-// kernels are launched on the current device and read the model's tables through device pointers
-inline int model_ready(const ecco_pb_model* m) {
-    if (!m || !m->dev || m->device < 0) return ECCO_EINVAL;
-    int cur = -1;
-    return (hipGetDevice(&cur) == hipSuccess && cur == m->device) ? ECCO_OK : ECCO_EINVAL;
-}
-
-template <class K>
-int allow_lds(K kernel, size_t bytes) {
-    if (bytes > 64 * 1024)
-        ECCO_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
-    return ECCO_OK;
-}
-
 }  // namespace
 
 extern "C" {
-
-int ecco_pb_encode(const ecco_pb_model* m, const uint16_t* src, size_t n_groups, void* blocks, void* stream) {
-    if (!m) return ECCO_EINVAL;
-    if (n_groups == 0) return model_ready(m);
-    if (!src || !blocks) return ECCO_EINVAL;
-    if (!aligned(src, 4) || !aligned(blocks, 64)) return ECCO_EALIGN;
-    if (model_ready(m) != ECCO_OK) return ECCO_EINVAL;
-    const size_t wgs = (n_groups + kEncWaves - 1) / kEncWaves;
-    const int grid = (int)std::min<size_t>(wgs, 256 * 16);
-    float inv_tscale = 1.0f;  // 2^-texp, exact
-    for (int i = 0; i < (m->texp < 0 ? -m->texp : m->texp); ++i) inv_tscale *= m->texp < 0 ? 2.0f : 0.5f;
-    hipLaunchKernelGGL(pb_encode_kernel, dim3(grid), dim3(kEncThreads), enc_lds_bytes(m->S), static_cast<hipStream_t>(stream), m->dev, m->S,
-                       inv_tscale, reinterpret_cast<const uint32_t*>(src), n_groups, static_cast<uint32_t*>(blocks));
-    ECCO_HIP_CHECK(hipGetLastError());
-    return ECCO_OK;
-}
 
 int ecco_pb_decode_gemv(const ecco_pb_model* m, const void* blocks, int rows, int cols, const uint16_t* x, float* y, void* stream) {
     if (!m || !blocks || !x || !y) return ECCO_EINVAL;
@@ -602,7 +366,7 @@ int ecco_pb_decode_gemv(const ecco_pb_model* m, const void* blocks, int rows, in
     const size_t lds = gv_lds_bytes(m->S, cols);
     hipStream_t st = static_cast<hipStream_t>(stream);
     auto launch = [&](auto kernel) -> int {
-        const int rc = allow_lds(kernel, lds);
+        const int rc = ecco::allow_lds(kernel, m->device, lds);
         if (rc != ECCO_OK) return rc;
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(kGvThreads), lds, st, m->dev, m->S, static_cast<const uint4*>(blocks), rows, gpr, band,
                            reinterpret_cast<const uint4*>(x), y);
@@ -620,7 +384,7 @@ int ecco_pb_decode(const ecco_pb_model* m, const void* blocks, size_t n_groups, 
     if (!aligned(blocks, 64) || !aligned(dst, 16)) return ECCO_EALIGN;
     if (model_ready(m) != ECCO_OK) return ECCO_EINVAL;
     const size_t lds = dec_lds_bytes(m->S);
-    const int rc = allow_lds(pb_decode_kernel, lds);
+    const int rc = ecco::allow_lds(pb_decode_kernel, m->device, lds);
     if (rc != ECCO_OK) return rc;
     const size_t units = (n_groups + kUnit - 1) / kUnit;
     const int grid = (int)std::min<size_t>((units + kDecWaves - 1) / kDecWaves, 1024);

@@ -69,13 +69,15 @@ void build_image(const ecco_pb_model* m, uint32_t* img) {
     uint16_t* kplut = reinterpret_cast<uint16_t*>(img + D.kplut());
     uint16_t* cent = reinterpret_cast<uint16_t*>(img + D.cent());
     uint16_t* fp8 = reinterpret_cast<uint16_t*>(img + D.fp8());
-    uint32_t* enc = img + D.enc();
+    uint16_t* codes = reinterpret_cast<uint16_t*>(img + D.codes());
+    uint8_t* lens = reinterpret_cast<uint8_t*>(img + D.lens());
     uint32_t* kpenc = img + D.kpenc();
     for (int t = 0; t < m->S * kBooks; ++t)
         for (int k = 0; k < kSym; ++k) {
             const int l = m->lens[t * kSym + k];
             const uint32_t code = m->codes[t * kSym + k];
-            enc[t * kSym + k] = code | ((uint32_t)l << 16);
+            codes[t * kSym + k] = (uint16_t)(code << 8 | (uint32_t)l);
+            lens[((t / kBooks) * kSym + k) * kBooks + t % kBooks] = (uint8_t)l;
             for (uint32_t j = 0; j < (1u << (kMaxLen - l)); ++j) lut[t * 256 + (code << (kMaxLen - l)) + j] = (uint8_t)((k << 4) | l);
         }
     for (int i = 0; i < 256; ++i) kplut[i] = (uint16_t)(((m->S - 1) << 8) | 8);
@@ -90,6 +92,7 @@ void build_image(const ecco_pb_model* m, uint32_t* img) {
         cent[p * 16 + 15] = 0x3C00;  // index 15 stands for the scale itself: 1.0 times the scale
     }
     for (int b = 0; b < 256; ++b) fp8[b] = float_to_half_bits((float)std::ldexp(fp8_value((uint8_t)b), m->texp));  // exact
+    ecco::build_search_tables(m->cent, kCent, kCent, m->S, (double)kSearchStep, img + D.near(), img + D.pair(), img + D.coef());
 }
 
 // ---- fit helpers ------------------------------------------------------------------------------------------

@@ -76,6 +76,15 @@ struct RowValues {
     __device__ __forceinline__ uint32_t bin(int i) const { return (bins[i >> 2] >> (8 * (i & 3))) & 255u; }
 };
 __device__ __forceinline__ _Float16 value(const RowValues& v, int i) { return as_half2(v.x[i >> 1])[i & 1]; }
+// the values of group `local` of batch b (the last group's beyond the end)
+template <int kBatch>
+__device__ __forceinline__ void load_values(RowValues& v, const uint32_t* src, size_t groups, size_t b, int local, int l) {
+    const size_t first = min(b * kBatch, groups - 1);  // uniform
+    const int last = (int)min(groups - 1 - first, (size_t)(kBatch - 1));
+    const u32x4_dword t = *reinterpret_cast<const u32x4_dword*>(src + first * (kRowLanes * 4) + (min(local, last) * kRowLanes + l) * 4);
+    v.x[0] = t.x; v.x[1] = t.y; v.x[2] = t.z; v.x[3] = t.w;
+}
+
 // the largest magnitude of the lane's values, as FP16 bits
 __device__ __forceinline__ uint32_t lane_absmax(const RowValues& v) {
     ushort2_t m = __builtin_bit_cast(ushort2_t, v.x[0] & 0x7FFF7FFFu);
@@ -155,9 +164,12 @@ __device__ __forceinline__ void rate_pattern(const uint8_t* near, uint32_t pair,
         __builtin_amdgcn_sched_barrier(0);
     }
     if (__builtin_amdgcn_ballot_w64((marks & ecco::kNearTwo) != 0u) != 0ull) {
+        // the table addresses are formed again here: kept from above they would take eight registers through the search
+        uint32_t base = lds_address(near);
+        asm volatile("" : "+v"(base));
 #pragma unroll
         for (int i = 0; i < kRowValues; ++i) {
-            const uint32_t nb = near[v.bin(i)];
+            const uint32_t nb = *(const lds_u8*)(size_t)(base + v.bin(i));
             if (nb & ecco::kNearTwo) {
                 const half2_t r = as_half2(lds_word(((nb & 0x3Cu) | pair) + 4u)) * s2;
                 const float d1 = distance<0>(v, i, r), d2 = distance<1>(v, i, r);
@@ -201,7 +213,8 @@ __device__ __forceinline__ void rate_pattern(const uint8_t* near, uint32_t pair,
 
 // ---- bounds on every pattern's error, and the patterns that can be the best ------------------------------------------
 // Workgroup-wide LDS of the bounds: histogram, partial sums of the matrix product, the pattern tiles' least upper bounds,
-// the patterns left per group.
+// the patterns left per group.  kOver: the partial sums lie over the histogram, at the price of a barrier, so that two
+// workgroups with larger tables still fit a compute unit.
 struct SearchLds {
     uint32_t* hist;   // [kSearchBatch][kHistStride]
     float4_t* part;   // [wavefront (and tile of groups)][sum, error][64]
@@ -210,13 +223,16 @@ struct SearchLds {
 };
 // one tile of patterns per 16; the wavefronts share the tiles evenly, each over its own part of the bins
 constexpr int search_parts(int tiles) { return tiles == 1 ? 8 : tiles == 2 ? 4 : 2; }
+static_assert(kSearchWaves * 4 * 64 * 4 <= kSearchBatch * kHistStride, "the partial sums fit over the histogram");
 constexpr int search_part_words(int tiles) { return kSearchWaves * (search_parts(tiles) == 2 ? 1 : 2) * 2 * 64 * 4; }
-constexpr int search_lds_words(int tiles) { return kSearchBatch * kHistStride + search_part_words(tiles) + 4 * kSearchBatch + kSearchBatch * 2; }
+template <bool kOver>
+constexpr int search_lds_words(int tiles) { return kSearchBatch * kHistStride + (kOver ? 0 : search_part_words(tiles)) + 4 * kSearchBatch + kSearchBatch * 2; }
+template <bool kOver>
 __device__ __forceinline__ SearchLds search_lds(uint32_t* base, int tiles) {
     SearchLds s;
     s.hist = base;
-    s.part = reinterpret_cast<float4_t*>(base + kSearchBatch * kHistStride);
-    s.least = reinterpret_cast<float*>(base + kSearchBatch * kHistStride + search_part_words(tiles));
+    s.part = reinterpret_cast<float4_t*>(kOver ? base : base + kSearchBatch * kHistStride);
+    s.least = reinterpret_cast<float*>(base + kSearchBatch * kHistStride + (kOver ? 0 : search_part_words(tiles)));
     s.left = reinterpret_cast<uint16_t*>(s.least + 4 * kSearchBatch);
     return s;
 }
@@ -237,7 +253,9 @@ struct Coefs {
 
 // this wavefront's four rows of the histogram, to "no values"
 __device__ __forceinline__ void clear_hist(uint32_t* rows, int lane) {
-    const uint4 none = make_uint4(0u, 0u, 0u, 0u);
+    uint32_t zero = 0u;  // formed here: a constant in four registers would be kept through the search
+    asm volatile("" : "+v"(zero));
+    const uint4 none = make_uint4(zero, zero, zero, zero);
     constexpr int kPieces = kWaveRows * kHistStride / 4;
 #pragma unroll
     for (int i = 0; i < kPieces / 64; ++i) reinterpret_cast<uint4*>(rows)[i * 64 + lane] = none;
@@ -263,7 +281,7 @@ __device__ __forceinline__ void convert_hist(uint32_t* rows, int lane) {
 
 // For the batch's converted histogram: the patterns of this wavefront's group (wave, row) that can have the least error,
 // one bit each.  Called by all wavefronts of the workgroup together (barriers inside); the histogram is free afterwards.
-template <int kTiles>
+template <int kTiles, bool kOver>
 __device__ __forceinline__ uint64_t patterns_left(const SearchLds& L, const Coefs<kTiles>& C, int tiles, int wave, int lane) {
     constexpr int kParts = Coefs<kTiles>::kParts, kBlocks = Coefs<kTiles>::kBlocks;
     const int tile = wave / kParts, part = wave % kParts;
@@ -286,6 +304,7 @@ __device__ __forceinline__ uint64_t patterns_left(const SearchLds& L, const Coef
             sum[m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a1), __builtin_bit_cast(half8_t, C.w[3 * j + 1]), sum[m], 0, 0, 0);
         }
     }
+    if (kOver) __syncthreads();
     // parts 0 and 1 of a tile of patterns add up the parts for groups 0..15 and 16..31
     float4_t s, e;
     if (kParts == 2) {
