@@ -68,19 +68,25 @@ struct EncTables {
     const uint32_t* enc;
 };
 constexpr int kTableWords = kSearchBins / 4 + 16 + kK;  // per pattern
+__device__ __forceinline__ uint32_t code_word(uint32_t enc) { return ((enc & 0xFFFFu) << 8) | (enc >> 16); }
 template <int kThreads>
 __device__ __forceinline__ EncTables stage_enc_tables(uint32_t* lds, const uint32_t* __restrict__ dev, int S) {
     const DevLayout D{S};
     const uint4* a = reinterpret_cast<const uint4*>(dev + D.near());  // near and pair follow each other
-    uint4* d = reinterpret_cast<uint4*>(lds);
-    const int n0 = S * (kSearchBins / 4 + 16) / 4, n1 = S * kK / 4;
-    for (int i = threadIdx.x; i < n0; i += kThreads) d[i] = a[i];
     const uint4* e = reinterpret_cast<const uint4*>(dev + D.enc());
-    const auto code = [](uint32_t w) { return ((w & 0xFFFFu) << 8) | (w >> 16); };
-    for (int i = threadIdx.x; i < n1; i += kThreads) {
-        const uint4 w = e[i];
-        d[n0 + i] = make_uint4(code(w.x), code(w.y), code(w.z), code(w.w));
-    }
+    uint4* d = reinterpret_cast<uint4*>(lds);
+    const int n0 = S * (kSearchBins / 4 + 16) / 4, n1 = S * kK / 4, tid = threadIdx.x;
+    constexpr int kPieces = kMaxS * (kSearchBins / 4 + 16) / 4 / kThreads + (kMaxS * (kSearchBins / 4 + 16) / 4 % kThreads != 0);
+    static_assert(kMaxS * kK / 4 <= kThreads, "one piece of the codes per thread");
+    // all pieces requested before the first is stored; indices past the end repeat the last piece
+    uint4 v[kPieces];
+    const uint4 w = e[min(tid, n1 - 1)];
+#pragma unroll
+    for (int i = 0; i < kPieces; ++i) v[i] = a[min(tid + i * kThreads, n0 - 1)];
+    if (tid < n1) d[n0 + tid] = make_uint4(code_word(w.x), code_word(w.y), code_word(w.z), code_word(w.w));
+#pragma unroll
+    for (int i = 0; i < kPieces; ++i)
+        if (tid + i * kThreads < n0) d[tid + i * kThreads] = v[i];
     EncTables t;
     t.near = reinterpret_cast<const uint8_t*>(lds);
     t.pair = lds_address(lds + S * (kSearchBins / 4));
@@ -211,7 +217,7 @@ __device__ __forceinline__ half2_t pk_max(half2_t a, half2_t b) {
     asm("v_pk_max_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
     return r;
 }
-__device__ __forceinline__ uint32_t select_minmax(const uint32_t* ends, int S, half2_t s2, const RowValues& v, int l) {
+__device__ __forceinline__ uint32_t select_minmax(const uint32_t* cent, int stride, int S, half2_t s2, const RowValues& v, int l) {
     // (least value, least negated value) of the row
     half2_t lo2 = as_half2(v.x[0]), hi2 = lo2;
 #pragma unroll
@@ -226,7 +232,9 @@ __device__ __forceinline__ uint32_t select_minmax(const uint32_t* ends, int S, h
     float least = __builtin_inff();
     uint32_t at = 0xFFFFu;
     for (int p = l; p < S; p += kRowLanes) {
-        const half2_t e = as_half2(ends[p]) * s2;
+        // first and last centroid: of the words with the ends (stride 1), or of a row of the pattern's pairs
+        const uint32_t c = stride == 1 ? cent[p] : __builtin_amdgcn_perm(cent[p * stride + stride - 1], cent[p * stride], 0x07060100u);
+        const half2_t e = as_half2(c) * s2;
         const float dlo = __fsub_rn(lo, (float)e[0]), dhi = __fsub_rn(hi, (float)e[1]);
         const float f = __fadd_rn(__fmul_rn(dlo, dlo), __fmul_rn(dhi, dhi));
         if (f < least) {
@@ -239,6 +247,119 @@ __device__ __forceinline__ uint32_t select_minmax(const uint32_t* ends, int S, h
     return p < (uint32_t)S ? p : 0u;
 }
 
+// ---- few groups ------------------------------------------------------------------------------------------------------------
+// One workgroup per group: its 16 rows of lanes hold the same values and rate a sixteenth of the patterns each, value by
+// value.  The search above starts with 120 KB of tables per workgroup and passes through four barriers for 32 groups at a
+// time: appending 2 x 256 groups took 9.9 us with it.  Rating with the table of nearest centroids took as long here: among
+// all 64 patterns there are always some whose centroids crowd a bin.  With the min/max selector every row selects alike and only the index step is left to share.
+constexpr int kFewThreads = 256;
+constexpr int kFewRows = kFewThreads / kRowLanes;
+
+// least of d and the distances of x's kX-th half to both halves of r
+template <int kX>
+__device__ __forceinline__ float nearer(float d, uint32_t x, uint32_t r) {
+    const float a = half_diff<kX, 0>(x, r), b = half_diff<kX, 1>(x, r);
+    float m;
+    asm("v_min3_f32 %0, %1, |%2|, |%3|" : "=v"(m) : "v"(d), "v"(a), "v"(b));
+    return m;
+}
+
+template <bool kMinMax, bool kLong, class Io>
+__global__ __launch_bounds__(kFewThreads) void encode_few_kernel(Job<Io> j0, Job<Io> j1) {
+    __shared__ __align__(16) uint32_t cent[kMaxS * kK / 2];  // pairs of neighbouring centroids
+    __shared__ __align__(16) uint32_t enc[kMaxS * kK];
+    __shared__ __align__(16) uint32_t values[kGroup / 2];
+    __shared__ __align__(16) uint8_t index[kGroup];
+    __shared__ uint32_t row_sse[kFewRows], row_pattern[kFewRows], image[20];
+    const Job<Io>& job = blockIdx.y ? j1 : j0;
+    const int S = job.S;
+    const Io io = job.io;
+    const int tid = threadIdx.x, l = tid & 15, row = tid >> 4;
+    const size_t g = blockIdx.x;
+    size_t at;
+    if (!io.place(g, at)) return;  // uniform
+    RowValues v;
+    load_values<1>(v, io.values(), io.groups(), g, 0, l);
+    static_assert(kMaxS * kK / 4 <= kFewThreads, "a piece of each table per thread");
+    {
+        const DevLayout D{S};
+        const int n0 = S * kK / 8, n1 = S * kK / 4;
+        const uint4 c = reinterpret_cast<const uint4*>(job.dev + D.cent())[min(tid, n0 - 1)];
+        const uint4 e = reinterpret_cast<const uint4*>(job.dev + D.enc())[min(tid, n1 - 1)];
+        if (tid < n0) reinterpret_cast<uint4*>(cent)[tid] = c;
+        if (tid < n1) reinterpret_cast<uint4*>(enc)[tid] = make_uint4(code_word(e.x), code_word(e.y), code_word(e.z), code_word(e.w));
+    }
+    if (row == 0) *reinterpret_cast<uint4*>(values + 4 * l) = make_uint4(v.x[0], v.x[1], v.x[2], v.x[3]);
+    const uint32_t smax = row_max(lane_absmax(v));
+    const half2_t s2 = splat_half(smax);
+    __syncthreads();
+    uint32_t win;
+    if (kMinMax) {
+        win = select_minmax(cent, kK / 2, S, s2, v, l);
+    } else {
+        uint32_t pattern = 0;
+        float best = __builtin_inff();
+        for (int p0 = 0; p0 < S; p0 += kFewRows) {
+            const uint32_t p = (uint32_t)min(p0 + row, S - 1);
+            const uint4* c = reinterpret_cast<const uint4*>(cent + p * (kK / 2));
+            const uint4 c0 = c[0], c1 = c[1];
+            const uint32_t pairs[kK / 2] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
+            float d[kRowValues];
+    #pragma unroll
+            for (int i = 0; i < kRowValues; ++i) d[i] = __builtin_inff();
+    #pragma unroll
+            for (int k = 0; k < kK / 2; ++k) {
+                const uint32_t r = __builtin_bit_cast(uint32_t, as_half2(pairs[k]) * s2);
+    #pragma unroll
+                for (int i = 0; i < kRowValues / 2; ++i) {
+                    d[2 * i] = nearer<0>(d[2 * i], v.x[i], r);
+                    d[2 * i + 1] = nearer<1>(d[2 * i + 1], v.x[i], r);
+                }
+            }
+            const float sse = tree_sum(d, -1);
+            if (p0 + row < S && (sse < best || p0 == 0)) {  // strict <: the lowest pattern wins a tie
+                best = sse;
+                pattern = p;
+            }
+        }
+        if (l == 0) {
+            row_sse[row] = __builtin_bit_cast(uint32_t, best);
+            row_pattern[row] = pattern;
+        }
+        __syncthreads();
+        static_assert(kFewRows == kRowLanes, "lane l compares row l");
+        const uint32_t sse_l = row_sse[l], least = row_min(sse_l);
+        win = row_min(sse_l == least ? row_pattern[l] : 0xFFFFFFFFu);
+    }
+    // its indices, a value per thread: the last k at which the distance strictly drops (rate_pattern)
+    if (tid < kGroup) {
+        const uint32_t x = values[tid >> 1] >> (16 * (tid & 1));
+        const uint4* c = reinterpret_cast<const uint4*>(cent + win * (kK / 2));
+        const uint4 c0 = c[0], c1 = c[1];
+        const uint32_t pairs[kK / 2] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
+        uint32_t k = 0;
+        float last = __builtin_inff();
+#pragma unroll
+        for (int j = 0; j < kK / 2; ++j) {
+            const uint32_t r = __builtin_bit_cast(uint32_t, as_half2(pairs[j]) * s2);
+            const float a = fabsf(half_diff<0, 0>(x, r)), b = fabsf(half_diff<0, 1>(x, r));
+            k = a < last ? 2u * j : k;
+            k = b < a ? 2u * j + 1u : k;
+            last = b;
+        }
+        index[tid] = (uint8_t)k;
+    }
+    __syncthreads();
+    if (row != 0) return;
+    const uint2 b = *reinterpret_cast<const uint2*>(index + 8 * l);  // eight indices, a byte each, to nibbles, first on top
+    const auto nibbles = [](uint32_t w) { return (w & 15u) << 12 | (w & 0xF00u) | (w >> 12 & 0xF0u) | (w >> 24 & 15u); };
+    uint32_t mw;
+    const uint32_t word = pack_row<kLong>(enc + win * kK, image, nibbles(b.x) << 16 | nibbles(b.y), l, smax, win, mw);
+    io.blocks[at * kBlockWords + l] = word;
+    if (l == 0) io.meta[at] = mw;
+}
+
+// ---- bulk encoder with the min/max selector --------------------------------------------------------------------------------
 constexpr int kImageStride = 20;  // words per group of the payload being assembled
 constexpr size_t minmax_lds_bytes(int S) { return ((size_t)S * (kTableWords + 1) + kMinmaxBatch * kImageStride + 3) * 4; }
 
@@ -267,7 +388,7 @@ __global__ __launch_bounds__(kMinmaxThreads) void encode_minmax_kernel(Job<Io> j
         const uint32_t smax = row_max(lane_absmax(v));
         const float s = half_bits_f(smax);
         const half2_t s2 = splat_half(smax);
-        const uint32_t pattern = select_minmax(ends, S, s2, v, l);
+        const uint32_t pattern = select_minmax(ends, 1, S, s2, v, l);
         set_bins<false>(v, kSearchStep * __builtin_amdgcn_rcpf(s), nullptr, -1);
         float sse;
         uint32_t idx;
@@ -282,6 +403,13 @@ __global__ __launch_bounds__(kMinmaxThreads) void encode_minmax_kernel(Job<Io> j
 #pragma unroll
         for (int i = 0; i < 4; ++i) v.x[i] = next.x[i];
     }
+}
+
+// Whether a workgroup per group is the faster way.  On 256 compute units it takes 2.9 us + 6.4 ns per group for the full
+// search at S = 64, 2.7 us + 2.1 ns at S = 16, 2.1 us + 1.2 ns with the min/max selector, where the bulk kernels start at
+// 8.5, 6.5 and 3.9 us: the lines cross at 860, 1800 and 1500 groups.
+bool few_groups(bool minmax, size_t groups, int S, int cus) {
+    return minmax ? groups <= (size_t)cus * 6 : groups * (size_t)(S + 24) <= (size_t)cus * 288;
 }
 
 // ---- host side -----------------------------------------------------------------------------------------------------------
@@ -301,7 +429,15 @@ int launch_encode(bool minmax, const ecco_model* m0, const Io& io0, const ecco_m
         return ECCO_OK;
     };
     int rc;
-    if (minmax) {
+    if (few_groups(minmax, groups * jobs, S, cu_count(m0->device))) {
+        const auto few = [&](auto kernel) -> int {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)groups, jobs), dim3(kFewThreads), 0, st, j0, j1);
+            ECCO_HIP_CHECK(hipGetLastError());
+            return ECCO_OK;
+        };
+        if (minmax) rc = lng ? few(encode_few_kernel<true, true, Io>) : few(encode_few_kernel<true, false, Io>);
+        else rc = lng ? few(encode_few_kernel<false, true, Io>) : few(encode_few_kernel<false, false, Io>);
+    } else if (minmax) {
         const size_t lds = minmax_lds_bytes(S);
         rc = lng ? run(encode_minmax_kernel<true, Io>, lds, kMinmaxBatch, kMinmaxThreads, 6) : run(encode_minmax_kernel<false, Io>, lds, kMinmaxBatch, kMinmaxThreads, 6);
     } else {

@@ -135,9 +135,20 @@ typedef __attribute__((address_space(3))) uint8_t lds_u8;
 __device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(size_t)(const lds_u8*)p; }
 __device__ __forceinline__ uint32_t lds_word(uint32_t address) { return *(const lds_u32*)(size_t)address; }
 
+// sum of the squares of the row's 128 distances, in FP32 by the balanced tree over value pairs (i, i ^ 1), (.., i ^ 2), ...;
+// the value whose place is `skip` counts as zero
+__device__ __forceinline__ float tree_sum(const float (&d)[kRowValues], int skip) {
+    float q[kRowValues / 2];
+#pragma unroll
+    for (int i = 0; i < kRowValues / 2; ++i) {
+        const float a = __fmul_rn(d[2 * i], d[2 * i]), b = __fmul_rn(d[2 * i + 1], d[2 * i + 1]);
+        q[i] = __fadd_rn(2 * i == skip ? 0.0f : a, 2 * i + 1 == skip ? 0.0f : b);
+    }
+    return row_all(__fadd_rn(__fadd_rn(q[0], q[1]), __fadd_rn(q[2], q[3])), [](float a, float b) { return __fadd_rn(a, b); });
+}
+
 // The row's values under one pattern: every value's index (the lowest of the nearest reconstructed centroids
-// fp16(c * s)), eight nibbles per lane, first value on top; and the group's squared error, in FP32 by the balanced tree
-// over value pairs (i, i ^ 1), (.., i ^ 2), ... (kSse).  near, pair: the pattern's rows of the tables in LDS (pair as an LDS
+// fp16(c * s)), eight nibbles per lane, first value on top; and the group's squared error (kSse, by tree_sum).  near, pair: the pattern's rows of the tables in LDS (pair as an LDS
 // address, a multiple of 64); plain rows compare every value with all kCent centroids.  A value whose place is `skip` counts as without error, with index 15.
 // The distance falls (weakly) with k up to its least value and rises (weakly) after it, so the lowest nearest index is
 // the last k at which it strictly drops.
@@ -201,13 +212,7 @@ __device__ __forceinline__ void rate_pattern(const uint8_t* near, uint32_t pair,
 #pragma unroll
     for (int i = 0; i < kRowValues; ++i) idx = (idx << 4) | (i == skip ? 15u : k[i]);
     if (kSse) {
-        float q[kRowValues / 2];
-#pragma unroll
-        for (int i = 0; i < kRowValues / 2; ++i) {
-            const float a = __fmul_rn(d[2 * i], d[2 * i]), b = __fmul_rn(d[2 * i + 1], d[2 * i + 1]);
-            q[i] = __fadd_rn(2 * i == skip ? 0.0f : a, 2 * i + 1 == skip ? 0.0f : b);
-        }
-        sse = row_all(__fadd_rn(__fadd_rn(q[0], q[1]), __fadd_rn(q[2], q[3])), [](float a, float b) { return __fadd_rn(a, b); });
+        sse = tree_sum(d, skip);
     }
 }
 

@@ -1,0 +1,104 @@
+"""The encoders' branches against the oracle, blocks and meta words bit-exact: a workgroup per group and the bulk kernels
+(one, two, four tiles of patterns; 32 groups of the full search and 16 of the min/max selector at a time, ragged ends),
+groups for which the search's tables do not hold, patterns with crowded or equal centroids, codes beyond 8 bits."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+import paper_2505_06901_amd as E  # noqa: E402
+from test_paper_block_pins import _model as pb_model  # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch.device("cuda:0")
+
+
+def model_tables(S, seed, long_codes=False):
+    """Patterns of every width: spread over [-1, 1], crowded around 0, with equal neighbours, all equal."""
+    from oracle import oracle as O
+    rng = np.random.default_rng(seed)
+    cent = np.sort(rng.uniform(-1, 1, (S, 16)) * 10.0 ** rng.uniform(-2.5, 0, (S, 1)), axis=1)
+    cent[rng.random((S, 16)) < 0.1] = 0.25
+    cent[S // 2, 5:9] = cent[S // 2, 5]
+    if S > 2:
+        cent[S - 1] = 0.5
+    cent = np.sort(cent, axis=1).astype(np.float16)
+    lens = np.zeros((S, 16), np.uint8)
+    for p in range(S):
+        counts = np.array([int((3.0 if long_codes else 1.5) ** k) + 1 for k in range(16)], np.uint64)[rng.permutation(16)]
+        lens[p] = O.limited_lengths(counts, 12 if long_codes else 8)
+    return cent, lens
+
+
+def groups(cent, n, seed):
+    """Values near a pattern's centroids and Gaussian ones, scales over the whole FP16 range, and degenerate groups."""
+    rng = np.random.default_rng(seed)
+    c = cent.astype(np.float64)[rng.integers(0, len(cent), n)]
+    x = np.take_along_axis(c, rng.integers(0, 16, (n, 128)), axis=1)
+    odd = rng.random(n) < 0.5
+    x[odd] = rng.standard_normal((odd.sum(), 128)) / 3
+    x = x * (1 + 0.01 * rng.standard_normal((n, 128))) * 10.0 ** rng.uniform(-6, 4, (n, 1))
+    x = np.clip(x, -65504, 65504).astype(np.float16)
+    edge = [np.zeros(128), -np.zeros(128), np.full(128, 6e-8), np.full(128, -65504.0), np.linspace(-1, 1, 128), np.linspace(-1, 1, 128) * 4.88e-4,
+            np.linspace(-1, 1, 128) * 4.9e-4, np.where(np.arange(128) == 77, 1000.0, 3e-8), np.repeat([0.5, -0.5], 64)]
+    for i, e in enumerate(edge):
+        x[(i * 37) % n] = e.astype(np.float16)
+    return x
+
+
+@pytest.mark.parametrize("S,n,long_codes", [(1, 1, False), (3, 47, True), (16, 31, False), (16, 4001, False), (17, 2405, True), (33, 3000, False),
+                                            (48, 33, False), (64, 1201, True), (64, 2113, False), (64, 20011, False)])
+def test_encode_and_minmax(dev, S, n, long_codes):
+    from oracle import oracle as O
+    cent, lens = model_tables(S, S, long_codes)
+    m = E.ecco_model_to_device(E.ecco_model_create(cent, lens), 0)
+    x = groups(cent, n, n)
+    t = torch.from_numpy(np.concatenate([np.zeros(2, np.float16), x.reshape(-1)])).to(dev)[2:].view(n, 128)  # 4-byte aligned only
+    for name, want in (("full", O.encode(cent.view(np.uint16), lens, x.view(np.uint16))), ("minmax", O.encode_minmax(cent.view(np.uint16), lens, x.view(np.uint16)))):
+        blocks, meta = (E.ecco_encode if name == "full" else E.ecco_encode_minmax)(m, t)
+        assert np.array_equal(meta.cpu().numpy().view(np.uint32), want[1]), name
+        assert np.array_equal(blocks.cpu().numpy(), want[0]), name
+
+
+@pytest.mark.parametrize("B,H,Sk,Sv", [(3, 5, 16, 64), (7, 37, 33, 16), (16, 64, 64, 16), (16, 96, 3, 17)])
+@pytest.mark.parametrize("minmax", [False, True])
+def test_append_with_unlike_models(dev, B, H, Sk, Sv, minmax):
+    """Keys and values under models of different sizes; sequences whose position lies outside the cache write nothing."""
+    from oracle import oracle as O
+    T = 3
+    models, new, want = [], [], []
+    for S, seed in ((Sk, 1), (Sv, 2)):
+        cent, lens = model_tables(S, seed)
+        models.append(E.ecco_model_to_device(E.ecco_model_create(cent, lens), 0))
+        x = groups(cent, B * H, seed)
+        new.append(torch.from_numpy(x.reshape(B, H, 128)).to(dev))
+        want.append((O.encode_minmax if minmax else O.encode)(cent.view(np.uint16), lens, x.view(np.uint16)))
+    at = np.arange(B, dtype=np.int32) % 5 - 1
+    caches = [torch.full((B, H, T, 64), 0xA5, dtype=torch.uint8, device=dev), torch.full((B, H, T), -3, dtype=torch.int32, device=dev),
+              torch.full((B, H, T, 64), 0xA5, dtype=torch.uint8, device=dev), torch.full((B, H, T), -3, dtype=torch.int32, device=dev)]
+    (E.ecco_kv_append_minmax if minmax else E.ecco_kv_append)(*models, *new, *caches, torch.from_numpy(at).to(dev), B, H, T)
+    for (ob, om), blocks, meta in zip(want, caches[::2], caches[1::2]):
+        eb, em = np.full((B, H, T, 64), 0xA5, np.uint8), np.full((B, H, T), -3, np.int32)
+        for b in range(B):
+            if 0 <= at[b] < T:
+                eb[b, :, at[b]] = ob.reshape(B, H, 64)[b]
+                em[b, :, at[b]] = om.view(np.int32).reshape(B, H)[b]
+        assert np.array_equal(blocks.cpu().numpy(), eb) and np.array_equal(meta.cpu().numpy(), em)
+
+
+@pytest.mark.parametrize("S,n,texp", [(1, 1, -6), (16, 33, -9), (31, 1000, -8), (48, 65, -7), (64, 16421, -9)])
+def test_self_contained_block(dev, S, n, texp):
+    from oracle import paper_block as P
+    om = pb_model(P, S=S, texp=texp, seed=S)
+    m = E.ecco_pb_model_to_device(E.ecco_pb_model_create(om.cent, om.lens, om.kp_lens, om.texp), 0)
+    x = groups(np.pad(om.cent.view(np.float16), ((0, 0), (0, 1)), mode="edge"), n, n)
+    want = P.encode(om, x.view(np.uint16))
+    assert np.array_equal(E.ecco_pb_encode(m, torch.from_numpy(x).to(dev)).cpu().numpy(), want)
