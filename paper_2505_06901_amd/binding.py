@@ -99,17 +99,26 @@ def _check(status: int, where: str):
         raise EccoError(status, where)
 
 
-def _stream():
-    import torch
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+_rt = None  # torch's runtime layer, imported with the first device call
+
+
+def _stream() -> int:
+    """The current stream of the current device, as an integer.  Asked of torch's runtime layer directly: building the
+    Stream object of torch.cuda.current_stream() takes 3 us, as long as a kernel launch."""
+    global _rt
+    if _rt is None:
+        import torch
+        torch.cuda.current_stream()  # initialises
+        _rt = torch._C
+    return _rt._cuda_getCurrentRawStream(_rt._cuda_getDevice())
 
 
 def _dp(t):
-    """Device pointer of a contiguous torch tensor (None -> NULL)."""
+    """Device pointer of a contiguous torch tensor, as an integer (None -> NULL)."""
     if t is None:
-        return C.c_void_p(0)
+        return None
     assert t.is_cuda and t.is_contiguous(), "device tensors must be contiguous CUDA tensors"
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 class Model:
@@ -208,18 +217,18 @@ def ecco_encode_minmax(m: Model, src, blocks=None, meta=None):
 
 
 def ecco_decode(m: Model, blocks, meta, dst=None):
-    import torch
     n = meta.numel()
     if dst is None:
+        import torch
         dst = torch.empty((n, GROUP), dtype=torch.float16, device=blocks.device)
     _check(lib().ecco_decode(m.handle, _dp(blocks), _dp(meta), n, _dp(dst), _stream()), "ecco_decode")
     return dst
 
 
 def ecco_decode_indices(m: Model, blocks, meta, idx=None):
-    import torch
     n = meta.numel()
     if idx is None:
+        import torch
         idx = torch.empty((n, GROUP), dtype=torch.uint8, device=blocks.device)
     _check(lib().ecco_decode_indices(m.handle, _dp(blocks), _dp(meta), n, _dp(idx), _stream()), "ecco_decode_indices")
     return idx
@@ -227,9 +236,9 @@ def ecco_decode_indices(m: Model, blocks, meta, idx=None):
 
 def ecco_decode_gemv(m: Model, blocks, meta, rows: int, cols: int, x, y=None):
     """x: CUDA FP16 [batch, cols]; returns y FP32 [batch, rows]."""
-    import torch
     batch = x.shape[0] if x.dim() == 2 else 1
     if y is None:
+        import torch
         y = torch.empty((batch, rows), dtype=torch.float32, device=x.device)
     _check(lib().ecco_decode_gemv(m.handle, _dp(blocks), _dp(meta), rows, cols, _dp(x), batch, _dp(y), _stream()),
            "ecco_decode_gemv")
@@ -248,8 +257,8 @@ def ecco_kv_append_minmax(mk: Model, mv: Model, k_new, v_new, k_blocks, k_meta, 
 
 
 def ecco_kv_attend(mk: Model, mv: Model, q, k_blocks, k_meta, v_blocks, v_meta, seq_len, B, H, T_max, out=None):
-    import torch
     if out is None:
+        import torch
         out = torch.empty((B, H, GROUP), dtype=torch.float32, device=q.device)
     _check(lib().ecco_kv_attend(mk.handle, mv.handle, _dp(q), _dp(k_blocks), _dp(k_meta), _dp(v_blocks), _dp(v_meta),
                                 _dp(seq_len), B, H, T_max, _dp(out), _stream()), "ecco_kv_attend")
@@ -272,10 +281,11 @@ def ecco_kv_attend_gqa_splits(device: int, B: int, Hkv: int, tokens: int) -> int
 def ecco_kv_attend_gqa(mk: Model, mv: Model, q, k_blocks, k_meta, v_blocks, v_meta, seq_len, B, Hq, Hkv, T_max,
                        n_splits: int = 1, workspace=None, out=None):
     """q [B, Hq, 128] FP16; caches [B, Hkv, T_max]; workspace: uint8/float tensor of ecco_kv_attend_gqa_workspace bytes."""
-    import torch
     if out is None:
+        import torch
         out = torch.empty((B, Hq, GROUP), dtype=torch.float32, device=q.device)
     if n_splits > 1 and workspace is None:
+        import torch
         workspace = torch.empty((int(lib().ecco_kv_attend_gqa_workspace(B, Hq, n_splits)),), dtype=torch.uint8, device=q.device)
     _check(lib().ecco_kv_attend_gqa(mk.handle, mv.handle, _dp(q), _dp(k_blocks), _dp(k_meta), _dp(v_blocks), _dp(v_meta),
                                     _dp(seq_len), B, Hq, Hkv, T_max, n_splits, _dp(workspace), _dp(out), _stream()),
@@ -315,9 +325,9 @@ def ecco_act_encode(src, blocks=None):
 
 
 def ecco_act_decode(blocks, dst=None):
-    import torch
     n = blocks.numel() // BLOCK_BYTES
     if dst is None:
+        import torch
         dst = torch.empty((n, ACT_GROUP), dtype=torch.float16, device=blocks.device)
     _check(lib().ecco_act_decode(_dp(blocks), n, _dp(dst), _stream()), "ecco_act_decode")
     return dst
@@ -414,9 +424,9 @@ def ecco_pb_encode(m: PbModel, src, blocks=None):
 
 
 def ecco_pb_decode(m: PbModel, blocks, dst=None):
-    import torch
     n = blocks.numel() // BLOCK_BYTES
     if dst is None:
+        import torch
         dst = torch.empty((n, GROUP), dtype=torch.float16, device=blocks.device)
     _check(lib().ecco_pb_decode(m.handle, _dp(blocks), n, _dp(dst), _stream()), "ecco_pb_decode")
     return dst
@@ -424,8 +434,8 @@ def ecco_pb_decode(m: PbModel, blocks, dst=None):
 
 def ecco_pb_decode_gemv(m: PbModel, blocks, rows: int, cols: int, x, y=None):
     """x: CUDA FP16 [cols]; returns y FP32 [rows]."""
-    import torch
     if y is None:
+        import torch
         y = torch.empty((rows,), dtype=torch.float32, device=x.device)
     _check(lib().ecco_pb_decode_gemv(m.handle, _dp(blocks), rows, cols, _dp(x), _dp(y), _stream()), "ecco_pb_decode_gemv")
     return y
