@@ -28,7 +28,7 @@ typedef __attribute__((address_space(3))) uint8_t lds_u8;
 constexpr int kSlot = kBlockWords + 1;    // LDS words per staged block; the last one is a zero pad
 constexpr int kUnit = 64;                 // blocks per wavefront pass, one per lane
 constexpr int kPayWords = kUnit * kSlot + 4;
-constexpr int kIdxStride = 17;            // words per block of the index image: 16 of eight nibbles, first value on top
+constexpr int kIdxStride = 17;            // words per block of the index image: values 8 w .. 8 w + 3 in the upper nibbles of word w, the next four in the lower ones
 constexpr int kInfoWords = 2 * kUnit;     // per block: where its centroids are, values present, padded entries, scale; where its stream ends
 constexpr int kRows = 4;                  // blocks per wavefront in step 2
 constexpr int kPair = 2;                  // blocks per row at a time: their table reads are in flight together
@@ -145,18 +145,18 @@ __device__ __forceinline__ void walk_block(const WaveLds& L, const Tables& T, in
     uint32_t* out = L.idx + lane * kIdxStride;
 #pragma unroll
     for (int i0 = 0; i0 < kGroup; i0 += 8) {
-        uint32_t nib = 0;
+        uint32_t packed[2];  // four table bytes each
 #pragma unroll
         for (int h = 0; h < 8; h += 4) {
             uint64_t win = (((uint64_t)w0 << 32) | (uint64_t)w1) << (fetch & 31u);
-            uint32_t len[4];
+            uint32_t e[4], len[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const uint32_t e = tab[(uint32_t)(win >> 56)];
-                len[j] = e & 15u;
+                e[j] = tab[(uint32_t)(win >> 56)];
+                len[j] = e[j] & 15u;
                 win <<= len[j];
-                nib = (nib << 4) | (e >> 4);
             }
+            packed[h >> 2] = __builtin_amdgcn_perm(e[1], e[0], 0x0C0C0400u) | __builtin_amdgcn_perm(e[3], e[2], 0x04000C0Cu);
             const uint32_t used = (len[0] + len[1]) + (len[2] + len[3]);
             if (i0 + h + 3 >= kAlwaysPresent) {
                 // all four, or, in the run that crosses the end, those that end inside
@@ -180,11 +180,11 @@ __device__ __forceinline__ void walk_block(const WaveLds& L, const Tables& T, in
                 const bool adv = nwi != wi;
                 w0 = adv ? w1 : w0;
                 w1 = adv ? w2 : w1;
-                w2 = w[min(nwi + 2u, (uint32_t)kBlockWords)];  // used one run later at the earliest
+                w2 = w[nwi + 2u];  // used one run later at the earliest; past the pad it is never looked at
                 wi = nwi;
             }
         }
-        out[i0 >> 3] = nib;
+        out[i0 >> 3] = (packed[0] & 0xF0F0F0F0u) | ((packed[1] >> 4) & 0x0F0F0F0Fu);
     }
     const uint32_t entries = reach <= (uint32_t)kBlockBits ? ((uint32_t)kBlockBits - reach) / kOutlierBits : 0u;
     L.info[lane] = make_uint2((p * 32u + ((sv & 0x8000u) ? T.minus : 0u)) | (present << 16) | (entries << 24), (sv & 0x7FFFu) | (min(reach, 0xFFFFu) << 16));
@@ -208,11 +208,10 @@ __device__ __forceinline__ RowBlock row_block(const WaveLds& L, const Tables& T,
     r.entries = i.x >> 24;
     r.scale = i.y & 0xFFFFu;
     r.end = i.y >> 16;
-    // twice the indices, a byte each: values 0, 2, 4, 6 and 1, 3, 5, 7, the first on top; a byte is then one addition away
-    // from its address
-    const uint32_t even = (nibbles >> 3) & 0x1E1E1E1Eu, odd = (nibbles << 1) & 0x1E1E1E1Eu;
+    // twice the indices, a byte each (values 0..3 and 4..7): a byte is then one addition away from its address
+    const uint32_t twice[2] = {(nibbles >> 3) & 0x1E1E1E1Eu, (nibbles << 1) & 0x1E1E1E1Eu};
 #pragma unroll
-    for (int k = 0; k < 8; ++k) r.c[k] = lds_half(r.cent + (((k & 1 ? odd : even) >> (24 - 8 * (k >> 1))) & 0xFFu));
+    for (int k = 0; k < 8; ++k) r.c[k] = lds_half(r.cent + ((twice[k >> 2] >> (8 * (k & 3))) & 0xFFu));
     return r;
 }
 // Takes out the absent values of the blocks in hand.  Most cut streams lose a value or two, so the first four of a lane
@@ -427,7 +426,7 @@ __global__ __launch_bounds__(kThreads) void pb_gemv_kernel(const uint32_t* __res
                     const Entry e = row_entry(L, T, r[q], blk, l);
                     if (e.valid) {
                         const float xi = half_f(reinterpret_cast<const uint16_t*>(x)[(size_t)cg[i0 + q] * kGroup + e.pos]);
-                        const uint32_t k = (L.idx[blk * kIdxStride + (e.pos >> 3)] >> (28u - 4u * (e.pos & 7u))) & 15u;
+                        const uint32_t k = (L.idx[blk * kIdxStride + (e.pos >> 3)] >> (8u * (e.pos & 3u) + ((e.pos & 4u) ? 0u : 4u))) & 15u;
                         acc[q] = fmaf(-half_f(lds_half(r[q].cent + k * 2u)), xi, acc[q]);
                         extra[q] = half_f(e.value) * xi;
                     }
