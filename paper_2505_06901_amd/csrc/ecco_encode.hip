@@ -140,7 +140,13 @@ __device__ __forceinline__ uint32_t pack_row(const uint32_t* enc, uint32_t* imag
 }
 
 // ---- the full search ---------------------------------------------------------------------------------------------------
-constexpr size_t search_lds_bytes(int S) { return ((size_t)S * kTableWords + search_lds_words<false>(search_tiles(S))) * 4; }
+// Up to 16 patterns the partial sums lie over the histogram: three workgroups then fit a compute unit instead of two (131072
+// groups 48.1 -> 44.3 us, 262144 91.3 -> 82.8 us, below 16384 the same).  More patterns take registers for two workgroups only.
+constexpr bool search_over(int tiles) { return tiles == 1; }
+constexpr size_t search_lds_bytes(int S) {
+    const int tiles = search_tiles(S);
+    return ((size_t)S * kTableWords + (search_over(tiles) ? search_lds_words<true>(tiles) : search_lds_words<false>(tiles))) * 4;
+}
 
 template <int kTiles, bool kLong, class Io>
 __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(4))) void encode_search_kernel(Job<Io> j0, Job<Io> j1) {
@@ -150,7 +156,7 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
     const Io io = job.io;
     const int lane = threadIdx.x & 63, l = lane & 15, row = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const SearchLds L = search_lds<false>(smem + S * kTableWords, kTiles);
+    const SearchLds L = search_lds<search_over(kTiles)>(smem + S * kTableWords, kTiles);
     uint32_t* hist = L.hist + (wave * kWaveRows + row) * kHistStride;
     const size_t batches = (io.groups() + kSearchBatch - 1) / kSearchBatch;
     RowValues v;
@@ -168,7 +174,7 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
         set_bins<true>(v, kSearchStep * __builtin_amdgcn_rcpf(s), hist, -1);
         wave_fence();
         convert_hist(L.hist + wave * kWaveRows * kHistStride, lane);
-        uint64_t left = patterns_left<kTiles, false>(L, C, tiles, wave, lane);
+        uint64_t left = patterns_left<kTiles, search_over(kTiles)>(L, C, tiles, wave, lane);
         const bool plain = !(s >= kSearchLeastScale);  // all patterns, value by value
         if (plain) left = S == 64 ? ~0ull : (1ull << S) - 1ull;
         uint32_t pattern = 0, idx = 0;
@@ -439,11 +445,12 @@ int launch_encode(bool minmax, const ecco_model* m0, const Io& io0, const ecco_m
         else rc = lng ? few(encode_few_kernel<false, true, Io>) : few(encode_few_kernel<false, false, Io>);
     } else if (minmax) {
         const size_t lds = minmax_lds_bytes(S);
-        rc = lng ? run(encode_minmax_kernel<true, Io>, lds, kMinmaxBatch, kMinmaxThreads, 6) : run(encode_minmax_kernel<false, Io>, lds, kMinmaxBatch, kMinmaxThreads, 6);
+        const int per_cu = (int)std::min<size_t>(8, 160 * 1024 / lds);  // at 64 patterns six fit; at 16 eight take 38.8 us for 262144 groups, six 39.8 us
+        rc = lng ? run(encode_minmax_kernel<true, Io>, lds, kMinmaxBatch, kMinmaxThreads, per_cu) : run(encode_minmax_kernel<false, Io>, lds, kMinmaxBatch, kMinmaxThreads, per_cu);
     } else {
         const size_t lds = search_lds_bytes(S);
         switch (search_tiles(S)) {
-            case 1: rc = lng ? run(encode_search_kernel<1, true, Io>, lds, kSearchBatch, kSearchThreads, 2) : run(encode_search_kernel<1, false, Io>, lds, kSearchBatch, kSearchThreads, 2); break;
+            case 1: rc = lng ? run(encode_search_kernel<1, true, Io>, lds, kSearchBatch, kSearchThreads, 3) : run(encode_search_kernel<1, false, Io>, lds, kSearchBatch, kSearchThreads, 3); break;
             case 2: rc = lng ? run(encode_search_kernel<2, true, Io>, lds, kSearchBatch, kSearchThreads, 2) : run(encode_search_kernel<2, false, Io>, lds, kSearchBatch, kSearchThreads, 2); break;
             default: rc = lng ? run(encode_search_kernel<4, true, Io>, lds, kSearchBatch, kSearchThreads, 2) : run(encode_search_kernel<4, false, Io>, lds, kSearchBatch, kSearchThreads, 2);
         }

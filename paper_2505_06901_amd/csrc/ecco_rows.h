@@ -218,8 +218,8 @@ __device__ __forceinline__ void rate_pattern(const uint8_t* near, uint32_t pair,
 
 // ---- bounds on every pattern's error, and the patterns that can be the best ------------------------------------------
 // Workgroup-wide LDS of the bounds: histogram, partial sums of the matrix product, the pattern tiles' least upper bounds,
-// the patterns left per group.  kOver: the partial sums lie over the histogram, at the price of a barrier, so that two
-// workgroups with larger tables still fit a compute unit.
+// the patterns left per group.  kOver: the partial sums lie over the histogram, at the price of a barrier, so that one
+// more workgroup fits a compute unit.
 struct SearchLds {
     uint32_t* hist;   // [kSearchBatch][kHistStride]
     float4_t* part;   // [wavefront (and tile of groups)][sum, error][64]
