@@ -562,6 +562,30 @@ def test_kv_attend_gqa_matches_oracle(dev, oracle, grp, n_splits):
         assert e.value.status == -2
 
 
+@pytest.mark.parametrize("lengths,T,grp,n_splits", [
+    ([1300, 0, 1, 33, 640, 31, 1024, 7], 1300, 2, 4),    # ranges dealt by length: none, one and many ranges per sequence
+    ([900, 899], 900, 9, 2),                              # more than eight heads: two products per unit
+    ([4096 + 31, 40, 40, 40, 40, 40], 4127, 3, 2),        # one sequence over a hundred units longer than the rest
+    ([3, 0, 65, 96] * 16 + [96, 17], 96, 1, 3),           # more than 64 sequences: every one is cut into n_splits
+    ([0, 0, 0], 64, 4, 5),                                # nothing to attend to
+])
+def test_gqa_ranges_follow_the_lengths(dev, oracle, lengths, T, grp, n_splits):
+    """Unequal sequences under token splits: whatever the deal, every token counts once.  Each call twice, same bits."""
+    B, Hkv = len(lengths), 2
+    k, v, mk, mv = _kv_setup(dev, oracle, B, Hkv, T, 16)
+    kb, km, okb, okm = enc_both(dev, oracle, mk, k); vb, vm, ovb, ovm = enc_both(dev, oracle, mv, v)
+    q = W.activation(B * Hkv * grp, 128, 109).reshape(B, Hkv * grp, 128)
+    seq = np.array(lengths, np.int32)
+    args = (mk, mv, t16(q, dev), kb, km, vb, vm, ti32(seq, dev), B, Hkv * grp, Hkv, T)
+    first = E.ecco_kv_attend_gqa(*args, n_splits=n_splits)
+    assert torch.equal(first, E.ecco_kv_attend_gqa(*args, n_splits=n_splits))
+    want = oracle.kv_attend_gqa(mk.centroids, mk.code_lens, mv.centroids, mv.code_lens, q.view(np.uint16),
+                                okb, okm, ovb, ovm, seq, B, Hkv * grp, Hkv, T)
+    out = first.cpu().numpy()
+    assert not out[seq == 0].any()
+    assert_attn_close(oracle, mv, ovb, ovm, seq, B, Hkv * grp, Hkv, T, out, want)
+
+
 def test_gqa_long_context(dev, oracle):
     """One sequence of 20 000 tokens, 8 query heads over 2 key/value heads, 16 token splits (several spans per split)."""
     B, Hkv, grp, T = 1, 2, 4, 20000
