@@ -20,10 +20,10 @@ def _hipcc() -> str:
     return "hipcc"
 
 
-# Kernels that may park a few scalar registers in vector-register lanes.  Only the grouped-query attention kernel
-# for two models with long codes does (2 registers) and passes its tests; every other kernel stays clear, so that
-# a change which starts to spill is noticed when it is made.
-_SGPR_SPILL_TOLERATED = ("kv_attend_gqa_kernelILb1ELb1E",)
+# Kernels that may park scalar registers in vector-register lanes.  Only the grouped-query attention kernels for models
+# with long codes do (the masks of that decoder's rare path, 14 to 34 registers) and pass their tests; every other kernel
+# stays clear, so that a change which starts to spill is noticed when it is made.
+_SGPR_SPILL_TOLERATED = ("kv_attend_gqa_kernelILb1E", "kv_attend_gqa_kernelILb0ELb1E")
 
 
 def _check_kernel_resources(remarks: str, verbose: bool) -> dict:

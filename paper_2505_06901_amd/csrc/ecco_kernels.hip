@@ -19,6 +19,7 @@
 #include <algorithm>
 #include <atomic>
 #include <mutex>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -298,20 +299,23 @@ struct UnitLoad {
     uint4 v0, v1;
     uint32_t meta;
 };
-// the payload pieces and the meta word of this lane for unit (row, ct).  Block indices are clamped into
+// the payload pieces of this lane for unit (row, ct) and the meta word of the unit's block `slot` (the one it decodes).  Block indices are clamped into
 // the row, so every lane issues the same loads and a slot past the row end holds a copy of the row's
 // last block: it decodes to finite values, which the caller drops.  Nothing here uses the loaded
 // data, so the loads stay in flight while the previous unit is decoded.
 __device__ __forceinline__ UnitLoad load_unit(const uint4* __restrict__ blocks, const uint32_t* __restrict__ meta,
-                                              int row, int gpr, int ct, int lane) {
+                                              int row, int gpr, int ct, int lane, int slot) {
     UnitLoad u;
     const size_t row_base = (size_t)row * gpr;
     const int g0 = ct * kUnitBlocks + (lane >> 2), g1 = g0 + 16;
     u.v0 = blocks[(row_base + min(g0, gpr - 1)) * 4 + (lane & 3)];
     u.v1 = blocks[(row_base + min(g1, gpr - 1)) * 4 + (lane & 3)];
-    const int g = ct * kUnitBlocks + (lane & (kUnitBlocks - 1));
-    u.meta = meta[row_base + min(g, gpr - 1)];
+    u.meta = meta[row_base + min(ct * kUnitBlocks + slot, gpr - 1)];
     return u;
+}
+__device__ __forceinline__ UnitLoad load_unit(const uint4* __restrict__ blocks, const uint32_t* __restrict__ meta,
+                                              int row, int gpr, int ct, int lane) {
+    return load_unit(blocks, meta, row, gpr, ct, lane, lane & (kUnitBlocks - 1));
 }
 // Lane l writes pieces of blocks l / 4 and l / 4 + 16; the chains are then read by other lanes (lane b and b + 32
 // read block b).  The exchange goes through the wavefront's private buffer without a workgroup barrier, so it is
@@ -899,212 +903,284 @@ __global__ __launch_bounds__(kLongV ? 512 : kAttnThreads) void kv_attend_kernel(
 
 // ---- grouped-query attention over compressed K / V, split over the tokens ---------------------------------
 // Several query heads share one key/value head (Section 5.3: with grouped-query attention the batched
-// matrix-vector products become small matrix products).  One workgroup of 8 wavefronts per (sequence,
-// key/value head, token split) decodes every K and V block of its token range once and serves all
-// grp = Hq / Hkv query heads of the group with it, on the matrix cores:
-//   scores  S[token][head] = sum_dim K[token][dim] q[head][dim]:  v_mfma_f32_32x32x16_f16 with the 32 tokens
-//           of a unit as rows; lane l decodes chain l / 32 of token l % 32, which is exactly the A layout (row
-//           l % 32, eight consecutive k per lane, k group l / 32) once the 16 k of a step are taken to be
-//           dimensions 8j..8j+7 of chain 0 and of chain 1; B holds the queries (head l % 32, zero past grp).
+// matrix-vector products become small matrix products).  One workgroup of 8 or 12 wavefronts per (sequence, key/value head, token range) decodes every K and V block of its range once and serves all
+// grp = Hq / Hkv query heads of the group with it, on the matrix cores, in 16 x 16 tiles (v_mfma_f32_16x16x32_f16):
+// a lane's four accumulator registers per tile leave room for three wavefronts per SIMD, where 32 x 32 tiles, half of
+// whose columns no group of at most 16 heads can use, left two.
+// A unit is 32 tokens; lane l decodes chain (l / 16) % 2 of token l % 16 + 16 (l / 32).
+//   scores  S[token][head] = sum_dim K[token][dim] q[head][dim]: eight decoded values of a lane are its A operand (row
+//           l % 16, k slice l / 16).  Slices 0 and 1 belong to tokens 0..15, slices 2 and 3 to tokens 16..31; with up to
+//           eight heads, B holds the queries in columns 0..7 for the former and in columns 8..15 for the latter (zeros
+//           elsewhere), so one product gives 32 tokens x 8 heads.  With more heads (kWide) there are two products, the
+//           other tokens' rows of A zeroed.
 //   output  O[dim][head] = sum_token V[token][dim] P[head][token]: here the reduction runs over the tokens, so the
 //           decoded values have to be turned: every 16 values the wavefront writes a 32 dims x 32 tokens FP16 tile
 //           to its private LDS buffer (neighbouring lanes first swap halves so that each writes two tokens of one
 //           dimension), reads it back as A operands (row = dimension, eight tokens per lane) and multiplies with
-//           the FP16 probabilities; the four 32 x 32 accumulator tiles (64 registers) live across the spans.
-// The sequence is walked in spans; per span the scores go to LDS, each head's running maximum and
-// denominator are updated (one wavefront per head), the accumulators of a lane -- all of one head -- are
-// rescaled, and the probabilities are stored as FP16 (the denominator sums the rounded values).  With one
-// split the result is normalised and written; otherwise (maximum, denominator, unnormalised output) of the
-// split go to the caller's workspace and kv_attend_combine_kernel merges the splits.
-constexpr int kGqaThreads = 512;
-constexpr int kGqaWaves = kGqaThreads / 64;
+//           the FP16 probabilities; the eight 16 x 16 accumulator tiles (32 registers) live across the spans.
+// The sequence is walked in spans whose scores fit LDS.  Per span: the wavefronts' maxima meet in LDS, all wavefronts
+// turn scores into probabilities, 256 of a head at a time, held in registers until every score has been read, since
+// the FP16 probabilities take the scores' place (the denominator sums the rounded values); the accumulators of a lane --
+// all of one head -- are rescaled.  If both models' tables fit they are built once, otherwise the V tables replace the
+// K tables in every span.  With one range per sequence the result is normalised and written; otherwise (maximum, denominator,
+// unnormalised output) of the range go to the caller's workspace and kv_attend_combine_kernel merges them.
+// Wavefronts per workgroup.  Twelve decode faster than eight where they take fewer rounds over the units of a range (8 x 8
+// heads in groups of 4, 4096 tokens, 32 units per range: 37.6 us with twelve, 41.5 us with eight); where they take as many, eight
+// meet and are summed faster (8 x 4 heads in groups of 8, 16 units per range: 29.7 us with eight, 30.2 us with twelve; 8 x 8 heads in
+// groups of 8, 1024 tokens, 8 units: 22.5 and 23.7 us).  The decoder of long codes needs the registers of eight.
+constexpr int kGqaWaves = 12, kGqaWavesFew = 8;
+constexpr int gqa_waves(bool lng, int units) {
+    return lng || (units + kGqaWavesFew - 1) / kGqaWavesFew == (units + kGqaWaves - 1) / kGqaWaves ? kGqaWavesFew : kGqaWaves;
+}
 constexpr int kGqaMaxGroup = 16;
 constexpr int kTileStride = 20;                 // words per row of the transposition tile: 32 tokens (16 words) + 4 of padding
 constexpr int kTileWords = 32 * kTileStride;
-constexpr int kGqaSpanBudget = 7680;            // query heads x tokens of a span kept in LDS (FP32 scores + FP16 probabilities)
-typedef float float16_t __attribute__((ext_vector_type(16)));
+constexpr int kItemTokens = 256;                // tokens a wavefront turns into probabilities at a time
+constexpr int kGqaScoreWords = 7936;            // query heads x tokens of a span kept in LDS, at most
+constexpr int kRedTile = 276, kRedRow = 68;     // words of a tile, and of 16 lanes of it, in the sum over wavefronts (skewed over the banks)
+constexpr int kGqaStateWords = 4 * kGqaMaxGroup + kGqaWaves * kGqaMaxGroup + 64;
 
-__host__ __device__ constexpr int gqa_span(int grp) { return (kGqaSpanBudget / grp) & ~(kUnitBlocks - 1); }
-__host__ __device__ constexpr int gqa_score_stride(int span) { return span + 1; }   // words; odd, so that heads fall on different banks
-__host__ __device__ constexpr int gqa_prob_stride(int span) { return span + 8; }    // halves; rows stay 16-byte aligned
-// LDS words of the span's scores (FP32, rounded up to a 16-byte boundary) and probabilities (FP16); the same region
-// holds the cross-wavefront sum of one accumulator tile at the end
-__host__ __device__ constexpr int gqa_score_words(int grp, int span) { return (grp * gqa_score_stride(span) + 3) & ~3; }
-__host__ __device__ constexpr int gqa_shared_words(int grp, int span) {
-    const int a = gqa_score_words(grp, span) + (grp * gqa_prob_stride(span) + 1) / 2, b = kGqaWaves * 16 * 64;
-    return a > b ? a : b;
-}
-constexpr int kGqaStateWords = 64;  // running maximum, denominator and rescale factor per query head
-inline size_t gqa_lds_bytes(int Sk, int Sv, int grp) {
-    return (table_words(std::max(Sk, Sv)) + (size_t)kGqaWaves * (kUnitWords + kTileWords) + kGqaStateWords +
-            gqa_shared_words(grp, gqa_span(grp))) * 4;
+// LDS words of the decode tables: the long-code lists and the centroids are only copied for models that need them
+__host__ __device__ constexpr int decode_table_words(int S, bool lng) { return S * (kPeekEntries + kK + (lng ? kK + kK / 2 : 0)); }
+__host__ __device__ constexpr int gqa_score_stride(int span) { return span + 4; }   // words: 16-byte aligned, and 4 modulo 32 so that heads fall on different banks
+struct GqaPlan {
+    int table_words;  // LDS words of the tables: both models', or the larger one's
+    int both;         // the V tables have their own place, behind those of K
+    int span;         // tokens per span, a multiple of 32
+    size_t lds;
+};
+inline GqaPlan gqa_plan(int Sk, bool lk, int Sv, bool lv, int grp, int waves) {
+    constexpr int kLdsWords = 160 * 1024 / 4;
+    const int wk = decode_table_words(Sk, lk), wv = decode_table_words(Sv, lv);
+    const int fixed = waves * (kUnitWords + kTileWords) + kGqaStateWords;
+    GqaPlan p;
+    p.both = wk + wv + fixed + kGqaScoreWords <= kLdsWords;
+    p.table_words = p.both ? wk + wv : std::max(wk, wv);
+    const int scores = std::min(kGqaScoreWords, kLdsWords - p.table_words - fixed);
+    p.span = (scores / grp - 4) & ~(kUnitBlocks - 1);
+    p.lds = (size_t)std::max(p.table_words + fixed + grp * gqa_score_stride(p.span), waves * 8 * kRedTile) * 4;
+    return p;
 }
 
-template <bool kLongK, bool kLongV>
-__global__ __launch_bounds__(kGqaThreads) void kv_attend_gqa_kernel(const uint32_t* __restrict__ dev_k, int Sk,
-                                                                    const uint32_t* __restrict__ dev_v, int Sv,
-                                                                    const uint16_t* __restrict__ q,
-                                                                    const uint4* __restrict__ k_blocks, const uint32_t* __restrict__ k_meta,
-                                                                    const uint4* __restrict__ v_blocks, const uint32_t* __restrict__ v_meta,
-                                                                    const int32_t* __restrict__ seq_len, int Hq, int Hkv, int T_max,
-                                                                    float* __restrict__ out, float* __restrict__ ws) {
+// grid: (B * Hkv, n_splits).  The partial result of a split and query head is at
+// index (sequence * Hq + query head) * n_splits + split of the workspace: 128 outputs each, then (maximum, denominator) pairs.
+struct GqaArgs {
+    const uint32_t* dev_k;
+    const uint32_t* dev_v;
+    const uint16_t* q;
+    const uint4* k_blocks;
+    const uint32_t* k_meta;
+    const uint4* v_blocks;
+    const uint32_t* v_meta;
+    const int32_t* seq_len;
+    float* out;
+    float* ws;
+    int Sk, Sv, B, Hq, Hkv, T_max, table_words, both, span;
+};
+typedef __attribute__((address_space(4))) const GqaArgs late_args;  // the arguments, read where they are used: all at once they exceed the scalar registers
+
+template <bool kLongK, bool kLongV, bool kWide, int kWaves>
+__global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args) {
+    constexpr int kThreads = kWaves * 64;
+    constexpr int kItems = (48 + kWaves - 1) / kWaves;                       // pieces of the probabilities per wavefront (gqa_plan: at most 48)
+    constexpr int kOutputs = (kGqaMaxGroup * kGroup + kThreads - 1) / kThreads;  // output elements per thread
+    // one register more than the 152 that this instantiation uses: the amount of a 64-bit shift must not be the last
+    // register of the allocation (the build checks every kernel for it)
+    if (!kLongK && !kLongV && !kWide && kWaves == kGqaWaves) asm volatile("" ::: "v152");
+    const int Sk = args.Sk, B = args.B, Hq = args.Hq, Hkv = args.Hkv, T_max = args.T_max, both = args.both, table_words = args.table_words, span_max = args.span;
+    const auto late = [] {
+        late_args* p = (late_args*)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(p));
+        return p;
+    };
     extern __shared__ __align__(16) uint32_t smem[];
-    const int Smax = max(Sk, Sv);
-    const int grp = Hq / Hkv, span_max = gqa_span(grp);
-    const int sstride = gqa_score_stride(span_max), pstride = gqa_prob_stride(span_max);
+    const int grp = Hq / Hkv, sstride = gqa_score_stride(span_max), n_splits = gridDim.y;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    uint32_t* wbuf = smem + table_words(Smax) + wave * kUnitWords;
-    uint32_t* tile = smem + table_words(Smax) + kGqaWaves * kUnitWords + wave * kTileWords;
-    float* st_max = reinterpret_cast<float*>(smem + table_words(Smax) + kGqaWaves * (kUnitWords + kTileWords));
-    float* st_den = st_max + kGqaMaxGroup;
+    uint32_t* wbuf = smem + table_words + wave * kUnitWords;
+    uint32_t* tile = smem + table_words + kWaves * kUnitWords + wave * kTileWords;
+    float* st_max = reinterpret_cast<float*>(smem + table_words + kWaves * (kUnitWords + kTileWords));  // [2][16]: before and after the span
+    float* st_den = st_max + 2 * kGqaMaxGroup;
     float* st_alpha = st_den + kGqaMaxGroup;
-    uint32_t* shared0 = smem + table_words(Smax) + kGqaWaves * (kUnitWords + kTileWords) + kGqaStateWords;
-    float* scores = reinterpret_cast<float*>(shared0);                                             // [grp][sstride]
-    _Float16* probs = reinterpret_cast<_Float16*>(shared0 + gqa_score_words(grp, span_max));       // [grp][pstride]
-    float* red = reinterpret_cast<float*>(shared0);                                                // [wavefront][16][64], after the last span
+    float* wave_max = st_alpha + kGqaMaxGroup;                  // [wavefront][16]
+    float* item_den = wave_max + kWaves * kGqaMaxGroup;      // per piece of the probabilities
+    float* scores = item_den + 64;           // [grp][sstride], then FP16 probabilities at the same rows
+    uint32_t* v_tables = smem + (both ? decode_table_words(Sk, kLongK) : 0);
     if (lane < kUnitBlocks) wbuf[lane * kStride + kBlockWords] = 0u;
     if (lane == 0) wbuf[kUnitBlocks * kStride] = 0u;
     if (tid < kGqaMaxGroup) {
         st_max[tid] = -INFINITY;
         st_den[tid] = 0.0f;
-        st_alpha[tid] = 1.0f;
     }
 
-    const int bkv = blockIdx.x, b = bkv / Hkv, hkv = bkv - b * Hkv;
-    const int n_splits = gridDim.y, split = blockIdx.y;
-    const int T = max(0, min(seq_len[b], T_max));
-    const int units_total = (T + kUnitBlocks - 1) / kUnitBlocks;
-    const int units_per_split = (units_total + n_splits - 1) / n_splits;
-    const int t_begin = min(T, split * units_per_split * kUnitBlocks), t_end = min(T, (split + 1) * units_per_split * kUnitBlocks);
-    const int blk = lane & (kUnitBlocks - 1), half = lane >> 5;   // token of the unit and chain of this lane; also MFMA row / column and k group
-    const bool head_ok = blk < grp;
-    const size_t q_row = ((size_t)b * Hq + (size_t)hkv * grp + (head_ok ? blk : 0)) * kGroup;
+    const int b = blockIdx.x / Hkv, hkv = blockIdx.x - b * Hkv, split = blockIdx.y, bkv = blockIdx.x;
+    const int T = max(0, min(args.seq_len[b], T_max));
+    const int per_range = ((T + kUnitBlocks - 1) / kUnitBlocks + n_splits - 1) / n_splits;
+    const int t_begin = min(T, split * per_range * kUnitBlocks), t_end = min(T, (split + 1) * per_range * kUnitBlocks);
+    const int n = lane & 15, slice = lane >> 4, half = slice & 1;   // matrix-core row or column and k slice; chain of this lane
+    const int tok = n + 16 * (lane >> 5);                          // its token of the unit
+    const int head = kWide ? n : n & 7;                             // head of this lane's column
+    const bool head_ok = head < grp, b_ok = head_ok && (kWide || (n >> 3) == (lane >> 5));
+    const size_t q_row = ((size_t)b * Hq + (size_t)hkv * grp + (head_ok ? head : 0)) * kGroup;
     const float inv_sqrt_d = 0.08838834764831845f;  // 1 / sqrt(128)
     const uint32_t swap_sel = (lane & 1) ? 0x03020706u : 0x05040100u;  // odd lanes keep the high halves, even lanes the low halves
-    float16_t o[4];
+    float4_t o[8];  // tile 4 h + s: dimensions 64 h + 16 s .. + 15 x heads
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) o[j][i] = 0.0f;
+    for (int j = 0; j < 8; ++j) o[j] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
 
-    for (int s0 = t_begin; s0 < t_end; s0 += span_max) {
+    int parity = 0;
+    for (int s0 = t_begin; s0 < t_end; s0 += span_max, parity ^= 1) {
         const int span = min(span_max, t_end - s0);
         const int units = (span + kUnitBlocks - 1) / kUnitBlocks, unit0 = s0 / kUnitBlocks;  // s0 is a multiple of 32
         // ---- scores of the span, all query heads of the group
         __syncthreads();
         int u = wave;
         UnitLoad pre;
-        const Tables TK = stage_tables_around<kLongK>(smem, dev_k, Sk, [&] { pre = load_unit(k_blocks, k_meta, bkv, T_max, unit0 + min(u, units - 1), lane); });
+        const auto load_k = [&](int at) { pre = load_unit(args.k_blocks, args.k_meta, bkv, T_max, unit0 + min(at, units - 1), lane, tok); };
+        if (!both || s0 == t_begin) stage_tables_around<kLongK>(smem, args.dev_k, Sk, [&] { load_k(u); });
+        else load_k(u);
+        if (both && s0 == t_begin) stage_tables_around<kLongV>(v_tables, args.dev_v, args.Sv, [] {});
+        const Tables TK = table_pointers(smem, Sk);
         __syncthreads();
         {
-            uint4 bq[kHalf / 8];  // B operands: the query of head blk, dimensions 64 * half + 8j .. + 7
+            uint4 bq[kHalf / 8];  // B operands: the query of this lane's head, dimensions 64 * half + 8j .. + 7
             // reloaded per span rather than kept alive across the V phase (address space restored as above)
-            const uint4* qgen = reinterpret_cast<const uint4*>(q + q_row + half * kHalf);
+            const uint4* qgen = reinterpret_cast<const uint4*>(args.q + q_row + half * kHalf);
             asm volatile("" : "+v"(qgen));
             const global_u4* qsrc = (const global_u4*)qgen;
 #pragma unroll
             for (int j = 0; j < kHalf / 8; ++j) {
                 const u32x4 v = qsrc[j];
-                bq[j] = head_ok ? make_uint4(v.x, v.y, v.z, v.w) : make_uint4(0u, 0u, 0u, 0u);
+                bq[j] = b_ok ? make_uint4(v.x, v.y, v.z, v.w) : make_uint4(0u, 0u, 0u, 0u);
             }
-            for (; u < units; u += kGqaWaves) {
+            float mx = -INFINITY;
+            for (; u < units; u += kWaves) {
                 store_unit(wbuf, pre, lane);
-                const uint32_t mw = pre.meta;
-                if (u + kGqaWaves < units) pre = load_unit(k_blocks, k_meta, bkv, T_max, unit0 + u + kGqaWaves, lane);
+                // a slot past the range may hold anything: scale 0, so that its values are zeros (tokens m and 16 + m share a row
+                // of the product, and NaN * 0 would poison it)
+                const uint32_t mw = (u * kUnitBlocks + tok < span) ? pre.meta : (pre.meta & 0xFFFF0000u);
+                if (u + kWaves < units) load_k(u + kWaves);
                 const Lane L = lane_setup(TK, mw, Sk);
-                const _Float16 sh = __builtin_bit_cast(_Float16, (unsigned short)(mw & 0xFFFFu));
-                const half2_t s2 = {sh, sh};
+                const _Float16 sh16 = __builtin_bit_cast(_Float16, (unsigned short)(mw & 0xFFFFu));
+                const half2_t s2 = {sh16, sh16};
                 uint32_t pk[4];
-                float16_t acc;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
-                decode_chain<kLongK, kHalf>(wbuf + blk * kStride, half ? L.second_start : 0u, L, [&](int i, uint32_t e) {
+                float4_t acc[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
+                decode_chain<kLongK, kHalf>(wbuf + tok * kStride, half ? L.second_start : 0u, L, [&](int i, uint32_t e) {
                     if ((i & 1) == 0) {
                         pk[(i >> 1) & 3] = e >> 16;
                         return;
                     }
                     pk[(i >> 1) & 3] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, pk[(i >> 1) & 3] | (e & 0xFFFF0000u)) * s2);
                     if ((i & 7) != 7) return;
-                    const uint4 av = make_uint4(pk[0], pk[1], pk[2], pk[3]);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8_t, av), __builtin_bit_cast(half8_t, bq[i >> 3]), acc, 0, 0, 0);
-                });
-                // accumulator layout of the 32 x 32 tile: register i of lane l is row 8 * (i / 4) + 4 * (l / 32) + i % 4, column l % 32
-                if (head_ok) {
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int t = u * kUnitBlocks + 8 * (i >> 2) + 4 * half + (i & 3);
-                        scores[blk * sstride + t] = t < span ? acc[i] * inv_sqrt_d : -INFINITY;
+                    const half8_t bv = __builtin_bit_cast(half8_t, bq[i >> 3]);
+                    if (kWide) {
+                        const bool low = lane < 32;
+                        const uint4 a0 = make_uint4(low ? pk[0] : 0u, low ? pk[1] : 0u, low ? pk[2] : 0u, low ? pk[3] : 0u);
+                        const uint4 a1 = make_uint4(low ? 0u : pk[0], low ? 0u : pk[1], low ? 0u : pk[2], low ? 0u : pk[3]);
+                        acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a0), bv, acc[0], 0, 0, 0);
+                        acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a1), bv, acc[1], 0, 0, 0);
+                    } else {
+                        const uint4 av = make_uint4(pk[0], pk[1], pk[2], pk[3]);
+                        acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, av), bv, acc[0], 0, 0, 0);
                     }
+                });
+                // accumulator layout of the 16 x 16 tile: register i of lane l is row 4 * (l / 16) + i, column l % 16
+#pragma unroll
+                for (int w = 0; w < (kWide ? 2 : 1); ++w) {
+                    const int t0 = u * kUnitBlocks + 4 * slice + (kWide ? 16 * w : 16 * (n >> 3));
+                    float4_t v;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        v[i] = t0 + i < span ? acc[w][i] * inv_sqrt_d : -INFINITY;
+                        mx = fmaxf(mx, v[i]);
+                    }
+                    if (head_ok) *reinterpret_cast<float4_t*>(scores + head * sstride + t0) = v;
+                }
+            }
+            // the wavefront's maximum per head: over the lanes of the column
+            if (!kWide) mx = fmaxf(mx, __shfl_xor(mx, 8));
+            mx = fmaxf(mx, __shfl_xor(mx, 16));
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            if (lane < 16) wave_max[wave * kGqaMaxGroup + n] = mx;  // columns past the heads hold something, which nobody reads
+        }
+        __syncthreads();
+        // ---- running softmax: all wavefronts, 256 tokens of a head at a time
+        const int pieces = (units * kUnitBlocks + kItemTokens - 1) / kItemTokens, items = pieces * grp;
+        uint2 ph[kItems];
+        uint32_t ph_at[kItems];  // where they go, as a byte offset into the scores (in a vector register: the scalar ones are spent)
+#pragma unroll
+        for (int k = 0; k < kItems; ++k) {
+            ph_at[k] = 0xFFFFFFFFu;
+            const int it = wave + k * kWaves;
+            if (it < items) {  // uniform
+                const int g = it / pieces, t0 = (it - g * pieces) * kItemTokens + 4 * lane;
+                float m = n < kWaves ? wave_max[n * kGqaMaxGroup + g] : -INFINITY;
+                m = fmaxf(m, dpp_mov<0xB1>(m));
+                m = fmaxf(m, dpp_mov<0x4E>(m));
+                m = fmaxf(m, dpp_mov<0x141>(m));
+                m = fmaxf(m, dpp_mov<0x140>(m));
+                m = fmaxf(m, st_max[parity * kGqaMaxGroup + g]);
+                float4_t s = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+                if (t0 < units * kUnitBlocks) {
+                    s = *reinterpret_cast<const float4_t*>(scores + g * sstride + t0);
+                    ph_at[k] = (uint32_t)(g * sstride * 4 + t0 * 2);
+                }
+                float den = 0.0f;
+                half2_t p[2];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    p[i >> 1][i & 1] = (_Float16)__expf(s[i] - m);  // 0 for the tokens past the span
+                    den += (float)p[i >> 1][i & 1];
+                }
+                ph[k] = make_uint2(__builtin_bit_cast(uint32_t, p[0]), __builtin_bit_cast(uint32_t, p[1]));
+                den = wave_sum(den);
+                if (lane == 0) {
+                    item_den[it] = den;
+                    if (t0 == 0) st_max[(parity ^ 1) * kGqaMaxGroup + g] = m;
                 }
             }
         }
         __syncthreads();
-        // ---- running softmax, one wavefront per query head
-        for (int g = wave; g < grp; g += kGqaWaves) {
-            const int n = units * kUnitBlocks;
-            // both passes take four scores per lane at a time, so that their LDS reads are in flight together (a loop
-            // over single reads waits for each); indices past the end are clamped for the read (a repeated score does
-            // not change a maximum) and left out of the second pass; the additions keep their order
-            float mx = -INFINITY;
-            for (int t0 = lane; t0 < n; t0 += 4 * 64) {
-                float a[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) a[j] = scores[g * sstride + min(t0 + 64 * j, n - 1)];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) mx = fmaxf(mx, a[j]);
-            }
-            mx = wave_all(mx, [](float a, float c) { return fmaxf(a, c); });
-            const float old_max = st_max[g], new_max = fmaxf(old_max, mx);
+        for (int k = 0; k < kItems; ++k) {
+            asm volatile("" : "+v"(ph_at[k]));
+            if (ph_at[k] != 0xFFFFFFFFu) *reinterpret_cast<uint2*>(reinterpret_cast<unsigned char*>(scores) + ph_at[k]) = ph[k];
+        }
+        if (tid < grp) {
+            const float before = st_max[parity * kGqaMaxGroup + tid], after = st_max[(parity ^ 1) * kGqaMaxGroup + tid];
+            const float alpha = before == -INFINITY ? 0.0f : __expf(before - after);
             float den = 0.0f;
-            for (int t0 = lane; t0 < n; t0 += 4 * 64) {
-                float a[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) a[j] = scores[g * sstride + min(t0 + 64 * j, n - 1)];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (t0 + 64 * j < n) {
-                        const _Float16 ph = (_Float16)__expf(a[j] - new_max);  // 0 for the tokens past the span
-                        probs[g * pstride + t0 + 64 * j] = ph;
-                        den += (float)ph;
-                    }
-                }
-            }
-            den = wave_sum(den);
-            if (lane == 0) {
-                const float alpha = (old_max == -INFINITY) ? 0.0f : __expf(old_max - new_max);
-                st_alpha[g] = alpha;
-                st_den[g] = st_den[g] * alpha + den;
-                st_max[g] = new_max;
-            }
+            for (int c = 0; c < pieces; ++c) den += item_den[tid * pieces + c];
+            st_alpha[tid] = alpha;
+            st_den[tid] = st_den[tid] * alpha + den;
         }
         // ---- weighted sum of V over the span
-        __syncthreads();
         u = wave;
-        const Tables TV = stage_tables_around<kLongV>(smem, dev_v, Sv, [&] { pre = load_unit(v_blocks, v_meta, bkv, T_max, unit0 + min(u, units - 1), lane); });
+        const auto* av = late();
+        const uint4* v_blocks = av->v_blocks;
+        const uint32_t* v_meta = av->v_meta;
+        const int Sv = av->Sv;
+        const auto load_v = [&](int at) { pre = load_unit(v_blocks, v_meta, bkv, T_max, unit0 + min(at, units - 1), lane, tok); };
+        if (both) load_v(u);
+        else stage_tables_around<kLongV>(v_tables, av->dev_v, Sv, [&] { load_v(u); });
+        const Tables TV = table_pointers(v_tables, Sv);
         __syncthreads();
         {
-            const float alpha = head_ok ? st_alpha[blk] : 1.0f;  // every accumulator of a lane belongs to head l % 32
+            const float alpha = n < grp ? st_alpha[n] : 1.0f;  // every accumulator of a lane belongs to head l % 16
+            const _Float16* prob = reinterpret_cast<const _Float16*>(scores + min(n, grp - 1) * sstride) + 8 * slice;
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) o[j][i] *= alpha;
-            for (; u < units; u += kGqaWaves) {
+            for (int j = 0; j < 8; ++j) o[j] *= alpha;
+            for (; u < units; u += kWaves) {
                 store_unit(wbuf, pre, lane);
-                // a slot past the range may hold anything: scale 0, so that its values are zeros (NaN * 0 would poison the sum)
-                const uint32_t mw = (u * kUnitBlocks + blk < span) ? pre.meta : (pre.meta & 0xFFFF0000u);
-                if (u + kGqaWaves < units) pre = load_unit(v_blocks, v_meta, bkv, T_max, unit0 + u + kGqaWaves, lane);
+                const uint32_t mw = (u * kUnitBlocks + tok < span) ? pre.meta : (pre.meta & 0xFFFF0000u);
+                if (u + kWaves < units) load_v(u + kWaves);
                 const Lane L = lane_setup(TV, mw, Sv);
-                const _Float16 sh = __builtin_bit_cast(_Float16, (unsigned short)(mw & 0xFFFFu));
-                const half2_t s2 = {sh, sh};
-                // B operands: probabilities of head blk for tokens 16 ks + 8 * half .. + 7 of the unit
-                uint4 pb[2];
-#pragma unroll
-                for (int ks = 0; ks < 2; ++ks)
-                    pb[ks] = head_ok ? *reinterpret_cast<const uint4*>(probs + blk * pstride + u * kUnitBlocks + 16 * ks + 8 * half)
-                                     : make_uint4(0u, 0u, 0u, 0u);
+                const _Float16 sh16 = __builtin_bit_cast(_Float16, (unsigned short)(mw & 0xFFFFu));
+                const half2_t s2 = {sh16, sh16};
+                // B operand: probabilities of head l % 16 for tokens 8 * (l / 16) .. + 7 of the unit
+                const uint4 pb = n < grp ? *reinterpret_cast<const uint4*>(prob + u * kUnitBlocks) : make_uint4(0u, 0u, 0u, 0u);
                 uint32_t pk[8];
-                decode_chain<kLongV, kHalf>(wbuf + blk * kStride, half ? L.second_start : 0u, L, [&](int i, uint32_t e) {
+                decode_chain<kLongV, kHalf>(wbuf + tok * kStride, half ? L.second_start : 0u, L, [&](int i, uint32_t e) {
                     if ((i & 1) == 0) {
                         pk[(i >> 1) & 7] = e >> 16;
                         return;
@@ -1117,50 +1193,51 @@ __global__ __launch_bounds__(kGqaThreads) void kv_attend_gqa_kernel(const uint32
 #pragma unroll
                     for (int r2 = 0; r2 < 8; ++r2) {
                         const uint32_t other = (uint32_t)__builtin_amdgcn_mov_dpp((int)pk[r2], 0xB1, 0xF, 0xF, true);  // quad_perm [1,0,3,2]
-                        tile[(16 * half + 2 * r2 + (lane & 1)) * kTileStride + (blk >> 1)] = __builtin_amdgcn_perm(other, pk[r2], swap_sel);
+                        tile[(16 * half + 2 * r2 + (lane & 1)) * kTileStride + (tok >> 1)] = __builtin_amdgcn_perm(other, pk[r2], swap_sel);
                     }
                     wave_lds_fence();
-                    const uint4 a0 = *reinterpret_cast<const uint4*>(tile + blk * kTileStride + 4 * half);
-                    const uint4 a1 = *reinterpret_cast<const uint4*>(tile + blk * kTileStride + 8 + 4 * half);
-                    o[i >> 4] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8_t, a0), __builtin_bit_cast(half8_t, pb[0]), o[i >> 4], 0, 0, 0);
-                    o[i >> 4] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8_t, a1), __builtin_bit_cast(half8_t, pb[1]), o[i >> 4], 0, 0, 0);
+                    const uint4 a0 = *reinterpret_cast<const uint4*>(tile + n * kTileStride + 4 * slice);
+                    const uint4 a1 = *reinterpret_cast<const uint4*>(tile + (16 + n) * kTileStride + 4 * slice);
+                    const half8_t bv = __builtin_bit_cast(half8_t, pb);
+                    o[i >> 4] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a0), bv, o[i >> 4], 0, 0, 0);
+                    o[4 + (i >> 4)] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a1), bv, o[4 + (i >> 4)], 0, 0, 0);
                 });
             }
         }
     }
-    // ---- sum over the wavefronts, one accumulator tile at a time; tile j row m is dimension 64 * (m / 16) + 16 j + m % 16
-    const size_t part = ((size_t)b * Hq + (size_t)hkv * grp) * n_splits;
+    // ---- sum over the wavefronts; everything else in LDS is dead once the state has been read
+    const size_t part = ((size_t)b * Hq + (size_t)hkv * grp) * n_splits + split, total = (size_t)B * Hq * n_splits;  // of the group's first head
+    float* out = late()->out;
+    float* ws = late()->ws;
+    __syncthreads();
+    float den[kOutputs];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < 16; ++i) red[(wave * 16 + i) * 64 + lane] = o[j][i];
-        __syncthreads();
-        for (int e = tid; e < 16 * 64; e += kGqaThreads) {
-            float sum = 0.0f;
-            for (int w = 0; w < kGqaWaves; ++w) sum += red[w * 16 * 64 + e];
-            const int i = e >> 6, ln = e & 63, head = ln & 31;
-            if (head >= grp) continue;
-            const int m = 8 * (i >> 2) + 4 * (ln >> 5) + (i & 3);
-            const int dim = 64 * (m >> 4) + 16 * j + (m & 15);
-            if (n_splits == 1) {
-                const float den = st_den[head];
-                out[((size_t)b * Hq + (size_t)hkv * grp + head) * kGroup + dim] = den > 0.0f ? sum / den : 0.0f;
-            } else {
-                ws[((part + (size_t)head * n_splits) + split) * kGroup + dim] = sum;
-            }
-        }
-    }
+    for (int k = 0; k < kOutputs; ++k) den[k] = st_den[min((tid + k * kThreads) / kGroup, kGqaMaxGroup - 1)];
     if (n_splits > 1 && tid < grp) {
-        // behind the partial outputs: [B * Hq][n_splits][2] = (maximum, denominator)
-        float* ml = ws + (size_t)gridDim.x / Hkv * Hq * n_splits * kGroup;
-        const size_t at = (part + (size_t)tid * n_splits + split) * 2;
-        ml[at] = st_max[tid];
-        ml[at + 1] = st_den[tid];
+        const size_t at = total * kGroup + (part + (size_t)tid * n_splits) * 2;
+        ws[at] = st_max[parity * kGqaMaxGroup + tid];
+        ws[at + 1] = st_den[tid];
+    }
+    __syncthreads();
+    float* red = reinterpret_cast<float*>(smem);  // [wavefront][8 tiles][4 slices][16 lanes][4]
+#pragma unroll
+    for (int j = 0; j < 8; ++j) *reinterpret_cast<float4_t*>(red + (wave * 8 + j) * kRedTile + slice * kRedRow + n * 4) = o[j];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kOutputs; ++k) {
+        const int e = tid + k * kThreads, g = e / kGroup, dim = e % kGroup;
+        if (g < grp) {
+            const float* at = red + (dim >> 4) * kRedTile + ((dim & 15) >> 2) * kRedRow + g * 4 + (dim & 3);
+            float sum = 0.0f;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) sum += at[w * 8 * kRedTile];
+            if (n_splits == 1) out[((size_t)b * Hq + (size_t)hkv * grp + g) * kGroup + dim] = den[k] > 0.0f ? sum / den[k] : 0.0f;
+            else ws[(part + (size_t)g * n_splits) * kGroup + dim] = sum;
+        }
     }
 }
 
-// merges the token splits of one (sequence, query head): grid B * Hq, 128 threads
+// merges the token ranges of one (sequence, query head): grid B * Hq, 128 threads
 __global__ __launch_bounds__(kGroup) void kv_attend_combine_kernel(const float* __restrict__ ws, int n_heads, int n_splits, float* __restrict__ out) {
     const size_t bh = blockIdx.x;
     const float* ml = ws + (size_t)n_heads * n_splits * kGroup + bh * n_splits * 2;
@@ -1371,21 +1448,27 @@ static int gqa_launch(const ecco_model* mk, const ecco_model* mv, const uint16_t
                       const void* k_blocks, const uint32_t* k_meta, const void* v_blocks, const uint32_t* v_meta,
                       const int32_t* seq_len, int B, int Hq, int Hkv, int T_max, int n_splits, float* workspace,
                       float* out, void* stream) {
-    const size_t lds = gqa_lds_bytes(mk->S, mv->S, Hq / Hkv);
     const bool lk = mk->max_len > kPeekBits, lv = mv->max_len > kPeekBits;
+    const int waves = gqa_waves(lk || lv, ((T_max - 1) / kUnitBlocks + n_splits) / n_splits);  // units of a range: ceil(ceil(T_max / 32) / n_splits)
+    const GqaPlan plan = gqa_plan(mk->S, lk, mv->S, lv, Hq / Hkv, waves);
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int dev_id = mk->device;
     auto launch = [&](auto kernel) -> int {
-        int rc = allow_lds(kernel, dev_id, lds);
+        int rc = allow_lds(kernel, dev_id, plan.lds);
         if (rc != ECCO_OK) return rc;
-        hipLaunchKernelGGL(kernel, dim3(B * Hkv, n_splits), dim3(kGqaThreads), lds, st, mk->dev, mk->S, mv->dev, mv->S, q,
-                           static_cast<const uint4*>(k_blocks), k_meta, static_cast<const uint4*>(v_blocks), v_meta, seq_len,
-                           Hq, Hkv, T_max, out, workspace);
+        hipLaunchKernelGGL(kernel, dim3(B * Hkv, n_splits), dim3(waves * 64), plan.lds, st,
+                           GqaArgs{mk->dev, mv->dev, q, static_cast<const uint4*>(k_blocks), k_meta, static_cast<const uint4*>(v_blocks), v_meta, seq_len,
+                                   out, workspace, mk->S, mv->S, B, Hq, Hkv, T_max, plan.table_words, plan.both, plan.span});
         ECCO_HIP_CHECK(hipGetLastError());
         return ECCO_OK;
     };
-    const int rc = lk ? (lv ? launch(kv_attend_gqa_kernel<true, true>) : launch(kv_attend_gqa_kernel<true, false>))
-                      : (lv ? launch(kv_attend_gqa_kernel<false, true>) : launch(kv_attend_gqa_kernel<false, false>));
+    const auto pick = [&](auto wide) -> int {
+        constexpr bool kWide = decltype(wide)::value;
+        if (lk) return lv ? launch(kv_attend_gqa_kernel<true, true, kWide, kGqaWavesFew>) : launch(kv_attend_gqa_kernel<true, false, kWide, kGqaWavesFew>);
+        if (lv) return launch(kv_attend_gqa_kernel<false, true, kWide, kGqaWavesFew>);
+        return waves == kGqaWaves ? launch(kv_attend_gqa_kernel<false, false, kWide, kGqaWaves>) : launch(kv_attend_gqa_kernel<false, false, kWide, kGqaWavesFew>);
+    };
+    const int rc = Hq / Hkv > 8 ? pick(std::true_type{}) : pick(std::false_type{});
     if (rc != ECCO_OK || n_splits == 1) return rc;
     hipLaunchKernelGGL(kv_attend_combine_kernel, dim3(B * Hq), dim3(kGroup), 0, st, workspace, B * Hq, n_splits, out);
     ECCO_HIP_CHECK(hipGetLastError());

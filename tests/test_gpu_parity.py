@@ -563,7 +563,7 @@ def test_kv_attend_gqa_matches_oracle(dev, oracle, grp, n_splits):
 
 
 @pytest.mark.parametrize("lengths,T,grp,n_splits", [
-    ([1300, 0, 1, 33, 640, 31, 1024, 7], 1300, 2, 4),    # ranges dealt by length: none, one and many ranges per sequence
+    ([1300, 0, 1, 33, 640, 31, 1024, 7], 1300, 2, 4),    # empty, one-token and full sequences side by side
     ([900, 899], 900, 9, 2),                              # more than eight heads: two products per unit
     ([4096 + 31, 40, 40, 40, 40, 40], 4127, 3, 2),        # one sequence over a hundred units longer than the rest
     ([3, 0, 65, 96] * 16 + [96, 17], 96, 1, 3),           # more than 64 sequences: every one is cut into n_splits
