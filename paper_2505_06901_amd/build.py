@@ -20,16 +20,11 @@ def _hipcc() -> str:
     return "hipcc"
 
 
-# Kernels that may park scalar registers in vector-register lanes.  Only the grouped-query attention kernels for models
-# with long codes do (the masks of that decoder's rare path, 14 to 34 registers) and pass their tests; every other kernel
-# stays clear, so that a change which starts to spill is noticed when it is made.
-_SGPR_SPILL_TOLERATED = ("kv_attend_gqa_kernelILb1E", "kv_attend_gqa_kernelILb0ELb1E")
-
-
 def _check_kernel_resources(remarks: str, verbose: bool) -> dict:
     """Every kernel must keep its working set in registers: a kernel that spills to scratch memory is
     far off its design point (the decode loops are sized for 1024-thread workgroups, 128 VGPRs), so
-    a register spill is a build error rather than a silent slowdown."""
+    a register spill is a build error rather than a silent slowdown.  Scalar registers parked in
+    vector-register lanes count as spilled too, in every kernel."""
     name, found, vgprs = None, 0, {}
     for line in remarks.splitlines():
         m = re.search(r"remark:\s+Function Name: (\S+)", line)
@@ -50,8 +45,7 @@ def _check_kernel_resources(remarks: str, verbose: bool) -> dict:
         if m and name:
             if verbose and int(m.group(2)):
                 print("  %s: %s spilled: %s" % (name, m.group(1), m.group(2)))
-            tolerated = m.group(1) == "SGPRs" and any(k in name for k in _SGPR_SPILL_TOLERATED)
-            if int(m.group(2)) != 0 and not tolerated and not os.environ.get("ECCO_ALLOW_SCRATCH"):
+            if int(m.group(2)) != 0 and not os.environ.get("ECCO_ALLOW_SCRATCH"):
                 raise RuntimeError("kernel %s spills %s %s" % (name, m.group(2), m.group(1)))
     if found == 0:
         raise RuntimeError("no kernel resource remarks found: cannot verify register use")

@@ -982,16 +982,23 @@ typedef __attribute__((address_space(4))) const GqaArgs late_args;  // the argum
 template <bool kLongK, bool kLongV, bool kWide, int kWaves>
 __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args) {
     constexpr int kThreads = kWaves * 64;
+    constexpr bool kLate = kLongK || kLongV;  // the decoder of long codes takes more scalar registers: more of the arguments are read late
     constexpr int kItems = (48 + kWaves - 1) / kWaves;                       // pieces of the probabilities per wavefront (gqa_plan: at most 48)
     constexpr int kOutputs = (kGqaMaxGroup * kGroup + kThreads - 1) / kThreads;  // output elements per thread
-    // one register more than the 152 that this instantiation uses: the amount of a 64-bit shift must not be the last
+    // one register more than the 152 that these instantiations use: the amount of a 64-bit shift must not be the last
     // register of the allocation (the build checks every kernel for it)
-    if (!kLongK && !kLongV && !kWide && kWaves == kGqaWaves) asm volatile("" ::: "v152");
+    if (!kLongK && !kWide && (kLongV || kWaves == kGqaWaves)) asm volatile("" ::: "v152");
     const int Sk = args.Sk, B = args.B, Hq = args.Hq, Hkv = args.Hkv, T_max = args.T_max, both = args.both, table_words = args.table_words, span_max = args.span;
     const auto late = [] {
         late_args* p = (late_args*)__builtin_amdgcn_kernarg_segment_ptr();
         asm volatile("" : "+s"(p));
         return p;
+    };
+    // a model's size, as the staging of its tables in a span sees it: what the staging of a model with long codes derives
+    // from it (masks, addresses) would otherwise be formed once for all spans and take scalar registers throughout
+    const auto fresh = [](int S) {
+        asm volatile("" : "+s"(S));
+        return S;
     };
     extern __shared__ __align__(16) uint32_t smem[];
     const int grp = Hq / Hkv, sstride = gqa_score_stride(span_max), n_splits = gridDim.y;
@@ -1014,6 +1021,8 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
     }
 
     const int b = blockIdx.x / Hkv, hkv = blockIdx.x - b * Hkv, split = blockIdx.y, bkv = blockIdx.x;
+    int kept[3] = {bkv, split, n_splits};  // until the end
+    if (kLate) asm volatile("" : "+v"(kept[0]), "+v"(kept[1]), "+v"(kept[2]));
     const int T = max(0, min(args.seq_len[b], T_max));
     const int per_range = ((T + kUnitBlocks - 1) / kUnitBlocks + n_splits - 1) / n_splits;
     const int t_begin = min(T, split * per_range * kUnitBlocks), t_end = min(T, (split + 1) * per_range * kUnitBlocks);
@@ -1037,15 +1046,15 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
         int u = wave;
         UnitLoad pre;
         const auto load_k = [&](int at) { pre = load_unit(args.k_blocks, args.k_meta, bkv, T_max, unit0 + min(at, units - 1), lane, tok); };
-        if (!both || s0 == t_begin) stage_tables_around<kLongK>(smem, args.dev_k, Sk, [&] { load_k(u); });
+        if (!both || s0 == t_begin) stage_tables_around<kLongK>(smem, kLate ? late()->dev_k : args.dev_k, kLongK ? fresh(Sk) : Sk, [&] { load_k(u); });
         else load_k(u);
-        if (both && s0 == t_begin) stage_tables_around<kLongV>(v_tables, args.dev_v, args.Sv, [] {});
+        if (both && s0 == t_begin) stage_tables_around<kLongV>(v_tables, kLate ? late()->dev_v : args.dev_v, kLongV ? fresh(args.Sv) : args.Sv, [] {});
         const Tables TK = table_pointers(smem, Sk);
         __syncthreads();
         {
             uint4 bq[kHalf / 8];  // B operands: the query of this lane's head, dimensions 64 * half + 8j .. + 7
             // reloaded per span rather than kept alive across the V phase (address space restored as above)
-            const uint4* qgen = reinterpret_cast<const uint4*>(args.q + q_row + half * kHalf);
+            const uint4* qgen = reinterpret_cast<const uint4*>((kLate ? late()->q : args.q) + q_row + half * kHalf);
             asm volatile("" : "+v"(qgen));
             const global_u4* qsrc = (const global_u4*)qgen;
 #pragma unroll
@@ -1101,7 +1110,9 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
             if (!kWide) mx = fmaxf(mx, __shfl_xor(mx, 8));
             mx = fmaxf(mx, __shfl_xor(mx, 16));
             mx = fmaxf(mx, __shfl_xor(mx, 32));
-            if (lane < 16) wave_max[wave * kGqaMaxGroup + n] = mx;  // columns past the heads hold something, which nobody reads
+            int at = lane;
+            if (kLate) asm volatile("" : "+v"(at));  // as in `fresh`
+            if (at < 16) wave_max[wave * kGqaMaxGroup + n] = mx;  // columns past the heads hold something, which nobody reads
         }
         __syncthreads();
         // ---- running softmax: all wavefronts, 256 tokens of a head at a time
@@ -1162,7 +1173,7 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
         const int Sv = av->Sv;
         const auto load_v = [&](int at) { pre = load_unit(v_blocks, v_meta, bkv, T_max, unit0 + min(at, units - 1), lane, tok); };
         if (both) load_v(u);
-        else stage_tables_around<kLongV>(v_tables, av->dev_v, Sv, [&] { load_v(u); });
+        else stage_tables_around<kLongV>(v_tables, av->dev_v, kLongV ? fresh(Sv) : Sv, [&] { load_v(u); });
         const Tables TV = table_pointers(v_tables, Sv);
         __syncthreads();
         {
@@ -1206,15 +1217,20 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
         }
     }
     // ---- sum over the wavefronts; everything else in LDS is dead once the state has been read
-    const size_t part = ((size_t)b * Hq + (size_t)hkv * grp) * n_splits + split, total = (size_t)B * Hq * n_splits;  // of the group's first head
-    float* out = late()->out;
-    float* ws = late()->ws;
+    const auto* end = late();
+    float* out = end->out;
+    float* ws = end->ws;
+    const auto scalar = [](int v) { return kLate ? __builtin_amdgcn_readfirstlane(v) : v; };
+    const int bkv_end = scalar(kept[0]), split_end = scalar(kept[1]), n_splits_end = scalar(kept[2]);
+    const size_t heads = kLate ? (size_t)end->B * end->Hq : (size_t)B * Hq;
+    const size_t first_head = kLate ? (size_t)(bkv_end / end->Hkv) * end->Hq + (size_t)(bkv_end % end->Hkv) * grp : (size_t)b * Hq + (size_t)hkv * grp;
+    const size_t part = first_head * n_splits_end + split_end, total = heads * n_splits_end;  // of the group's first head
     __syncthreads();
     float den[kOutputs];
 #pragma unroll
     for (int k = 0; k < kOutputs; ++k) den[k] = st_den[min((tid + k * kThreads) / kGroup, kGqaMaxGroup - 1)];
-    if (n_splits > 1 && tid < grp) {
-        const size_t at = total * kGroup + (part + (size_t)tid * n_splits) * 2;
+    if (n_splits_end > 1 && tid < grp) {
+        const size_t at = total * kGroup + (part + (size_t)tid * n_splits_end) * 2;
         ws[at] = st_max[parity * kGqaMaxGroup + tid];
         ws[at + 1] = st_den[tid];
     }
@@ -1231,8 +1247,8 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
             float sum = 0.0f;
 #pragma unroll
             for (int w = 0; w < kWaves; ++w) sum += at[w * 8 * kRedTile];
-            if (n_splits == 1) out[((size_t)b * Hq + (size_t)hkv * grp + g) * kGroup + dim] = den[k] > 0.0f ? sum / den[k] : 0.0f;
-            else ws[(part + (size_t)g * n_splits) * kGroup + dim] = sum;
+            if (n_splits_end == 1) out[(first_head + g) * kGroup + dim] = den[k] > 0.0f ? sum / den[k] : 0.0f;
+            else ws[(part + (size_t)g * n_splits_end) * kGroup + dim] = sum;
         }
     }
 }

@@ -586,6 +586,42 @@ def test_gqa_ranges_follow_the_lengths(dev, oracle, lengths, T, grp, n_splits):
     assert_attn_close(oracle, mv, ovb, ovm, seq, B, Hkv * grp, Hkv, T, out, want)
 
 
+@pytest.mark.parametrize("long_k,long_v,S,grp,T,n_splits", [
+    (True, False, 5, 9, 1500, 1),     # long codes under more than eight heads, two to four spans, six units per wavefront
+    (False, True, 5, 9, 1500, 1),
+    (True, True, 5, 16, 1500, 1),
+    (True, True, 5, 16, 1500, 3),
+    (False, False, 64, 16, 1500, 1),  # two 64-pattern models: the K and V tables replace each other in each of four spans; twelve wavefronts
+    (False, False, 64, 16, 500, 1),   # 16 units per range: eight wavefronts, two spans
+    (False, False, 64, 4, 4100, 2),   # up to eight heads, two spans
+    (True, True, 64, 9, 1500, 1),     # long codes and tables that replace each other
+    (True, False, 64, 2, 8000, 2),
+])
+def test_gqa_variants(dev, oracle, long_k, long_v, S, grp, T, n_splits):
+    """The variants of the grouped-query kernel: long codes in K, V or both, at most or more than eight heads, tables of both
+    models side by side or in turn over several spans.  Against the oracle, and the same bits on every launch."""
+    B, Hkv = 2, 1
+    seq = np.array([T, T * 2 // 3 - 5], np.int32)
+    rng = np.random.default_rng(S + grp)
+    blocks = []
+    for long, seed in ((long_k, 31), (long_v, 32)):
+        cent, lens, probs = _skewed_model(oracle, S, seed)
+        if not long:
+            lens = np.stack([oracle.limited_lengths((p * 1e6).astype(np.uint64) + 1, 8) for p in probs])
+        m = E.ecco_model_to_device(E.ecco_model_create(cent, lens), 0)
+        x = _skewed_data(cent, probs, 512, seed + 2)[rng.integers(0, 512, B * Hkv * T)].reshape(B, Hkv, T, 128)
+        blocks.append((m, *enc_both(dev, oracle, m, x)))
+    (mk, kb, km, okb, okm), (mv, vb, vm, ovb, ovm) = blocks
+    q = W.activation(B * Hkv * grp, 128, 110).reshape(B, Hkv * grp, 128)
+    args = (mk, mv, t16(q, dev), kb, km, vb, vm, ti32(seq, dev), B, Hkv * grp, Hkv, T)
+    first = E.ecco_kv_attend_gqa(*args, n_splits=n_splits)
+    want = oracle.kv_attend_gqa(mk.centroids, mk.code_lens, mv.centroids, mv.code_lens, q.view(np.uint16),
+                                okb, okm, ovb, ovm, seq, B, Hkv * grp, Hkv, T)
+    assert_attn_close(oracle, mv, ovb, ovm, seq, B, Hkv * grp, Hkv, T, first.cpu().numpy(), want)
+    for _ in range(15):
+        assert torch.equal(first, E.ecco_kv_attend_gqa(*args, n_splits=n_splits))
+
+
 def test_gqa_long_context(dev, oracle):
     """One sequence of 20 000 tokens, 8 query heads over 2 key/value heads, 16 token splits (several spans per split)."""
     B, Hkv, grp, T = 1, 2, 4, 20000

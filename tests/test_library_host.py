@@ -228,8 +228,8 @@ def test_paper_block_fit_invariants():
 
 
 def test_build_rejects_register_spills(monkeypatch):
-    """The build reads the compiler's resource remarks: scratch memory or spilled registers in any kernel stop it
-    (scalar spills are tolerated in the one kernel that is known to have them)."""
+    """The build reads the compiler's resource remarks: scratch memory or spilled registers, vector or scalar, stop it in
+    every kernel, the grouped-query kernels of long-code models included."""
     from paper_2505_06901_amd import build as B
 
     monkeypatch.delenv("ECCO_ALLOW_SCRATCH", raising=False)
@@ -246,9 +246,12 @@ def test_build_rejects_register_spills(monkeypatch):
     for bad in (dict(scratch=52), dict(sgpr=8), dict(vgpr=3)):
         with pytest.raises(RuntimeError, match="spills"):
             B._check_kernel_resources(remarks("_Z11gemm_kernelILb1EEvv", **bad), False)
-    B._check_kernel_resources(remarks("_ZN12_GLOBAL__N_120kv_attend_gqa_kernelILb1ELb1EEEvv", sgpr=4), False)
-    with pytest.raises(RuntimeError, match="spills"):
-        B._check_kernel_resources(remarks("_ZN12_GLOBAL__N_120kv_attend_gqa_kernelILb1ELb1EEEvv", vgpr=1), False)
+    for variant in ("Lb0ELb0ELb0ELi12E", "Lb1ELb0ELb0ELi8E", "Lb0ELb1ELb1ELi8E", "Lb1ELb1ELb1ELi8E"):
+        name = "_ZN12_GLOBAL__N_120kv_attend_gqa_kernelI%sEEvNS_7GqaArgsE" % variant
+        B._check_kernel_resources(remarks(name), False)
+        for bad in (dict(sgpr=1), dict(vgpr=1)):
+            with pytest.raises(RuntimeError, match="spills"):
+                B._check_kernel_resources(remarks(name, **bad), False)
     with pytest.raises(RuntimeError, match="no kernel resource remarks"):
         B._check_kernel_resources("nothing here", False)
 
