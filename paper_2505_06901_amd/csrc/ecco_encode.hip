@@ -148,8 +148,9 @@ constexpr size_t search_lds_bytes(int S) {
     return ((size_t)S * kTableWords + (search_over(tiles) ? search_lds_words<true>(tiles) : search_lds_words<false>(tiles))) * 4;
 }
 
+// (six wavefronts per SIMD: the three workgroups)
 template <int kTiles, bool kLong, class Io>
-__global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(4))) void encode_search_kernel(Job<Io> j0, Job<Io> j1) {
+__global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(search_over(kTiles) ? 6 : 4))) void encode_search_kernel(Job<Io> j0, Job<Io> j1) {
     extern __shared__ __align__(16) uint32_t smem[];
     const Job<Io>& job = blockIdx.y ? j1 : j0;
     const int S = job.S, tiles = search_tiles(S);
@@ -164,42 +165,62 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
     Coefs<kTiles> C;
     C.load(job.dev + DevLayout{S}.coef(), wave, tiles, lane);
     const EncTables T = stage_enc_tables<kSearchThreads>(smem, job.dev, S);
+    bool slack_set = false;
+    if (l == 0) L.slack[wave * kWaveRows + row] = 0.0f;
     for (size_t b = blockIdx.x; b < batches; b += gridDim.x) {
-        const size_t g = b * kSearchBatch + wave * kWaveRows + row;
         const uint32_t smax = row_max(lane_absmax(v));
         const float s = half_bits_f(smax);
         const half2_t s2 = splat_half(smax);
+        set_slack(L.slack + wave * kWaveRows + row, s, l, slack_set);
         clear_hist(L.hist + wave * kWaveRows * kHistStride, lane);
         wave_fence();
         set_bins<true>(v, kSearchStep * __builtin_amdgcn_rcpf(s), hist, -1);
         wave_fence();
         convert_hist(L.hist + wave * kWaveRows * kHistStride, lane);
         uint64_t left = patterns_left<kTiles, search_over(kTiles)>(L, C, tiles, wave, lane);
-        const bool plain = !(s >= kSearchLeastScale);  // all patterns, value by value
-        if (plain) left = S == 64 ? ~0ull : (1ull << S) - 1ull;
+        // What the table of nearest centroids does not serve is rated value by value (scan_patterns), scales too small for it
+        // from the start.  Of scale 0 all patterns are alike: the first wins with index 0.
+        uint64_t later = 0;
+        if (!(s >= kSearchLeastScale)) {
+            later = smax == 0u ? 0ull : left;
+            left = 0;
+        }
         uint32_t pattern = 0, idx = 0;
-        float best = 0.0f;
-        bool first = true;
-        do {  // the patterns left, ascending; a row that has none left repeats its last one
-            const bool more = left != 0ull;
-            const uint32_t p = more ? (uint32_t)__builtin_ctzll(left) : pattern;
-            left &= left - 1ull;
+        float best = __builtin_inff();
+        int rated = 0;
+        while (__builtin_amdgcn_ballot_w64(left != 0) != 0ull) {  // the patterns left, ascending; a row that has none left repeats its last one
+            const uint32_t p = left != 0 ? (uint32_t)__builtin_ctzll(left) : pattern;
             float sse;
             uint32_t id;
-            rate_pattern<kK, true>(T.near + p * kSearchBins, T.pair + p * 64u, s2, v, plain, -1, sse, id);
-            if (first || (more && sse < best)) {  // strict <: the lowest pattern wins a tie
+            const uint32_t marks = rate_pattern<true>(T.near + p * kSearchBins, T.pair + p * 64u, s2, v, -1, sse, id);
+            const uint64_t lanes = __builtin_amdgcn_ballot_w64((marks & ecco::kNearWide) != 0u);
+            if (lanes != 0ull && row_any(lanes, row)) {  // this pattern and those after it value by value
+                later |= left;
+                left = 0;
+            }
+            if (left != 0 && sse < best) {  // strict <: the lowest pattern wins a tie
                 best = sse;
                 pattern = p;
                 idx = id;
             }
-            first = false;
-        } while (__builtin_amdgcn_ballot_w64(left != 0ull) != 0ull);
+            left &= left - 1ull;
+            if (++rated == kLookAfter && __builtin_amdgcn_ballot_w64(most_left(left, S)) != 0ull) {
+                later |= left;
+                left = 0;
+            }
+        }
+        if (__builtin_amdgcn_ballot_w64(later != 0) != 0ull) {
+            bool won;
+            scan_patterns(reinterpret_cast<float*>(L.hist + wave * kWaveRows * kHistStride), smem + S * (kSearchBins / 4), S, v, smax, kGroup, later, lane, best, pattern, won);
+            const uint32_t id = scan_indices(T.pair + pattern * 64u, s2, v, -1);
+            idx = won ? id : idx;
+        }
         // the next group is requested here, when the search has given its registers back
         load_values<kSearchBatch>(v, io.values(), io.groups(), b + gridDim.x, wave * kWaveRows + row, l);
         uint32_t mw;
         const uint32_t word = pack_row<kLong>(T.enc + pattern * kK, hist, idx, l, smax, pattern, mw);
         size_t at;
-        if (io.place(g, at)) {
+        if (io.place(b * kSearchBatch + (uint32_t)(wave * kWaveRows + row), at)) {
             io.blocks[at * kBlockWords + l] = word;
             if (l == 0) io.meta[at] = mw;
         }
@@ -398,7 +419,13 @@ __global__ __launch_bounds__(kMinmaxThreads) void encode_minmax_kernel(Job<Io> j
         set_bins<false>(v, kSearchStep * __builtin_amdgcn_rcpf(s), nullptr, -1);
         float sse;
         uint32_t idx;
-        rate_pattern<kK, false>(T.near + pattern * kSearchBins, T.pair + pattern * 64u, s2, v, !(s >= kSearchLeastScale), -1, sse, idx);
+        const uint32_t marks = rate_pattern<false>(T.near + pattern * kSearchBins, T.pair + pattern * 64u, s2, v, -1, sse, idx);
+        const uint64_t lanes = __builtin_amdgcn_ballot_w64(((marks & kNearWide) != 0u || !(s >= kSearchLeastScale)) && smax != 0u);
+        if (lanes != 0ull) {  // rows with crowded bins or a scale too small for the tables
+            const uint32_t id = scan_indices(T.pair + pattern * 64u, s2, v, -1);
+            idx = row_any(lanes, row) ? id : idx;
+        }
+        idx = smax == 0u ? 0u : idx;
         uint32_t mw;
         const uint32_t word = pack_row<kLong>(T.enc + pattern * kK, image, idx, l, smax, pattern, mw);
         size_t at;

@@ -73,7 +73,6 @@ void pb_encode_kernel(const uint32_t* __restrict__ dev, int S, float inv_tscale,
     const uint16_t* codes = reinterpret_cast<const uint16_t*>(codes_at);
     const uint16_t* fp8 = reinterpret_cast<const uint16_t*>(fp8_at);
     const SearchLds L = search_lds<true>(smem + table_words(S), kTiles);
-    uint32_t* hist = L.hist + (wave * kWaveRows + row) * kHistStride;
 
     const size_t batches = (n_groups + kSearchBatch - 1) / kSearchBatch;
     RowValues v;
@@ -83,9 +82,16 @@ void pb_encode_kernel(const uint32_t* __restrict__ dev, int S, float inv_tscale,
     copy_words(smem, dev + D.near(), S * kTableWords);  // near, pair, codes, lengths follow each other
     copy_words(fp8_at, dev + D.fp8(), kFp8Words);
     copy_words(kpenc, dev + D.kpenc(), (S + 3) & ~3);
+    bool slack_set = false;
+    if ((threadIdx.x & 15) == 0) L.slack[threadIdx.x >> 4] = 0.0f;
     __syncthreads();
 
     for (size_t b = blockIdx.x; b < batches; b += gridDim.x) {
+        // the lane taken afresh for each batch: what is derived from it would otherwise take registers through the search
+        int at = threadIdx.x & 63;
+        asm volatile("" : "+v"(at));
+        const int lane = at, l = lane & 15, row = lane >> 4;
+        uint32_t* hist = L.hist + (wave * kWaveRows + row) * kHistStride;
         // the element of largest magnitude, first position on ties: the least (position, value) of those that have it
         const uint32_t mag = row_max(lane_absmax(v));
         uint32_t first = 0xFFFFFFFFu;
@@ -102,34 +108,56 @@ void pb_encode_kernel(const uint32_t* __restrict__ dev, int S, float inv_tscale,
         const uint32_t smag = fp8[s8] & 0x7FFFu;
         const float s = half_bits_f(smag);
         const half2_t s2 = splat_half(smag);
+        set_slack(L.slack + wave * kWaveRows + row, s, l, slack_set);
         clear_hist(L.hist + wave * kWaveRows * kHistStride, lane);
         wave_fence();
         set_bins<true>(v, kSearchStep * __builtin_amdgcn_rcpf(s), hist, skip);
         wave_fence();
         convert_hist(L.hist + wave * kWaveRows * kHistStride, lane);
         uint64_t left = patterns_left<kTiles, true>(L, C, tiles, wave, lane);
-        // the bins hold values of up to 1.09 scales; a scale that was rounded further than that, or is small: all patterns
-        const bool plain = !(s >= ecco::kSearchLeastScale && half_bits_f(mag) <= 1.08f * s);
-        if (plain) left = S == 64 ? ~0ull : (1ull << S) - 1ull;
-        // the scale's code waits in a spare word of the row's histogram: the search has no register left for it
-        if (l == 0) hist[kHistStride - 1] = s8;
-        uint32_t pattern = 0, idx = 0;
-        float best = 0.0f;
-        bool none = true;
-        do {  // the patterns left, ascending; a row that has none left repeats its last one
-            const bool more = left != 0ull;
-            const uint32_t p = more ? (uint32_t)__builtin_ctzll(left) : pattern;
-            left &= left - 1ull;
+        // What the table of nearest centroids does not serve is rated value by value (scan_patterns): from the start scales too
+        // small for it, and all patterns where the scale was rounded so far that values lie beyond the bins (which reach 1.09
+        // scales).  Of scale 0 all patterns are alike: the first wins with index 0.
+        const bool beyond = !(half_bits_f(mag) <= 1.08f * s);
+        // the scale's code waits in LDS: the search has no register left for it
+        if (l == 0) L.spare[wave * kWaveRows + row] = s8;
+        uint64_t later = 0;
+        if (beyond || !(s >= ecco::kSearchLeastScale)) {
+            later = s == 0.0f ? 0ull : !beyond ? left : S == 64 ? ~0ull : (1ull << S) - 1ull;
+            left = 0;
+        }
+        uint32_t pattern = 0, idx = skip < 0 ? 0u : 15u << (28 - 4 * skip);
+        float best = __builtin_inff();
+        int rated = 0;
+        while (__builtin_amdgcn_ballot_w64(left != 0) != 0ull) {  // the patterns left, ascending; a row that has none left repeats its last one
+            const uint32_t p = left != 0 ? (uint32_t)__builtin_ctzll(left) : pattern;
             float sse;
             uint32_t id;
-            rate_pattern<kCent, true>(near + p * ecco::kSearchBins, pair + p * 64u, s2, v, plain, skip, sse, id);
-            if (none || (more && sse < best)) {  // strict <: the lowest pattern wins a tie
+            const uint32_t marks = rate_pattern<true>(near + p * ecco::kSearchBins, pair + p * 64u, s2, v, skip, sse, id);
+            const uint64_t lanes = __builtin_amdgcn_ballot_w64((marks & ecco::kNearWide) != 0u);
+            if (lanes != 0ull && row_any(lanes, row)) {  // this pattern and those after it value by value
+                later |= left;
+                left = 0;
+            }
+            if (left != 0 && sse < best) {  // strict <: the lowest pattern wins a tie
                 best = sse;
                 pattern = p;
                 idx = id;
             }
-            none = false;
-        } while (__builtin_amdgcn_ballot_w64(left != 0ull) != 0ull);
+            left &= left - 1ull;
+            if (++rated == kLookAfter && __builtin_amdgcn_ballot_w64(most_left(left, S)) != 0ull) {
+                later |= left;
+                left = 0;
+            }
+        }
+        if (__builtin_amdgcn_ballot_w64(later != 0) != 0ull) {
+            bool won;
+            int skip_again = skip;  // its comparisons are formed here, not kept through the search
+            asm volatile("" : "+v"(skip_again));
+            scan_patterns(reinterpret_cast<float*>(L.hist + wave * kWaveRows * kHistStride), pair_at, S, v, __builtin_bit_cast(uint32_t, s2) & 0xFFFFu, top >> 16, later, lane, best, pattern, won);
+            const uint32_t id = scan_indices(pair + pattern * 64u, s2, v, skip_again);
+            idx = won ? id : idx;
+        }
 
         // the codebook of least total length, lowest on ties
         uint32_t sum = 0;  // four bytes, at most 8 x 8 each
@@ -143,9 +171,15 @@ void pb_encode_kernel(const uint32_t* __restrict__ dev, int S, float inv_tscale,
         if ((odd >> 16) < total) { total = odd >> 16; book = 3; }
 
         // header, then the codes at their positions
-        uint32_t* image = hist;
+        // taken afresh: what is derived from the lane's place and from the scale is then formed here, not kept through the search
+        int at_lane = lane;
+        uint32_t top_again = top;
+        asm volatile("" : "+v"(at_lane), "+v"(top_again));
+        const int place = at_lane & 15;
+        const int top_place = (int)(top_again >> 19) == place ? (int)((top_again >> 16) & 7u) : -1;
+        uint32_t* image = L.hist + (wave * kWaveRows + (at_lane >> 4)) * kHistStride;
         const uint32_t kp = kpenc[pattern], base = 10u + (kp >> 16), end = base + total;
-        image[l] = l == 0 ? (hist[kHistStride - 1] << 24) | (book << 22) | ((kp & 0xFFFFu) << (22u - (kp >> 16))) : 0u;
+        image[place] = place == 0 ? (L.spare[wave * kWaveRows + (at_lane >> 4)] << 24) | (book << 22) | ((kp & 0xFFFFu) << (22u - (kp >> 16))) : 0u;
         uint32_t bits[2], n[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -167,14 +201,12 @@ void pb_encode_kernel(const uint32_t* __restrict__ dev, int S, float inv_tscale,
         // room left: the largest remaining magnitudes, lower position first, as (position, 8-bit float) entries
         const uint32_t slots = end <= (uint32_t)kBlockBits ? ((uint32_t)kBlockBits - end) / kOutlierBits : 0u;
         if (__builtin_amdgcn_ballot_w64(slots != 0u) != 0ull) {
-            // taken afresh: what is derived from the lane's place is then formed here, not kept through the search
-            uint32_t place = 127u - 8u * (uint32_t)l;
-            asm volatile("" : "+v"(place));
+            const uint32_t from_end = 127u - 8u * (uint32_t)place;
             uint32_t key[kRowValues];  // magnitude, 127 - position, sign: all different
 #pragma unroll
             for (int i = 0; i < kRowValues; ++i) {
                 const uint32_t x = (i & 1) ? v.x[i >> 1] >> 16 : v.x[i >> 1] & 0xFFFFu;
-                key[i] = i == skip ? 0u : ((x & 0x7FFFu) << 8) | ((place - i) << 1) | (x >> 15) | 0x1000000u;
+                key[i] = i == top_place ? 0u : ((x & 0x7FFFu) << 8) | ((from_end - i) << 1) | (x >> 15) | 0x1000000u;
             }
             uint32_t entry = 0, last = 0xFFFFFFFFu;  // lane j keeps entry j
             for (uint32_t j = 0; __builtin_amdgcn_ballot_w64(j < slots) != 0ull; ++j) {
@@ -182,17 +214,17 @@ void pb_encode_kernel(const uint32_t* __restrict__ dev, int S, float inv_tscale,
 #pragma unroll
                 for (int i = 0; i < kRowValues; ++i) most = max(most, key[i] < last ? key[i] : 0u);
                 last = row_max(most);
-                if ((uint32_t)l == j) entry = last;
+                if ((uint32_t)place == j) entry = last;
             }
-            if ((uint32_t)l < slots && entry != 0u) {
+            if ((uint32_t)place < slots && entry != 0u) {
                 const uint32_t x = ((entry >> 8) & 0x7FFFu) | ((entry & 1u) << 15);
-                put_bits(image, end + l * kOutlierBits, ((127u - ((entry >> 1) & 127u)) << 8) | fp8_round(half_bits_f(x) * inv_tscale), kOutlierBits);
+                put_bits(image, end + place * kOutlierBits, ((127u - ((entry >> 1) & 127u)) << 8) | fp8_round(half_bits_f(x) * inv_tscale), kOutlierBits);
             }
         }
         load_values<kSearchBatch>(v, src, n_groups, b + gridDim.x, wave * kWaveRows + row, l);
         wave_fence();
         // the batch's words in the order of the threads
-        if (b * kSearchBatch + (uint32_t)(wave * kWaveRows + row) < n_groups) (blocks + b * (kSearchBatch * kBlockWords))[threadIdx.x] = image[l];
+        if (b * kSearchBatch + (uint32_t)(wave * kWaveRows + row) < n_groups) (blocks + b * (kSearchBatch * kBlockWords))[threadIdx.x] = image[place];
         wave_fence();
     }
 }

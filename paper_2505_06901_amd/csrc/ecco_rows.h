@@ -5,6 +5,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "ecco_search.h"
 
 namespace ecco_rows {
@@ -148,13 +150,12 @@ __device__ __forceinline__ float tree_sum(const float (&d)[kRowValues], int skip
 }
 
 // The row's values under one pattern: every value's index (the lowest of the nearest reconstructed centroids
-// fp16(c * s)), eight nibbles per lane, first value on top; and the group's squared error (kSse, by tree_sum).  near, pair: the pattern's rows of the tables in LDS (pair as an LDS
-// address, a multiple of 64); plain rows compare every value with all kCent centroids.  A value whose place is `skip` counts as without error, with index 15.
-// The distance falls (weakly) with k up to its least value and rises (weakly) after it, so the lowest nearest index is
-// the last k at which it strictly drops.
-template <int kCent, bool kSse>
-__device__ __forceinline__ void rate_pattern(const uint8_t* near, uint32_t pair, half2_t s2, const RowValues& v, bool plain, int skip,
-                                             float& sse, uint32_t& idx) {
+// fp16(c * s)), eight nibbles per lane, first value on top; and the group's squared error (kSse, by tree_sum).  near, pair: the
+// pattern's rows of the tables in LDS (pair as an LDS address, a multiple of 64).  A value whose place is `skip` counts as
+// without error, with index 15.  Returns the marks of the lane's bins: with kNearWide (more than three candidates) in one of its
+// lanes, a row's results do not hold.
+template <bool kSse>
+__device__ __forceinline__ uint32_t rate_pattern(const uint8_t* near, uint32_t pair, half2_t s2, const RowValues& v, int skip, float& sse, uint32_t& idx) {
     uint32_t k[kRowValues], marks = 0;
     float d[kRowValues];
     // four values at a time: all eight in flight need 24 more registers than three workgroups per compute unit leave
@@ -191,39 +192,174 @@ __device__ __forceinline__ void rate_pattern(const uint8_t* near, uint32_t pair,
             }
         }
     }
-    const bool all = plain || (marks & ecco::kNearWide) != 0u;
-    if (__builtin_amdgcn_ballot_w64(all) != 0ull) {
-#pragma unroll
-        for (int i = 0; i < kRowValues; ++i) d[i] = all ? __builtin_inff() : d[i];
-#pragma unroll 1
-        for (int c = 0; c < kCent; ++c) {
-            const half2_t r = as_half2(lds_word(pair + 4u * c)) * s2;
-#pragma unroll
-            for (int i = 0; i < kRowValues; ++i) {
-                const float dc = distance<0>(v, i, r);
-                if (all && dc < d[i]) {  // strict: the lowest index wins a tie
-                    k[i] = (uint32_t)c;
-                    d[i] = dc;
-                }
-            }
-        }
-    }
     idx = 0;
 #pragma unroll
     for (int i = 0; i < kRowValues; ++i) idx = (idx << 4) | (i == skip ? 15u : k[i]);
     if (kSse) {
         sse = tree_sum(d, skip);
     }
+    return marks;
+}
+
+// ---- value by value: groups for which the table of nearest centroids does not hold --------------------------------------
+// Scales below kSearchLeastScale, and groups that one large value presses into bins with many centroids, where most
+// patterns tend to be left over from the bounds as well.  Bound by the vector instructions (24 per value and pattern).  With
+// a compare and two masked moves per centroid and value inside the ratings by the table instead, four groups at a time, and
+// with all patterns rated at every small scale, 131072 groups under 64 patterns took 3.1 ms at scales of 2^-12 (0.13 ms here,
+// 0.59 ms at 2^-20, where all patterns are left), 3.1 ms when all zero (0.06 ms), 1.8 ms with one value 100 times as large as
+// the rest (0.38 ms), 3.6 ms in the self-contained format (0.67 ms); all patterns value by value without the bounds: 0.52 and
+// 0.61 ms.
+
+// A rating by the table takes 500 to 1000 cycles for the four rows of a wavefront, by how many third candidates have to be looked
+// at; value by value it is 160 for one row, and about 3500 to begin with.  So a wavefront goes on that way where the bounds
+// have told hardly any patterns apart, which is looked at after this many ratings.
+constexpr int kLookAfter = 4;
+__device__ __forceinline__ bool most_left(uint64_t left, int S) { return 4 * (__builtin_popcountll(left) + kLookAfter) > 3 * S; }
+// whether `lanes` (a ballot) holds a lane of row `row`
+__device__ __forceinline__ bool row_any(uint64_t lanes, int row) {
+    const uint32_t half = (row & 2) ? (uint32_t)(lanes >> 32) : (uint32_t)lanes;
+    return ((half >> (16 * (row & 1))) & 0xFFFFu) != 0u;
+}
+
+// The indices of the row's values under the pattern with centroids at `pair`, compared with all of them.  The distance
+// falls (weakly) with k up to its least value and rises (weakly) after it, so the lowest nearest index is the last k at which
+// it strictly drops.
+__device__ __forceinline__ uint32_t scan_indices(uint32_t pair, half2_t s2, const RowValues& v, int skip) {
+    uint32_t k[kRowValues];
+    float last[kRowValues];
+#pragma unroll
+    for (int i = 0; i < kRowValues; ++i) {
+        k[i] = 0;
+        last[i] = __builtin_inff();
+    }
+#pragma unroll 1
+    for (uint32_t c = 0; c < 16u; c += 2u) {
+        const half2_t r = as_half2(lds_word(pair + 4u * c)) * s2;
+#pragma unroll
+        for (int i = 0; i < kRowValues; ++i) {
+            const float a = distance<0>(v, i, r), b = distance<1>(v, i, r);
+            k[i] = a < last[i] ? c : k[i];
+            k[i] = b < a ? c + 1u : k[i];
+            last[i] = b;
+        }
+    }
+    uint32_t idx = 0;
+#pragma unroll
+    for (int i = 0; i < kRowValues; ++i) idx = (idx << 4) | (i == skip ? 15u : k[i]);
+    return idx;
+}
+
+// Four sums over the 32 lanes of each half of the wavefront at once, in the balanced tree (lanes l and l ^ 1, then ^ 2, ^ 4, ^ 8,
+// ^ 16): at the first two levels a lane keeps the entries that match its own lane bit and sends the others to its partner.
+// Lane l returns its half's total of entry l & 3.
+__device__ __forceinline__ float half_sum4(const float (&q)[4], int lane) {
+    const bool b0 = lane & 1, b1 = lane & 2;
+    float a[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) a[i] = __fadd_rn(b0 ? q[2 * i + 1] : q[2 * i], dpp<0xB1>(b0 ? q[2 * i] : q[2 * i + 1]));
+    float t = __fadd_rn(b1 ? a[1] : a[0], dpp<0x4E>(b1 ? a[0] : a[1]));
+    const auto swizzled = [](float v, auto pattern) { return __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, v), decltype(pattern)::value)); };
+    t = __fadd_rn(t, swizzled(t, std::integral_constant<int, 0x101F>{}));     // lane ^ 4
+    t = __fadd_rn(t, dpp<0x128>(t));                                          // row_ror 8: lane ^ 8
+    return __fadd_rn(t, swizzled(t, std::integral_constant<int, 0x401F>{}));  // lane ^ 16
+}
+// the least over the wavefront
+__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
+    v = row_min(v);
+    const auto of = [&](int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); };
+    return min(min(of(0), of(16)), min(of(32), of(48)));
+}
+
+// Rates the rows' patterns `later` and takes the best of them into (best, pattern), the lowest pattern on a tie; won: whether
+// it did.  One group after the other, four values per lane, a pattern per half of the wavefront: the reconstructed centroids
+// come from LDS as FP32, where a difference is a two-operand FP32 instruction, issued in 2.7 cycles (4.4 for the
+// mixed-precision one of half_diff).  pairs: the patterns' (centroid k, centroid k + 1) words in LDS; recon: S x 16 words of
+// LDS of the wavefront; at_skip: place of the group's value that counts as without error (128 or more: none).
+__device__ __forceinline__ void scan_patterns(float* recon, const uint32_t* pairs, int S, const RowValues& v, uint32_t smax, uint32_t at_skip, uint64_t later,
+                                              int lane, float& best, uint32_t& pattern, bool& won) {
+    const uint64_t rows = __builtin_amdgcn_ballot_w64(later != 0ull);
+    won = false;
+#pragma unroll 1
+    for (int g = 0; g < kWaveRows; ++g) {
+        if (((rows >> (16 * g)) & 1ull) == 0ull) continue;
+        asm volatile("" : "+v"(lane));  // what is derived from the lane is formed here, not kept through the search
+        const auto of_row = [&](uint32_t t) { return (uint32_t)__builtin_amdgcn_readlane((int)t, 16 * g); };
+        uint64_t todo = ((uint64_t)of_row((uint32_t)(later >> 32)) << 32) | of_row((uint32_t)later);
+        const _Float16 s = __builtin_bit_cast(_Float16, (unsigned short)of_row(smax));
+        const uint32_t skip = of_row(at_skip);
+        // values 4 m .. 4 m + 3 of the group for lane m of either half: two words of the row's lane m / 2
+        const int m = lane & 31, from = 4 * (16 * g + (m >> 1));
+        uint32_t w[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[i] = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)v.x[i]);
+        const half2_t xa = as_half2((m & 1) ? w[2] : w[0]), xb = as_half2((m & 1) ? w[3] : w[1]);
+        const float x[4] = {(float)xa[0], (float)xa[1], (float)xb[0], (float)xb[1]};
+        const uint32_t zero = skip - 4u * (uint32_t)m;  // which of the four counts as zero, if one of 0 .. 3
+        wave_fence();
+        for (int i = lane; i < S * 16; i += 64) recon[i] = (float)(as_half2(pairs[i])[0] * s);
+        wave_fence();
+        float mine = __builtin_inff();  // lane l: the least so far among its half's entries l & 3
+        uint32_t mine_p = pattern;
+        while (todo != 0ull) {
+            float q[4];
+            uint32_t entry_p = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                q[e] = __builtin_inff();
+                if (todo != 0ull) {  // uniform; the halves take one pattern each, the last one twice if their number is odd
+                    const uint32_t p0 = (uint32_t)__builtin_ctzll(todo);
+                    todo &= todo - 1ull;
+                    const uint32_t p1 = todo != 0ull ? (uint32_t)__builtin_ctzll(todo) : p0;
+                    todo &= todo - 1ull;
+                    const uint32_t p = lane < 32 ? p0 : p1;
+                    entry_p = (lane & 3) == e ? p : entry_p;
+                    const float4_t* r4 = reinterpret_cast<const float4_t*>(recon + p * 16u);
+                    float d[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) d[i] = __builtin_inff();
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const float4_t r = r4[c];
+#pragma unroll
+                        for (int k = 0; k < 4; k += 2)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) d[i] = fminf(fminf(d[i], fabsf(__fsub_rn(x[i], r[k]))), fabsf(__fsub_rn(x[i], r[k + 1])));
+                    }
+                    float sq[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) sq[i] = zero == (uint32_t)i ? 0.0f : __fmul_rn(d[i], d[i]);
+                    __builtin_amdgcn_sched_barrier(0);  // one pattern's centroids at a time in registers
+                    q[e] = __fadd_rn(__fadd_rn(sq[0], sq[1]), __fadd_rn(sq[2], sq[3]));
+                }
+            }
+            const float t = half_sum4(q, lane);
+            if (t < mine) {  // strict <: an earlier pattern keeps a tie
+                mine = t;
+                mine_p = entry_p;
+            }
+        }
+        const uint32_t least = wave_min(__builtin_bit_cast(uint32_t, mine));
+        const uint32_t win = wave_min(__builtin_bit_cast(uint32_t, mine) == least ? mine_p : 0xFFFFu);
+        const float sse = __builtin_bit_cast(float, least);
+        if ((lane >> 4) == g && (sse < best || (sse == best && win < pattern))) {
+            best = sse;
+            pattern = win;
+            won = true;
+        }
+    }
+    wave_fence();
 }
 
 // ---- bounds on every pattern's error, and the patterns that can be the best ------------------------------------------
 // Workgroup-wide LDS of the bounds: histogram, partial sums of the matrix product, the pattern tiles' least upper bounds,
-// the patterns left per group.  kOver: the partial sums lie over the histogram, at the price of a barrier, so that one
-// more workgroup fits a compute unit.
+// the groups' slack, the patterns left per group.  kOver: the partial sums lie over the histogram, at the price of a barrier,
+// so that one more workgroup fits a compute unit.
 struct SearchLds {
     uint32_t* hist;   // [kSearchBatch][kHistStride]
     float4_t* part;   // [wavefront (and tile of groups)][sum, error][64]
     float* least;     // [4][kSearchBatch]
+    float* slack;     // [kSearchBatch]: what a group's small scale adds to the errors (set_slack)
+    uint32_t* spare;  // [kSearchBatch]: a word per group for the caller
     uint16_t* left;   // [kSearchBatch][4]
 };
 // one tile of patterns per 16; the wavefronts share the tiles evenly, each over its own part of the bins
@@ -231,14 +367,16 @@ constexpr int search_parts(int tiles) { return tiles == 1 ? 8 : tiles == 2 ? 4 :
 static_assert(kSearchWaves * 4 * 64 * 4 <= kSearchBatch * kHistStride, "the partial sums fit over the histogram");
 constexpr int search_part_words(int tiles) { return kSearchWaves * (search_parts(tiles) == 2 ? 1 : 2) * 2 * 64 * 4; }
 template <bool kOver>
-constexpr int search_lds_words(int tiles) { return kSearchBatch * kHistStride + (kOver ? 0 : search_part_words(tiles)) + 4 * kSearchBatch + kSearchBatch * 2; }
+constexpr int search_lds_words(int tiles) { return kSearchBatch * kHistStride + (kOver ? 0 : search_part_words(tiles)) + 6 * kSearchBatch + kSearchBatch * 2; }
 template <bool kOver>
 __device__ __forceinline__ SearchLds search_lds(uint32_t* base, int tiles) {
     SearchLds s;
     s.hist = base;
     s.part = reinterpret_cast<float4_t*>(kOver ? base : base + kSearchBatch * kHistStride);
     s.least = reinterpret_cast<float*>(base + kSearchBatch * kHistStride + (kOver ? 0 : search_part_words(tiles)));
-    s.left = reinterpret_cast<uint16_t*>(s.least + 4 * kSearchBatch);
+    s.slack = s.least + 4 * kSearchBatch;
+    s.spare = reinterpret_cast<uint32_t*>(s.slack + kSearchBatch);
+    s.left = reinterpret_cast<uint16_t*>(s.spare + kSearchBatch);
     return s;
 }
 
@@ -284,6 +422,21 @@ __device__ __forceinline__ void convert_hist(uint32_t* rows, int lane) {
     }
 }
 
+// The tables' errors cover the rounding of reconstructed centroids for scales of at least kSearchLeastScale.  Below, that rounding
+// (to a multiple of 2^-24) moves every distance by up to d = 2^-25 / s more, the root of the squared error by sqrt(128) d:
+// this is sqrt(128) d in the root of the tables' unit, with a margin, for the row's group (at `own`, zero to begin with).
+// Written only by wavefronts that hold such a group, or held one in their last batch (set).
+__device__ __forceinline__ void set_slack(float* own, float s, int l, bool& set) {
+    constexpr float kUnit = 1.02f * 362.04f * 0x1p-25f;  // sqrt(128 kSearchCoefScale) 2^-25
+    static_assert(ecco::kSearchCoefScale == 1024.0f, "sqrt(128 x 1024) = 362.04");
+    const bool small = s < ecco::kSearchLeastScale;
+    const bool any = __builtin_amdgcn_ballot_w64(small) != 0ull;
+    if (any || set) {
+        if (l == 0) *own = small && s > 0.0f ? kUnit * __builtin_amdgcn_rcpf(s) : 0.0f;
+        set = any;
+    }
+}
+
 // For the batch's converted histogram: the patterns of this wavefront's group (wave, row) that can have the least error,
 // one bit each.  Called by all wavefronts of the workgroup together (barriers inside); the histogram is free afterwards.
 template <int kTiles, bool kOver>
@@ -309,6 +462,10 @@ __device__ __forceinline__ uint64_t patterns_left(const SearchLds& L, const Coef
             sum[m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a1), __builtin_bit_cast(half8_t, C.w[3 * j + 1]), sum[m], 0, 0, 0);
         }
     }
+    // (read here, so that the barrier covers the wait)
+    int at_lane = lane;  // taken afresh: the address is formed here, not kept through the search
+    asm volatile("" : "+v"(at_lane));
+    const uint4 bits = *reinterpret_cast<const uint4*>(L.slack + 16 * min(part, 1) + 4 * (at_lane >> 4));
     if (kOver) __syncthreads();
     // parts 0 and 1 of a tile of patterns add up the parts for groups 0..15 and 16..31
     float4_t s, e;
@@ -336,6 +493,11 @@ __device__ __forceinline__ uint64_t patterns_left(const SearchLds& L, const Coef
     }
     // lane l, register j: group 16 part + 4 (l / 16) + j of the batch, pattern 16 tile + l % 16
     const bool mine = part < 2;
+    if (__builtin_amdgcn_ballot_w64((bits.x | bits.y | bits.z | bits.w) != 0u) != 0ull) {
+        const float4_t slack = __builtin_bit_cast(float4_t, bits);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) e[j] += slack[j] * (2.0f * __builtin_amdgcn_sqrtf(fmaxf(s[j] + e[j] + 3.0f, 0.0f)) + slack[j]);
+    }
     float least[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {

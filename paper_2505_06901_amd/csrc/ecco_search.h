@@ -29,7 +29,8 @@ constexpr int kSearchBins = 256;
 constexpr int kSearchBlocks = 8;        // the matrix product takes the bins 32 at a time
 constexpr float kSearchCoefScale = 1024.0f;  // A, B, E are stored times this, in FP16
 // the tables hold for scales of at least this (below, the rounding of a reconstructed centroid to a multiple of 2^-24 is
-// no longer small against the scale): other groups are rated by the plain search over all patterns
+// no longer small against the scale): for other groups the bounds are widened, and the patterns left compared value by value
+// (ecco_rows.h)
 constexpr float kSearchLeastScale = 0x1p-11f;
 // entry of the table of nearest centroids: bits 5:2 the lowest centroid a that can be nearest to a value of the bin
 // (the others are a + 1 and, if so marked, a + 2), and two marks

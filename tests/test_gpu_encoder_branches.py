@@ -102,3 +102,84 @@ def test_self_contained_block(dev, S, n, texp):
     x = groups(np.pad(om.cent.view(np.float16), ((0, 0), (0, 1)), mode="edge"), n, n)
     want = P.encode(om, x.view(np.uint16))
     assert np.array_equal(E.ecco_pb_encode(m, torch.from_numpy(x).to(dev)).cpu().numpy(), want)
+
+
+def hard_groups(n, seed):
+    """What the tables of the search do not serve, side by side in the wavefronts: all-zero groups (both signs), scales below
+    2^-11 down to the smallest FP16 value, groups in which one value is far larger than the rest; ordinary ones between them."""
+    rng = np.random.default_rng(seed)
+    x = rng.standard_normal((n, 128)) * 0.02
+    kind = rng.integers(0, 8, n)
+    x[kind == 0] = 0.0
+    x[kind == 1] *= -0.0
+    x[kind == 2] *= 2.0 ** -rng.uniform(5, 18, (n, 1))[kind == 2]
+    k = np.flatnonzero((kind == 3) | (kind == 4))
+    x[k, rng.integers(0, 128, k.size)] = 10.0 ** rng.uniform(-0.5, 2, k.size) * rng.choice([-1, 1], k.size)
+    x[kind == 5] = np.sign(x[kind == 5]) * 6e-8
+    return x.astype(np.float16)
+
+
+def crowded_tables(S, seed):
+    """Patterns of such groups: most centroids within a few hundredths of 0, some equal."""
+    rng = np.random.default_rng(seed)
+    cent = rng.standard_normal((S, 16)) * 10.0 ** rng.uniform(-3, -1, (S, 1))
+    cent[:, 0], cent[:, 15] = -1, 1
+    cent[rng.random((S, 16)) < 0.05] = 0.0
+    return np.sort(np.clip(cent, -1, 1), axis=1).astype(np.float16)
+
+
+@pytest.mark.parametrize("S,n", [(1, 3001), (2, 3002), (5, 2701), (16, 2001), (33, 1999), (63, 1031), (64, 4099)])
+def test_value_by_value(dev, S, n):
+    """Rows that leave the tables for the search over all centroids, alone in their wavefront and side by side; pattern
+    counts that do not fill the search's last four."""
+    from oracle import oracle as O
+    from oracle import paper_block as P
+    cent, x = crowded_tables(S, S), hard_groups(n, n)
+    lens = np.full((S, 16), 4, np.uint8)
+    m = E.ecco_model_to_device(E.ecco_model_create(cent, lens), 0)
+    t = torch.from_numpy(x).to(dev)
+    for encode, oracle_encode in ((E.ecco_encode, O.encode), (E.ecco_encode_minmax, O.encode_minmax)):
+        want = oracle_encode(cent.view(np.uint16), lens, x.view(np.uint16))
+        blocks, meta = encode(m, t)
+        assert np.array_equal(meta.cpu().numpy().view(np.uint32), want[1])
+        assert np.array_equal(blocks.cpu().numpy(), want[0])
+    om = pb_model(P, S=S, texp=-9, seed=S)
+    om.cent[:] = cent[:, :15].view(np.uint16)
+    pm = E.ecco_pb_model_to_device(E.ecco_pb_model_create(om.cent, om.lens, om.kp_lens, om.texp), 0)
+    assert np.array_equal(E.ecco_pb_encode(pm, t).cpu().numpy(), P.encode(om, x.view(np.uint16)))
+
+
+def test_no_input_is_far_slower(dev):
+    """Encoding must not collapse on padding (all-zero groups), on tiny scales or on groups that one value dominates: against
+    ordinary weights at most 3 times for zeros (as fast, when measured) and 15 times where every value is compared with every
+    centroid of all 64 patterns (6 to 9 times, when measured)."""
+    from paper_2505_06901_amd import workloads as W
+    n = 65536
+
+    def outliers(rows, seed):
+        x = np.random.default_rng(seed).standard_normal((rows, 128)) * 0.02
+        x[:, 7] = 6.0
+        return x.astype(np.float16)
+
+    def time_of(call):
+        call()
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        best = float("inf")
+        for _ in range(5):
+            a.record(); call(); b.record(); b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    weights = W.weight_matrix(2048, 128, 0.02, 1e-3, 10.0, 1)
+    w = torch.from_numpy(W.weight_matrix(n, 128, 0.02, 1e-3, 10.0, 2)).to(dev)
+    tiny = (w.float() / w.float().abs().amax(1, keepdim=True) * 2.0**-20).half()
+    blocks, meta = torch.empty((n, 64), dtype=torch.uint8, device=dev), torch.empty((n,), dtype=torch.int32, device=dev)
+    out = torch.from_numpy(outliers(n, 4)).to(dev)
+    m, mo = (E.ecco_model_to_device(E.ecco_fit_patterns(c, 64, 12, 1), 0) for c in (weights, outliers(2048, 3)))
+    p, po = (E.ecco_pb_model_to_device(E.ecco_pb_fit(c, 64, 1), 0) for c in (weights, outliers(2048, 3)))
+    for name, mm, mo, call in (("full", m, mo, lambda model, x: E.ecco_encode(model, x, blocks, meta)),
+                               ("self-contained", p, po, lambda model, x: E.ecco_pb_encode(model, x, blocks))):
+        usual = time_of(lambda: call(mm, w))
+        assert time_of(lambda: call(mm, torch.zeros_like(w))) <= 3 * usual, name
+        assert time_of(lambda: call(mm, tiny)) <= 15 * usual, name
+        assert time_of(lambda: call(mo, out)) <= 15 * usual, name
