@@ -99,18 +99,19 @@ def _check(status: int, where: str):
         raise EccoError(status, where)
 
 
-_rt = None  # torch's runtime layer, imported with the first device call
+_current = None  # what _stream asks, chosen with the first device call
 
 
 def _stream() -> int:
-    """The current stream of the current device, as an integer.  Asked of torch's runtime layer directly: building the
-    Stream object of torch.cuda.current_stream() takes 3 us, as long as a kernel launch."""
-    global _rt
-    if _rt is None:
+    """The current stream of the current device, as an integer.  Asked of torch's runtime layer directly where it offers
+    that: building the Stream object of torch.cuda.current_stream() takes 3 us, as long as a kernel launch."""
+    global _current
+    if _current is None:
         import torch
         torch.cuda.current_stream()  # initialises
-        _rt = torch._C
-    return _rt._cuda_getCurrentRawStream(_rt._cuda_getDevice())
+        raw, device = (getattr(torch._C, name, None) for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+        _current = (raw, device) if raw and device else (lambda _: torch.cuda.current_stream().cuda_stream, int)
+    return _current[0](_current[1]())
 
 
 def _dp(t):

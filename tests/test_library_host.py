@@ -256,6 +256,25 @@ def test_build_rejects_register_spills(monkeypatch):
         B._check_kernel_resources("nothing here", False)
 
 
+@pytest.mark.parametrize("private", [True, False])
+def test_stream_with_and_without_torchs_private_functions(monkeypatch, private):
+    """The binding asks torch's runtime layer for the stream where it can, and torch.cuda.current_stream() otherwise."""
+    import torch
+    from paper_2505_06901_amd import binding
+
+    class Stream:
+        cuda_stream = 7
+
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    for name, f in (("_cuda_getDevice", lambda: 3), ("_cuda_getCurrentRawStream", lambda device: 40 + device)):
+        if private:
+            monkeypatch.setattr(torch._C, name, f, raising=False)
+        else:
+            monkeypatch.delattr(torch._C, name, raising=False)
+    monkeypatch.setattr(binding, "_current", None, raising=False)
+    assert [binding._stream(), binding._stream()] == ([43, 43] if private else [7, 7])
+
+
 def test_bench_refuses_more_than_one_gpu():
     """bench.py is a one-GPU program: any other --gpus value ends with a message before anything touches a device."""
     import subprocess
