@@ -211,7 +211,8 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
         }
         if (__builtin_amdgcn_ballot_w64(later != 0) != 0ull) {
             bool won;
-            scan_patterns(reinterpret_cast<float*>(L.hist + wave * kWaveRows * kHistStride), smem + S * (kSearchBins / 4), S, v, smax, kGroup, later, lane, best, pattern, won);
+            scan_patterns(reinterpret_cast<float*>(L.hist + wave * kWaveRows * kHistStride), smem + S * (kSearchBins / 4), S, v, smax, kGroup, later, lane,
+                          best, pattern, won);
             const uint32_t id = scan_indices(T.pair + pattern * 64u, s2, v, -1);
             idx = won ? id : idx;
         }
@@ -278,7 +279,8 @@ __device__ __forceinline__ uint32_t select_minmax(const uint32_t* cent, int stri
 // One workgroup per group: its 16 rows of lanes hold the same values and rate a sixteenth of the patterns each, value by
 // value.  The search above starts with 120 KB of tables per workgroup and passes through four barriers for 32 groups at a
 // time: appending 2 x 256 groups took 9.9 us with it.  Rating with the table of nearest centroids took as long here: among
-// all 64 patterns there are always some whose centroids crowd a bin.  With the min/max selector every row selects alike and only the index step is left to share.
+// all 64 patterns there are always some whose centroids crowd a bin.  With the min/max selector every row selects alike and
+// only the index step is left to share.
 constexpr int kFewThreads = 256;
 constexpr int kFewRows = kFewThreads / kRowLanes;
 
@@ -332,12 +334,12 @@ __global__ __launch_bounds__(kFewThreads) void encode_few_kernel(Job<Io> j0, Job
             const uint4 c0 = c[0], c1 = c[1];
             const uint32_t pairs[kK / 2] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
             float d[kRowValues];
-    #pragma unroll
+#pragma unroll
             for (int i = 0; i < kRowValues; ++i) d[i] = __builtin_inff();
-    #pragma unroll
+#pragma unroll
             for (int k = 0; k < kK / 2; ++k) {
                 const uint32_t r = __builtin_bit_cast(uint32_t, as_half2(pairs[k]) * s2);
-    #pragma unroll
+#pragma unroll
                 for (int i = 0; i < kRowValues / 2; ++i) {
                     d[2 * i] = nearer<0>(d[2 * i], v.x[i], r);
                     d[2 * i + 1] = nearer<1>(d[2 * i + 1], v.x[i], r);

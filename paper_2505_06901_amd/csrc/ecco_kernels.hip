@@ -36,10 +36,6 @@ typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ float half_bits_f(uint32_t bits) { return __half2float(__ushort_as_half((unsigned short)bits)); }
-// dequantisation: one exact FP32 product, one rounding to FP16
-__device__ __forceinline__ uint32_t dequant_bits(uint32_t cent_bits, float s) {
-    return __half_as_ushort(__float2half_rn(half_bits_f(cent_bits) * s));
-}
 
 // orders the LDS accesses of one wavefront (private buffers need no workgroup barrier)
 __device__ inline void wave_lds_fence() {
@@ -299,9 +295,9 @@ struct UnitLoad {
     uint4 v0, v1;
     uint32_t meta;
 };
-// the payload pieces of this lane for unit (row, ct) and the meta word of the unit's block `slot` (the one it decodes).  Block indices are clamped into
-// the row, so every lane issues the same loads and a slot past the row end holds a copy of the row's
-// last block: it decodes to finite values, which the caller drops.  Nothing here uses the loaded
+// the payload pieces of this lane for unit (row, ct) and the meta word of the unit's block `slot` (the one it decodes).
+// Block indices are clamped into the row, so every lane issues the same loads and a slot past the row end holds a copy of
+// the row's last block: it decodes to finite values, which the caller drops.  Nothing here uses the loaded
 // data, so the loads stay in flight while the previous unit is decoded.
 __device__ __forceinline__ UnitLoad load_unit(const uint4* __restrict__ blocks, const uint32_t* __restrict__ meta,
                                               int row, int gpr, int ct, int lane, int slot) {
@@ -903,10 +899,11 @@ __global__ __launch_bounds__(kLongV ? 512 : kAttnThreads) void kv_attend_kernel(
 
 // ---- grouped-query attention over compressed K / V, split over the tokens ---------------------------------
 // Several query heads share one key/value head (Section 5.3: with grouped-query attention the batched
-// matrix-vector products become small matrix products).  One workgroup of 8 or 12 wavefronts per (sequence, key/value head, token range) decodes every K and V block of its range once and serves all
-// grp = Hq / Hkv query heads of the group with it, on the matrix cores, in 16 x 16 tiles (v_mfma_f32_16x16x32_f16):
-// a lane's four accumulator registers per tile leave room for three wavefronts per SIMD, where 32 x 32 tiles, half of
-// whose columns no group of at most 16 heads can use, left two.
+// matrix-vector products become small matrix products).  One workgroup of 8 or 12 wavefronts per (sequence, key/value
+// head, token range) decodes every K and V block of its range once and serves all grp = Hq / Hkv query heads of the group
+// with it, on the matrix cores, in 16 x 16 tiles (v_mfma_f32_16x16x32_f16): a lane's four accumulator registers per tile
+// leave room for three wavefronts per SIMD, where 32 x 32 tiles, half of whose columns no group of at most 16 heads can use,
+// left two.
 // A unit is 32 tokens; lane l decodes chain (l / 16) % 2 of token l % 16 + 16 (l / 32).
 //   scores  S[token][head] = sum_dim K[token][dim] q[head][dim]: eight decoded values of a lane are its A operand (row
 //           l % 16, k slice l / 16).  Slices 0 and 1 belong to tokens 0..15, slices 2 and 3 to tokens 16..31; with up to

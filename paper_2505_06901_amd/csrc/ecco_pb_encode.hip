@@ -154,7 +154,8 @@ void pb_encode_kernel(const uint32_t* __restrict__ dev, int S, float inv_tscale,
             bool won;
             int skip_again = skip;  // its comparisons are formed here, not kept through the search
             asm volatile("" : "+v"(skip_again));
-            scan_patterns(reinterpret_cast<float*>(L.hist + wave * kWaveRows * kHistStride), pair_at, S, v, __builtin_bit_cast(uint32_t, s2) & 0xFFFFu, top >> 16, later, lane, best, pattern, won);
+            scan_patterns(reinterpret_cast<float*>(L.hist + wave * kWaveRows * kHistStride), pair_at, S, v, __builtin_bit_cast(uint32_t, s2) & 0xFFFFu,
+                          top >> 16, later, lane, best, pattern, won);
             const uint32_t id = scan_indices(pair + pattern * 64u, s2, v, skip_again);
             idx = won ? id : idx;
         }

@@ -538,7 +538,7 @@ def test_attend_ignores_cache_behind_seq_len(dev, oracle):
 
 @pytest.mark.parametrize("grp,n_splits", [(1, 1), (4, 1), (8, 3), (16, 2), (3, 5)])
 def test_kv_attend_gqa_matches_oracle(dev, oracle, grp, n_splits):
-    B, Hkv, T = 3, 2, 1500 if grp >= 8 else 700   # several spans for the larger groups (span = 7680 / group tokens), ragged tails
+    B, Hkv, T = 3, 2, 1500 if grp >= 8 else 700   # ragged tails; two spans per range for the group of 16 (a span holds 7936 / group - 4 tokens, in whole units)
     Hq = Hkv * grp
     k, v, mk, mv = _kv_setup(dev, oracle, B, Hkv, T, 16)
     kb, km, okb, okm = enc_both(dev, oracle, mk, k); vb, vm, ovb, ovm = enc_both(dev, oracle, mv, v)
@@ -562,15 +562,17 @@ def test_kv_attend_gqa_matches_oracle(dev, oracle, grp, n_splits):
         assert e.value.status == -2
 
 
+# eight wavefronts where twelve would take as many rounds over the units (32 tokens) of a range, twelve otherwise
 @pytest.mark.parametrize("lengths,T,grp,n_splits", [
-    ([1300, 0, 1, 33, 640, 31, 1024, 7], 1300, 2, 4),    # empty, one-token and full sequences side by side
-    ([900, 899], 900, 9, 2),                              # more than eight heads: two products per unit
-    ([4096 + 31, 40, 40, 40, 40, 40], 4127, 3, 2),        # one sequence over a hundred units longer than the rest
-    ([3, 0, 65, 96] * 16 + [96, 17], 96, 1, 3),           # more than 64 sequences: every one is cut into n_splits
+    ([1300, 0, 1, 33, 640, 31, 1024, 7], 1300, 2, 4),    # 11 units: twelve; empty, one-token and full sequences side by side
+    ([900, 899], 900, 9, 2),                              # 15 units: eight; more than eight heads: two products per unit
+    ([700, 1, 353], 700, 12, 2),                          # 11 units: twelve; more than eight heads
+    ([4096 + 31, 40, 40, 40, 40, 40], 4127, 3, 2),        # 65 units: twelve; one sequence over a hundred units longer than the rest
+    ([3, 0, 65, 96] * 16 + [96, 17], 96, 1, 3),           # 1 unit: eight; many sequences
     ([0, 0, 0], 64, 4, 5),                                # nothing to attend to
 ])
-def test_gqa_ranges_follow_the_lengths(dev, oracle, lengths, T, grp, n_splits):
-    """Unequal sequences under token splits: whatever the deal, every token counts once.  Each call twice, same bits."""
+def test_gqa_unequal_lengths(dev, oracle, lengths, T, grp, n_splits):
+    """Every sequence is cut into n_splits equal ranges of its own length: every token counts once.  Each call twice, same bits."""
     B, Hkv = len(lengths), 2
     k, v, mk, mv = _kv_setup(dev, oracle, B, Hkv, T, 16)
     kb, km, okb, okm = enc_both(dev, oracle, mk, k); vb, vm, ovb, ovm = enc_both(dev, oracle, mv, v)
@@ -623,7 +625,8 @@ def test_gqa_variants(dev, oracle, long_k, long_v, S, grp, T, n_splits):
 
 
 def test_gqa_long_context(dev, oracle):
-    """One sequence of 20 000 tokens, 8 query heads over 2 key/value heads, 16 token splits (several spans per split)."""
+    """One sequence of 20 000 tokens, 8 query heads over 2 key/value heads: 16 token splits (one span each), 3 (three spans) and
+    1 (eleven)."""
     B, Hkv, grp, T = 1, 2, 4, 20000
     k, v = W.kv_cache(B, Hkv, T, 128, seed=13)
     mk = E.ecco_model_to_device(E.ecco_fit_patterns(k[:, :, :512], 16, 12, 3), 0)
