@@ -211,7 +211,7 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
         }
         if (__builtin_amdgcn_ballot_w64(later != 0) != 0ull) {
             bool won;
-            scan_patterns(reinterpret_cast<float*>(L.hist + wave * kWaveRows * kHistStride), smem + S * (kSearchBins / 4), S, v, smax, kGroup, later, lane,
+            scan_patterns(reinterpret_cast<float*>(L.hist + wave * kWaveRows * kHistStride), smem + S * (kSearchBins / 4), v, smax, kGroup, later, lane,
                           best, pattern, won);
             const uint32_t id = scan_indices(T.pair + pattern * 64u, s2, v, -1);
             idx = won ? id : idx;

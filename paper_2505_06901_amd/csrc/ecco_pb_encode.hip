@@ -61,7 +61,7 @@ void pb_encode_kernel(const uint32_t* __restrict__ dev, int S, float inv_tscale,
     extern __shared__ __align__(16) uint32_t smem[];
     const DevLayout D{S};
     const int tiles = ecco::search_tiles(S);
-    const int lane = threadIdx.x & 63, l = lane & 15, row = lane >> 4;
+    const int lane0 = threadIdx.x & 63, l0 = lane0 & 15, row0 = lane0 >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint8_t* near = reinterpret_cast<const uint8_t*>(smem);
     uint32_t* pair_at = smem + S * (ecco::kSearchBins / 4);
@@ -76,9 +76,9 @@ void pb_encode_kernel(const uint32_t* __restrict__ dev, int S, float inv_tscale,
 
     const size_t batches = (n_groups + kSearchBatch - 1) / kSearchBatch;
     RowValues v;
-    load_values<kSearchBatch>(v, src, n_groups, blockIdx.x, wave * kWaveRows + row, l);
+    load_values<kSearchBatch>(v, src, n_groups, blockIdx.x, wave * kWaveRows + row0, l0);
     Coefs<kTiles> C;
-    C.load(dev + D.coef(), wave, tiles, lane);
+    C.load(dev + D.coef(), wave, tiles, lane0);
     copy_words(smem, dev + D.near(), S * kTableWords);  // near, pair, codes, lengths follow each other
     copy_words(fp8_at, dev + D.fp8(), kFp8Words);
     copy_words(kpenc, dev + D.kpenc(), (S + 3) & ~3);
@@ -114,7 +114,7 @@ void pb_encode_kernel(const uint32_t* __restrict__ dev, int S, float inv_tscale,
         set_bins<true>(v, kSearchStep * __builtin_amdgcn_rcpf(s), hist, skip);
         wave_fence();
         convert_hist(L.hist + wave * kWaveRows * kHistStride, lane);
-        uint64_t left = patterns_left<kTiles, true>(L, C, tiles, wave, lane);
+        uint64_t left = patterns_left<kTiles, true>(L, C, tiles, wave, lane0);
         // What the table of nearest centroids does not serve is rated value by value (scan_patterns): from the start scales too
         // small for it, and all patterns where the scale was rounded so far that values lie beyond the bins (which reach 1.09
         // scales).  Of scale 0 all patterns are alike: the first wins with index 0.
@@ -154,7 +154,7 @@ void pb_encode_kernel(const uint32_t* __restrict__ dev, int S, float inv_tscale,
             bool won;
             int skip_again = skip;  // its comparisons are formed here, not kept through the search
             asm volatile("" : "+v"(skip_again));
-            scan_patterns(reinterpret_cast<float*>(L.hist + wave * kWaveRows * kHistStride), pair_at, S, v, __builtin_bit_cast(uint32_t, s2) & 0xFFFFu,
+            scan_patterns(reinterpret_cast<float*>(L.hist + wave * kWaveRows * kHistStride), pair_at, v, __builtin_bit_cast(uint32_t, s2) & 0xFFFFu,
                           top >> 16, later, lane, best, pattern, won);
             const uint32_t id = scan_indices(pair + pattern * 64u, s2, v, skip_again);
             idx = won ? id : idx;

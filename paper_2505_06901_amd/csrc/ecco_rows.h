@@ -205,13 +205,13 @@ __device__ __forceinline__ uint32_t rate_pattern(const uint8_t* near, uint32_t p
 // Scales below kSearchLeastScale, and groups that one large value presses into bins with many centroids, where most
 // patterns tend to be left over from the bounds as well.  Bound by the vector instructions (24 per value and pattern).  With
 // a compare and two masked moves per centroid and value inside the ratings by the table instead, four groups at a time, and
-// with all patterns rated at every small scale, 131072 groups under 64 patterns took 3.1 ms at scales of 2^-12 (0.13 ms here,
-// 0.59 ms at 2^-20, where all patterns are left), 3.1 ms when all zero (0.06 ms), 1.8 ms with one value 100 times as large as
-// the rest (0.38 ms), 3.6 ms in the self-contained format (0.67 ms); all patterns value by value without the bounds: 0.52 and
+// with all patterns rated at every small scale, 131072 groups under 64 patterns took 3.1 ms at scales of 2^-12 (0.11 ms here,
+// 0.61 ms at 2^-20, where all patterns are left), 3.1 ms when all zero (0.06 ms), 1.8 ms with one value 100 times as large as
+// the rest (0.38 ms), 3.6 ms in the self-contained format (0.68 ms); all patterns value by value without the bounds: 0.52 and
 // 0.61 ms.
 
 // A rating by the table takes 500 to 1000 cycles for the four rows of a wavefront, by how many third candidates have to be looked
-// at; value by value it is 160 for one row, and about 3500 to begin with.  So a wavefront goes on that way where the bounds
+// at; value by value it is 160 for one row, and about 3000 to begin with.  So a wavefront goes on that way where the bounds
 // have told hardly any patterns apart, which is looked at after this many ratings.
 constexpr int kLookAfter = 4;
 __device__ __forceinline__ bool most_left(uint64_t left, int S) { return 4 * (__builtin_popcountll(left) + kLookAfter) > 3 * S; }
@@ -273,9 +273,9 @@ __device__ __forceinline__ uint32_t wave_min(uint32_t v) {
 // Rates the rows' patterns `later` and takes the best of them into (best, pattern), the lowest pattern on a tie; won: whether
 // it did.  One group after the other, four values per lane, a pattern per half of the wavefront: the reconstructed centroids
 // come from LDS as FP32, where a difference is a two-operand FP32 instruction, issued in 2.7 cycles (4.4 for the
-// mixed-precision one of half_diff).  pairs: the patterns' (centroid k, centroid k + 1) words in LDS; recon: S x 16 words of
-// LDS of the wavefront; at_skip: place of the group's value that counts as without error (128 or more: none).
-__device__ __forceinline__ void scan_patterns(float* recon, const uint32_t* pairs, int S, const RowValues& v, uint32_t smax, uint32_t at_skip, uint64_t later,
+// mixed-precision one of half_diff).  pairs: the patterns' (centroid k, centroid k + 1) words in LDS; recon: 128 words of LDS
+// of the wavefront; at_skip: place of the group's value that counts as without error (128 or more: none).
+__device__ __forceinline__ void scan_patterns(float* recon, const uint32_t* pairs, const RowValues& v, uint32_t smax, uint32_t at_skip, uint64_t later,
                                               int lane, float& best, uint32_t& pattern, bool& won) {
     const uint64_t rows = __builtin_amdgcn_ballot_w64(later != 0ull);
     won = false;
@@ -295,25 +295,36 @@ __device__ __forceinline__ void scan_patterns(float* recon, const uint32_t* pair
         const half2_t xa = as_half2((m & 1) ? w[2] : w[0]), xb = as_half2((m & 1) ? w[3] : w[1]);
         const float x[4] = {(float)xa[0], (float)xa[1], (float)xb[0], (float)xb[1]};
         const uint32_t zero = skip - 4u * (uint32_t)m;  // which of the four counts as zero, if one of 0 .. 3
-        wave_fence();
-        for (int i = lane; i < S * 16; i += 64) recon[i] = (float)(as_half2(pairs[i])[0] * s);
-        wave_fence();
         float mine = __builtin_inff();  // lane l: the least so far among its half's entries l & 3
         uint32_t mine_p = pattern;
         while (todo != 0ull) {
-            float q[4];
+            // eight patterns, one for each half and entry (the last one again where there are fewer): their reconstructed centroids
             uint32_t entry_p = 0;
+            int entries = 0, at = lane;
+            asm volatile("" : "+v"(at));  // as above
+            const uint32_t k = at & 15;
+            float* own = recon + (at >> 5) * 16;
+            wave_fence();
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                q[e] = __builtin_inff();
-                if (todo != 0ull) {  // uniform; the halves take one pattern each, the last one twice if their number is odd
+                if (todo != 0ull) {  // uniform
                     const uint32_t p0 = (uint32_t)__builtin_ctzll(todo);
                     todo &= todo - 1ull;
                     const uint32_t p1 = todo != 0ull ? (uint32_t)__builtin_ctzll(todo) : p0;
                     todo &= todo - 1ull;
-                    const uint32_t p = lane < 32 ? p0 : p1;
-                    entry_p = (lane & 3) == e ? p : entry_p;
-                    const float4_t* r4 = reinterpret_cast<const float4_t*>(recon + p * 16u);
+                    const uint32_t p = at < 32 ? p0 : p1;
+                    entry_p = (at & 3) == e ? p : entry_p;
+                    own[e * 32 + k] = (float)(as_half2(pairs[p * 16u + k])[0] * s);
+                    entries = e + 1;
+                }
+            }
+            wave_fence();
+            float q[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                q[e] = __builtin_inff();
+                if (e < entries) {  // uniform
+                    const float4_t* r4 = reinterpret_cast<const float4_t*>(own + e * 32);
                     float d[4];
 #pragma unroll
                     for (int i = 0; i < 4; ++i) d[i] = __builtin_inff();
@@ -321,9 +332,9 @@ __device__ __forceinline__ void scan_patterns(float* recon, const uint32_t* pair
                     for (int c = 0; c < 4; ++c) {
                         const float4_t r = r4[c];
 #pragma unroll
-                        for (int k = 0; k < 4; k += 2)
+                        for (int j = 0; j < 4; j += 2)
 #pragma unroll
-                            for (int i = 0; i < 4; ++i) d[i] = fminf(fminf(d[i], fabsf(__fsub_rn(x[i], r[k]))), fabsf(__fsub_rn(x[i], r[k + 1])));
+                            for (int i = 0; i < 4; ++i) d[i] = fminf(fminf(d[i], fabsf(__fsub_rn(x[i], r[j]))), fabsf(__fsub_rn(x[i], r[j + 1])));
                     }
                     float sq[4];
 #pragma unroll
