@@ -2,18 +2,20 @@
 //
 // Two steps per 64 blocks of a wavefront.  (1) The block is one code stream of 128 values behind a variable-length header,
 // so a lane owns a whole block and walks it: an 8-bit peek into a byte table per (pattern, codebook) -- 4 x S tables of 256
-// bytes, 64 KB for S = 64 -- gives the index and the length; only the 4-bit indices are kept, in LDS.  (2) The values are
-// formed with a block per row of 16 lanes, eight values per lane: a row's centroid reads fall into one pattern's 32 bytes,
-// the activations come and the decoded values leave in whole lines, and the padded entries (known only when the stream has
-// been walked to its end, at most 16) are taken up by the row's lanes side by side.
-// What bounds it: step 1 is a serial chain of 128 dependent table reads per lane, and the LDS holds eight wavefronts beside
-// the 64 KB of tables.  Doing everything in step 1 (a centroid read, presence and sign tests per value, a loop over the
-// padded entries as long as the wavefront's longest list) took twice as long: 29.3 us for the product over 4096 x 4096,
-// 21.4 us for the decode.
+// bytes, 64 KB for S = 64 -- gives the index and the length; only the 4-bit indices are kept.  (2) The values are formed with
+// a block per row of 16 lanes, eight values per lane: a row's centroid reads fall into one pattern's 32 bytes, and the
+// activations come and the decoded values leave in whole lines.  (With the lanes of a matrix-core operand, 16 blocks at a time, the
+// reads of one instruction fall into 16 patterns' tables and cost twice as much: 16.8 us where this takes 15.7.)  The padded entries
+// are few (one block in ten has any) and are taken up a block per lane, not by the rows.
+// What bounds it: step 1 is a serial chain of 128 table reads per lane, 97 cycles each when nothing else is in the way (56 of the
+// read, 8.5 for each of the three dependent instructions, the window), 5.2 us; step 2 the vector instructions.  Product over
+// 4096 x 4096, one pass per wavefront: 4.6 us launch, tables and payload, 6 us walk, 2 us padded entries, 3 us values; 18.2 us
+// with the entries taken up by the rows and the index image beside the payload.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cstdint>
+#include <type_traits>
 
 #include "ecco_pb_launch.h"
 
@@ -28,16 +30,14 @@ typedef __attribute__((address_space(3))) uint8_t lds_u8;
 constexpr int kSlot = kBlockWords + 1;    // LDS words per staged block; the last one is a zero pad
 constexpr int kUnit = 64;                 // blocks per wavefront pass, one per lane
 constexpr int kPayWords = kUnit * kSlot + 4;
-constexpr int kIdxStride = 17;            // words per block of the index image: values 8 w .. 8 w + 3 in the upper nibbles of word w, the next four in the lower ones
-constexpr int kInfoWords = 2 * kUnit;     // per block: where its centroids are, values present, padded entries, scale; where its stream ends
+constexpr int kInfoWords = 2 * kUnit;     // per block: where its centroids are and how many values are present; scale
+constexpr int kIdxWords = kGroup / 8;     // words per block of the index image: values 8 w .. 8 w + 3 in the upper nibbles of word w, the next four in the lower ones
 constexpr int kRows = 4;                  // blocks per wavefront in step 2
-constexpr int kPair = 2;                  // blocks per row at a time: their table reads are in flight together
-constexpr int kRowWords = kPair * kRows * kGroup / 2;  // decoded values of the blocks in hand, where padded entries are put in
-constexpr int kWaveWords = kInfoWords + kPayWords + kUnit * kIdxStride;  // private LDS of a wavefront, then (decoder only) kRowWords
+constexpr int kPair = 2;                  // decoder: blocks per row at a time, so that their table reads are in flight together
 // the header takes at most 18 bits and a code at most 8: value i ends at or before bit 18 + 8 (i + 1), inside the block for i < 61
 constexpr int kAlwaysPresent = (kBlockBits - 18) / kMaxLen;
-constexpr int kThreads = 512;
-constexpr int kWaves = kThreads / 64;
+constexpr int kDecodeThreads = 512;
+constexpr int kGemvThreads = 1024;
 
 __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -45,25 +45,9 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// words % 4 == 0, 16-byte aligned; eight loads in flight per thread
-__device__ __forceinline__ void stage_words(uint32_t* dst, const uint32_t* __restrict__ src, int words) {
-    const uint4* s = reinterpret_cast<const uint4*>(src);
-    uint4* d = reinterpret_cast<uint4*>(dst);
-    const int n = words >> 2;
-    for (int i = threadIdx.x; i < n; i += 8 * kThreads) {
-        uint4 v[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = s[min(i + j * kThreads, n - 1)];
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            if (i + j * kThreads < n) d[i + j * kThreads] = v[j];
-    }
-}
-
 // LDS of the tables, in words: those of the model, then its centroids once more with index 15 standing for -1 instead of 1
 // (a block with a negative scale uses these)
 constexpr size_t table_words(int S) { return DevLayout{S}.decode_words() + (size_t)S * 8; }
-inline size_t lds_bytes(int S, int wave_words) { return (table_words(S) + (size_t)kWaves * wave_words) * 4; }
 
 struct Tables {
     const uint8_t* lut;
@@ -72,14 +56,29 @@ struct Tables {
     uint32_t cent;           // LDS address
     uint32_t minus;          // from a pattern's centroids to those with -1
 };
-__device__ __forceinline__ Tables stage_tables(uint32_t* smem, const uint32_t* __restrict__ dev, int S) {
+// Copies the tables to LDS; `prefetch` issues the loads of the first unit.  Loads return in issue order and a wait names how many
+// may still be outstanding: every thread requests its pieces of the tables first, on one straight path (indices clamped), and
+// the payload behind them, so that the copy does not wait for the payload.  The caller synchronises afterwards.
+template <int kThreads, class Prefetch>
+__device__ __forceinline__ Tables stage_tables(uint32_t* smem, const uint32_t* __restrict__ dev, int S, Prefetch&& prefetch) {
     const DevLayout D{S};
-    stage_words(smem, dev, (int)D.decode_words());
-    for (int i = threadIdx.x; i < S * 8; i += kThreads) {
-        uint32_t c = dev[D.cent() + i];
-        if ((i & 7) == 7) c ^= 0x80000000u;
-        smem[D.decode_words() + i] = c;
-    }
+    constexpr int kMaxPieces = (int)(DevLayout{kMaxS}.decode_words() / 4);
+    constexpr int kEach = (kMaxPieces + kThreads - 1) / kThreads;
+    static_assert(kMaxS * 8 <= kDecodeThreads && kMaxS * 8 <= kGemvThreads, "a word of the second centroids per thread");
+    const uint4* s = reinterpret_cast<const uint4*>(dev);
+    uint4* d = reinterpret_cast<uint4*>(smem);
+    const int n = (int)(D.decode_words() / 4), tid = threadIdx.x;
+    const uint32_t c = dev[D.cent() + min(tid, S * 8 - 1)];
+    uint4 v[kEach];
+#pragma unroll
+    for (int j = 0; j < kEach; ++j) v[j] = s[min(tid + j * kThreads, n - 1)];
+    __builtin_amdgcn_sched_barrier(0);
+    prefetch();
+    __builtin_amdgcn_sched_barrier(0);
+    if (tid < S * 8) smem[D.decode_words() + tid] = (tid & 7) == 7 ? c ^ 0x80000000u : c;
+#pragma unroll
+    for (int j = 0; j < kEach; ++j)
+        if (tid + j * kThreads < n) d[tid + j * kThreads] = v[j];
     Tables t;
     t.lut = reinterpret_cast<const uint8_t*>(smem + D.lut());
     t.kplut = reinterpret_cast<const uint16_t*>(smem + D.kplut());
@@ -89,6 +88,7 @@ __device__ __forceinline__ Tables stage_tables(uint32_t* smem, const uint32_t* _
     return t;
 }
 __device__ __forceinline__ uint32_t lds_half(uint32_t address) { return *(const lds_u16*)(size_t)address; }
+__device__ __forceinline__ float half_f(uint32_t bits) { return (float)__builtin_bit_cast(_Float16, (unsigned short)bits); }
 
 struct PieceLoad {
     uint4 v[4];
@@ -112,37 +112,29 @@ __device__ __forceinline__ void store_pieces(uint32_t* pay, const PieceLoad& L, 
     }
 }
 
-// A wavefront's private LDS.
-struct WaveLds {
-    uint32_t* rows;  // decoder: values of the blocks in hand
-    uint32_t* pay;   // payloads, kSlot words per block
-    uint32_t* idx;   // indices, kIdxStride words per block
-    uint2* info;     // per block: x = offset of its centroids | values present << 16 | padded entries << 24;  y = |scale| (FP16 bits) | end of the stream << 16
+// What the walk of a block leaves in its lane.
+struct Walked {
+    uint32_t cent;     // offset of the block's centroids
+    uint32_t scale;    // |scale|, FP16 bits
+    uint32_t present;  // values present
+    uint32_t entries;  // padded entries
+    uint32_t end;      // where they start
 };
-__device__ __forceinline__ WaveLds wave_lds(uint32_t* base) {
-    WaveLds w;
-    w.info = reinterpret_cast<uint2*>(base);
-    w.pay = base + kInfoWords;
-    w.idx = w.pay + kPayWords;
-    w.rows = w.idx + kUnit * kIdxStride;
-    return w;
-}
-
-// Step 1: walks the block staged in this lane's slot and leaves its indices and its info word in LDS.  Values are taken in
-// runs of four out of a 64-bit window (at least 33 valid bits); the words of the next run's window are requested before the
+// Step 1: walks the block staged in this lane's slot; put(i, word) receives the indices of values 8 i .. 8 i + 7.  Values are taken
+// in runs of four out of a 64-bit window (at least 33 valid bits); the words of the next run's window are requested before the
 // run, so that the dependent chain holds only the table reads.  A value is present iff its code ends inside the block; the
 // position stops at bit 512, where the window is zero.
-__device__ __forceinline__ void walk_block(const WaveLds& L, const Tables& T, int lane) {
-    const uint32_t* w = L.pay + lane * kSlot;
+template <class Put>
+__device__ __forceinline__ Walked walk_block(const uint32_t* w, const Tables& T, Put&& put) {
     const uint32_t first = w[0];
     const uint32_t kpe = T.kplut[(first >> 14) & 0xFFu], p = kpe >> 8;
     const uint32_t sv = T.fp8[first >> 24];  // the signed scale, FP16 bits
     const uint8_t* tab = T.lut + (p * kBooks + ((first >> 22) & 3u)) * 256u;
     uint32_t fetch = 10u + (kpe & 0xFFu);    // where the next run is fetched from; stops at 512
     uint32_t reach = fetch;                   // where the codes read so far end; keeps counting past 512
-    uint32_t present = 0;
     uint32_t wi = 0, w0 = first, w1 = w[1], w2 = w[2];
-    uint32_t* out = L.idx + lane * kIdxStride;
+    // of the last run that starts inside the block: how many came before it, where it starts, its table bytes
+    uint32_t runs = 0, last_start = 0, last_run = 0;
 #pragma unroll
     for (int i0 = 0; i0 < kGroup; i0 += 8) {
         uint32_t packed[2];  // four table bytes each
@@ -157,22 +149,13 @@ __device__ __forceinline__ void walk_block(const WaveLds& L, const Tables& T, in
                 win <<= len[j];
             }
             packed[h >> 2] = __builtin_amdgcn_perm(e[1], e[0], 0x0C0C0400u) | __builtin_amdgcn_perm(e[3], e[2], 0x04000C0Cu);
-            const uint32_t used = (len[0] + len[1]) + (len[2] + len[3]);
             if (i0 + h + 3 >= kAlwaysPresent) {
-                // all four, or, in the run that crosses the end, those that end inside
-                const bool whole = reach + used <= (uint32_t)kBlockBits;
-                present += whole ? 4u : 0u;
-                if (!whole && reach <= (uint32_t)kBlockBits) {
-                    uint32_t at = reach;
-#pragma unroll
-                    for (int j = 0; j < 3; ++j) {
-                        at += len[j];
-                        present += at <= (uint32_t)kBlockBits ? 1u : 0u;
-                    }
-                }
-            } else {
-                present += 4u;
+                const bool inside = reach <= (uint32_t)kBlockBits;
+                runs += inside ? 1u : 0u;
+                last_start = inside ? reach : last_start;
+                last_run = inside ? packed[h >> 2] : last_run;
             }
+            const uint32_t used = (len[0] + len[1]) + (len[2] + len[3]);
             reach += used;
             if (i0 + h + 4 < kGroup) {
                 fetch = min(fetch + used, (uint32_t)kBlockBits);
@@ -184,34 +167,49 @@ __device__ __forceinline__ void walk_block(const WaveLds& L, const Tables& T, in
                 wi = nwi;
             }
         }
-        out[i0 >> 3] = (packed[0] & 0xF0F0F0F0u) | ((packed[1] >> 4) & 0x0F0F0F0Fu);
+        uint32_t word = (packed[0] & 0xF0F0F0F0u) | ((packed[1] >> 4) & 0x0F0F0F0Fu);
+        // finished here: left to the compiler, these are formed after the walk and its 128 table bytes stay in registers
+        asm volatile("" : "+v"(word), "+v"(reach), "+v"(runs), "+v"(last_start), "+v"(last_run));
+        put(i0 >> 3, word);
     }
-    const uint32_t entries = reach <= (uint32_t)kBlockBits ? ((uint32_t)kBlockBits - reach) / kOutlierBits : 0u;
-    L.info[lane] = make_uint2((p * 32u + ((sv & 0x8000u) ? T.minus : 0u)) | (present << 16) | (entries << 24), (sv & 0x7FFFu) | (min(reach, 0xFFFFu) << 16));
+    Walked r;
+    r.cent = p * 32u + ((sv & 0x8000u) ? T.minus : 0u);
+    r.scale = sv & 0x7FFFu;
+    r.end = reach;
+    r.entries = reach <= (uint32_t)kBlockBits ? ((uint32_t)kBlockBits - reach) / kOutlierBits : 0u;
+    constexpr int kSure = kAlwaysPresent / 4 * 4;  // values before the runs that were counted
+    r.present = kSure - 4u + 4u * runs;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        last_start += (last_run >> (8 * j)) & 15u;
+        r.present += last_start <= (uint32_t)kBlockBits ? 1u : 0u;
+    }
+    return r;
 }
 
-// Step 2, common part: block `blk` of the pass, lane l of its row.
+// Padded entry j (< 16) of the block staged at w: position << 8 | 8-bit float.
+__device__ __forceinline__ uint32_t entry_code(const uint32_t* w, uint32_t end, uint32_t j) {
+    const uint32_t at = min(end + j * kOutlierBits, (uint32_t)kBlockBits - 1u), wi = at >> 5;
+    return (uint32_t)(((((uint64_t)w[wi] << 32) | (uint64_t)w[wi + 1]) << (at & 31u)) >> 49);
+}
+
+// Step 2, common part: the lane's eight centroids (FP16 bits) for the indices `nibbles`, 0 where the value is absent.
 struct RowBlock {
-    uint32_t cent;       // LDS address of its centroids
-    uint32_t c[8];       // the lane's eight centroids, FP16 bits; 0 where the value is absent
+    uint32_t c[8];
     int present;         // how many of the lane's values are present (may be negative or beyond 8)
-    uint32_t entries;    // padded entries of the block
-    uint32_t end;        // where they start
-    uint32_t scale;      // FP16 bits
+    uint32_t scale;      // as the info word has it
 };
-__device__ __forceinline__ RowBlock row_block(const WaveLds& L, const Tables& T, int blk, int l) {
-    const uint2 i = L.info[blk];
-    const uint32_t nibbles = L.idx[blk * kIdxStride + l];
+__device__ __forceinline__ RowBlock row_block(const Tables& T, uint2 info, uint32_t nibbles, int l) {
     RowBlock r;
-    r.cent = T.cent + (i.x & 0xFFFFu);
-    r.present = (int)((i.x >> 16) & 0xFFu) - 8 * l;
-    r.entries = i.x >> 24;
-    r.scale = i.y & 0xFFFFu;
-    r.end = i.y >> 16;
+    const uint32_t cent = T.cent + (info.x & 0xFFFFu);
+    r.present = (int)(info.x >> 16) - 8 * l;
+    r.scale = info.y;
     // twice the indices, a byte each (values 0..3 and 4..7): a byte is then one addition away from its address
-    const uint32_t twice[2] = {(nibbles >> 3) & 0x1E1E1E1Eu, (nibbles << 1) & 0x1E1E1E1Eu};
+    // (passed through an empty asm statement: the compiler would take each byte out of the indices by a shift and a mask of its own)
+    uint32_t twice[2] = {(nibbles >> 3) & 0x1E1E1E1Eu, (nibbles << 1) & 0x1E1E1E1Eu};
+    asm("" : "+v"(twice[0]), "+v"(twice[1]));
 #pragma unroll
-    for (int k = 0; k < 8; ++k) r.c[k] = lds_half(r.cent + ((twice[k >> 2] >> (8 * (k & 3))) & 0xFFu));
+    for (int k = 0; k < 8; ++k) r.c[k] = lds_half(cent + ((twice[k >> 2] >> (8 * (k & 3))) & 0xFFu));
     return r;
 }
 // Takes out the absent values of the blocks in hand.  Most cut streams lose a value or two, so the first four of a lane
@@ -233,112 +231,89 @@ __device__ __forceinline__ void drop_absent(RowBlock (&r)[kBlocks]) {
         for (int k = 0; k < 4; ++k) r[q].c[k] = k < r[q].present ? r[q].c[k] : 0u;
 }
 
-// The padded entry of this lane (entry l of the block), if there is one and no later entry has the same position: a
-// sequential reader of the block ends up with the last one.
-struct Entry {
-    bool valid;
-    uint32_t pos, value;  // position in the block; FP16 bits
-};
-template <int kShift>
-__device__ __forceinline__ bool later_has(uint32_t key) {
-    return (uint32_t)__builtin_amdgcn_mov_dpp((int)key, 0x100 + kShift, 0xF, 0xF, true) == key;  // row_shl: from lane l + kShift, 0 beyond the row
-}
-__device__ __forceinline__ Entry row_entry(const WaveLds& L, const Tables& T, const RowBlock& r, int blk, int l) {
-    const uint32_t* w = L.pay + blk * kSlot;
-    const uint32_t at = min(r.end + (uint32_t)l * kOutlierBits, (uint32_t)kBlockBits - 1u), wi = at >> 5;
-    const uint64_t win = (((uint64_t)w[wi] << 32) | (uint64_t)w[wi + 1]) << (at & 31u);
-    const uint32_t code = (uint32_t)(win >> 49);   // 7-bit position, 8-bit float
-    Entry e;
-    e.valid = (uint32_t)l < r.entries;
-    e.pos = code >> 8;
-    e.value = T.fp8[code & 0xFFu];
-    const uint32_t key = e.valid ? e.pos + 1u : 0xFFFFu;
-    if (__builtin_amdgcn_ballot_w64(r.entries > 1u) != 0ull) {
-        bool dup = later_has<1>(key) || later_has<2>(key) || later_has<3>(key);
-        if (__builtin_amdgcn_ballot_w64(r.entries > 4u) != 0ull) {
-            dup = dup || later_has<4>(key) || later_has<5>(key) || later_has<6>(key) || later_has<7>(key) || later_has<8>(key) || later_has<9>(key);
-            dup = dup || later_has<10>(key) || later_has<11>(key) || later_has<12>(key) || later_has<13>(key) || later_has<14>(key) || later_has<15>(key);
-        }
-        e.valid = e.valid && !dup;
-    }
-    return e;
-}
-
+// ---- decode ------------------------------------------------------------------------------------------------------------
 // grid x 8 wavefronts, each `unit` consecutive blocks at a time (a multiple of four, at most 64): small inputs are spread
 // over all wavefronts of the chip, since a chain takes as long for one lane as for 64
-__global__ __launch_bounds__(kThreads) void pb_decode_kernel(const uint32_t* __restrict__ dev, int S, const uint4* __restrict__ blocks, size_t n_groups,
-                                                             int unit, uint4* __restrict__ dst) {
+constexpr int kDecodeWaves = kDecodeThreads / 64;
+constexpr int kDecodeIdxStride = kIdxWords + 1;
+constexpr int kDecodeWaveWords = kInfoWords + kPayWords + kUnit * kDecodeIdxStride;  // private LDS of a wavefront
+inline size_t decode_lds_bytes(int S) { return (table_words(S) + (size_t)kDecodeWaves * kDecodeWaveWords) * 4; }
+
+__global__ __launch_bounds__(kDecodeThreads) void pb_decode_kernel(const uint32_t* __restrict__ dev, int S, const uint4* __restrict__ blocks, size_t n_groups,
+                                                                   int unit, uint4* __restrict__ dst) {
     extern __shared__ __align__(16) uint32_t smem[];
     const int lane = threadIdx.x & 63, l = lane & 15, row = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const WaveLds L = wave_lds(smem + table_words(S) + wave * (kWaveWords + kRowWords));
-    const size_t n_units = (n_groups + unit - 1) / unit, step = (size_t)gridDim.x * kWaves;
-    size_t u = (size_t)blockIdx.x * kWaves + wave;
+    uint2* info = reinterpret_cast<uint2*>(smem + table_words(S) + wave * kDecodeWaveWords);
+    uint32_t* pay = reinterpret_cast<uint32_t*>(info) + kInfoWords;
+    uint32_t* idx = pay + kPayWords;
+    const size_t n_units = (n_groups + unit - 1) / unit, step = (size_t)gridDim.x * kDecodeWaves;
+    size_t u = (size_t)blockIdx.x * kDecodeWaves + wave;
     const auto load = [&](size_t v) {
         const size_t first = min(v * unit, n_groups - 1);
         return load_pieces(blocks + first * 4, (int)min(n_groups - first, (size_t)unit), lane);
     };
-    PieceLoad pre = load(u);
-    const Tables T = stage_tables(smem, dev, S);
-    L.pay[lane * kSlot + kBlockWords] = 0u;
-    if (lane < 4) L.pay[kUnit * kSlot + lane] = 0u;
+    PieceLoad pre;
+    const Tables T = stage_tables<kDecodeThreads>(smem, dev, S, [&] { pre = load(u); });
+    pay[lane * kSlot + kBlockWords] = 0u;
+    if (lane < 4) pay[kUnit * kSlot + lane] = 0u;
     __syncthreads();
 
     for (; u < n_units; u += step) {
         wave_lds_fence();
-        store_pieces(L.pay, pre, lane);
+        store_pieces(pay, pre, lane);
         wave_lds_fence();
         pre = load(u + step);
-        walk_block(L, T, lane);
+        const uint32_t* own = pay + lane * kSlot;
+        const Walked b = walk_block(own, T, [&](int i, uint32_t word) { idx[lane * kDecodeIdxStride + i] = word; });
+        info[lane] = make_uint2(b.cent | (b.present << 16), b.scale);
         wave_lds_fence();
         const int count = (int)min(n_groups - u * unit, (size_t)unit);
         uint4* out = dst + u * unit * (kGroup / 8);
+#pragma unroll 1
         for (int b0 = 0; b0 < count; b0 += kPair * kRows) {
             RowBlock r[kPair];
 #pragma unroll
-            for (int q = 0; q < kPair; ++q) r[q] = row_block(L, T, b0 + q * kRows + row, l);
+            for (int q = 0; q < kPair; ++q) {
+                const int blk = b0 + q * kRows + row;
+                r[q] = row_block(T, info[blk], idx[blk * kDecodeIdxStride + l], l);
+            }
             drop_absent(r);
-            uint32_t entries = 0;
 #pragma unroll
             for (int q = 0; q < kPair; ++q) {
                 const half2_t s2 = __builtin_bit_cast(half2_t, r[q].scale | (r[q].scale << 16));
+                uint32_t v[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i)  // each product rounds once
-                    r[q].c[i] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, r[q].c[2 * i] | (r[q].c[2 * i + 1] << 16)) * s2);
-                entries |= r[q].entries;
-            }
-            if (__builtin_amdgcn_ballot_w64(entries != 0u) != 0ull) {  // through LDS, where each entry's lane puts its value in
-                wave_lds_fence();
-#pragma unroll
-                for (int q = 0; q < kPair; ++q) {
-                    const Entry e = row_entry(L, T, r[q], b0 + q * kRows + row, l);
-                    uint32_t* at = L.rows + (q * kRows + row) * (kGroup / 2);
-                    reinterpret_cast<uint4*>(at)[l] = make_uint4(r[q].c[0], r[q].c[1], r[q].c[2], r[q].c[3]);
-                    wave_lds_fence();
-                    if (e.valid) reinterpret_cast<uint16_t*>(at)[e.pos] = (uint16_t)e.value;
-                }
-                wave_lds_fence();
-#pragma unroll
-                for (int q = 0; q < kPair; ++q) {
-                    const uint4 t = reinterpret_cast<const uint4*>(L.rows + (q * kRows + row) * (kGroup / 2))[l];
-                    r[q].c[0] = t.x; r[q].c[1] = t.y; r[q].c[2] = t.z; r[q].c[3] = t.w;
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < kPair; ++q) {
+                    v[i] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, r[q].c[2 * i] | (r[q].c[2 * i + 1] << 16)) * s2);
                 const int blk = b0 + q * kRows + row;
-                if (blk < count) out[blk * (kGroup / 8) + l] = make_uint4(r[q].c[0], r[q].c[1], r[q].c[2], r[q].c[3]);
+                if (blk < count) out[blk * (kGroup / 8) + l] = make_uint4(v[0], v[1], v[2], v[3]);
             }
         }
+        // The padded entries, a block per lane again, over the values just written, in the order of the stream: a later one at the
+        // same position wins.  (A wavefront's stores to one address arrive in the order they were issued.)
+        wave_lds_fence();
+        uint16_t* values = reinterpret_cast<uint16_t*>(out) + lane * kGroup;
+        const uint32_t entries = lane < count ? b.entries : 0u;
+        for (uint32_t j = 0; __builtin_amdgcn_ballot_w64(j < entries) != 0ull; ++j)
+            if (j < entries) {
+                const uint32_t code = entry_code(own, b.end, j);
+                values[code >> 8] = T.fp8[code & 0xFFu];
+            }
     }
 }
 
 // ---- decode fused into the matrix-vector product --------------------------------------------------------------------
-// y = W x without writing W: a workgroup owns a band of rows (its blocks are consecutive in memory); per-block sums go to
-// LDS, and each row's blocks are added in a fixed tree.  A padded entry takes centroid * x at its position back and adds its
-// own value (times x) instead.
-constexpr int kPartFloats = 1536;        // per-block sums of a band: band rows x column groups
-inline size_t gemv_lds_bytes(int S) { return lds_bytes(S, kWaveWords) + kPartFloats * 4; }
+// y = W x without writing W: a workgroup owns a band of rows (its blocks are consecutive in memory) and takes it in chunks
+// of whole rows; per-block sums go to LDS, and each row's blocks are added in a fixed tree.  A padded entry takes
+// centroid * x at its position back and adds its own value (times x) instead; this is done right after the walk, a block per lane,
+// when the indices still lie in registers.  They then take the payload's place in LDS, so that sixteen wavefronts fit beside 64
+// patterns' tables (eight with a place of their own): 4096 x 28672 takes 58.5 us, 122 us with eight.
+constexpr int kGemvWaves = kGemvThreads / 64;
+constexpr int kGemvWaveWords = kInfoWords + kPayWords;  // private LDS of a wavefront
+constexpr int kMaxPartFloats = 8192;   // per-block sums of a chunk: rows x column groups, at most
+inline int gemv_part_floats(int S) { return std::min<int>(kMaxPartFloats, (int)(160 * 1024 / 4 - table_words(S) - kGemvWaves * kGemvWaveWords)); }
+static_assert(160 * 1024 / 4 - table_words(kMaxS) - kGemvWaves * kGemvWaveWords >= 65536 / kGroup, "the sums of a row fit");
 
 template <int kCtrl>
 __device__ __forceinline__ float dpp_add(float t) {
@@ -351,102 +326,169 @@ __device__ __forceinline__ float row_sum(float t) {
     t = dpp_add<0x141>(t);   // row_half_mirror
     return dpp_add<0x140>(t);  // row_mirror
 }
+// Four sums over a row of 16 lanes at once, in the same tree: at the first two levels a lane keeps the sums that match its own
+// lane bit and sends the others to its partner.  Lane l returns sum l & 3.
+__device__ __forceinline__ float row_sum4(const float (&q)[4], int l) {
+    const bool b0 = l & 1, b1 = l & 2;
+    const auto moved = [](float v, auto ctrl) { return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), decltype(ctrl)::value, 0xF, 0xF, true)); };
+    float a[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) a[i] = __fadd_rn(b0 ? q[2 * i + 1] : q[2 * i], moved(b0 ? q[2 * i] : q[2 * i + 1], std::integral_constant<int, 0xB1>{}));
+    float t = __fadd_rn(b1 ? a[1] : a[0], moved(b1 ? a[0] : a[1], std::integral_constant<int, 0x4E>{}));
+    t = dpp_add<0x124>(t);     // row_ror 4
+    return dpp_add<0x128>(t);  // row_ror 8
+}
 __device__ __forceinline__ float wave_sum(float t) {
     t = row_sum(t);
     const auto lane_of = [&](int l) { return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, t), l)); };
     return __fadd_rn(__fadd_rn(lane_of(0), lane_of(16)), __fadd_rn(lane_of(32), lane_of(48)));
 }
-__device__ __forceinline__ float half_f(uint32_t bits) { return (float)__builtin_bit_cast(_Float16, (unsigned short)bits); }
 
-__global__ __launch_bounds__(kThreads) void pb_gemv_kernel(const uint32_t* __restrict__ dev, int S, const uint4* __restrict__ blocks, int rows, int gpr, int band,
-                                                           int unit, const uint4* __restrict__ x, float* __restrict__ y) {
+__global__ __launch_bounds__(kGemvThreads) void pb_gemv_kernel(const uint32_t* __restrict__ dev, int S, const uint4* __restrict__ blocks, int rows, int gpr, int band,
+                                                               int chunk, int unit, const uint4* __restrict__ x, float* __restrict__ y) {
     extern __shared__ __align__(16) uint32_t smem[];
     const int lane = threadIdx.x & 63, l = lane & 15, row = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const WaveLds L = wave_lds(smem + table_words(S) + wave * kWaveWords);
-    float* part = reinterpret_cast<float*>(smem + table_words(S) + kWaves * kWaveWords);
+    uint2* info = reinterpret_cast<uint2*>(smem + table_words(S) + wave * kGemvWaveWords);
+    uint32_t* pay = reinterpret_cast<uint32_t*>(info) + kInfoWords;
+    float* part = reinterpret_cast<float*>(smem + table_words(S) + kGemvWaves * kGemvWaveWords);
 
-    const int r0 = blockIdx.x * band, nrows = min(band, rows - r0);
-    const uint4* first = blocks + (size_t)r0 * gpr * 4;   // first block of the band
-    const int n_blocks = nrows * gpr;                     // <= kPartFloats
-    const auto load = [&](int at) {
+    const int band0 = blockIdx.x * band, band1 = min(rows, band0 + band);
+    PieceLoad pre;
+    const auto load = [&](const uint4* first, int n_blocks, int at) {
         at = min(at, n_blocks - 1);
-        return load_pieces(first + (size_t)at * 4, min(n_blocks - at, unit), lane);
+        pre = load_pieces(first + (size_t)at * 4, min(n_blocks - at, unit), lane);
     };
-    int at = wave * unit;
-    PieceLoad pre = load(at);
-    const Tables T = stage_tables(smem, dev, S);
-    L.pay[lane * kSlot + kBlockWords] = 0u;
-    if (lane < 4) L.pay[kUnit * kSlot + lane] = 0u;
+    const Tables T = stage_tables<kGemvThreads>(smem, dev, S, [&] { load(blocks + (size_t)band0 * gpr * 4, min(chunk, band1 - band0) * gpr, wave * unit); });
+    pay[lane * kSlot + kBlockWords] = 0u;
+    if (lane < 4) pay[kUnit * kSlot + lane] = 0u;
     __syncthreads();
 
-    const int four = kRows % gpr;
-    for (; at < n_blocks; at += kWaves * unit) {
-        const int count = min(n_blocks - at, unit);
-        wave_lds_fence();
-        store_pieces(L.pay, pre, lane);
-        wave_lds_fence();
-        // the activations of the pass, requested ahead of the walk: eight of each block's column group per lane
-        uint4 xs[kUnit / kRows];
-        int cg[kUnit / kRows];
-        cg[0] = (at + row) % gpr;
+    constexpr int kAhead = 4;
+    const uint32_t four = (uint32_t)(kRows % gpr) * (kGroup * 2), x_end = (uint32_t)gpr * (kGroup * 2);  // bytes
+    for (int r0 = band0; r0 < band1; r0 += chunk) {
+        const int nrows = min(chunk, band1 - r0), n_blocks = nrows * gpr;
+        const uint4* first = blocks + (size_t)r0 * gpr * 4;   // first block of the chunk
+        for (int at = wave * unit; at < n_blocks; at += kGemvWaves * unit) {
+            const int count = min(n_blocks - at, unit);
+            wave_lds_fence();
+            store_pieces(pay, pre, lane);
+            wave_lds_fence();
+            if (at + kGemvWaves * unit < n_blocks) load(first, n_blocks, at + kGemvWaves * unit);
+            else if (r0 + chunk < band1) load(first + (size_t)chunk * gpr * 4, min(chunk, band1 - r0 - chunk) * gpr, wave * unit);
+            uint32_t* own = pay + lane * kSlot;
+            uint32_t k[kIdxWords];
+            const Walked b = walk_block(own, T, [&](int i, uint32_t word) { k[i] = word; });
+            info[lane] = make_uint2(b.cent | (b.present << 16), __builtin_bit_cast(uint32_t, half_f(b.scale)));
+            // The padded entries, last one first: an earlier one at the same position does not count.  The last two (few blocks have
+            // more) are only multiplied with their activations at the end of the pass, so that nothing waits for those here.
+            const uint32_t entries = lane < count ? b.entries : 0u;
+            const uint16_t* xb = reinterpret_cast<const uint16_t*>(x) + (size_t)((uint32_t)(at + min(lane, count - 1)) % (uint32_t)gpr) * kGroup;
+            const auto entry = [&](uint32_t j, uint32_t& pos) {  // entry j: its position, and what it adds to the value there
+                const uint32_t code = entry_code(own, b.end, j);
+                pos = code >> 8;
+                uint32_t t[kIdxWords];  // word pos / 8 of the indices
 #pragma unroll
-        for (int i = 1; i < kUnit / kRows; ++i) {
-            cg[i] = cg[i - 1] + four;
-            cg[i] -= cg[i] >= gpr ? gpr : 0;
-        }
+                for (int i = 0; i < kIdxWords; ++i) t[i] = k[i];
 #pragma unroll
-        for (int i = 0; i < kUnit / kRows; ++i)
-            if (i * kRows < count) xs[i] = x[(size_t)cg[i] * 16 + l];
-        pre = load(at + kWaves * unit);
-        walk_block(L, T, lane);
-        wave_lds_fence();
+                for (int n = kIdxWords / 2; n != 0; n >>= 1) {
+                    // masks, not conditions: of these the compiler makes a loop over the lanes with an indexed register
+                    uint32_t upper = (pos & (8u * n)) ? 0xFFFFFFFFu : 0u;
+                    asm("" : "+v"(upper));
 #pragma unroll
-        for (int i0 = 0; i0 < kUnit / kRows; i0 += kPair) {
-            if (i0 * kRows >= count) break;
-            RowBlock r[kPair];
-#pragma unroll
-            for (int q = 0; q < kPair; ++q) r[q] = row_block(L, T, (i0 + q) * kRows + row, l);
-            drop_absent(r);
-            float acc[kPair], extra[kPair];
-            uint32_t entries = 0;
-#pragma unroll
-            for (int q = 0; q < kPair; ++q) {
-                const uint32_t xw[4] = {xs[i0 + q].x, xs[i0 + q].y, xs[i0 + q].z, xs[i0 + q].w};
-                acc[q] = 0.0f;
-                extra[q] = 0.0f;
-#pragma unroll
-                for (int k = 0; k < 8; ++k) acc[q] = fmaf(half_f(r[q].c[k]), half_f(k & 1 ? xw[k >> 1] >> 16 : xw[k >> 1] & 0xFFFFu), acc[q]);
-                entries |= r[q].entries;
-            }
+                    for (int i = 0; i < n; ++i) t[i] = (t[i] & ~upper) | (t[i + n] & upper);
+                }
+                const uint32_t i = (t[0] >> (8u * (pos & 3u) + ((pos & 4u) ? 0u : 4u))) & 15u;
+                return fmaf(-half_f(lds_half(T.cent + b.cent + i * 2u)), half_f(b.scale), half_f(T.fp8[code & 0xFFu]));
+            };
+            float add = 0.0f, last[2] = {0.0f, 0.0f};
+            uint32_t last_x[2] = {0u, 0u};  // FP16 bits
             if (__builtin_amdgcn_ballot_w64(entries != 0u) != 0ull) {
+                uint32_t pos[2];
 #pragma unroll
-                for (int q = 0; q < kPair; ++q) {
-                    const int blk = (i0 + q) * kRows + row;
-                    const Entry e = row_entry(L, T, r[q], blk, l);
-                    if (e.valid) {
-                        const float xi = half_f(reinterpret_cast<const uint16_t*>(x)[(size_t)cg[i0 + q] * kGroup + e.pos]);
-                        const uint32_t k = (L.idx[blk * kIdxStride + (e.pos >> 3)] >> (8u * (e.pos & 3u) + ((e.pos & 4u) ? 0u : 4u))) & 15u;
-                        acc[q] = fmaf(-half_f(lds_half(r[q].cent + k * 2u)), xi, acc[q]);
-                        extra[q] = half_f(e.value) * xi;
-                    }
+                for (uint32_t q = 0; q < 2; ++q) {
+                    last[q] = entry(entries - 1u - q, pos[q]);  // (of a block without: some position, and not used)
+                    last_x[q] = xb[pos[q]];
+                }
+                last[0] = entries > 0u ? last[0] : 0.0f;
+                last[1] = entries > 1u && pos[1] != pos[0] ? last[1] : 0.0f;
+                if (__builtin_amdgcn_ballot_w64(entries > 2u) != 0ull) {
+                    uint64_t seen[2] = {0ull, 0ull};
+                    const auto see = [&](uint32_t p) {  // whether p was there before
+                        const uint64_t bit = 1ull << (p & 63u);
+                        const bool high = p >= 64u, again = ((high ? seen[1] : seen[0]) & bit) != 0ull;
+                        seen[0] |= high ? 0ull : bit;
+                        seen[1] |= high ? bit : 0ull;
+                        return again;
+                    };
+                    see(pos[0]);
+                    see(pos[1]);
+                    for (uint32_t j = 2; __builtin_amdgcn_ballot_w64(j < entries) != 0ull; ++j)
+                        if (j < entries) {
+                            uint32_t p;
+                            const float d = entry(entries - 1u - j, p), xv = half_f(xb[p]);
+                            if (!see(p)) add = fmaf(d, xv, add);
+                        }
                 }
             }
+            wave_lds_fence();
 #pragma unroll
-            for (int q = 0; q < kPair; ++q) {
-                const int blk = (i0 + q) * kRows + row;
-                const float t = row_sum(fmaf(acc[q], half_f(r[q].scale), extra[q]));
-                if (l == 0 && blk < count) part[at + blk] = t;
+            for (int i = 0; i < kIdxWords; ++i) own[i] = k[i];
+            wave_lds_fence();
+            // sixteen blocks at a time, four per row of lanes: eight activations of each block's column group per lane, those of the
+            // next sixteen requested while these are multiplied
+            uint4 xs[kAhead];
+            uint32_t x_at = (uint32_t)((at + row) % gpr) * 256u + (uint32_t)l * 16u;  // byte offset into x
+            const auto load_x = [&](uint4& to) {
+                to = *reinterpret_cast<const uint4*>(reinterpret_cast<const unsigned char*>(x) + x_at);
+                x_at += four;
+                x_at = min(x_at, x_at - x_end);  // past the row's end (before it the difference wraps round)
+            };
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q) load_x(xs[q]);
+#pragma unroll 1
+            for (int i0 = 0; i0 < count; i0 += kAhead * kRows) {
+                uint2 in[kAhead];
+                uint32_t nibbles[kAhead];
+#pragma unroll
+                for (int q = 0; q < kAhead; ++q) {
+                    in[q] = info[i0 + q * kRows + row];
+                    nibbles[q] = pay[(i0 + q * kRows + row) * kSlot + l];
+                }
+                RowBlock r[kAhead];
+#pragma unroll
+                for (int q = 0; q < kAhead; ++q) r[q] = row_block(T, in[q], nibbles[q], l);
+                drop_absent(r);
+                float t[kAhead] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int i = 0; i < 8; ++i)  // the four sums side by side: each is a chain of eight multiply-adds
+#pragma unroll
+                    for (int q = 0; q < kAhead; ++q) {
+                        const uint32_t xw[4] = {xs[q].x, xs[q].y, xs[q].z, xs[q].w};
+                        t[q] = fmaf(half_f(r[q].c[i]), half_f(i & 1 ? xw[i >> 1] >> 16 : xw[i >> 1] & 0xFFFFu), t[q]);
+                    }
+#pragma unroll
+                for (int q = 0; q < kAhead; ++q) {
+                    t[q] *= __builtin_bit_cast(float, r[q].scale);
+                    load_x(xs[q]);
+                }
+                const float sum = row_sum4(t, l);  // of block i0 + 4 (l % 4) + row
+                const int blk = i0 + (l & 3) * kRows + row;
+                if (l < kAhead && blk < count) part[at + blk] = sum;
             }
+            add = fmaf(last[0], half_f(last_x[0]), fmaf(last[1], half_f(last_x[1]), add));
+            wave_lds_fence();
+            if (entries != 0u) part[at + lane] += add;
         }
-    }
-    __syncthreads();
-    // row sums: the blocks of a row in a fixed order (lane-strided partial sums, then the wavefront tree)
-    for (int r = wave; r < nrows; r += kWaves) {
-        float sum = 0.0f;
-        for (int c = lane; c < gpr; c += 64) sum += part[r * gpr + c];
-        sum = wave_sum(sum);
-        if (lane == 0) y[r0 + r] = sum;
+        __syncthreads();
+        // row sums: the blocks of a row in a fixed order (lane-strided partial sums, then the wavefront tree)
+        for (int r = wave; r < nrows; r += kGemvWaves) {
+            float sum = 0.0f;
+            for (int c = lane; c < gpr; c += 64) sum += part[r * gpr + c];
+            sum = wave_sum(sum);
+            if (lane == 0) y[r0 + r] = sum;
+        }
+        if (r0 + chunk < band1) __syncthreads();
     }
 }
 
@@ -463,14 +505,18 @@ int ecco_pb_decode_gemv(const ecco_pb_model* m, const void* blocks, int rows, in
     if (!aligned(blocks, 64) || !aligned(x, 16) || !aligned(y, 4)) return ECCO_EALIGN;
     if (model_ready(m) != ECCO_OK) return ECCO_EINVAL;
     const int gpr = cols / kGroup, cus = ecco::cu_count(m->device);
-    // a band of rows per workgroup: about one band per compute unit, at most kPartFloats blocks
-    const int band = std::min(std::max(1, (rows + cus - 1) / cus), std::max(1, kPartFloats / gpr));
-    const int grid = (rows + band - 1) / band;
-    const size_t lds = gemv_lds_bytes(m->S);
+    // a band of rows per workgroup and a workgroup per compute unit; the band in chunks whose sums fit the LDS
+    const int band = (rows + cus - 1) / cus, grid = (rows + band - 1) / band;
+    const int chunk = std::min(band, gemv_part_floats(m->S) / gpr);
+    // as few wavefronts as hold the blocks 64 at a time, but four (one per SIMD): a chain takes as long for one lane as for 64, and
+    // longer the more wavefronts read tables beside it (512 blocks: 18.5 us on eight, 19.9 us on sixteen; 40 blocks: 11.5 us on four, 12.5 us
+    // on two, 13.1 us on ten)
+    const size_t waves = std::min<size_t>(kGemvWaves, std::max<size_t>(4, ((size_t)chunk * gpr + kUnit - 1) / kUnit));
+    const size_t lds = (table_words(m->S) + (size_t)kGemvWaves * kGemvWaveWords + (size_t)chunk * gpr) * 4;
     const int rc = ecco::allow_lds(pb_gemv_kernel, m->device, lds);
     if (rc != ECCO_OK) return rc;
-    hipLaunchKernelGGL(pb_gemv_kernel, dim3(grid), dim3(kThreads), lds, static_cast<hipStream_t>(stream), m->dev, m->S, static_cast<const uint4*>(blocks), rows, gpr,
-                       band, unit_of((size_t)band * gpr, kWaves), reinterpret_cast<const uint4*>(x), y);
+    hipLaunchKernelGGL(pb_gemv_kernel, dim3(grid), dim3(kGemvThreads), lds, static_cast<hipStream_t>(stream), m->dev, m->S, static_cast<const uint4*>(blocks), rows, gpr,
+                       band, chunk, unit_of((size_t)chunk * gpr, waves), reinterpret_cast<const uint4*>(x), y);
     ECCO_HIP_CHECK(hipGetLastError());
     return ECCO_OK;
 }
@@ -482,14 +528,14 @@ int ecco_pb_decode(const ecco_pb_model* m, const void* blocks, size_t n_groups, 
     if (n_groups >= ((size_t)1 << 31)) return ECCO_ESHAPE;
     if (!aligned(blocks, 64) || !aligned(dst, 16)) return ECCO_EALIGN;
     if (model_ready(m) != ECCO_OK) return ECCO_EINVAL;
-    const size_t lds = lds_bytes(m->S, kWaveWords + kRowWords);
+    const size_t lds = decode_lds_bytes(m->S);
     const int rc = ecco::allow_lds(pb_decode_kernel, m->device, lds);
     if (rc != ECCO_OK) return rc;
     const size_t cus = (size_t)ecco::cu_count(m->device);
-    const int unit = unit_of(n_groups, cus * kWaves);
+    const int unit = unit_of(n_groups, cus * kDecodeWaves);
     const size_t units = (n_groups + unit - 1) / unit;
-    const int grid = (int)std::min<size_t>((units + kWaves - 1) / kWaves, cus);
-    hipLaunchKernelGGL(pb_decode_kernel, dim3(grid), dim3(kThreads), lds, static_cast<hipStream_t>(stream), m->dev, m->S, static_cast<const uint4*>(blocks), n_groups,
+    const int grid = (int)std::min<size_t>((units + kDecodeWaves - 1) / kDecodeWaves, cus);
+    hipLaunchKernelGGL(pb_decode_kernel, dim3(grid), dim3(kDecodeThreads), lds, static_cast<hipStream_t>(stream), m->dev, m->S, static_cast<const uint4*>(blocks), n_groups,
                        unit, reinterpret_cast<uint4*>(dst));
     ECCO_HIP_CHECK(hipGetLastError());
     return ECCO_OK;

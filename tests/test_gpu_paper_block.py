@@ -153,3 +153,26 @@ def test_fused_gemv_matches_oracle(pb, dev):
     with pytest.raises(E.EccoError) as e:
         E.ecco_pb_decode_gemv(m, torch.from_numpy(blocks).to(dev), 8, 200, _t16(np.zeros(200, np.float16), dev))
     assert e.value.status == -2
+
+
+@pytest.mark.parametrize("rows,gpr,S", [(2821, 256, 64), (257, 65, 64), (512, 32, 16), (1025, 257, 16), (255, 1, 64), (769, 5, 1)])
+def test_gemv_passes_and_chunks(dev, rows, gpr, S):
+    """Bands of several chunks of rows (2821 x 256 groups: the sums of a band exceed the LDS), passes that end inside a
+    wavefront's 64 blocks, one wavefront up to all of them, blocks with many padded entries: every row against the
+    decoder's values (bit-exact against the oracle above) in double precision."""
+    w0 = W.weight_matrix(256, 128, 0.02, 1e-3, 10.0, 1)
+    m = E.ecco_pb_model_to_device(E.ecco_pb_fit(w0, S, 1), 0)
+    gen = torch.Generator(device=dev).manual_seed(rows)
+    w = torch.randn(rows * gpr, 128, device=dev, generator=gen) * 0.02
+    w[::3] *= torch.rand(w[::3].shape, device=dev, generator=gen) < 0.05       # mostly zeros: short streams, up to 16 entries
+    blocks = E.ecco_pb_encode(m, w.to(torch.float16))
+    dec = E.ecco_pb_decode(m, blocks).view(rows, gpr * 128)
+    x = torch.randn(gpr * 128, device=dev, generator=gen).to(torch.float16)
+    y = E.ecco_pb_decode_gemv(m, blocks, rows, gpr * 128, x).double()
+    for r0 in range(0, rows, 512):
+        d = dec[r0:r0 + 512].double()
+        ref, mag = d @ x.double(), d.abs() @ x.double().abs()
+        # the decoder rounds centroid * scale to FP16 (2^-11, or 2^-25 of the smallest numbers); FP32 sums of cols products
+        bound = (2.0 ** -11 + gpr * 128 * 2.0 ** -24) * mag + 2.0 ** -25 * x.double().abs().sum()
+        assert ((y[r0:r0 + 512] - ref).abs() <= bound).all(), r0
+    assert torch.equal(E.ecco_pb_decode_gemv(m, blocks, rows, gpr * 128, x).double(), y)
