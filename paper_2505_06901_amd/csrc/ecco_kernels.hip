@@ -122,28 +122,34 @@ __device__ __forceinline__ Tables table_pointers(uint32_t* base, int S) {
     return tb;
 }
 // The whole job for a workgroup of at least S * 16 / 2 threads, with a payload prefetch in its shadow: every
-// thread first requests its (up to) two table items, then calls `prefetch` (the loads of its first unit), then
+// thread first requests its (up to) two table items, then the loads of its first unit, then
 // builds the tables.  Loads return in issue order and a wait names how many may still be outstanding, so with
 // the items requested first -- the same loads on one straight path in every thread, indices clamped, threads
 // beyond the items repeating the last one -- the build does not wait for the payload.  The lists of the long
 // codes and the centroids are copied only for a model that needs them (behind the payload, then).  The caller
 // synchronises afterwards.
-template <bool kLong, class Prefetch>
-__device__ __forceinline__ Tables stage_tables_around(uint32_t* base, const uint32_t* __restrict__ dev, int S, Prefetch&& prefetch) {
+struct TableItems {
+    TableItem item[2];
+};
+__device__ __forceinline__ TableItems load_table_items(const uint32_t* __restrict__ dev, int S) {
     const int n = S * kK;
-    const int t0 = min((int)threadIdx.x, n - 1), t1 = min((int)(threadIdx.x + blockDim.x), n - 1);
-    const TableItem i0 = load_table_item(dev, S, t0), i1 = load_table_item(dev, S, t1);
+    TableItems t;
+    t.item[0] = load_table_item(dev, S, min((int)threadIdx.x, n - 1));
+    t.item[1] = load_table_item(dev, S, min((int)(threadIdx.x + blockDim.x), n - 1));
     __builtin_amdgcn_sched_barrier(0);
-    prefetch();
+    return t;
+}
+template <bool kLong>
+__device__ __forceinline__ void build_tables(uint32_t* base, const uint32_t* __restrict__ dev, int S, const TableItems& t) {
     __builtin_amdgcn_sched_barrier(0);
-    build_table_item(base, S, t0, i0);
-    build_table_item(base, S, t1, i1);
+    const int n = S * kK;
+    build_table_item(base, S, min((int)threadIdx.x, n - 1), t.item[0]);
+    build_table_item(base, S, min((int)(threadIdx.x + blockDim.x), n - 1), t.item[1]);
     if (kLong) {
         const DevLayout D{S};
         stage_vec(base + S * (kPeekEntries + kK), dev + D.longtab(), S * kK);
         stage_vec(base + S * (kPeekEntries + 2 * kK), dev + D.cent(), S * kK / 2);
     }
-    return table_pointers(base, S);
 }
 
 // what one lane needs to decode one chain
@@ -730,7 +736,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemm_kernel(const uint32_t* __re
 constexpr int kAttnThreads = 768;      // workgroup size; 512 for a V model with long codes
 constexpr int kAttnWaves = kAttnThreads / 64;
 constexpr int kSpan = 8192;
-static_assert(2 * 512 >= ECCO_MAX_S * kK, "stage_tables_around: two table items per thread cover every model (the smallest attention workgroup has 512 threads)");
+static_assert(2 * 512 >= ECCO_MAX_S * kK, "load_table_items: two table items per thread cover every model (the smallest attention workgroup has 512 threads)");
 inline size_t attn_lds_bytes(int Sk, int Sv) {
     return (table_words(std::max(Sk, Sv)) + (size_t)kAttnWaves * kUnitWords + kSpan + kAttnWaves * 2 * kGroup + 64) * 4;
 }
@@ -781,11 +787,10 @@ __global__ __launch_bounds__(kLongV ? 512 : kAttnThreads) void kv_attend_kernel(
         __syncthreads();
         int u = wave;
         UnitLoad pre;
-        const Tables TK = stage_tables_around<kLongK>(smem, dev_k, Sk, [&] { pre = load_unit(k_blocks, k_meta, bh, T_max, unit0 + min(u, units - 1), lane); });
-        __syncthreads();
-        float my_max = -INFINITY;
+        uint32_t qx[kHalf / 2];  // the query elements of this lane's chain, FP16 pairs
         {
-            uint32_t qx[kHalf / 2];  // the query elements of this lane's chain, FP16 pairs
+            const TableItems items = load_table_items(dev_k, Sk);
+            pre = load_unit(k_blocks, k_meta, bh, T_max, unit0 + min(u, units - 1), lane);
             // reloaded per span (from cache) rather than kept alive across the V phase; the pointer that comes back from
             // the empty asm statement is given its address space again, or its loads would be flat loads
             const uint4* qgen = reinterpret_cast<const uint4*>(q + (size_t)bh * kGroup + half * kHalf);
@@ -796,6 +801,12 @@ __global__ __launch_bounds__(kLongV ? 512 : kAttnThreads) void kv_attend_kernel(
                 const u32x4 v = qsrc[j];
                 qx[4 * j] = v.x; qx[4 * j + 1] = v.y; qx[4 * j + 2] = v.z; qx[4 * j + 3] = v.w;
             }
+            build_tables<kLongK>(smem, dev_k, Sk, items);
+        }
+        const Tables TK = table_pointers(smem, Sk);
+        __syncthreads();
+        float my_max = -INFINITY;
+        {
             for (; u < units; u += waves) {
                 store_unit(wbuf, pre, lane);
                 const uint32_t mw = pre.meta;
@@ -827,6 +838,11 @@ __global__ __launch_bounds__(kLongV ? 512 : kAttnThreads) void kv_attend_kernel(
                 my_max = fmaxf(my_max, sc);
             }
         }
+        // the V tables' items and first unit, requested here: they arrive during the softmax (512 sequences and heads of up to 100 tokens,
+        // with the append: 31.5 -> 31.1 us; 256 of 4096: no difference)
+        const TableItems v_items = load_table_items(dev_v, Sv);
+        u = wave;
+        pre = load_unit(v_blocks, v_meta, bh, T_max, unit0 + min(u, units - 1), lane);
         // ---- running softmax
         const float new_max = fmaxf(run_max, wg_reduce(my_max, scratch, true, waves));
         float my_den = 0.0f;
@@ -840,8 +856,8 @@ __global__ __launch_bounds__(kLongV ? 512 : kAttnThreads) void kv_attend_kernel(
         run_max = new_max;
         // ---- weighted sum of V over the span
         __syncthreads();
-        u = wave;
-        const Tables TV = stage_tables_around<kLongV>(smem, dev_v, Sv, [&] { pre = load_unit(v_blocks, v_meta, bh, T_max, unit0 + min(u, units - 1), lane); });
+        build_tables<kLongV>(smem, dev_v, Sv, v_items);
+        const Tables TV = table_pointers(smem, Sv);
         __syncthreads();
         {
             float o[kHalf];
@@ -1043,22 +1059,42 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
         int u = wave;
         UnitLoad pre;
         const auto load_k = [&](int at) { pre = load_unit(args.k_blocks, args.k_meta, bkv, T_max, unit0 + min(at, units - 1), lane, tok); };
-        if (!both || s0 == t_begin) stage_tables_around<kLongK>(smem, kLate ? late()->dev_k : args.dev_k, kLongK ? fresh(Sk) : Sk, [&] { load_k(u); });
-        else load_k(u);
-        if (both && s0 == t_begin) stage_tables_around<kLongV>(v_tables, kLate ? late()->dev_v : args.dev_v, kLongV ? fresh(args.Sv) : args.Sv, [] {});
-        const Tables TK = table_pointers(smem, Sk);
-        __syncthreads();
-        {
-            uint4 bq[kHalf / 8];  // B operands: the query of this lane's head, dimensions 64 * half + 8j .. + 7
-            // reloaded per span rather than kept alive across the V phase (address space restored as above)
+        const bool first = s0 == t_begin;
+        uint4 bq[kHalf / 8];  // B operands: the query of this lane's head, dimensions 64 * half + 8j .. + 7
+        // requested behind the payload, so that it arrives during the builds; reloaded per span rather than kept alive across the V
+        // phase (the pointer passes through an empty asm statement and is given its address space again)
+        const auto load_q = [&] {
             const uint4* qgen = reinterpret_cast<const uint4*>((kLate ? late()->q : args.q) + q_row + half * kHalf);
             asm volatile("" : "+v"(qgen));
             const global_u4* qsrc = (const global_u4*)qgen;
 #pragma unroll
             for (int j = 0; j < kHalf / 8; ++j) {
                 const u32x4 v = qsrc[j];
-                bq[j] = b_ok ? make_uint4(v.x, v.y, v.z, v.w) : make_uint4(0u, 0u, 0u, 0u);
+                bq[j] = make_uint4(v.x, v.y, v.z, v.w);
             }
+        };
+        if (both && first) {  // both models' items, then the payload, then both builds
+            const uint32_t *dk = kLate ? late()->dev_k : args.dev_k, *dv = kLate ? late()->dev_v : args.dev_v;
+            const TableItems k_items = load_table_items(dk, kLongK ? fresh(Sk) : Sk), v_items = load_table_items(dv, kLongV ? fresh(args.Sv) : args.Sv);
+            load_k(u);
+            load_q();
+            build_tables<kLongK>(smem, dk, kLongK ? fresh(Sk) : Sk, k_items);
+            build_tables<kLongV>(v_tables, dv, kLongV ? fresh(args.Sv) : args.Sv, v_items);
+        } else if (!both) {
+            const uint32_t* dk = kLate ? late()->dev_k : args.dev_k;
+            const TableItems items = load_table_items(dk, kLongK ? fresh(Sk) : Sk);
+            load_k(u);
+            load_q();
+            build_tables<kLongK>(smem, dk, kLongK ? fresh(Sk) : Sk, items);
+        } else {
+            load_k(u);
+            load_q();
+        }
+        const Tables TK = table_pointers(smem, Sk);
+        __syncthreads();
+        {
+#pragma unroll
+            for (int j = 0; j < kHalf / 8; ++j) bq[j] = b_ok ? bq[j] : make_uint4(0u, 0u, 0u, 0u);
             float mx = -INFINITY;
             for (; u < units; u += kWaves) {
                 store_unit(wbuf, pre, lane);
@@ -1111,6 +1147,18 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
             if (kLate) asm volatile("" : "+v"(at));  // as in `fresh`
             if (at < 16) wave_max[wave * kGqaMaxGroup + n] = mx;  // columns past the heads hold something, which nobody reads
         }
+        // the V tables' items and the first unit, requested here: they arrive during the softmax.  Together with both models' items and the query
+        // requested ahead of the builds, a step (append, attention, merge) over 8 sequences of 2048..4096 tokens, 8 heads in groups of 4, 16
+        // patterns, takes 35.6 instead of 36.9 us, over 4 sequences of 300 tokens 18.4 instead of 19.3 us
+        u = wave;
+        const auto* av = late();
+        const uint4* v_blocks = av->v_blocks;
+        const uint32_t* v_meta = av->v_meta;
+        const int Sv = av->Sv;
+        const auto load_v = [&](int at) { pre = load_unit(v_blocks, v_meta, bkv, T_max, unit0 + min(at, units - 1), lane, tok); };
+        TableItems v_items{};
+        if (!both) v_items = load_table_items(av->dev_v, kLongV ? fresh(Sv) : Sv);
+        load_v(u);
         __syncthreads();
         // ---- running softmax: all wavefronts, 256 tokens of a head at a time
         const int pieces = (units * kUnitBlocks + kItemTokens - 1) / kItemTokens, items = pieces * grp;
@@ -1163,14 +1211,7 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
             st_den[tid] = st_den[tid] * alpha + den;
         }
         // ---- weighted sum of V over the span
-        u = wave;
-        const auto* av = late();
-        const uint4* v_blocks = av->v_blocks;
-        const uint32_t* v_meta = av->v_meta;
-        const int Sv = av->Sv;
-        const auto load_v = [&](int at) { pre = load_unit(v_blocks, v_meta, bkv, T_max, unit0 + min(at, units - 1), lane, tok); };
-        if (both) load_v(u);
-        else stage_tables_around<kLongV>(v_tables, av->dev_v, kLongV ? fresh(Sv) : Sv, [&] { load_v(u); });
+        if (!both) build_tables<kLongV>(v_tables, av->dev_v, kLongV ? fresh(Sv) : Sv, v_items);
         const Tables TV = table_pointers(v_tables, Sv);
         __syncthreads();
         {
@@ -1255,41 +1296,45 @@ __global__ __launch_bounds__(kGroup) void kv_attend_combine_kernel(const float* 
     const size_t bh = blockIdx.x;
     const float* ml = ws + (size_t)n_heads * n_splits * kGroup + bh * n_splits * 2;
     const float* part = ws + bh * n_splits * kGroup + threadIdx.x;
-    // the largest of the splits' maxima: a few splits per lane and a wavefront maximum (exact whatever the order),
-    // instead of a chain of n_splits dependent loads
-    float mx = -INFINITY;
-    for (int s = threadIdx.x & 63; s < n_splits; s += 64) mx = fmaxf(mx, ml[2 * s]);
-    mx = wave_all(mx, [](float a, float b) { return fmaxf(a, b); });
-    // Sixteen splits at a time with all their loads in flight together (indices clamped, the surplus given weight 0
-    // by a select, no branch); the additions run in split order.  An empty split (maximum -inf, zeros) gets weight
-    // 0, also when every split is empty (mx = -inf).
+    // Sixteen splits at a time (four or eight where there are no more) with all their loads in flight together, indices
+    // clamped; the additions run in split order.  An empty split (maximum -inf, zeros) gets weight 0, also when every
+    // split is empty (mx = -inf).  The kernel is bound by the latency of the partial results, which come from memory: up to
+    // sixteen splits the maximum is formed from the values in hand and not in a round trip of its own.
     float num = 0.0f, den = 0.0f;
-    if (n_splits <= 8) {  // few splits: four at a time cost fewer surplus loads
-#pragma unroll 4
-        for (int s = 0; s < n_splits; ++s) {
-            const float m = ml[2 * s], d = ml[2 * s + 1], v = part[(size_t)s * kGroup];
-            const float w = m == -INFINITY ? 0.0f : __expf(m - mx);
-            num += w * v;
-            den += w * d;
-        }
-    } else
-    for (int s0 = 0; s0 < n_splits; s0 += 16) {
-        float m[16], d[16], v[16];
+    const auto batch = [&](auto count, int s0, float mx) {
+        constexpr int kCount = decltype(count)::value;
+        float m[kCount], d[kCount], v[kCount];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
+        for (int j = 0; j < kCount; ++j) {
             const int sj = min(s0 + j, n_splits - 1);
             m[j] = ml[2 * sj];
             d[j] = ml[2 * sj + 1];
             v[j] = part[(size_t)sj * kGroup];
         }
+        if (s0 == 0 && n_splits <= kCount) {
+            mx = m[0];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
+            for (int j = 1; j < kCount; ++j) mx = fmaxf(mx, m[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < kCount; ++j) {
             if (s0 + j < n_splits) {  // uniform
                 const float w = m[j] == -INFINITY ? 0.0f : __expf(m[j] - mx);
                 num += w * v[j];
                 den += w * d[j];
             }
         }
+    };
+    if (n_splits <= 4) batch(std::integral_constant<int, 4>{}, 0, 0.0f);
+    else if (n_splits <= 8) batch(std::integral_constant<int, 8>{}, 0, 0.0f);
+    else if (n_splits <= 16) batch(std::integral_constant<int, 16>{}, 0, 0.0f);
+    else {
+        // the largest of the splits' maxima: a few splits per lane and a wavefront maximum (exact whatever the order),
+        // instead of a chain of n_splits dependent loads
+        float mx = -INFINITY;
+        for (int s = threadIdx.x & 63; s < n_splits; s += 64) mx = fmaxf(mx, ml[2 * s]);
+        mx = wave_all(mx, [](float a, float b) { return fmaxf(a, b); });
+        for (int s0 = 0; s0 < n_splits; s0 += 16) batch(std::integral_constant<int, 16>{}, s0, mx);
     }
     out[bh * kGroup + threadIdx.x] = den > 0.0f ? num / den : 0.0f;
 }
