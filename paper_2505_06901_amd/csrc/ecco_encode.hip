@@ -192,7 +192,7 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
             const uint32_t p = left != 0 ? (uint32_t)__builtin_ctzll(left) : pattern;
             float sse;
             uint32_t id;
-            const uint32_t marks = rate_pattern<true>(T.near + p * kSearchBins, T.pair + p * 64u, s2, v, -1, sse, id);
+            const uint32_t marks = rate_pattern<true, true>(T.near + p * kSearchBins, T.pair + p * 64u, s2, v, -1, sse, id);
             const uint64_t lanes = __builtin_amdgcn_ballot_w64((marks & ecco::kNearWide) != 0u);
             if (lanes != 0ull && row_any(lanes, row)) {  // this pattern and those after it value by value
                 later |= left;
@@ -421,7 +421,7 @@ __global__ __launch_bounds__(kMinmaxThreads) void encode_minmax_kernel(Job<Io> j
         set_bins<false>(v, kSearchStep * __builtin_amdgcn_rcpf(s), nullptr, -1);
         float sse;
         uint32_t idx;
-        const uint32_t marks = rate_pattern<false>(T.near + pattern * kSearchBins, T.pair + pattern * 64u, s2, v, -1, sse, idx);
+        const uint32_t marks = rate_pattern<false, true>(T.near + pattern * kSearchBins, T.pair + pattern * 64u, s2, v, -1, sse, idx);
         const uint64_t lanes = __builtin_amdgcn_ballot_w64(((marks & kNearWide) != 0u || !(s >= kSearchLeastScale)) && smax != 0u);
         if (lanes != 0ull) {  // rows with crowded bins or a scale too small for the tables
             const uint32_t id = scan_indices(T.pair + pattern * 64u, s2, v, -1);

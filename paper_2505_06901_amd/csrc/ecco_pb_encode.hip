@@ -126,14 +126,19 @@ void pb_encode_kernel(const uint32_t* __restrict__ dev, int S, float inv_tscale,
             later = s == 0.0f ? 0ull : !beyond ? left : S == 64 ? ~0ull : (1ull << S) - 1ull;
             left = 0;
         }
-        uint32_t pattern = 0, idx = skip < 0 ? 0u : 15u << (28 - 4 * skip);
+        // A single pattern left has won; several are rated, ascending (a row that has none left repeats its last one), by their errors
+        // alone, all eight values of a lane in flight; the winner's indices follow.  (Errors and indices together, four values at a
+        // time: 108.5 us for encoding and decoding 131072 groups at 64 patterns, 105.0 us so.  The two-chain encoder, with fewer
+        // registers taken and nothing to leave out of the sums, does not gain: 64.1 us, 64.5 us so.)
+        uint32_t pattern = left != 0 ? (uint32_t)__builtin_ctzll(left) : 0u;
+        if ((left & (left - 1ull)) == 0ull) left = 0;
         float best = __builtin_inff();
         int rated = 0;
-        while (__builtin_amdgcn_ballot_w64(left != 0) != 0ull) {  // the patterns left, ascending; a row that has none left repeats its last one
+        while (__builtin_amdgcn_ballot_w64(left != 0) != 0ull) {
             const uint32_t p = left != 0 ? (uint32_t)__builtin_ctzll(left) : pattern;
             float sse;
-            uint32_t id;
-            const uint32_t marks = rate_pattern<true>(near + p * ecco::kSearchBins, pair + p * 64u, s2, v, skip, sse, id);
+            uint32_t none;
+            const uint32_t marks = rate_pattern<true, false, 8>(near + p * ecco::kSearchBins, pair + p * 64u, s2, v, skip, sse, none);
             const uint64_t lanes = __builtin_amdgcn_ballot_w64((marks & ecco::kNearWide) != 0u);
             if (lanes != 0ull && row_any(lanes, row)) {  // this pattern and those after it value by value
                 later |= left;
@@ -142,7 +147,6 @@ void pb_encode_kernel(const uint32_t* __restrict__ dev, int S, float inv_tscale,
             if (left != 0 && sse < best) {  // strict <: the lowest pattern wins a tie
                 best = sse;
                 pattern = p;
-                idx = id;
             }
             left &= left - 1ull;
             if (++rated == kLookAfter && __builtin_amdgcn_ballot_w64(most_left(left, S)) != 0ull) {
@@ -150,15 +154,21 @@ void pb_encode_kernel(const uint32_t* __restrict__ dev, int S, float inv_tscale,
                 left = 0;
             }
         }
-        if (__builtin_amdgcn_ballot_w64(later != 0) != 0ull) {
-            bool won;
-            int skip_again = skip;  // its comparisons are formed here, not kept through the search
-            asm volatile("" : "+v"(skip_again));
+        bool won = false;  // by the comparison value by value
+        if (__builtin_amdgcn_ballot_w64(later != 0) != 0ull)
             scan_patterns(reinterpret_cast<float*>(L.hist + wave * kWaveRows * kHistStride), pair_at, v, __builtin_bit_cast(uint32_t, s2) & 0xFFFFu,
                           top >> 16, later, lane, best, pattern, won);
+        int skip_again = skip;  // its comparisons are formed here, not kept through the search
+        asm volatile("" : "+v"(skip_again));
+        float none;
+        uint32_t idx;
+        const uint32_t marks = rate_pattern<false, true>(near + pattern * ecco::kSearchBins, pair + pattern * 64u, s2, v, skip_again, none, idx);
+        const uint64_t scan = __builtin_amdgcn_ballot_w64((won || (marks & ecco::kNearWide) != 0u) && s != 0.0f);
+        if (scan != 0ull) {
             const uint32_t id = scan_indices(pair + pattern * 64u, s2, v, skip_again);
-            idx = won ? id : idx;
+            idx = row_any(scan, row) ? id : idx;
         }
+        if (s == 0.0f) idx = skip_again < 0 ? 0u : 15u << (28 - 4 * skip_again);
 
         // the codebook of least total length, lowest on ties
         uint32_t sum = 0;  // four bytes, at most 8 x 8 each

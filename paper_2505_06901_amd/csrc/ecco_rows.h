@@ -126,12 +126,14 @@ __device__ __forceinline__ float half_diff(uint32_t x, uint32_t r) {
     if (kX == 1 && kR == 1) asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,1] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(x), "v"(r));
     return d;
 }
-// distance of the lane's i-th value to the kR-th half of r
+// the lane's i-th value less the kR-th half of r, and its distance to it
 template <int kR>
-__device__ __forceinline__ float distance(const RowValues& v, int i, half2_t r) {
+__device__ __forceinline__ float difference(const RowValues& v, int i, half2_t r) {
     const uint32_t x = v.x[i >> 1], rb = __builtin_bit_cast(uint32_t, r);
-    return fabsf((i & 1) ? half_diff<1, kR>(x, rb) : half_diff<0, kR>(x, rb));
+    return (i & 1) ? half_diff<1, kR>(x, rb) : half_diff<0, kR>(x, rb);
 }
+template <int kR>
+__device__ __forceinline__ float distance(const RowValues& v, int i, half2_t r) { return fabsf(difference<kR>(v, i, r)); }
 typedef __attribute__((address_space(3))) uint32_t lds_u32;
 typedef __attribute__((address_space(3))) uint8_t lds_u8;
 __device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(size_t)(const lds_u8*)p; }
@@ -150,27 +152,32 @@ __device__ __forceinline__ float tree_sum(const float (&d)[kRowValues], int skip
 }
 
 // The row's values under one pattern: every value's index (the lowest of the nearest reconstructed centroids
-// fp16(c * s)), eight nibbles per lane, first value on top; and the group's squared error (kSse, by tree_sum).  near, pair: the
+// fp16(c * s)), eight nibbles per lane, first value on top; (kIdx); and the group's squared error (kSse, by tree_sum).  near, pair: the
 // pattern's rows of the tables in LDS (pair as an LDS address, a multiple of 64).  A value whose place is `skip` counts as
 // without error, with index 15.  Returns the marks of the lane's bins: with kNearWide (more than three candidates) in one of its
 // lanes, a row's results do not hold.
-template <bool kSse>
+template <bool kSse, bool kIdx, int kAtOnce = 4>
 __device__ __forceinline__ uint32_t rate_pattern(const uint8_t* near, uint32_t pair, half2_t s2, const RowValues& v, int skip, float& sse, uint32_t& idx) {
     uint32_t k[kRowValues], marks = 0;
     float d[kRowValues];
-    // four values at a time: all eight in flight need 24 more registers than three workgroups per compute unit leave
+    // kAtOnce values at a time: with the indices, all eight in flight need 24 more registers than three workgroups per compute unit leave
 #pragma unroll
-    for (int h = 0; h < kRowValues; h += 4) {
-        uint32_t nb[4];
+    for (int h = 0; h < kRowValues; h += kAtOnce) {
+        uint32_t nb[kAtOnce];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) nb[i] = near[v.bin(h + i)];
+        for (int i = 0; i < kAtOnce; ++i) nb[i] = near[v.bin(h + i)];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < kAtOnce; ++i) {
             const half2_t r = as_half2(lds_word((nb[i] & 0x3Cu) | pair)) * s2;
-            const float d0 = distance<0>(v, h + i, r), d1 = distance<1>(v, h + i, r);
-            const bool up = d1 < d0;
-            k[h + i] = (nb[i] >> 2) + (up ? 1u : 0u);
-            d[h + i] = up ? d1 : d0;
+            if (kIdx) {
+                const float d0 = distance<0>(v, h + i, r), d1 = distance<1>(v, h + i, r);
+                const bool up = d1 < d0;
+                k[h + i] = (nb[i] >> 2) + (up ? 1u : 0u);
+                d[h + i] = up ? d1 : d0;
+            } else {
+                const float d0 = difference<0>(v, h + i, r), d1 = difference<1>(v, h + i, r);
+                asm("v_min_f32 %0, |%1|, |%2|" : "=v"(d[h + i]) : "v"(d0), "v"(d1));
+            }
             marks |= nb[i];
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -186,15 +193,16 @@ __device__ __forceinline__ uint32_t rate_pattern(const uint8_t* near, uint32_t p
                 const half2_t r = as_half2(lds_word(((nb & 0x3Cu) | pair) + 4u)) * s2;
                 const float d1 = distance<0>(v, i, r), d2 = distance<1>(v, i, r);
                 if (d2 < d1) {
-                    k[i] = (nb >> 2) + 2u;
+                    if (kIdx) k[i] = (nb >> 2) + 2u;
                     d[i] = d2;
                 }
             }
         }
     }
     idx = 0;
+    if (kIdx)
 #pragma unroll
-    for (int i = 0; i < kRowValues; ++i) idx = (idx << 4) | (i == skip ? 15u : k[i]);
+        for (int i = 0; i < kRowValues; ++i) idx = (idx << 4) | (i == skip ? 15u : k[i]);
     if (kSse) {
         sse = tree_sum(d, skip);
     }
