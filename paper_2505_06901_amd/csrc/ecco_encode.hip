@@ -60,23 +60,27 @@ struct Job {  // one model and the groups it encodes; blockIdx.y picks one of tw
     Io io;
 };
 
-// tables of a model in LDS, in words: near [S][64], pair [S][16], codes [S][16] as code << 8 | length: the word serves as a
-// shift count as it is (its low five bits), and the lengths of up to 16 words can be summed with the codes still on top
+// tables of a model in LDS: near [S][64] (full search) or fine (min/max selector), pair [S][16], codes [S][16] as
+// code << 8 | length: the word serves as a shift count as it is (its low five bits), and the lengths of up to 16 words can be
+// summed with the codes still on top
 struct EncTables {
     const uint8_t* near;
-    uint32_t pair;         // LDS address, a multiple of 64
+    uint32_t pair, fine;  // LDS addresses, pair a multiple of 64
     const uint32_t* enc;
 };
-constexpr int kTableWords = kSearchBins / 4 + 16 + kK;  // per pattern
+constexpr int kTableWords = kSearchBins / 4 + 16 + kK;  // per pattern, full search
+constexpr size_t minmax_table_words(int S) { return search_fine_words(S) + (size_t)S * (16 + kK); }
 __device__ __forceinline__ uint32_t code_word(uint32_t enc) { return ((enc & 0xFFFFu) << 8) | (enc >> 16); }
-template <int kThreads>
+template <int kThreads, bool kFine>
 __device__ __forceinline__ EncTables stage_enc_tables(uint32_t* lds, const uint32_t* __restrict__ dev, int S) {
     const DevLayout D{S};
-    const uint4* a = reinterpret_cast<const uint4*>(dev + D.near());  // near and pair follow each other
+    const uint4* a = reinterpret_cast<const uint4*>(dev + (kFine ? D.pair() : D.near()));  // near and pair, or pair and fine, follow each other
     const uint4* e = reinterpret_cast<const uint4*>(dev + D.enc());
     uint4* d = reinterpret_cast<uint4*>(lds);
-    const int n0 = S * (kSearchBins / 4 + 16) / 4, n1 = S * kK / 4, tid = threadIdx.x;
-    constexpr int kPieces = kMaxS * (kSearchBins / 4 + 16) / 4 / kThreads + (kMaxS * (kSearchBins / 4 + 16) / 4 % kThreads != 0);
+    const int n0 = (int)(S * 16 + (kFine ? search_fine_words(S) : search_near_words(S))) / 4, n1 = S * kK / 4, tid = threadIdx.x;
+    constexpr int kMost = kMaxS * (kSearchBins / 4 + 16) / 4;
+    static_assert(search_fine_words(kMaxS) == search_near_words(kMaxS), "of the same size");
+    constexpr int kPieces = kMost / kThreads + (kMost % kThreads != 0);
     static_assert(kMaxS * kK / 4 <= kThreads, "one piece of the codes per thread");
     // all pieces requested before the first is stored; indices past the end repeat the last piece
     uint4 v[kPieces];
@@ -89,8 +93,9 @@ __device__ __forceinline__ EncTables stage_enc_tables(uint32_t* lds, const uint3
         if (tid + i * kThreads < n0) d[tid + i * kThreads] = v[i];
     EncTables t;
     t.near = reinterpret_cast<const uint8_t*>(lds);
-    t.pair = lds_address(lds + S * (kSearchBins / 4));
-    t.enc = lds + S * (kSearchBins / 4 + 16);
+    t.pair = lds_address(lds + (kFine ? 0 : S * (kSearchBins / 4)));
+    t.fine = lds_address(lds + S * 16);
+    t.enc = lds + 4 * n0;
     return t;
 }
 
@@ -164,7 +169,7 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
     load_values<kSearchBatch>(v, io.values(), io.groups(), blockIdx.x, wave * kWaveRows + row, l);
     Coefs<kTiles> C;
     C.load(job.dev + DevLayout{S}.coef(), wave, tiles, lane);
-    const EncTables T = stage_enc_tables<kSearchThreads>(smem, job.dev, S);
+    const EncTables T = stage_enc_tables<kSearchThreads, false>(smem, job.dev, S);
     bool slack_set = false;
     if (l == 0) L.slack[wave * kWaveRows + row] = 0.0f;
     for (size_t b = blockIdx.x; b < batches; b += gridDim.x) {
@@ -174,7 +179,7 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
         set_slack(L.slack + wave * kWaveRows + row, s, l, slack_set);
         clear_hist(L.hist + wave * kWaveRows * kHistStride, lane);
         wave_fence();
-        set_bins<true>(v, kSearchStep * __builtin_amdgcn_rcpf(s), hist, -1);
+        set_bins(v, kSearchStep * __builtin_amdgcn_rcpf(s), hist, -1);
         wave_fence();
         convert_hist(L.hist + wave * kWaveRows * kHistStride, lane);
         uint64_t left = patterns_left<kTiles, search_over(kTiles)>(L, C, tiles, wave, lane);
@@ -390,7 +395,38 @@ __global__ __launch_bounds__(kFewThreads) void encode_few_kernel(Job<Io> j0, Job
 
 // ---- bulk encoder with the min/max selector --------------------------------------------------------------------------------
 constexpr int kImageStride = 20;  // words per group of the payload being assembled
-constexpr size_t minmax_lds_bytes(int S) { return ((size_t)S * (kTableWords + 1) + kMinmaxBatch * kImageStride + 3) * 4; }
+constexpr size_t minmax_lds_bytes(int S) { return (minmax_table_words(S) + S + kMinmaxBatch * kImageStride + 3) * 4; }
+
+// The indices of the row's values under the pattern whose centroids are at `pair` and whose row of the fine table (ecco_search.h)
+// is at `fine`, eight nibbles per lane, first value on top.  per: kFinePer / scale.  Returns the marks of the lane's bins: with
+// kFineCrowded in one of its lanes, a row's indices do not hold.  What the kernel takes is VALU issue (92 % of its time): the places
+// of two values are formed by four instructions, and an index is its table entry plus the comparison's carry.  Over the uniform
+// bins of the full search nearly every wavefront of keys also looked up third candidates: 2 x 131072 groups of keys and values
+// at 16 patterns 42.7 -> 37.5 us.
+// Every bit pattern of t, NaN included, stays inside the workgroup's LDS: the place is below 1024, the entry below 256, and
+// tables and images of at least 2.4 KB follow one another.
+__device__ __forceinline__ uint32_t fine_indices(uint32_t fine, uint32_t pair, half2_t s2, half2_t per, const RowValues& v, uint32_t& idx) {
+    const uint32_t base = fine - (uint32_t)kFineBins;
+    const half2_t least = splat_half(kFineLeast);
+    uint32_t nb[kRowValues], marks = 0;
+#pragma unroll
+    for (int i = 0; i < kRowValues / 2; ++i) {
+        const half2_t c = as_half2((v.x[i] & 0x80008000u) | __builtin_bit_cast(uint32_t, least));
+        const half2_t t = __builtin_elementwise_fma(as_half2(v.x[i]), per, c);
+        const ushort2_t place = __builtin_bit_cast(ushort2_t, t) >> 6;
+        nb[2 * i] = *(const lds_u8*)(size_t)(base + place.x);
+        nb[2 * i + 1] = *(const lds_u8*)(size_t)(base + place.y);
+    }
+    idx = 0;
+#pragma unroll
+    for (int i = 0; i < kRowValues; ++i) {
+        const half2_t r = as_half2(lds_word(pair + 4u * nb[i])) * s2;
+        const float d0 = distance<0>(v, i, r), d1 = distance<1>(v, i, r);
+        idx = (idx << 4) + nb[i] + (d1 < d0 ? 1u : 0u);
+        marks |= nb[i];
+    }
+    return marks;
+}
 
 template <bool kLong, class Io>
 __global__ __launch_bounds__(kMinmaxThreads) void encode_minmax_kernel(Job<Io> j0, Job<Io> j1) {
@@ -400,12 +436,12 @@ __global__ __launch_bounds__(kMinmaxThreads) void encode_minmax_kernel(Job<Io> j
     const Io io = job.io;
     const int lane = threadIdx.x & 63, l = lane & 15, row = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    uint32_t* ends = smem + S * kTableWords;
+    uint32_t* ends = smem + minmax_table_words(S);
     uint32_t* image = ends + S + (wave * kWaveRows + row) * kImageStride;
     const size_t batches = (io.groups() + kMinmaxBatch - 1) / kMinmaxBatch;
     RowValues v, next;
     load_values<kMinmaxBatch>(v, io.values(), io.groups(), blockIdx.x, wave * kWaveRows + row, l);
-    const EncTables T = stage_enc_tables<kMinmaxThreads>(smem, job.dev, S);
+    const EncTables T = stage_enc_tables<kMinmaxThreads, true>(smem, job.dev, S);
     if ((int)threadIdx.x < S) {
         const uint32_t* pair = job.dev + DevLayout{S}.pair() + threadIdx.x * 16;
         ends[threadIdx.x] = __builtin_amdgcn_perm(pair[kK - 1], pair[0], 0x05040100u);  // first and last centroid
@@ -418,11 +454,10 @@ __global__ __launch_bounds__(kMinmaxThreads) void encode_minmax_kernel(Job<Io> j
         const float s = half_bits_f(smax);
         const half2_t s2 = splat_half(smax);
         const uint32_t pattern = select_minmax(ends, 1, S, s2, v, l);
-        set_bins<false>(v, kSearchStep * __builtin_amdgcn_rcpf(s), nullptr, -1);
-        float sse;
+        const uint32_t per = __builtin_bit_cast(unsigned short, (_Float16)(kFinePer * __builtin_amdgcn_rcpf(s)));
         uint32_t idx;
-        const uint32_t marks = rate_pattern<false, true>(T.near + pattern * kSearchBins, T.pair + pattern * 64u, s2, v, -1, sse, idx);
-        const uint64_t lanes = __builtin_amdgcn_ballot_w64(((marks & kNearWide) != 0u || !(s >= kSearchLeastScale)) && smax != 0u);
+        const uint32_t marks = fine_indices(T.fine + (pattern >> 2) * (8 * kFineBins) + (pattern & 3u) * kFineBins, T.pair + pattern * 64u, s2, splat_half(per), v, idx);
+        const uint64_t lanes = __builtin_amdgcn_ballot_w64(((marks & kFineCrowded) != 0u || !(s >= kSearchLeastScale)) && smax != 0u);
         if (lanes != 0ull) {  // rows with crowded bins or a scale too small for the tables
             const uint32_t id = scan_indices(T.pair + pattern * 64u, s2, v, -1);
             idx = row_any(lanes, row) ? id : idx;

@@ -27,7 +27,7 @@ constexpr int kPeekEntries = 1 << kPeekBits;
 
 // Device memory of a model, one allocation, in 32-bit words:
 //   decode and codes [enc S x 16][centroids S x 8][longtab S x 16]   (a few KB; the decoders expand them in LDS)
-//   encoder search   [near][pair][coef]                              (ecco_search.h; 118 KB for S = 64)
+//   encoder search   [near][pair][fine][coef]                        (ecco_search.h; 134 KB for S = 64)
 // The decode table itself (S x 256 entries) is never stored in global memory: every workgroup
 // builds it in LDS from `enc` and the centroids, which costs less than fetching 64 KB per workgroup.
 struct DevLayout {
@@ -38,7 +38,8 @@ struct DevLayout {
     constexpr size_t table_words() const { return longtab() + (size_t)S * kK; }
     constexpr size_t near() const { return table_words(); }
     constexpr size_t pair() const { return near() + search_near_words(S); }
-    constexpr size_t coef() const { return pair() + search_pair_words(S); }
+    constexpr size_t fine() const { return pair() + search_pair_words(S); }
+    constexpr size_t coef() const { return fine() + search_fine_words(S); }
     constexpr size_t image_words() const { return coef() + search_coef_words(S); }
     constexpr size_t total_bytes() const { return image_words() * 4; }
 };

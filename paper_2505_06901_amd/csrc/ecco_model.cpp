@@ -69,6 +69,7 @@ void build_device_image(const ecco_model* m, uint32_t* img) {
         for (int k = 0; k < kK; ++k) enc[p * kK + k] = (uint32_t)m->codes[p * kK + k] | ((uint32_t)m->lens[p * kK + k] << 16);
     }
     build_search_tables(m->cent, kK, kK, m->S, (double)kSearchStep, img + D.near(), img + D.pair(), img + D.coef());
+    build_fine_table(m->cent, kK, kK, m->S, img + D.fine());
 }
 
 }  // namespace ecco

@@ -13,7 +13,8 @@
 // pattern of least error is therefore always among those whose lower bound does not exceed the least upper bound
 // (1.7 of 64 on the weight workloads), and only these are rated exactly.
 //
-// The second table answers, per pattern and bin, which of two (rarely three) neighbouring centroids can be nearest.
+// The second table answers, per pattern and bin, which of two (rarely three) neighbouring centroids can be nearest.  A third
+// does so for the min/max selector, which forms no histogram, over bins that are finer around zero (kFineBins).
 #pragma once
 
 #include <algorithm>
@@ -37,10 +38,21 @@ constexpr float kSearchLeastScale = 0x1p-11f;
 constexpr uint32_t kNearTwo = 1u;   // a + 2 can be nearest as well
 constexpr uint32_t kNearWide = 2u;  // more than three: compare with all centroids
 
+// Bins of the min/max selector: t = 2^-7 + kFinePer |u| in FP16, from 2^-7 to below 2, by its four leading mantissa bits -- 16 bins
+// to each of 8 octaves, and the sign of u.  Where one channel's magnitude sets the scale (keys) most centroids lie within a few
+// hundredths of zero: the uniform bins above, 2^-7 wide, hold midpoints of two pairs there in 97 % of the wavefronts, these
+// in none (they are 2^-11 wide at zero, and 2^-4 next to the scale).  The half-precision bits of t with u's sign, shifted right
+// by 6, are the place of the pattern's byte: patterns p & 3 lie 128 bytes apart, the signs 512, four patterns 1024.
+constexpr int kFineBins = 128;          // per sign
+constexpr float kFinePer = 1.988f;      // t stays below 2 with the roundings of build_fine_table
+constexpr uint32_t kFineLeast = 0x2000;  // 2^-7 as FP16 bits: bit 13 is set throughout, the place starts at 128
+constexpr uint32_t kFineCrowded = 16u;  // entry: more than two candidates, compare with all centroids; else the lower of two
+
 // words of the tables of S patterns
 constexpr int search_tiles(int S) { return (S + 15) / 16; }
 constexpr size_t search_near_words(int S) { return (size_t)S * (kSearchBins / 4); }                          // a byte per pattern and bin
 constexpr size_t search_pair_words(int S) { return (size_t)S * 16; }                                          // (centroid k, centroid k + 1) per pattern
+constexpr size_t search_fine_words(int S) { return (size_t)((S + 3) / 4) * (4 * 2 * kFineBins / 4); }          // a byte per pattern, sign and bin
 constexpr size_t search_coef_words(int S) { return (size_t)search_tiles(S) * kSearchBlocks * 3 * 64 * 4; }   // A, B, E in matrix-core operand order
 
 // cent: [S][stride] FP16 bits, n_cent ascending centroids each; step: bin axis units per u = 1 (at most 32700)
@@ -69,6 +81,23 @@ inline double nearest_sq(const double* c, int n, double u) {
     double best = (u - c[0]) * (u - c[0]);
     for (int k = 1; k < n; ++k) best = std::min(best, (u - c[k]) * (u - c[k]));
     return best;
+}
+
+// how far a reconstructed centroid fp16(c s) can lie from c s, in units of s
+inline double recon_eps(double c) { return 1.02 * (std::fabs(c) * 0x1p-11 + 0x1p-25 / (double)kSearchLeastScale) + 1e-6; }
+
+// the lowest and the highest of n ascending centroids (off by eps) that can be nearest to a u from lo to hi
+inline void candidates(const double* c, const double* eps, int n, double lo, double hi, int& kmin, int& kmax) {
+    // the nearest centroid is k when k of the midpoints lie below u; a midpoint is off by its centroids' rounding
+    kmin = 0;
+    kmax = 0;
+    for (int k = 0; k + 1 < n; ++k) {
+        const double m = 0.5 * (c[k] + c[k + 1]), off = std::max(eps[k], eps[k + 1]);
+        if (m + off < lo) kmin = k + 1;
+        if (m - off <= hi) kmax = k + 1;
+    }
+    // of centroids that round to the same value the lowest counts as nearest, also to values above them
+    while (kmin > 0 && c[kmin] - c[kmin - 1] <= 2.0 * (eps[kmin] + eps[kmin - 1])) --kmin;
 }
 
 struct Coef {
@@ -115,7 +144,7 @@ inline void build_search_tables(const uint16_t* cent, int stride, int n_cent, in
         double c[16], eps[16];
         for (int k = 0; k < n_cent; ++k) {
             c[k] = half_value(cent[p * stride + k]);
-            eps[k] = 1.02 * (std::fabs(c[k]) * 0x1p-11 + 0x1p-25 / (double)kSearchLeastScale) + 1e-6;
+            eps[k] = recon_eps(c[k]);
         }
         for (int k = 0; k < 16; ++k) {
             const int a = std::min(k, n_cent - 1), b = std::min(k + 1, n_cent - 1);
@@ -124,15 +153,8 @@ inline void build_search_tables(const uint16_t* cent, int stride, int n_cent, in
         for (int bin = 0; bin < kSearchBins; ++bin) {
             co[(size_t)p * kSearchBins + bin] = bin_coef(c, n_cent, bin, step);
             const double lo = (256.0 * bin - 32768.0 - 0.52) / step, hi = (256.0 * bin + 255.0 - 32768.0 + 0.52) / step;
-            // the nearest centroid is k when k of the midpoints lie below u; a midpoint is off by its centroids' rounding
-            int kmin = 0, kmax = 0;
-            for (int k = 0; k + 1 < n_cent; ++k) {
-                const double m = 0.5 * (c[k] + c[k + 1]), off = std::max(eps[k], eps[k + 1]);
-                if (m + off < lo) kmin = k + 1;
-                if (m - off <= hi) kmax = k + 1;
-            }
-            // of centroids that round to the same value the lowest counts as nearest, also to values above them
-            while (kmin > 0 && c[kmin] - c[kmin - 1] <= 2.0 * (eps[kmin] + eps[kmin - 1])) --kmin;
+            int kmin, kmax;
+            candidates(c, eps, n_cent, lo, hi, kmin, kmax);
             const int range = kmax - kmin;
             nb[p * kSearchBins + bin] = (uint8_t)((range > 1 ? kmin : std::min(kmin, n_cent - 2)) * 4 + (range > 2 ? kNearWide : range == 2 ? kNearTwo : 0u));
         }
@@ -156,6 +178,32 @@ inline void build_search_tables(const uint16_t* cent, int stride, int n_cent, in
                         const Coef& r = co[(size_t)p * kSearchBins + bin];
                         *out = op == 2 ? r.e : is_a ? r.a : r.b;
                     }
+}
+
+// The min/max selector's table (kFineBins).  t differs from the true 2^-7 + kFinePer |u| by its rounding to FP16, 2^-11 of itself,
+// and by that of kFinePer / s: 2^-11 of kFinePer |u|, 2^-10 where the quotient is a subnormal (s above 2^15), and the
+// reciprocal's error.
+inline void build_fine_table(const uint16_t* cent, int stride, int n_cent, int S, uint32_t* fine) {
+    using namespace search_detail;
+    uint8_t* out = reinterpret_cast<uint8_t*>(fine);
+    for (int p = 0; p < S; ++p) {
+        double c[16], eps[16];
+        for (int k = 0; k < n_cent; ++k) {
+            c[k] = half_value(cent[p * stride + k]);
+            eps[k] = recon_eps(c[k]);
+        }
+        uint8_t* row = out + (size_t)(p >> 2) * (4 * 2 * kFineBins) + (p & 3) * kFineBins;
+        for (int bin = 0; bin < kFineBins; ++bin) {
+            const auto edge = [](int b) { return std::ldexp(1.0 + (b & 15) / 16.0, (b >> 4) - 7); };
+            const double least = std::max(0.0, edge(bin) * (1.0 - 0x1p-10) - 0x1p-7) / kFinePer * (1.0 - 0x1p-9);
+            const double most = (edge(bin + 1) * (1.0 + 0x1p-10) - 0x1p-7) / kFinePer * (1.0 + 0x1p-9);
+            for (int sign = 0; sign < 2; ++sign) {
+                int kmin, kmax;
+                candidates(c, eps, n_cent, sign ? -most : least, sign ? -least : most, kmin, kmax);
+                row[sign * 4 * kFineBins + bin] = (uint8_t)(kmax - kmin > 1 ? kFineCrowded : std::min(kmin, n_cent - 2));
+            }
+        }
+    }
 }
 
 }  // namespace ecco

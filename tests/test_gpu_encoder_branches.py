@@ -183,3 +183,29 @@ def test_no_input_is_far_slower(dev):
         assert time_of(lambda: call(mm, torch.zeros_like(w))) <= 3 * usual, name
         assert time_of(lambda: call(mm, tiny)) <= 15 * usual, name
         assert time_of(lambda: call(mo, out)) <= 15 * usual, name
+
+
+@pytest.mark.parametrize("S", [1, 2, 5, 16, 63])
+def test_minmax_bin_edges(dev, S):
+    """Values on either side of every edge of the min/max selector's bins and of every midpoint between centroids, which lie
+    far apart, a few per bin or many, at the smallest and largest scales of its table and across 2^15, where the factor
+    onto its axis becomes a subnormal."""
+    from oracle import oracle as O
+    rng = np.random.default_rng(S)
+    cent = crowded_tables(S, S + 100)
+    cent[::3] = model_tables(S, S)[0][::3]
+    lens = np.full((S, 16), 4, np.uint8)
+    edges = (2.0 ** (np.arange(128) // 16 - 7) * (1 + np.arange(128) % 16 / 16) - 2.0 ** -7) / 1.988
+    c = cent.astype(np.float64)
+    marks = np.concatenate([edges, -edges, ((c[:, 1:] + c[:, :-1]) / 2).reshape(-1), c.reshape(-1)])
+    n = 2048
+    scale = np.array([2.0 ** -11, 2.0 ** -11 * 1.001, 0.02, 1.0, 3.3, 32752.0, 32800.0, 49152.0, 65504.0])[rng.integers(0, 9, n)].astype(np.float16)
+    x = (rng.choice(marks, (n, 128)) * scale[:, None].astype(np.float64)).astype(np.float16)
+    x = (x.view(np.int16) + np.where(x == 0, 0, rng.integers(-2, 3, x.shape)).astype(np.int16)).view(np.float16)  # up to two steps off
+    x = np.where(np.abs(x) > scale[:, None], scale[:, None], x)
+    x[np.arange(n), rng.integers(0, 128, n)] = scale * rng.choice([-1, 1], n)
+    m = E.ecco_model_to_device(E.ecco_model_create(cent, lens), 0)
+    want = O.encode_minmax(cent.view(np.uint16), lens, x.view(np.uint16))
+    blocks, meta = E.ecco_encode_minmax(m, torch.from_numpy(x).to(dev))
+    assert np.array_equal(meta.cpu().numpy().view(np.uint32), want[1])
+    assert np.array_equal(blocks.cpu().numpy(), want[0])
