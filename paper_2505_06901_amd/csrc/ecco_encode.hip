@@ -60,17 +60,16 @@ struct Job {  // one model and the groups it encodes; blockIdx.y picks one of tw
     Io io;
 };
 
-// tables of a model in LDS: near [S][64] (full search) or fine (min/max selector), pair [S][16], codes [S][16] as
-// code << 8 | length: the word serves as a shift count as it is (its low five bits), and the lengths of up to 16 words can be
-// summed with the codes still on top
+// tables of a model in LDS: near [S][64] (full search) or fine (min/max selector), pair [S][16], codes [S][16] with the
+// code on top and 32 - length in the low byte: joined to a stream by one v_alignbit, which takes the word as the shift count
+// as well, and the low bytes of up to eight words can be summed with the codes still on top
 struct EncTables {
     const uint8_t* near;
-    uint32_t pair, fine;  // LDS addresses, pair a multiple of 64
-    const uint32_t* enc;
+    uint32_t pair, fine, enc;  // LDS addresses; pair and enc multiples of 64
 };
 constexpr int kTableWords = kSearchBins / 4 + 16 + kK;  // per pattern, full search
 constexpr size_t minmax_table_words(int S) { return search_fine_words(S) + (size_t)S * (16 + kK); }
-__device__ __forceinline__ uint32_t code_word(uint32_t enc) { return ((enc & 0xFFFFu) << 8) | (enc >> 16); }
+__device__ __forceinline__ uint32_t code_word(uint32_t enc) { return (enc << (32u - (enc >> 16))) | (32u - (enc >> 16)); }
 template <int kThreads, bool kFine>
 __device__ __forceinline__ EncTables stage_enc_tables(uint32_t* lds, const uint32_t* __restrict__ dev, int S) {
     const DevLayout D{S};
@@ -95,32 +94,41 @@ __device__ __forceinline__ EncTables stage_enc_tables(uint32_t* lds, const uint3
     t.near = reinterpret_cast<const uint8_t*>(lds);
     t.pair = lds_address(lds + (kFine ? 0 : S * (kSearchBins / 4)));
     t.fine = lds_address(lds + S * 16);
-    t.enc = lds + 4 * n0;
+    t.enc = lds_address(lds + 4 * n0);
     return t;
 }
 
-// Packs the row's group with the codes `enc` of its pattern: lane l returns payload word l and the meta word.  idx: the
-// lane's eight indices as nibbles, which is also the lane's payload word in raw mode.  image: 18 words of LDS of the row.
+// Packs the row's group with the codes at the LDS address `enc` (a multiple of 64) of its pattern: lane l returns payload word l
+// and the meta word.  idx: the lane's eight indices as nibbles, which is also the lane's payload word in raw mode.  image: 18
+// words of LDS of the row.  A lane's codes are joined in one 64-bit word (two where the model has codes beyond 8 bits) and go
+// into the image with two or three ORs (in runs of 32 bits with two each: min/max selector, 2 x 131072 groups, 16 patterns,
+// 37.5 us with that and a scale found apart from the group's ends, 32.7 us so).
 template <bool kLong>
-__device__ __forceinline__ uint32_t pack_row(const uint32_t* enc, uint32_t* image, uint32_t idx, int l, uint32_t smax, uint32_t pattern, uint32_t& meta) {
+__device__ __forceinline__ uint32_t pack_row(uint32_t enc, uint32_t* image, uint32_t idx, int l, uint32_t smax, uint32_t pattern, uint32_t& meta) {
     image[l] = 0u;
     if (l < 2) image[kRowLanes + l] = 0u;
     uint32_t e[kRowValues];
 #pragma unroll
-    for (int i = 0; i < kRowValues; ++i) e[i] = enc[(idx >> (28 - 4 * i)) & 15u];
-    constexpr int kRun = kLong ? 2 : 4;  // values whose codes always fit 32 bits together
-    constexpr int kRuns = kRowValues / kRun;
-    uint32_t bits[kRuns], n[kRuns], lane_bits = 0;
+    for (int i = 0; i < kRowValues; ++i) e[i] = lds_word(enc | ((i < 7 ? idx >> (26 - 4 * i) : idx << 2) & 60u));
+    constexpr int kParts = kLong ? 2 : 1, kRun = kRowValues / kParts;  // codes of kRun values always fit 64 bits together
+    uint64_t bits[kParts];
+    uint32_t n[kParts], lane_bits = 0;
 #pragma unroll
-    for (int r = 0; r < kRuns; ++r) {
-        bits[r] = e[r * kRun] >> 8;
-        n[r] = e[r * kRun];
+    for (int r = 0; r < kParts; ++r) {
+        uint32_t h[2], pad[2];  // the codes of half a run; 32 per value less their bits, in the low byte
 #pragma unroll
-        for (int i = 1; i < kRun; ++i) {
-            bits[r] = (bits[r] << (e[r * kRun + i] & 31u)) | (e[r * kRun + i] >> 8);
-            n[r] += e[r * kRun + i];
+        for (int j = 0; j < 2; ++j) {
+            const uint32_t* c = e + r * kRun + j * (kRun / 2);
+            h[j] = c[0] >> (c[0] & 31u);
+            pad[j] = c[0];
+#pragma unroll
+            for (int i = 1; i < kRun / 2; ++i) {
+                h[j] = __builtin_amdgcn_alignbit(h[j], c[i], c[i]);
+                pad[j] += c[i];
+            }
         }
-        n[r] &= 0xFFu;
+        bits[r] = ((uint64_t)h[0] << (16u * kRun - (pad[1] & 0xFFu))) | h[1];
+        n[r] = 32u * kRun - ((pad[0] + pad[1]) & 0xFFu);
         lane_bits += n[r];
     }
     const uint32_t end = row_scan(lane_bits);
@@ -130,10 +138,13 @@ __device__ __forceinline__ uint32_t pack_row(const uint32_t* enc, uint32_t* imag
     if (!raw) {
         uint32_t at = end - lane_bits;
 #pragma unroll
-        for (int r = 0; r < kRuns; ++r) {
-            const uint64_t v = (uint64_t)bits[r] << (64u - n[r] - (at & 31u));  // left-aligned at stream bit `at`
-            atomicOr(&image[at >> 5], (uint32_t)(v >> 32));
-            if ((uint32_t)v != 0u) atomicOr(&image[(at >> 5) + 1], (uint32_t)v);
+        for (int r = 0; r < kParts; ++r) {
+            const uint64_t v = bits[r] << (64u - n[r]);  // at least two bits: the shift is below 64
+            const uint32_t hi = (uint32_t)(v >> 32), lo = (uint32_t)v, third = __builtin_amdgcn_alignbit(lo, 0u, at);
+            uint32_t* to = image + (at >> 5);
+            atomicOr(to, hi >> (at & 31u));
+            atomicOr(to + 1, __builtin_amdgcn_alignbit(hi, lo, at));
+            if (third != 0u) atomicOr(to + 2, third);
             at += n[r];
         }
     }
@@ -224,7 +235,7 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
         // the next group is requested here, when the search has given its registers back
         load_values<kSearchBatch>(v, io.values(), io.groups(), b + gridDim.x, wave * kWaveRows + row, l);
         uint32_t mw;
-        const uint32_t word = pack_row<kLong>(T.enc + pattern * kK, hist, idx, l, smax, pattern, mw);
+        const uint32_t word = pack_row<kLong>(T.enc + pattern * (kK * 4u), hist, idx, l, smax, pattern, mw);
         size_t at;
         if (io.place(b * kSearchBatch + (uint32_t)(wave * kWaveRows + row), at)) {
             io.blocks[at * kBlockWords + l] = word;
@@ -239,37 +250,31 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
 // fitness = (min - first)^2 + (max - last)^2, every operation rounded to FP32 on its own.  The lanes of a row rate the
 // patterns l, l + 16, ...; the least fitness wins, the lowest pattern on a tie (pattern 0 if the input held a NaN, against
 // the contract).
-// (the wait states belong to the cross-lane moves that may follow: the compiler does not see into the instruction)
-__device__ __forceinline__ half2_t pk_min(half2_t a, half2_t b) {
-    half2_t r;
-    asm("v_pk_min_f16 %0, %1, %2\n\ts_nop 1" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-__device__ __forceinline__ half2_t pk_max(half2_t a, half2_t b) {
-    half2_t r;
-    asm("v_pk_max_f16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-__device__ __forceinline__ uint32_t select_minmax(const uint32_t* cent, int stride, int S, half2_t s2, const RowValues& v, int l) {
-    // (least value, least negated value) of the row
+// (least value, least negated value) of the row; a NaN stays one.  Their magnitudes' greater is the group's scale.
+__device__ __forceinline__ half2_t row_ends(const RowValues& v) {
     half2_t lo2 = as_half2(v.x[0]), hi2 = lo2;
 #pragma unroll
     for (int i = 1; i < 4; ++i) {
-        lo2 = pk_min(lo2, as_half2(v.x[i]));
-        hi2 = pk_max(hi2, as_half2(v.x[i]));
+        lo2 = __builtin_elementwise_minimum(lo2, as_half2(v.x[i]));
+        hi2 = __builtin_elementwise_maximum(hi2, as_half2(v.x[i]));
     }
-    half2_t ends2 = pk_min(as_half2(__builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, -hi2), __builtin_bit_cast(uint32_t, lo2), 0x05040100u)),
-                           as_half2(__builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, -hi2), __builtin_bit_cast(uint32_t, lo2), 0x07060302u)));
-    ends2 = row_all(ends2, [](half2_t a, half2_t b) { return pk_min(a, b); });
+    const half2_t ends2 = __builtin_elementwise_minimum(as_half2(__builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, -hi2), __builtin_bit_cast(uint32_t, lo2), 0x05040100u)),
+                                                        as_half2(__builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, -hi2), __builtin_bit_cast(uint32_t, lo2), 0x07060302u)));
+    return row_all(ends2, [](half2_t a, half2_t b) { return __builtin_elementwise_minimum(a, b); });
+}
+__device__ __forceinline__ uint32_t select_minmax(const uint32_t* cent, int stride, int S, half2_t s2, half2_t ends2, int l) {
     const float lo = (float)ends2[0], hi = -(float)ends2[1];
-    float least = __builtin_inff();
-    uint32_t at = 0xFFFFu;
-    for (int p = l; p < S; p += kRowLanes) {
+    const auto fitness = [&](int p) {
         // first and last centroid: of the words with the ends (stride 1), or of a row of the pattern's pairs
         const uint32_t c = stride == 1 ? cent[p] : __builtin_amdgcn_perm(cent[p * stride + stride - 1], cent[p * stride], 0x07060100u);
         const half2_t e = as_half2(c) * s2;
         const float dlo = __fsub_rn(lo, (float)e[0]), dhi = __fsub_rn(hi, (float)e[1]);
-        const float f = __fadd_rn(__fmul_rn(dlo, dlo), __fmul_rn(dhi, dhi));
+        return __fadd_rn(__fmul_rn(dlo, dlo), __fmul_rn(dhi, dhi));
+    };
+    uint32_t at = (uint32_t)min(l, S - 1);  // lanes beyond the patterns rate the last one
+    float least = fitness((int)at);
+    for (int p = l + kRowLanes; p < S; p += kRowLanes) {
+        const float f = fitness(p);
         if (f < least) {
             least = f;
             at = (uint32_t)p;
@@ -301,7 +306,7 @@ __device__ __forceinline__ float nearer(float d, uint32_t x, uint32_t r) {
 template <bool kMinMax, bool kLong, class Io>
 __global__ __launch_bounds__(kFewThreads) void encode_few_kernel(Job<Io> j0, Job<Io> j1) {
     __shared__ __align__(16) uint32_t cent[kMaxS * kK / 2];  // pairs of neighbouring centroids
-    __shared__ __align__(16) uint32_t enc[kMaxS * kK];
+    __shared__ __align__(64) uint32_t enc[kMaxS * kK];
     __shared__ __align__(16) uint32_t values[kGroup / 2];
     __shared__ __align__(16) uint8_t index[kGroup];
     __shared__ uint32_t row_sse[kFewRows], row_pattern[kFewRows], image[20];
@@ -329,7 +334,7 @@ __global__ __launch_bounds__(kFewThreads) void encode_few_kernel(Job<Io> j0, Job
     __syncthreads();
     uint32_t win;
     if (kMinMax) {
-        win = select_minmax(cent, kK / 2, S, s2, v, l);
+        win = select_minmax(cent, kK / 2, S, s2, row_ends(v), l);
     } else {
         uint32_t pattern = 0;
         float best = __builtin_inff();
@@ -388,7 +393,7 @@ __global__ __launch_bounds__(kFewThreads) void encode_few_kernel(Job<Io> j0, Job
     const uint2 b = *reinterpret_cast<const uint2*>(index + 8 * l);  // eight indices, a byte each, to nibbles, first on top
     const auto nibbles = [](uint32_t w) { return (w & 15u) << 12 | (w & 0xF00u) | (w >> 12 & 0xF0u) | (w >> 24 & 15u); };
     uint32_t mw;
-    const uint32_t word = pack_row<kLong>(enc + win * kK, image, nibbles(b.x) << 16 | nibbles(b.y), l, smax, win, mw);
+    const uint32_t word = pack_row<kLong>(lds_address(enc) + win * (kK * 4u), image, nibbles(b.x) << 16 | nibbles(b.y), l, smax, win, mw);
     io.blocks[at * kBlockWords + l] = word;
     if (l == 0) io.meta[at] = mw;
 }
@@ -407,15 +412,18 @@ constexpr size_t minmax_lds_bytes(int S) { return (minmax_table_words(S) + S + k
 // tables and images of at least 2.4 KB follow one another.
 __device__ __forceinline__ uint32_t fine_indices(uint32_t fine, uint32_t pair, half2_t s2, half2_t per, const RowValues& v, uint32_t& idx) {
     const uint32_t base = fine - (uint32_t)kFineBins;
-    const half2_t least = splat_half(kFineLeast);
+    // (in a register, so that sign and constant are joined by one instruction)
+    uint32_t least = kFineLeast * 0x10001u;
+    asm volatile("" : "+v"(least));
     uint32_t nb[kRowValues], marks = 0;
 #pragma unroll
     for (int i = 0; i < kRowValues / 2; ++i) {
-        const half2_t c = as_half2((v.x[i] & 0x80008000u) | __builtin_bit_cast(uint32_t, least));
+        const half2_t c = as_half2((v.x[i] & 0x80008000u) | least);
         const half2_t t = __builtin_elementwise_fma(as_half2(v.x[i]), per, c);
-        const ushort2_t place = __builtin_bit_cast(ushort2_t, t) >> 6;
-        nb[2 * i] = *(const lds_u8*)(size_t)(base + place.x);
-        nb[2 * i + 1] = *(const lds_u8*)(size_t)(base + place.y);
+        uint32_t place = __builtin_bit_cast(uint32_t, __builtin_bit_cast(ushort2_t, t) >> 6);
+        asm("" : "+v"(place));  // (what is known of its bits would turn a half into a mask and an addition)
+        nb[2 * i] = *(const lds_u8*)(size_t)(base + (place & 0xFFFFu));
+        nb[2 * i + 1] = *(const lds_u8*)(size_t)(base + (place >> 16));
     }
     idx = 0;
 #pragma unroll
@@ -450,13 +458,14 @@ __global__ __launch_bounds__(kMinmaxThreads) void encode_minmax_kernel(Job<Io> j
     for (size_t b = blockIdx.x; b < batches; b += gridDim.x) {
         const size_t g = b * kMinmaxBatch + wave * kWaveRows + row;
         load_values<kMinmaxBatch>(next, io.values(), io.groups(), b + gridDim.x, wave * kWaveRows + row, l);
-        const uint32_t smax = row_max(lane_absmax(v));
+        const half2_t ends2 = row_ends(v);
+        const uint32_t both = __builtin_bit_cast(uint32_t, ends2) & 0x7FFF7FFFu, smax = max(both & 0xFFFFu, both >> 16);
         const float s = half_bits_f(smax);
         const half2_t s2 = splat_half(smax);
-        const uint32_t pattern = select_minmax(ends, 1, S, s2, v, l);
+        const uint32_t pattern = select_minmax(ends, 1, S, s2, ends2, l);
         const uint32_t per = __builtin_bit_cast(unsigned short, (_Float16)(kFinePer * __builtin_amdgcn_rcpf(s)));
         uint32_t idx;
-        const uint32_t marks = fine_indices(T.fine + (pattern >> 2) * (8 * kFineBins) + (pattern & 3u) * kFineBins, T.pair + pattern * 64u, s2, splat_half(per), v, idx);
+        const uint32_t marks = fine_indices(T.fine + (pattern + (pattern & ~3u)) * kFineBins, T.pair + pattern * 64u, s2, splat_half(per), v, idx);
         const uint64_t lanes = __builtin_amdgcn_ballot_w64(((marks & kFineCrowded) != 0u || !(s >= kSearchLeastScale)) && smax != 0u);
         if (lanes != 0ull) {  // rows with crowded bins or a scale too small for the tables
             const uint32_t id = scan_indices(T.pair + pattern * 64u, s2, v, -1);
@@ -464,7 +473,7 @@ __global__ __launch_bounds__(kMinmaxThreads) void encode_minmax_kernel(Job<Io> j
         }
         idx = smax == 0u ? 0u : idx;
         uint32_t mw;
-        const uint32_t word = pack_row<kLong>(T.enc + pattern * kK, image, idx, l, smax, pattern, mw);
+        const uint32_t word = pack_row<kLong>(T.enc + pattern * (kK * 4u), image, idx, l, smax, pattern, mw);
         size_t at;
         if (io.place(g, at)) {
             io.blocks[at * kBlockWords + l] = word;
@@ -509,7 +518,7 @@ int launch_encode(bool minmax, const ecco_model* m0, const Io& io0, const ecco_m
         else rc = lng ? few(encode_few_kernel<false, true, Io>) : few(encode_few_kernel<false, false, Io>);
     } else if (minmax) {
         const size_t lds = minmax_lds_bytes(S);
-        const int per_cu = (int)std::min<size_t>(8, 160 * 1024 / lds);  // at 64 patterns six fit; at 16 eight take 38.8 us for 262144 groups, six 39.8 us
+        const int per_cu = (int)std::min<size_t>(8, 160 * 1024 / lds);  // at 64 patterns six fit; at 16 eight took 38.8 us for 262144 groups, six 39.8 us
         rc = lng ? run(encode_minmax_kernel<true, Io>, lds, kMinmaxBatch, kMinmaxThreads, per_cu) : run(encode_minmax_kernel<false, Io>, lds, kMinmaxBatch, kMinmaxThreads, per_cu);
     } else {
         const size_t lds = search_lds_bytes(S);

@@ -202,7 +202,7 @@ def test_minmax_bin_edges(dev, S):
     scale = np.array([2.0 ** -11, 2.0 ** -11 * 1.001, 0.02, 1.0, 3.3, 32752.0, 32800.0, 49152.0, 65504.0])[rng.integers(0, 9, n)].astype(np.float16)
     x = (rng.choice(marks, (n, 128)) * scale[:, None].astype(np.float64)).astype(np.float16)
     x = (x.view(np.int16) + np.where(x == 0, 0, rng.integers(-2, 3, x.shape)).astype(np.int16)).view(np.float16)  # up to two steps off
-    x = np.where(np.abs(x) > scale[:, None], scale[:, None], x)
+    x = np.where(np.abs(x) <= scale[:, None], x, scale[:, None])  # steps beyond 65504 are no numbers
     x[np.arange(n), rng.integers(0, 128, n)] = scale * rng.choice([-1, 1], n)
     m = E.ecco_model_to_device(E.ecco_model_create(cent, lens), 0)
     want = O.encode_minmax(cent.view(np.uint16), lens, x.view(np.uint16))
