@@ -476,7 +476,9 @@ __global__ __launch_bounds__(kGemvThreads) void pb_gemv_kernel(const uint32_t* _
                 const int blk = i0 + (l & 3) * kRows + row;
                 if (l < kAhead && blk < count) part[at + blk] = sum;
             }
-            add = fmaf(last[0], half_f(last_x[0]), fmaf(last[1], half_f(last_x[1]), add));
+            // (an entry that does not count adds nothing, also where the activation read for it is infinite)
+#pragma unroll
+            for (int q = 1; q >= 0; --q) add = last[q] != 0.0f ? fmaf(last[q], half_f(last_x[q]), add) : add;
             wave_lds_fence();
             if (entries != 0u) part[at + lane] += add;
         }

@@ -11,7 +11,8 @@ torch = pytest.importorskip("torch")
 
 import paper_2505_06901_amd as E  # noqa: E402
 from paper_2505_06901_amd import workloads as W  # noqa: E402
-from test_paper_block_pins import _groups, _model  # noqa: E402
+from helpers import stream_bits  # noqa: E402
+from test_paper_block_pins import _groups, _model, _py_decode  # noqa: E402
 
 
 @pytest.fixture(scope="module")
@@ -153,6 +154,36 @@ def test_fused_gemv_matches_oracle(pb, dev):
     with pytest.raises(E.EccoError) as e:
         E.ecco_pb_decode_gemv(m, torch.from_numpy(blocks).to(dev), 8, 200, _t16(np.zeros(200, np.float16), dev))
     assert e.value.status == -2
+
+
+def _codes_end(om, block):
+    """The stream bit behind the last code of a block, and how many padded entries follow."""
+    _, idx, n_out, p, h, _ = _py_decode(om, block)
+    return 10 + int(om.kp_lens[p]) + sum(int(om.lens[p, h, k]) for k in idx), n_out
+
+
+def test_gemv_infinite_activation(pb, dev):
+    """One infinite activation among zeros, at every position in turn, over blocks with one padded entry: the sum is that
+    column's decoded value times infinity.  The entry's own position is left out (there the value that it replaces and the entry
+    are added separately), and so are decoded zeros."""
+    om = _model(pb, S=6, texp=-9, seed=21, skew=2.6)
+    m = _both(pb, om)
+    blocks = pb.encode(om, _groups(31, 2048, scale=2.0 ** -9 * 30).view(np.uint16))
+    blocks = blocks[pb.decode(om, blocks)[2] == 1][:48]
+    rows = len(blocks)
+    assert rows >= 16
+    dec = pb.decode(om, blocks)[0].view(np.float16).reshape(rows, 128).astype(np.float64)
+    entry = np.zeros(rows, int)
+    for r in range(rows):
+        end, n_out = _codes_end(om, blocks[r])
+        assert n_out == 1
+        entry[r] = int("".join(str(b) for b in stream_bits(blocks[r])[end:end + 7]), 2)
+    bd = torch.from_numpy(blocks).to(dev)
+    for j in range(128):
+        x = np.zeros(128, np.float16); x[j] = np.inf
+        y = E.ecco_pb_decode_gemv(m, bd, rows, 128, _t16(x, dev)).cpu().numpy()
+        at = (dec[:, j] != 0) & (entry != j)
+        assert np.array_equal(y[at], dec[at, j] * np.inf), (j, np.nonzero(at & ~(y == dec[:, j] * np.inf))[0][:8])
 
 
 @pytest.mark.parametrize("rows,gpr,S", [(2821, 256, 64), (257, 65, 64), (512, 32, 16), (1025, 257, 16), (255, 1, 64), (769, 5, 1)])
