@@ -60,15 +60,15 @@ struct Job {  // one model and the groups it encodes; blockIdx.y picks one of tw
     Io io;
 };
 
-// tables of a model in LDS: near [S][64] (full search) or fine (min/max selector), pair [S][16], codes [S][16] with the
+// tables of a model in LDS: near [S][64] (full search) or the min/max selector's bins, near or fine, pair [S][16], codes [S][16] with the
 // code on top and 32 - length in the low byte: joined to a stream by one v_alignbit, which takes the word as the shift count
 // as well, and the low bytes of up to eight words can be summed with the codes still on top
 struct EncTables {
     const uint8_t* near;
     uint32_t pair, fine, enc;  // LDS addresses; pair and enc multiples of 64
 };
-constexpr int kTableWords = kSearchBins / 4 + 16 + kK;  // per pattern, full search
-constexpr size_t minmax_table_words(int S) { return search_fine_words(S) + (size_t)S * (16 + kK); }
+constexpr int kTableWords = kSearchBins / 4 + 16 + kK;  // per pattern, with near
+constexpr size_t minmax_table_words(int S, bool fine) { return (fine ? search_fine_words(S) : search_near_words(S)) + (size_t)S * (16 + kK); }
 __device__ __forceinline__ uint32_t code_word(uint32_t enc) { return (enc << (32u - (enc >> 16))) | (32u - (enc >> 16)); }
 template <int kThreads, bool kFine>
 __device__ __forceinline__ EncTables stage_enc_tables(uint32_t* lds, const uint32_t* __restrict__ dev, int S) {
@@ -190,7 +190,7 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
         set_slack(L.slack + wave * kWaveRows + row, s, l, slack_set);
         clear_hist(L.hist + wave * kWaveRows * kHistStride, lane);
         wave_fence();
-        set_bins(v, kSearchStep * __builtin_amdgcn_rcpf(s), hist, -1);
+        set_bins<true>(v, kSearchStep * __builtin_amdgcn_rcpf(s), hist, -1);
         wave_fence();
         convert_hist(L.hist + wave * kWaveRows * kHistStride, lane);
         uint64_t left = patterns_left<kTiles, search_over(kTiles)>(L, C, tiles, wave, lane);
@@ -400,7 +400,7 @@ __global__ __launch_bounds__(kFewThreads) void encode_few_kernel(Job<Io> j0, Job
 
 // ---- bulk encoder with the min/max selector --------------------------------------------------------------------------------
 constexpr int kImageStride = 20;  // words per group of the payload being assembled
-constexpr size_t minmax_lds_bytes(int S) { return (minmax_table_words(S) + S + kMinmaxBatch * kImageStride + 3) * 4; }
+constexpr size_t minmax_lds_bytes(int S, bool fine) { return (minmax_table_words(S, fine) + S + kMinmaxBatch * kImageStride + 3) * 4; }
 
 // The indices of the row's values under the pattern whose centroids are at `pair` and whose row of the fine table (ecco_search.h)
 // is at `fine`, eight nibbles per lane, first value on top.  per: kFinePer / scale.  Returns the marks of the lane's bins: with
@@ -436,7 +436,7 @@ __device__ __forceinline__ uint32_t fine_indices(uint32_t fine, uint32_t pair, h
     return marks;
 }
 
-template <bool kLong, class Io>
+template <bool kFine, bool kLong, class Io>
 __global__ __launch_bounds__(kMinmaxThreads) void encode_minmax_kernel(Job<Io> j0, Job<Io> j1) {
     extern __shared__ __align__(16) uint32_t smem[];
     const Job<Io>& job = blockIdx.y ? j1 : j0;
@@ -444,12 +444,12 @@ __global__ __launch_bounds__(kMinmaxThreads) void encode_minmax_kernel(Job<Io> j
     const Io io = job.io;
     const int lane = threadIdx.x & 63, l = lane & 15, row = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    uint32_t* ends = smem + minmax_table_words(S);
+    uint32_t* ends = smem + minmax_table_words(S, kFine);
     uint32_t* image = ends + S + (wave * kWaveRows + row) * kImageStride;
     const size_t batches = (io.groups() + kMinmaxBatch - 1) / kMinmaxBatch;
     RowValues v, next;
     load_values<kMinmaxBatch>(v, io.values(), io.groups(), blockIdx.x, wave * kWaveRows + row, l);
-    const EncTables T = stage_enc_tables<kMinmaxThreads, true>(smem, job.dev, S);
+    const EncTables T = stage_enc_tables<kMinmaxThreads, kFine>(smem, job.dev, S);
     if ((int)threadIdx.x < S) {
         const uint32_t* pair = job.dev + DevLayout{S}.pair() + threadIdx.x * 16;
         ends[threadIdx.x] = __builtin_amdgcn_perm(pair[kK - 1], pair[0], 0x05040100u);  // first and last centroid
@@ -463,10 +463,16 @@ __global__ __launch_bounds__(kMinmaxThreads) void encode_minmax_kernel(Job<Io> j
         const float s = half_bits_f(smax);
         const half2_t s2 = splat_half(smax);
         const uint32_t pattern = select_minmax(ends, 1, S, s2, ends2, l);
-        const uint32_t per = __builtin_bit_cast(unsigned short, (_Float16)(kFinePer * __builtin_amdgcn_rcpf(s)));
-        uint32_t idx;
-        const uint32_t marks = fine_indices(T.fine + (pattern + (pattern & ~3u)) * kFineBins, T.pair + pattern * 64u, s2, splat_half(per), v, idx);
-        const uint64_t lanes = __builtin_amdgcn_ballot_w64(((marks & kFineCrowded) != 0u || !(s >= kSearchLeastScale)) && smax != 0u);
+        uint32_t idx, marks;
+        if (kFine) {
+            const uint32_t per = __builtin_bit_cast(unsigned short, (_Float16)(kFinePer * __builtin_amdgcn_rcpf(s)));
+            marks = fine_indices(T.fine + (pattern + (pattern & ~3u)) * kFineBins, T.pair + pattern * 64u, s2, splat_half(per), v, idx);
+        } else {
+            float none;
+            set_bins<false>(v, kSearchStep * __builtin_amdgcn_rcpf(s), nullptr, -1);
+            marks = rate_pattern<false, true>(T.near + pattern * kSearchBins, T.pair + pattern * 64u, s2, v, -1, none, idx);
+        }
+        const uint64_t lanes = __builtin_amdgcn_ballot_w64(((marks & (kFine ? kFineCrowded : kNearWide)) != 0u || !(s >= kSearchLeastScale)) && smax != 0u);
         if (lanes != 0ull) {  // rows with crowded bins or a scale too small for the tables
             const uint32_t id = scan_indices(T.pair + pattern * 64u, s2, v, -1);
             idx = row_any(lanes, row) ? id : idx;
@@ -517,9 +523,12 @@ int launch_encode(bool minmax, const ecco_model* m0, const Io& io0, const ecco_m
         if (minmax) rc = lng ? few(encode_few_kernel<true, true, Io>) : few(encode_few_kernel<true, false, Io>);
         else rc = lng ? few(encode_few_kernel<false, true, Io>) : few(encode_few_kernel<false, false, Io>);
     } else if (minmax) {
-        const size_t lds = minmax_lds_bytes(S);
+        const bool fine = m0->fine_bins && m1->fine_bins;
+        const size_t lds = minmax_lds_bytes(S, fine);
         const int per_cu = (int)std::min<size_t>(8, 160 * 1024 / lds);  // at 64 patterns six fit; at 16 eight took 38.8 us for 262144 groups, six 39.8 us
-        rc = lng ? run(encode_minmax_kernel<true, Io>, lds, kMinmaxBatch, kMinmaxThreads, per_cu) : run(encode_minmax_kernel<false, Io>, lds, kMinmaxBatch, kMinmaxThreads, per_cu);
+        const auto minmax_run = [&](auto kernel) { return run(kernel, lds, kMinmaxBatch, kMinmaxThreads, per_cu); };
+        if (fine) rc = lng ? minmax_run(encode_minmax_kernel<true, true, Io>) : minmax_run(encode_minmax_kernel<true, false, Io>);
+        else rc = lng ? minmax_run(encode_minmax_kernel<false, true, Io>) : minmax_run(encode_minmax_kernel<false, false, Io>);
     } else {
         const size_t lds = search_lds_bytes(S);
         switch (search_tiles(S)) {

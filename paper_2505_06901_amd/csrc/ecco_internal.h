@@ -59,6 +59,7 @@ struct ecco_model {
     uint16_t codes[ecco::kMaxS * ecco::kK] = {};  // canonical codes, derived from lens
     int device = -1;
     int max_len = 0;               // longest code length in the model
+    bool fine_bins = true;         // which bins the min/max selector uses (fine_bins_serve); set with dev
     uint32_t* dev = nullptr;       // DevLayout{S}.total_bytes() on `device`
 };
 

@@ -173,6 +173,7 @@ int ecco_model_to_device(ecco_model* m, int device) {
         (void)hipFree(d);
         return ECCO_EHIP;
     }
+    m->fine_bins = fine_bins_serve(img.data() + D.near(), img.data() + D.fine(), m->S);
     m->dev = static_cast<uint32_t*>(d);
     m->device = device;
     return ECCO_OK;

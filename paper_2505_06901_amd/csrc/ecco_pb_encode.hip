@@ -111,7 +111,7 @@ void pb_encode_kernel(const uint32_t* __restrict__ dev, int S, float inv_tscale,
         set_slack(L.slack + wave * kWaveRows + row, s, l, slack_set);
         clear_hist(L.hist + wave * kWaveRows * kHistStride, lane);
         wave_fence();
-        set_bins(v, kSearchStep * __builtin_amdgcn_rcpf(s), hist, skip);
+        set_bins<true>(v, kSearchStep * __builtin_amdgcn_rcpf(s), hist, skip);
         wave_fence();
         convert_hist(L.hist + wave * kWaveRows * kHistStride, lane);
         uint64_t left = patterns_left<kTiles, true>(L, C, tiles, wave, lane0);

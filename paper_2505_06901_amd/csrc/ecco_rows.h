@@ -96,7 +96,8 @@ __device__ __forceinline__ uint32_t lane_absmax(const RowValues& v) {
 }
 // Bins of the lane's values for axis units `per` = step / scale per unit of x.  Adding 2^23 + 32768 leaves
 // rint(x * per) + 32768 in the low 16 bits (q).  hist: this group's row of the histogram; a word counts the bin's values in its
-// upper half and sums their places q & 255 in its lower half.
+// upper half and sums their places q & 255 in its lower half (kHist).
+template <bool kHist>
 __device__ __forceinline__ void set_bins(RowValues& v, float per, uint32_t* hist, int skip) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -104,10 +105,12 @@ __device__ __forceinline__ void set_bins(RowValues& v, float per, uint32_t* hist
 #pragma unroll
         for (int i = 0; i < 4; ++i) q[i] = __builtin_bit_cast(uint32_t, fmaf((float)value(v, 4 * h + i), per, 8421376.0f));
         v.bins[h] = __builtin_amdgcn_perm(q[1], q[0], 0x0C0C0501u) | __builtin_amdgcn_perm(q[3], q[2], 0x05010C0Cu);  // byte 1 of each
+        if (kHist) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t one = 65536u | (q[i] & 255u);
-            atomicAdd(&hist[(q[i] >> 8) & 255u], 4 * h + i == skip ? 0u : one);
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t one = 65536u | (q[i] & 255u);
+                atomicAdd(&hist[(q[i] >> 8) & 255u], 4 * h + i == skip ? 0u : one);
+            }
         }
     }
 }

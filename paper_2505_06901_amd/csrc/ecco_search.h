@@ -206,4 +206,26 @@ inline void build_fine_table(const uint16_t* cent, int stride, int n_cent, int S
     }
 }
 
+// Whether the min/max selector uses these bins for a model or the uniform ones.  These are the wider ones from u = 0.5 on: patterns that
+// crowd centroids there (groups with a common offset, or of two magnitudes) have bins with more than two candidates, and a
+// wavefront with a value in one compares all of its values with all centroids.  131072 groups, models fitted to them, 16 patterns:
+// offset 1 +- 0.1 42.5 us by these bins, 18.1 us by the uniform ones; two magnitudes, 0.5 +- 0.02 42.2 and 17.8 us.  Where the
+// uniform bins have patterns with more than three candidates as well, nothing is gained: two magnitudes, 0.5 +- 0.005 (16 patterns
+// crowded here, 13 there) 42.2 and 47.6 us.  Hence the line: a pattern that both bins crowd costs a quarter more by the uniform ones
+// (30 us over the 18 us of a model that neither crowds, 24 us by these), and one crowded pattern in sixteen (a wavefront in
+// five) costs these what the uniform ones pay for third candidates (2 us for values, 8 us for keys).
+inline bool fine_bins_serve(const uint32_t* near, const uint32_t* fine, int S) {
+    const uint8_t *n = reinterpret_cast<const uint8_t*>(near), *f = reinterpret_cast<const uint8_t*>(fine);
+    int crowded = 0, wide = 0;
+    for (int p = 0; p < S; ++p) {
+        const uint8_t* row = f + (size_t)(p >> 2) * (4 * 2 * kFineBins) + (p & 3) * kFineBins;
+        bool c = false, w = false;
+        for (int bin = 0; bin < kFineBins; ++bin) c = c || ((row[bin] | row[4 * kFineBins + bin]) & kFineCrowded) != 0;
+        for (int bin = 0; bin < kSearchBins; ++bin) w = w || (n[p * kSearchBins + bin] & kNearWide) != 0;
+        crowded += c;
+        wide += w;
+    }
+    return 16 * crowded <= S + 20 * wide;
+}
+
 }  // namespace ecco
