@@ -791,8 +791,15 @@ __global__ __launch_bounds__(kLongV ? 512 : kAttnThreads) void kv_attend_kernel(
         {
             const TableItems items = load_table_items(dev_k, Sk);
             pre = load_unit(k_blocks, k_meta, bh, T_max, unit0 + min(u, units - 1), lane);
+            build_tables<kLongK>(smem, dev_k, Sk, items);
+        }
+        const Tables TK = table_pointers(smem, Sk);
+        __syncthreads();
+        float my_max = -INFINITY;
+        {
             // reloaded per span (from cache) rather than kept alive across the V phase; the pointer that comes back from
-            // the empty asm statement is given its address space again, or its loads would be flat loads
+            // the empty asm statement is given its address space again, or its loads would be flat loads.  (Requested ahead of the
+            // build, behind the payload: 4 sequences and heads of 64 tokens 13.71 -> 13.94 us, 256 of 4096 no difference.)
             const uint4* qgen = reinterpret_cast<const uint4*>(q + (size_t)bh * kGroup + half * kHalf);
             asm volatile("" : "+v"(qgen));
             const global_u4* qsrc = (const global_u4*)qgen;
@@ -801,12 +808,6 @@ __global__ __launch_bounds__(kLongV ? 512 : kAttnThreads) void kv_attend_kernel(
                 const u32x4 v = qsrc[j];
                 qx[4 * j] = v.x; qx[4 * j + 1] = v.y; qx[4 * j + 2] = v.z; qx[4 * j + 3] = v.w;
             }
-            build_tables<kLongK>(smem, dev_k, Sk, items);
-        }
-        const Tables TK = table_pointers(smem, Sk);
-        __syncthreads();
-        float my_max = -INFINITY;
-        {
             for (; u < units; u += waves) {
                 store_unit(wbuf, pre, lane);
                 const uint32_t mw = pre.meta;
@@ -838,8 +839,8 @@ __global__ __launch_bounds__(kLongV ? 512 : kAttnThreads) void kv_attend_kernel(
                 my_max = fmaxf(my_max, sc);
             }
         }
-        // the V tables' items and first unit, requested here: they arrive during the softmax (512 sequences and heads of up to 100 tokens,
-        // with the append: 31.5 -> 31.1 us; 256 of 4096: no difference)
+        // the V tables' items and first unit, requested here: they arrive during the softmax (64 patterns, 512 sequences and heads of 300
+        // tokens: 31.0 -> 30.7 us; 256 of 4096: 84.2 -> 83.8 us; 4 of 64: 13.74 -> 13.71 us)
         const TableItems v_items = load_table_items(dev_v, Sv);
         u = wave;
         pre = load_unit(v_blocks, v_meta, bh, T_max, unit0 + min(u, units - 1), lane);
