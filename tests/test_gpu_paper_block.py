@@ -162,6 +162,37 @@ def _codes_end(om, block):
     return 10 + int(om.kp_lens[p]) + sum(int(om.lens[p, h, k]) for k in idx), n_out
 
 
+def test_padded_entries_of_every_count(pb, dev):
+    """Blocks with 0 to 15 padded entries side by side, in half of them all entries at one position (the last one counts): the
+    decoder bit-exact, the product row by row."""
+    om = _model(pb, S=6, texp=-9, seed=21, skew=2.6)
+    m = _both(pb, om)
+    rng = np.random.default_rng(41)
+    x = _groups(42, 4096, scale=2.0 ** -9 * 30)
+    x[rng.random(x.shape) < rng.uniform(0, 1, (4096, 1))] = 0
+    blocks = pb.encode(om, x.view(np.uint16))
+    n_out = pb.decode(om, blocks)[2]
+    counts = np.unique(n_out)
+    assert counts[0] == 0 and counts[-1] >= 13 and counts.size >= 12, counts
+    blocks = np.concatenate([blocks[n_out == c][:13] for c in counts])
+    blocks = blocks[rng.permutation(len(blocks))]
+    same = blocks.copy()
+    for b in same:
+        end, n = _codes_end(om, b)
+        bits = stream_bits(b)
+        for j in range(n):
+            bits[end + 15 * j:end + 15 * j + 7] = bits[end:end + 7]
+        b[:] = np.packbits(bits).reshape(16, 4)[:, ::-1].reshape(-1)
+    blocks = np.concatenate([blocks, same])
+    want, _, n_out = pb.decode(om, blocks)
+    bd = torch.from_numpy(blocks).to(dev)
+    assert np.array_equal(E.ecco_pb_decode(m, bd).cpu().numpy().view(np.uint16), want)
+    xa = W.activation(1, 128, 210).reshape(-1)
+    y = E.ecco_pb_decode_gemv(m, bd, len(blocks), 128, _t16(xa, dev)).cpu().numpy()
+    bound = np.abs(want.view(np.float16).astype(np.float64)) @ np.abs(xa.astype(np.float64))
+    assert (np.abs(y - pb.gemv(om, blocks, len(blocks), 128, xa.view(np.uint16))) <= 1e-3 * bound + 1e-30).all()
+
+
 def test_gemv_infinite_activation(pb, dev):
     """One infinite activation among zeros, at every position in turn, over blocks with one padded entry: the sum is that
     column's decoded value times infinity.  The entry's own position is left out (there the value that it replaces and the entry
