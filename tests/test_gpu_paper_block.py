@@ -217,11 +217,21 @@ def test_gemv_infinite_activation(pb, dev):
         assert np.array_equal(y[at], dec[at, j] * np.inf), (j, np.nonzero(at & ~(y == dec[:, j] * np.inf))[0][:8])
 
 
-@pytest.mark.parametrize("rows,gpr,S", [(2821, 256, 64), (257, 65, 64), (512, 32, 16), (1025, 257, 16), (255, 1, 64), (769, 5, 1)])
-def test_gemv_passes_and_chunks(dev, rows, gpr, S):
-    """Bands of several chunks of rows (2821 x 256 groups: the sums of a band exceed the LDS), passes that end inside a
-    wavefront's 64 blocks, one wavefront up to all of them, blocks with many padded entries: every row against the
-    decoder's values (bit-exact against the oracle above) in double precision."""
+def _chunks(rows, gpr, S):
+    """Into how many chunks of rows the product cuts a workgroup's band: the sums of a chunk lie in LDS beside the tables (byte
+    tables, pattern ids, two sets of centroids, 8-bit floats) and sixteen wavefronts' payload and info words."""
+    band = -(-rows // E.ecco_device_info(0)[0])
+    room = 160 * 1024 // 4 - (S * 4 * 64 + 128 + 2 * S * 8 + 128) - 16 * (2 * 64 + 64 * 17 + 4)
+    return -(-band // min(band, room // gpr))
+
+
+@pytest.mark.parametrize("rows,gpr,S,chunks", [(2821, 256, 64, 1), (257, 65, 64, 1), (512, 32, 16, 1), (1025, 257, 16, 1), (255, 1, 64, 1), (769, 5, 1, 1),
+                                               (2305, 512, 64, 2), (4097, 224, 64, 2), (3841, 512, 64, 3)])
+def test_gemv_passes_and_chunks(dev, rows, gpr, S, chunks):
+    """Bands of one to three chunks of rows (the sums of all rows of a band exceed the LDS; the last chunk shorter than the others, the last
+    band shorter still), passes that end inside a wavefront's 64 blocks, one wavefront up to all of them, blocks with many padded
+    entries: every row against the decoder's values (bit-exact against the oracle above) in double precision."""
+    assert _chunks(rows, gpr, S) == chunks
     w0 = W.weight_matrix(256, 128, 0.02, 1e-3, 10.0, 1)
     m = E.ecco_pb_model_to_device(E.ecco_pb_fit(w0, S, 1), 0)
     gen = torch.Generator(device=dev).manual_seed(rows)

@@ -570,6 +570,9 @@ def test_kv_attend_gqa_matches_oracle(dev, oracle, grp, n_splits):
     ([4096 + 31, 40, 40, 40, 40, 40], 4127, 3, 2),        # 65 units: twelve; one sequence over a hundred units longer than the rest
     ([3, 0, 65, 96] * 16 + [96, 17], 96, 1, 3),           # 1 unit: eight; many sequences
     ([0, 0, 0], 64, 4, 5),                                # nothing to attend to
+    ([3000, 0, 700, 31], 3000, 4, 17),                    # more than sixteen ranges: the merge takes the maxima first, then sixteen at a time; many ranges empty
+    ([3000, 2999], 3000, 9, 40),
+    ([8192, 8191, 100], 8192, 2, 256),
 ])
 def test_gqa_unequal_lengths(dev, oracle, lengths, T, grp, n_splits):
     """Every sequence is cut into n_splits equal ranges of its own length: every token counts once.  Each call twice, same bits."""
