@@ -9,8 +9,8 @@
 // are few (one block in ten has any) and are taken up a block per lane, not by the rows.
 // What bounds it: step 1 is a serial chain of 128 table reads per lane, 97 cycles each when nothing else is in the way (56 of the
 // read, 8.5 for each of the three dependent instructions, the window), 5.2 us; step 2 the vector instructions.  Product over
-// 4096 x 4096, one pass per wavefront: 4.6 us launch, tables and payload, 6 us walk, 2 us padded entries, 3 us values; 18.2 us
-// with the entries taken up by the rows and the index image beside the payload.
+// 4096 x 4096, one pass per wavefront, by events around replayed graphs: 4.6 us launch, tables and payload, 6 us walk, 2 us padded
+// entries, 3 us values, 15.6 us together; 18.1 us with the entries taken up by the rows and the index image beside the payload.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -317,12 +317,12 @@ __global__ __launch_bounds__(kDecodeThreads) void pb_decode_kernel(const uint32_
 // of whole rows; per-block sums go to LDS, and each row's blocks are added in a fixed tree.  A padded entry takes
 // centroid * x at its position back and adds its own value (times x) instead; this is done right after the walk, a block per lane,
 // when the indices still lie in registers.  They then take the payload's place in LDS, so that sixteen wavefronts fit beside 64
-// patterns' tables (eight with a place of their own): 4096 x 28672 takes 58.5 us, 122 us with eight.
+// patterns' tables (eight with a place of their own): 4096 x 28672 takes 57.5 us, 121 us with eight.
 constexpr int kGemvWaves = kGemvThreads / 64;
 constexpr int kGemvWaveWords = kInfoWords + kPayWords;  // private LDS of a wavefront
-constexpr int kMaxPartFloats = 8192;   // per-block sums of a chunk: rows x column groups, at most
-inline int gemv_part_floats(int S) { return std::min<int>(kMaxPartFloats, (int)(160 * 1024 / 4 - table_words(S) - kGemvWaves * kGemvWaveWords)); }
-static_assert(160 * 1024 / 4 - table_words(kMaxS) - kGemvWaves * kGemvWaveWords >= 65536 / kGroup, "the sums of a row fit");
+// per-block sums of a chunk (rows x column groups) that fit the LDS: one workgroup takes a compute unit's wavefronts, nothing else needs it
+constexpr int gemv_part_floats(int S) { return (int)(160 * 1024 / 4 - table_words(S) - kGemvWaves * kGemvWaveWords); }
+static_assert(gemv_part_floats(kMaxS) >= 65536 / kGroup, "the sums of a row fit");
 
 template <int kCtrl>
 __device__ __forceinline__ float dpp_add(float t) {
@@ -520,8 +520,8 @@ int ecco_pb_decode_gemv(const ecco_pb_model* m, const void* blocks, int rows, in
     const int band = (rows + cus - 1) / cus, grid = (rows + band - 1) / band;
     const int chunk = std::min(band, gemv_part_floats(m->S) / gpr);
     // as few wavefronts as hold the blocks 64 at a time, but four (one per SIMD): a chain takes as long for one lane as for 64, and
-    // longer the more wavefronts read tables beside it (512 blocks: 18.5 us on eight, 19.9 us on sixteen; 40 blocks: 11.5 us on four, 12.5 us
-    // on two, 13.1 us on ten)
+    // longer the more wavefronts read tables beside it (512 blocks per workgroup: 15.3 us on eight, 16.9 us on sixteen; 40 blocks: 10.4 us on
+    // four, 11.1 us on two, 12.5 us on ten; by events around replayed graphs)
     const size_t waves = std::min<size_t>(kGemvWaves, std::max<size_t>(4, ((size_t)chunk * gpr + kUnit - 1) / kUnit));
     const size_t lds = (table_words(m->S) + (size_t)kGemvWaves * kGemvWaveWords + (size_t)chunk * gpr) * 4;
     const int rc = ecco::allow_lds(pb_gemv_kernel, m->device, lds);
