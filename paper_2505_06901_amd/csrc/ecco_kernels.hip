@@ -1149,8 +1149,9 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
             if (at < 16) wave_max[wave * kGqaMaxGroup + n] = mx;  // columns past the heads hold something, which nobody reads
         }
         // the V tables' items and the first unit, requested here: they arrive during the softmax.  Together with both models' items and the query
-        // requested ahead of the builds, a step (append, attention, merge) over 8 sequences of 2048..4096 tokens, 8 heads in groups of 4, 16
-        // patterns, takes 35.6 instead of 36.9 us, over 4 sequences of 300 tokens 18.4 instead of 19.3 us
+        // requested ahead of the builds, attention and merge over 8 sequences of 4096 tokens, 8 heads in groups of 4, 16 patterns, take 32.8 instead
+        // of 33.6 us, over 4 sequences of 300 tokens 15.0 instead of 15.7 us; under 64 patterns (tables in turn) 32.8 instead of 32.9 us and 16.1
+        // instead of 16.5 us, and over one sequence of 64 tokens, where there is no softmax to speak of, 12.7 where it was 12.5 us
         u = wave;
         const auto* av = late();
         const uint4* v_blocks = av->v_blocks;
