@@ -52,6 +52,8 @@ struct Tables {
     const __half* cent;       // [S][16]
 };
 __host__ __device__ constexpr size_t table_words(int S) { return (size_t)S * (kPeekEntries + kK + kK + kK / 2); }  // LDS words of a model's decode tables
+// LDS words of the decode tables: the long-code lists and the centroids are only copied for models that need them
+__host__ __device__ constexpr int decode_table_words(int S, bool lng) { return S * (kPeekEntries + kK + (lng ? kK + kK / 2 : 0)); }
 
 // copies `words` (a multiple of 4; both sides 16-byte aligned) from global memory to LDS with all
 // threads of the workgroup, four 16-byte loads in flight per thread
@@ -128,23 +130,36 @@ __device__ __forceinline__ Tables table_pointers(uint32_t* base, int S) {
 // beyond the items repeating the last one -- the build does not wait for the payload.  The lists of the long
 // codes and the centroids are copied only for a model that needs them (behind the payload, then).  The caller
 // synchronises afterwards.
+// A model's size, likewise: what the staging of a model with long codes derives from it (masks, addresses) would otherwise be formed
+// once for all spans and take scalar registers throughout
+__device__ __forceinline__ int fresh_size(int S) {
+    asm volatile("" : "+s"(S));
+    return S;
+}
 struct TableItems {
     TableItem item[2];
 };
+// The thread's index, taken afresh: in a kernel that stages tables in every span, what is derived from it is then formed there and
+// does not take registers through the decode loops.
+__device__ __forceinline__ int fresh_thread() {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    return tid;
+}
 __device__ __forceinline__ TableItems load_table_items(const uint32_t* __restrict__ dev, int S) {
-    const int n = S * kK;
+    const int n = S * kK, tid = fresh_thread();
     TableItems t;
-    t.item[0] = load_table_item(dev, S, min((int)threadIdx.x, n - 1));
-    t.item[1] = load_table_item(dev, S, min((int)(threadIdx.x + blockDim.x), n - 1));
+    t.item[0] = load_table_item(dev, S, min(tid, n - 1));
+    t.item[1] = load_table_item(dev, S, min(tid + (int)blockDim.x, n - 1));
     __builtin_amdgcn_sched_barrier(0);
     return t;
 }
 template <bool kLong>
 __device__ __forceinline__ void build_tables(uint32_t* base, const uint32_t* __restrict__ dev, int S, const TableItems& t) {
     __builtin_amdgcn_sched_barrier(0);
-    const int n = S * kK;
-    build_table_item(base, S, min((int)threadIdx.x, n - 1), t.item[0]);
-    build_table_item(base, S, min((int)(threadIdx.x + blockDim.x), n - 1), t.item[1]);
+    const int n = S * kK, tid = fresh_thread();
+    build_table_item(base, S, min(tid, n - 1), t.item[0]);
+    build_table_item(base, S, min(tid + (int)blockDim.x, n - 1), t.item[1]);
     if (kLong) {
         const DevLayout D{S};
         stage_vec(base + S * (kPeekEntries + kK), dev + D.longtab(), S * kK);
@@ -718,88 +733,105 @@ __global__ __launch_bounds__(kGemvThreads) void gemm_kernel(const uint32_t* __re
 }
 
 // ---- single-query attention over compressed K / V ----------------------------------------------------
-// One workgroup of 12 wavefronts per (sequence, head): three per SIMD, which leaves each lane the
-// registers for 64 private accumulators next to the decoder state (8 wavefronts when the V model has
-// codes longer than the table peek: that decoder needs more registers still).  The cache of a head is a band of T blocks,
-// so the kernel reuses the streaming scheme of the batch-1 GEMV: a unit is 32 consecutive tokens
-// (2 KB of payload), lane l of a wavefront decodes chain l / 32 of token l % 32, units are
-// prefetched into registers and decoded out of the wavefront's private LDS buffer.  The sequence is
-// walked in spans of kSpan tokens.  Per span: with the K tables in LDS the scores q.K_t / sqrt(128)
-// are formed (the lane keeps the 64 query elements of its chain in registers) and kept in LDS; the
-// span's maximum updates the running softmax (maximum, denominator, rescale of what has been
-// accumulated); then the V tables replace the K tables and every lane adds p_t * V_t of its chain
-// into 64 private FP32 accumulators (a static register per value position, nothing shared).  At the
-// end the accumulators are added over the lanes of a wavefront on the VALU and over the wavefronts
-// through LDS.  K and V enter as fp16(centroid * scale), formed two at a time by a packed FP16
-// multiply, which rounds exactly like the FP32-multiply-then-round rule.  Only one model's tables
-// are resident at a time, which keeps S = 64 for both K and V within 160 KB of LDS.
-constexpr int kAttnThreads = 768;      // workgroup size; 512 for a V model with long codes
-constexpr int kAttnWaves = kAttnThreads / 64;
-constexpr int kSpan = 8192;
-static_assert(2 * 512 >= ECCO_MAX_S * kK, "load_table_items: two table items per thread cover every model (the smallest attention workgroup has 512 threads)");
-inline size_t attn_lds_bytes(int Sk, int Sv) {
-    return (table_words(std::max(Sk, Sv)) + (size_t)kAttnWaves * kUnitWords + kSpan + kAttnWaves * 2 * kGroup + 64) * 4;
+// One workgroup per (sequence, head).  The cache of a head is a band of T blocks, so the kernel reuses the streaming scheme of
+// the batch-1 GEMV: a unit is 32 consecutive tokens (2 KB of payload), lane l of a wavefront decodes chain l / 32 of token
+// l % 32, units are prefetched into registers and decoded out of the wavefront's private LDS buffer.  The sequence is walked in
+// spans whose scores fit LDS.  Per span a wavefront takes its units twice.  With the K tables it forms the scores q.K_t / sqrt(128)
+// (the lane keeps the 64 query elements of its chain in registers), which wait in LDS; with the V tables every lane adds p_t * V_t of
+// its chain into 64 private FP32 accumulators (a static register per value position, nothing shared).  The softmax is the wavefront's
+// own: p_t is relative to the largest score of its units, and maxima, denominators and outputs of the wavefronts meet at the end of
+// the span, once.  (A maximum and a denominator common to the workgroup took four more barriers and a loop over the scores
+// between the passes.)  Where both models' tables fit they are built together, and a wavefront passes from K to V on its own;
+// otherwise the V tables replace those of K in between, behind a barrier.  The decoding is bound by the table reads; what is fixed per
+// span (builds, sums, waits at barriers) is what this form cuts.  Append and attention, 8 x 32 sequences and heads, 64 patterns:
+// 4096 tokens 95.4 -> 91.9 us, 512 tokens 26.8 -> 24.7 us; 16 patterns: 4096 tokens 89.5 -> 84.7 us, 512 tokens 22.5 -> 20.5 us.  K and V enter as fp16(centroid * scale), formed two at a time by a packed FP16 multiply, which rounds exactly like the
+// FP32-multiply-then-round rule.
+constexpr int kSpanMax = 8192, kSpanLeast = 2048;
+
+// Two workgroups of eight wavefronts share a compute unit where there are workgroups for it and both models' tables fit half its
+// LDS: each decodes while the other builds or sums (16 patterns, 16 x 32 sequences and heads of 1024 tokens 59.2 -> 48.1 us).  Otherwise
+// one of as few wavefronts as take the fewest rounds over the units of a span: a table read costs less the more wavefronts
+// wait for theirs (one workgroup, 8192 tokens: 166.7 us with sixteen, 177.9 us with twelve), barriers and sums the more the more
+// meet (64 patterns, ten units: 21.5 us with twelve, 22.2 us with sixteen; two units: 15.8 us with eight, 16.5 us with twelve).  The
+// decoders of long codes need the registers of twelve.
+struct AttnPlan {
+    int waves;
+    int table_words;  // LDS words of the tables: both models', or the larger one's
+    int both;         // the V tables have their own place, behind those of K
+    int span;         // tokens per span, a multiple of 32
+    size_t lds;
+};
+inline AttnPlan attn_plan(int Sk, bool lk, int Sv, bool lv, size_t wgs, int T_max, int cus) {
+    const int wk = decode_table_words(Sk, lk), wv = decode_table_words(Sv, lv), units = (T_max + kUnitBlocks - 1) / kUnitBlocks;
+    const auto plan = [&](int waves, int lds_words) {
+        AttnPlan p;
+        const int fixed = waves * (kUnitWords + 2);
+        p.waves = waves;
+        p.both = wk + wv + fixed + std::min(kSpanLeast, units * kUnitBlocks) <= lds_words;
+        p.table_words = p.both ? wk + wv : std::max(wk, wv);
+        p.span = std::min({kSpanMax, units * kUnitBlocks, (lds_words - p.table_words - fixed) / kUnitBlocks * kUnitBlocks});
+        p.lds = (size_t)(p.table_words + fixed + p.span) * 4;
+        return p;
+    };
+    constexpr int kLdsWords = 160 * 1024 / 4;
+    if (lk || lv) return plan(12, kLdsWords);
+    const AttnPlan two = plan(8, kLdsWords / 2);
+    if (wgs > (size_t)cus && two.both) return two;
+    const auto rounds = [&](int waves) { return (units + waves - 1) / waves; };
+    const int waves = rounds(8) == rounds(16) ? 8 : rounds(12) == rounds(16) ? 12 : 16;
+    return plan(waves, kLdsWords);
 }
 
-__device__ inline float wg_reduce(float v, float* scratch, bool is_max, int waves) {
-    for (int m = 1; m < 64; m <<= 1) {
-        float o = __shfl_xor(v, m);
-        v = is_max ? fmaxf(v, o) : v + o;
-    }
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = v;
-    __syncthreads();
-    float r = scratch[0];
-    for (int w = 1; w < waves; ++w) r = is_max ? fmaxf(r, scratch[w]) : r + scratch[w];
-    return r;
-}
-
-template <bool kLongK, bool kLongV>
-__global__ __launch_bounds__(kLongV ? 512 : kAttnThreads) void kv_attend_kernel(const uint32_t* __restrict__ dev_k, int Sk,
-                                                                 const uint32_t* __restrict__ dev_v, int Sv,
-                                                                 const uint16_t* __restrict__ q,
-                                                                 const uint4* __restrict__ k_blocks, const uint32_t* __restrict__ k_meta,
-                                                                 const uint4* __restrict__ v_blocks, const uint32_t* __restrict__ v_meta,
-                                                                 const int32_t* __restrict__ seq_len, int H, int T_max,
-                                                                 float* __restrict__ out) {
+template <bool kLongK, bool kLongV, int kWaves>
+__global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(kWaves == 12 ? 3 : 4))) void kv_attend_kernel(
+    const uint32_t* __restrict__ dev_k, int Sk, const uint32_t* __restrict__ dev_v, int Sv, const uint16_t* __restrict__ q,
+    const uint4* __restrict__ k_blocks, const uint32_t* __restrict__ k_meta, const uint4* __restrict__ v_blocks, const uint32_t* __restrict__ v_meta,
+    const int32_t* __restrict__ seq_len, int H, int T_max, int table_words, int both, int span_max, float* __restrict__ out) {
     extern __shared__ __align__(16) uint32_t smem[];
-    const int Smax = max(Sk, Sv);
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int waves = kLongV ? 8 : kAttnWaves, threads = waves * 64;
-    uint32_t* wbuf = smem + table_words(Smax) + wave * kUnitWords;
-    float* scores = reinterpret_cast<float*>(smem + table_words(Smax) + kAttnWaves * kUnitWords);
-    float* wred = scores + kSpan;               // [wavefront][row of 16 lanes][64] at the end
-    float* scratch = wred + kAttnWaves * 2 * kGroup;
-    if (lane < kUnitBlocks) wbuf[lane * kStride + kBlockWords] = 0u;
-    if (lane == 0) wbuf[kUnitBlocks * kStride] = 0u;
+    uint32_t* wbuf = smem + table_words + wave * kUnitWords;
+    float* state = reinterpret_cast<float*>(smem + table_words + kWaves * kUnitWords);  // per wavefront: its maximum, and its denominator
+    float* scores = state + 2 * kWaves;
+    uint32_t* v_tables = smem + (both ? decode_table_words(Sk, kLongK) : 0);
 
     const int bh = blockIdx.x;
     const int T = min(seq_len[bh / H], T_max);
-    const int blk = lane & (kUnitBlocks - 1), half = lane >> 5;
     float my_out = 0.0f;  // threads 0..127: output element `tid`, not yet divided by the denominator
     float run_max = -INFINITY, run_den = 0.0f;
     const float inv_sqrt_d = 0.08838834764831845f;  // 1 / sqrt(128)
-    for (int s0 = 0; s0 < T; s0 += kSpan) {
-        const int span = min(kSpan, T - s0);
+    for (int s0 = 0; s0 < T; s0 += span_max) {
+        const int span = min(span_max, T - s0);
         const int units = (span + kUnitBlocks - 1) / kUnitBlocks, unit0 = s0 / kUnitBlocks;
         // ---- scores of the span
         __syncthreads();
-        int u = wave;
         UnitLoad pre;
-        uint32_t qx[kHalf / 2];  // the query elements of this lane's chain, FP16 pairs
+        float wave_max;  // uniform
         {
-            const TableItems items = load_table_items(dev_k, Sk);
-            pre = load_unit(k_blocks, k_meta, bh, T_max, unit0 + min(u, units - 1), lane);
-            build_tables<kLongK>(smem, dev_k, Sk, items);
-        }
-        const Tables TK = table_pointers(smem, Sk);
-        __syncthreads();
-        float my_max = -INFINITY;
-        {
-            // reloaded per span (from cache) rather than kept alive across the V phase; the pointer that comes back from
-            // the empty asm statement is given its address space again, or its loads would be flat loads.  (Requested ahead of the
-            // build, behind the payload: 4 sequences and heads of 64 tokens 13.71 -> 13.94 us, 256 of 4096 no difference.)
+            const int lane = fresh_thread() & 63, blk = lane & (kUnitBlocks - 1), half = lane >> 5;
+            if (lane < kUnitBlocks) wbuf[lane * kStride + kBlockWords] = 0u;  // zero pads of the private buffer (the sums lay over it)
+            if (lane == 0) wbuf[kUnitBlocks * kStride] = 0u;
+            int u = wave;
+            const auto load_k = [&](int at) { pre = load_unit(k_blocks, k_meta, bh, T_max, unit0 + min(at, units - 1), lane); };
+            if (!both) {
+                const TableItems items = load_table_items(dev_k, kLongK ? fresh_size(Sk) : Sk);
+                load_k(u);
+                build_tables<kLongK>(smem, dev_k, kLongK ? fresh_size(Sk) : Sk, items);
+            } else if (s0 == 0) {  // both models' items, then the payload, then both builds
+                const TableItems k_items = load_table_items(dev_k, kLongK ? fresh_size(Sk) : Sk), v_items = load_table_items(dev_v, kLongV ? fresh_size(Sv) : Sv);
+                load_k(u);
+                build_tables<kLongK>(smem, dev_k, kLongK ? fresh_size(Sk) : Sk, k_items);
+                build_tables<kLongV>(v_tables, dev_v, kLongV ? fresh_size(Sv) : Sv, v_items);
+            } else {
+                load_k(u);
+            }
+            const Tables TK = table_pointers(smem, Sk);
+            __syncthreads();
+            // the query elements of this lane's chain, FP16 pairs: reloaded per span (from cache) rather than kept alive across the V
+            // pass; the pointer that comes back from the empty asm statement is given its address space again, or its loads would be
+            // flat loads.  (Requested ahead of the build, behind the payload: 4 sequences and heads of 64 tokens 13.71 -> 13.94 us, 256
+            // of 4096 no difference.)
+            uint32_t qx[kHalf / 2];
             const uint4* qgen = reinterpret_cast<const uint4*>(q + (size_t)bh * kGroup + half * kHalf);
             asm volatile("" : "+v"(qgen));
             const global_u4* qsrc = (const global_u4*)qgen;
@@ -808,10 +840,11 @@ __global__ __launch_bounds__(kLongV ? 512 : kAttnThreads) void kv_attend_kernel(
                 const u32x4 v = qsrc[j];
                 qx[4 * j] = v.x; qx[4 * j + 1] = v.y; qx[4 * j + 2] = v.z; qx[4 * j + 3] = v.w;
             }
-            for (; u < units; u += waves) {
+            float my_max = -INFINITY;
+            for (; u < units; u += kWaves) {
                 store_unit(wbuf, pre, lane);
                 const uint32_t mw = pre.meta;
-                if (u + waves < units) pre = load_unit(k_blocks, k_meta, bh, T_max, unit0 + u + waves, lane);
+                if (u + kWaves < units) load_k(u + kWaves);
                 // the query stays packed: without this the conversions to FP32 are hoisted out of the loop and
                 // occupy 64 registers instead of 32
 #pragma unroll
@@ -835,45 +868,42 @@ __global__ __launch_bounds__(kLongV ? 512 : kAttnThreads) void kv_attend_kernel(
                 acc += __shfl_xor(acc, 32);
                 const int t = u * kUnitBlocks + blk;
                 const float sc = t < span ? acc * inv_sqrt_d : -INFINITY;
-                if (half == 0) scores[t] = sc;
+                if (half == 0) scores[t] = sc;  // for this wavefront alone
                 my_max = fmaxf(my_max, sc);
             }
+            wave_max = wave_all(my_max, [](float a, float b) { return fmaxf(a, b); });
         }
-        // the V tables' items and first unit, requested here: they arrive during the softmax (64 patterns, 512 sequences and heads of 300
-        // tokens: 31.0 -> 30.7 us; 256 of 4096: 84.2 -> 83.8 us; 4 of 64: 13.74 -> 13.71 us)
-        const TableItems v_items = load_table_items(dev_v, Sv);
-        u = wave;
-        pre = load_unit(v_blocks, v_meta, bh, T_max, unit0 + min(u, units - 1), lane);
-        // ---- running softmax
-        const float new_max = fmaxf(run_max, wg_reduce(my_max, scratch, true, waves));
-        float my_den = 0.0f;
-        for (int t = tid; t < units * kUnitBlocks; t += threads) {
-            const float p = __expf(scores[t] - new_max);  // 0 for the tokens past the span
-            scores[t] = p;
-            my_den += p;
-        }
-        const float rescale = (run_max == -INFINITY) ? 0.0f : __expf(run_max - new_max);
-        run_den = run_den * rescale + wg_reduce(my_den, scratch, false, waves);
-        run_max = new_max;
         // ---- weighted sum of V over the span
-        __syncthreads();
-        build_tables<kLongV>(smem, dev_v, Sv, v_items);
-        const Tables TV = table_pointers(smem, Sv);
-        __syncthreads();
         {
+            const int lane = fresh_thread() & 63, blk = lane & (kUnitBlocks - 1), half = lane >> 5;
+            int u = wave;
+            const auto load_v = [&](int at) { pre = load_unit(v_blocks, v_meta, bh, T_max, unit0 + min(at, units - 1), lane); };
+            if (both) {
+                load_v(u);
+            } else {
+                const TableItems items = load_table_items(dev_v, kLongV ? fresh_size(Sv) : Sv);
+                load_v(u);
+                __syncthreads();
+                build_tables<kLongV>(v_tables, dev_v, kLongV ? fresh_size(Sv) : Sv, items);
+                __syncthreads();
+            }
+            const Tables TV = table_pointers(v_tables, Sv);
+            const float base = wave_max == -INFINITY ? 0.0f : wave_max;  // (a wavefront without units, or without a score above -inf)
+            float den = 0.0f;
             float o[kHalf];
 #pragma unroll
             for (int i = 0; i < kHalf; ++i) o[i] = 0.0f;
-            for (; u < units; u += waves) {
+            for (; u < units; u += kWaves) {
                 store_unit(wbuf, pre, lane);
                 // a slot past the sequence end may hold anything (the cache behind seq_len need not be initialised):
                 // its scale is taken as 0, so that its values are zeros and not, say, NaN times a zero weight
                 const uint32_t mw = (u * kUnitBlocks + blk < span) ? pre.meta : (pre.meta & 0xFFFF0000u);
-                if (u + waves < units) pre = load_unit(v_blocks, v_meta, bh, T_max, unit0 + u + waves, lane);
+                if (u + kWaves < units) load_v(u + kWaves);
                 const Lane L = lane_setup(TV, mw, Sv);
                 const _Float16 sh = __builtin_bit_cast(_Float16, (unsigned short)(mw & 0xFFFFu));
                 const half2_t s2 = {sh, sh};
-                const float p = scores[u * kUnitBlocks + blk];
+                const float p = __expf(scores[u * kUnitBlocks + blk] - base);  // 0 for the tokens past the span
+                den += p;
                 uint32_t pk = 0;
                 decode_chain<kLongV, kHalf>(wbuf + blk * kStride, half ? L.second_start : 0u, L, [&](int i, uint32_t e) {
                     if ((i & 1) == 0) {
@@ -882,33 +912,59 @@ __global__ __launch_bounds__(kLongV ? 512 : kAttnThreads) void kv_attend_kernel(
                         const half2_t w2 = __builtin_bit_cast(half2_t, pk | (e & 0xFFFF0000u)) * s2;
                         o[i - 1] = fmaf(p, (float)w2[0], o[i - 1]);
                         o[i] = fmaf(p, (float)w2[1], o[i]);
+                        if ((i & 3) == 3) asm volatile("" : "+v"(o[i - 3]), "+v"(o[i - 2]), "+v"(o[i - 1]), "+v"(o[i]));  // as above
                     }
                 });
             }
-            // the span's sums: over the lanes of a wavefront on the VALU (lanes 0..31 hold values 0..63, lanes
-            // 32..63 values 64..127), then over the wavefronts through LDS into the running output
-            int ln = lane;  // taken afresh: what is derived from it is then formed here, not kept across the loop above
-            asm volatile("" : "+v"(ln));
-            const bool row_first = (ln & 15) == 0;
-            float* wrow = wred + (wave * 4 + (ln >> 4)) * kHalf;
+            // The span's sums over the rows of 16 lanes (rows 0 and 1 hold values 0..63, rows 2 and 3 values 64..127).  At the first two
+            // levels a lane keeps the values that match its own lane bit and sends the others to its partner, so that lane l of a row ends
+            // with the row's totals of values 4 j + l % 4; the first four lanes put them over the wavefront's payload buffer.  (A tree per
+            // value and a store of its first lane: 256 additions and 64 stores, this way 144 instructions and 4 stores.)
+            const int ln = fresh_thread() & 63;
+            const bool b0 = ln & 1, b1 = ln & 2;
+            float a[kHalf / 4];
 #pragma unroll
-            for (int i = 0; i < kHalf; ++i) {
-                float t = o[i];
-                t += dpp_mov<0xB1>(t);   // quad_perm [1,0,3,2]
-                t += dpp_mov<0x4E>(t);   // quad_perm [2,3,0,1]
-                t += dpp_mov<0x141>(t);  // row_half_mirror
-                t += dpp_mov<0x140>(t);  // row_mirror: every lane of a row of 16 now holds the row's sum
-                // the first lane of each row stores it: rows 0 and 1 belong to values 0..63, rows 2 and 3 to 64..127
-                if (row_first) wrow[i] = t;
+            for (int j = 0; j < kHalf / 4; ++j) {
+                float t[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const float x = o[4 * j + 2 * i], y = o[4 * j + 2 * i + 1];
+                    t[i] = (b0 ? y : x) + dpp_mov<0xB1>(b0 ? x : y);  // quad_perm [1,0,3,2]
+                }
+                float r = (b1 ? t[1] : t[0]) + dpp_mov<0x4E>(b1 ? t[0] : t[1]);  // quad_perm [2,3,0,1]
+                r += dpp_mov<0x124>(r);       // row_ror 4
+                a[j] = r + dpp_mov<0x128>(r);  // row_ror 8
+            }
+            den = 0.5f * wave_sum(den);  // both halves hold the tokens' weights
+            wave_lds_fence();
+            if ((ln & 15) < 4) {
+                float4_t* to = reinterpret_cast<float4_t*>(wbuf) + (ln >> 4) * (kHalf / 4) + (ln & 3) * 4;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) to[j] = float4_t{a[4 * j], a[4 * j + 1], a[4 * j + 2], a[4 * j + 3]};
+            }
+            if (ln == 0) {
+                state[wave] = wave_max;
+                state[kWaves + wave] = den;
             }
         }
         __syncthreads();
         if (tid < kGroup) {
-            float v = 0.0f;
-            const int hrow = (tid >> 6) * 2, i = tid & (kHalf - 1);
+            const int i = tid & (kHalf - 1);
+            const float* rows = reinterpret_cast<const float*>(smem + table_words) + (tid >> 6) * kGroup + (i & 3) * 16 + (i >> 2);
+            float most = run_max;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) most = fmaxf(most, state[w]);
+            const float rescale = run_max == -INFINITY ? 0.0f : __expf(run_max - most);
+            float v = 0.0f, d = 0.0f;
 #pragma unroll 4
-            for (int w = 0; w < waves; ++w) v += wred[(w * 4 + hrow) * kHalf + i] + wred[(w * 4 + hrow + 1) * kHalf + i];
+            for (int w = 0; w < kWaves; ++w) {
+                const float part = state[w] == -INFINITY ? 0.0f : __expf(state[w] - most);
+                v += part * (rows[w * kUnitWords] + rows[w * kUnitWords + kHalf]);
+                d += part * state[kWaves + w];
+            }
             my_out = my_out * rescale + v;
+            run_den = run_den * rescale + d;
+            run_max = most;
         }
     }
     if (tid < kGroup) out[(size_t)bh * kGroup + tid] = T > 0 ? my_out / run_den : 0.0f;
@@ -954,8 +1010,6 @@ constexpr int kGqaScoreWords = 7936;            // query heads x tokens of a spa
 constexpr int kRedTile = 276, kRedRow = 68;     // words of a tile, and of 16 lanes of it, in the sum over wavefronts (skewed over the banks)
 constexpr int kGqaStateWords = 4 * kGqaMaxGroup + kGqaWaves * kGqaMaxGroup + 64;
 
-// LDS words of the decode tables: the long-code lists and the centroids are only copied for models that need them
-__host__ __device__ constexpr int decode_table_words(int S, bool lng) { return S * (kPeekEntries + kK + (lng ? kK + kK / 2 : 0)); }
 __host__ __device__ constexpr int gqa_score_stride(int span) { return span + 4; }   // words: 16-byte aligned, and 4 modulo 32 so that heads fall on different banks
 struct GqaPlan {
     int table_words;  // LDS words of the tables: both models', or the larger one's
@@ -1007,12 +1061,6 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
         late_args* p = (late_args*)__builtin_amdgcn_kernarg_segment_ptr();
         asm volatile("" : "+s"(p));
         return p;
-    };
-    // a model's size, as the staging of its tables in a span sees it: what the staging of a model with long codes derives
-    // from it (masks, addresses) would otherwise be formed once for all spans and take scalar registers throughout
-    const auto fresh = [](int S) {
-        asm volatile("" : "+s"(S));
-        return S;
     };
     extern __shared__ __align__(16) uint32_t smem[];
     const int grp = Hq / Hkv, sstride = gqa_score_stride(span_max), n_splits = gridDim.y;
@@ -1076,17 +1124,17 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
         };
         if (both && first) {  // both models' items, then the payload, then both builds
             const uint32_t *dk = kLate ? late()->dev_k : args.dev_k, *dv = kLate ? late()->dev_v : args.dev_v;
-            const TableItems k_items = load_table_items(dk, kLongK ? fresh(Sk) : Sk), v_items = load_table_items(dv, kLongV ? fresh(args.Sv) : args.Sv);
+            const TableItems k_items = load_table_items(dk, kLongK ? fresh_size(Sk) : Sk), v_items = load_table_items(dv, kLongV ? fresh_size(args.Sv) : args.Sv);
             load_k(u);
             load_q();
-            build_tables<kLongK>(smem, dk, kLongK ? fresh(Sk) : Sk, k_items);
-            build_tables<kLongV>(v_tables, dv, kLongV ? fresh(args.Sv) : args.Sv, v_items);
+            build_tables<kLongK>(smem, dk, kLongK ? fresh_size(Sk) : Sk, k_items);
+            build_tables<kLongV>(v_tables, dv, kLongV ? fresh_size(args.Sv) : args.Sv, v_items);
         } else if (!both) {
             const uint32_t* dk = kLate ? late()->dev_k : args.dev_k;
-            const TableItems items = load_table_items(dk, kLongK ? fresh(Sk) : Sk);
+            const TableItems items = load_table_items(dk, kLongK ? fresh_size(Sk) : Sk);
             load_k(u);
             load_q();
-            build_tables<kLongK>(smem, dk, kLongK ? fresh(Sk) : Sk, items);
+            build_tables<kLongK>(smem, dk, kLongK ? fresh_size(Sk) : Sk, items);
         } else {
             load_k(u);
             load_q();
@@ -1159,7 +1207,7 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
         const int Sv = av->Sv;
         const auto load_v = [&](int at) { pre = load_unit(v_blocks, v_meta, bkv, T_max, unit0 + min(at, units - 1), lane, tok); };
         TableItems v_items{};
-        if (!both) v_items = load_table_items(av->dev_v, kLongV ? fresh(Sv) : Sv);
+        if (!both) v_items = load_table_items(av->dev_v, kLongV ? fresh_size(Sv) : Sv);
         load_v(u);
         __syncthreads();
         // ---- running softmax: all wavefronts, 256 tokens of a head at a time
@@ -1213,7 +1261,7 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
             st_den[tid] = st_den[tid] * alpha + den;
         }
         // ---- weighted sum of V over the span
-        if (!both) build_tables<kLongV>(v_tables, av->dev_v, kLongV ? fresh(Sv) : Sv, v_items);
+        if (!both) build_tables<kLongV>(v_tables, av->dev_v, kLongV ? fresh_size(Sv) : Sv, v_items);
         const Tables TV = table_pointers(v_tables, Sv);
         __syncthreads();
         {
@@ -1583,20 +1631,21 @@ int ecco_kv_attend(const ecco_model* mk, const ecco_model* mv, const uint16_t* q
     if (B <= 0 || H <= 0 || T_max <= 0 || (long long)B * H > 0x7FFFFFFF) return ECCO_ESHAPE;
     if (!aligned(k_blocks, 64) || !aligned(v_blocks, 64) || !aligned(q, 16) || !aligned(out, 4)) return ECCO_EALIGN;
     if (model_ready(mk) != ECCO_OK || model_ready(mv) != ECCO_OK || mk->device != mv->device) return ECCO_EINVAL;
-    const size_t lds = attn_lds_bytes(mk->S, mv->S);
     const bool lk = mk->max_len > kPeekBits, lv = mv->max_len > kPeekBits;
     const int dev_id = mk->device;
+    const AttnPlan plan = attn_plan(mk->S, lk, mv->S, lv, (size_t)B * H, T_max, cu_count(dev_id));
     auto launch = [&](auto kernel) -> int {
-        int rc = allow_lds(kernel, dev_id, lds);
+        int rc = allow_lds(kernel, dev_id, plan.lds);
         if (rc != ECCO_OK) return rc;
-        hipLaunchKernelGGL(kernel, dim3(B * H), dim3(lv ? 512 : kAttnThreads), lds, static_cast<hipStream_t>(stream), mk->dev, mk->S, mv->dev,
+        hipLaunchKernelGGL(kernel, dim3(B * H), dim3(plan.waves * 64), plan.lds, static_cast<hipStream_t>(stream), mk->dev, mk->S, mv->dev,
                            mv->S, q, static_cast<const uint4*>(k_blocks), k_meta, static_cast<const uint4*>(v_blocks), v_meta,
-                           seq_len, H, T_max, out);
+                           seq_len, H, T_max, plan.table_words, plan.both, plan.span, out);
         ECCO_HIP_CHECK(hipGetLastError());
         return ECCO_OK;
     };
-    if (lk) return lv ? launch(kv_attend_kernel<true, true>) : launch(kv_attend_kernel<true, false>);
-    return lv ? launch(kv_attend_kernel<false, true>) : launch(kv_attend_kernel<false, false>);
+    if (lk) return lv ? launch(kv_attend_kernel<true, true, 12>) : launch(kv_attend_kernel<true, false, 12>);
+    if (lv) return launch(kv_attend_kernel<false, true, 12>);
+    return plan.waves == 8 ? launch(kv_attend_kernel<false, false, 8>) : plan.waves == 12 ? launch(kv_attend_kernel<false, false, 12>) : launch(kv_attend_kernel<false, false, 16>);
 }
 
 }  // extern "C"

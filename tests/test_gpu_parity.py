@@ -514,6 +514,46 @@ def test_kv_attend_matches_oracle(dev, oracle):
     assert np.allclose(out[1], vdec[1, :, 0].astype(np.float64), rtol=1e-6, atol=1e-9)
 
 
+# Units are 32 tokens.  The wavefronts of a workgroup: eight where twelve or sixteen take as many rounds over the capacity's units or
+# where two workgroups share a compute unit (more workgroups than compute units, tables of both models in half the LDS), else twelve
+# where sixteen take as many, else sixteen; tables side by side (16 patterns) or in turn (64); spans of up to 8192 tokens.
+@pytest.mark.parametrize("S,B,H,T,lengths", [
+    (16, 3, 2, 97, [97, 32, 1]),                # four units: eight wavefronts, some without units
+    (16, 2, 2, 300, [300, 289]),                # ten: twelve
+    (16, 2, 1, 500, [500, 33]),                 # sixteen: sixteen
+    (16, 2, 1, 8900, [8900, 8193]),             # two spans, the second one of a single token
+    (64, 2, 1, 700, [700, 64]),                 # tables in turn
+    (64, 2, 1, 8900, [8900, 8192]),             # and in each of two spans
+    (40, 2, 1, 700, [700, 699]),                # 40 patterns: both tables fit one workgroup's LDS
+    (16, 150, 2, 100, [100, 1, 0, 64, 65]),     # more workgroups than compute units: two per unit
+    (16, 150, 2, 7500, [7500, 7361, 33, 0, 7]), # two spans of such
+])
+def test_kv_attend_variants(dev, oracle, S, B, H, T, lengths):
+    """Against the oracle, and the same bits on a second launch.  The tokens are drawn from 512 encoded ones."""
+    n = 512
+    rng = np.random.default_rng(S + T)
+    k, v, mk, mv = _kv_setup(dev, oracle, 1, 1, n, S)
+    kb, km, okb, okm = enc_both(dev, oracle, mk, k); vb, vm, ovb, ovm = enc_both(dev, oracle, mv, v)
+    seq = np.array([lengths[b] if b < len(lengths) else 1 + b % 40 for b in range(B)], np.int32)
+    pick = rng.integers(0, n, (2, B * H * T))
+    at = torch.from_numpy(pick).to(dev)
+    caches = [kb.view(n, 64)[at[0]], km.view(-1)[at[0]], vb.view(n, 64)[at[1]], vm.view(-1)[at[1]]]
+    q = W.activation(B * H, 128, 104).reshape(B, H, 128)
+    args = (mk, mv, t16(q, dev), *caches, ti32(seq, dev), B, H, T)
+    first = E.ecco_kv_attend(*args)
+    assert torch.equal(first, E.ecco_kv_attend(*args))
+    out = first.cpu().numpy()
+    assert not out[seq == 0].any()
+    most = 6  # sequences looked at one by one: those listed and one more
+    for b in range(min(B, most)):
+        m = max(1, int(seq[b]))
+        ids = pick.reshape(2, B, H, T)[:, b, :, :m]
+        one = [a.reshape(n, -1)[ids[i // 2].reshape(-1)] for i, a in enumerate((okb, okm, ovb, ovm))]
+        one = [one[0], one[1].reshape(-1), one[2], one[3].reshape(-1)]
+        want = oracle.kv_attend(mk.centroids, mk.code_lens, mv.centroids, mv.code_lens, np.ascontiguousarray(q[b:b + 1]).view(np.uint16), *one, seq[b:b + 1], 1, H, m)
+        assert_attn_close(oracle, mv, one[2], one[3], seq[b:b + 1], 1, H, H, m, out[b:b + 1], want, b)
+
+
 def test_attend_ignores_cache_behind_seq_len(dev, oracle):
     """Slots at or behind seq_len may hold anything, NaN scales included: both attention kernels must not read them into the result."""
     B, H, T = 2, 2, 100
