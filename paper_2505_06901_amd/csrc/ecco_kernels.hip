@@ -972,10 +972,9 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(kWa
 
 // ---- grouped-query attention over compressed K / V, split over the tokens ---------------------------------
 // Several query heads share one key/value head (Section 5.3: with grouped-query attention the batched
-// matrix-vector products become small matrix products).  One workgroup of 8 or 12 wavefronts per (sequence, key/value
-// head, token range) decodes every K and V block of its range once and serves all grp = Hq / Hkv query heads of the group
+// matrix-vector products become small matrix products).  One workgroup per (sequence, key/value head, token range) decodes every K and V block of its range once and serves all grp = Hq / Hkv query heads of the group
 // with it, on the matrix cores, in 16 x 16 tiles (v_mfma_f32_16x16x32_f16): a lane's four accumulator registers per tile
-// leave room for three wavefronts per SIMD, where 32 x 32 tiles, half of whose columns no group of at most 16 heads can use,
+// leave room for four wavefronts per SIMD, where 32 x 32 tiles, half of whose columns no group of at most 16 heads can use,
 // left two.
 // A unit is 32 tokens; lane l decodes chain (l / 16) % 2 of token l % 16 + 16 (l / 32).
 //   scores  S[token][head] = sum_dim K[token][dim] q[head][dim]: eight decoded values of a lane are its A operand (row
@@ -984,50 +983,59 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(kWa
 //           elsewhere), so one product gives 32 tokens x 8 heads.  With more heads (kWide) there are two products, the
 //           other tokens' rows of A zeroed.
 //   output  O[dim][head] = sum_token V[token][dim] P[head][token]: here the reduction runs over the tokens, so the
-//           decoded values have to be turned: every 16 values the wavefront writes a 32 dims x 32 tokens FP16 tile
+//           decoded values have to be turned: every 8 values the wavefront writes a 16 dims x 32 tokens FP16 tile
 //           to its private LDS buffer (neighbouring lanes first swap halves so that each writes two tokens of one
-//           dimension), reads it back as A operands (row = dimension, eight tokens per lane) and multiplies with
+//           dimension), reads it back as an A operand (row = dimension, eight tokens per lane) and multiplies with
 //           the FP16 probabilities; the eight 16 x 16 accumulator tiles (32 registers) live across the spans.
-// The sequence is walked in spans whose scores fit LDS.  Per span: the wavefronts' maxima meet in LDS, all wavefronts
-// turn scores into probabilities, 256 of a head at a time, held in registers until every score has been read, since
-// the FP16 probabilities take the scores' place (the denominator sums the rounded values); the accumulators of a lane --
-// all of one head -- are rescaled.  If both models' tables fit they are built once, otherwise the V tables replace the
-// K tables in every span.  With one range per sequence the result is normalised and written; otherwise (maximum, denominator,
-// unnormalised output) of the range go to the caller's workspace and kv_attend_combine_kernel merges them.
-// Wavefronts per workgroup.  Twelve decode faster than eight where they take fewer rounds over the units of a range (8 x 8
-// heads in groups of 4, 4096 tokens, 32 units per range: 37.6 us with twelve, 41.5 us with eight); where they take as many, eight
-// meet and are summed faster (8 x 4 heads in groups of 8, 16 units per range: 29.7 us with eight, 30.2 us with twelve; 8 x 8 heads in
-// groups of 8, 1024 tokens, 8 units: 22.5 and 23.7 us).  The decoder of long codes needs the registers of eight.
-constexpr int kGqaWaves = 12, kGqaWavesFew = 8;
-constexpr int gqa_waves(bool lng, int units) {
-    return lng || (units + kGqaWavesFew - 1) / kGqaWavesFew == (units + kGqaWaves - 1) / kGqaWaves ? kGqaWavesFew : kGqaWaves;
-}
+// The sequence is walked in spans whose scores fit LDS; per span a wavefront takes its units twice, with the K and with the V tables.
+// The softmax is the wavefront's own: scores become FP16 probabilities, relative to the largest score that the wavefront has met, when
+// they are read as B operands (the denominator sums the rounded values), and the accumulators of a lane -- all of one head -- are
+// rescaled from span to span.  Maxima, denominators and outputs of the wavefronts meet once, at the end.  If both models' tables fit
+// they are built once, and that is the only barrier until then (8 x 8 heads in groups of 4, 16 patterns, append, attention and merge:
+// 4096 tokens 34.9 us with a softmax of the workgroup between the passes, 33.3 us so; groups of 8, 1024 tokens 19.1 -> 17.9 us); otherwise the V tables replace the K tables in every span.  With one
+// range per sequence the result is normalised and written; otherwise (maximum, denominator, unnormalised output) of the range go to the
+// caller's workspace and kv_attend_combine_kernel merges them.
 constexpr int kGqaMaxGroup = 16;
 constexpr int kTileStride = 20;                 // words per row of the transposition tile: 32 tokens (16 words) + 4 of padding
-constexpr int kTileWords = 32 * kTileStride;
-constexpr int kItemTokens = 256;                // tokens a wavefront turns into probabilities at a time
+constexpr int kTileWords = 16 * kTileStride;
 constexpr int kGqaScoreWords = 7936;            // query heads x tokens of a span kept in LDS, at most
 constexpr int kRedTile = 276, kRedRow = 68;     // words of a tile, and of 16 lanes of it, in the sum over wavefronts (skewed over the banks)
-constexpr int kGqaStateWords = 4 * kGqaMaxGroup + kGqaWaves * kGqaMaxGroup + 64;
+constexpr int gqa_state_words(int waves) { return 2 * waves * kGqaMaxGroup; }  // per wavefront and head: maximum, denominator
 
 __host__ __device__ constexpr int gqa_score_stride(int span) { return span + 4; }   // words: 16-byte aligned, and 4 modulo 32 so that heads fall on different banks
+// Two workgroups of eight wavefronts share a compute unit where there are workgroups for it and both models' tables fit half its
+// LDS (16 patterns, 16 x 32 heads in groups of 2, 1000 tokens: 57.4 -> 44.9 us).  Otherwise one of as few wavefronts as take the fewest
+// rounds over the units of a range (with 16 patterns: 16 units 23.6 us with sixteen, 24.6 us with twelve; 8 units 17.9 us with eight,
+// 19.3 us with twelve, 20.6 us with sixteen).  The decoders of long codes need the registers of twelve.
 struct GqaPlan {
+    int waves;
     int table_words;  // LDS words of the tables: both models', or the larger one's
     int both;         // the V tables have their own place, behind those of K
     int span;         // tokens per span, a multiple of 32
     size_t lds;
 };
-inline GqaPlan gqa_plan(int Sk, bool lk, int Sv, bool lv, int grp, int waves) {
-    constexpr int kLdsWords = 160 * 1024 / 4;
+inline GqaPlan gqa_plan(int Sk, bool lk, int Sv, bool lv, int grp, size_t wgs, int units, int cus) {
     const int wk = decode_table_words(Sk, lk), wv = decode_table_words(Sv, lv);
-    const int fixed = waves * (kUnitWords + kTileWords) + kGqaStateWords;
-    GqaPlan p;
-    p.both = wk + wv + fixed + kGqaScoreWords <= kLdsWords;
-    p.table_words = p.both ? wk + wv : std::max(wk, wv);
-    const int scores = std::min(kGqaScoreWords, kLdsWords - p.table_words - fixed);
-    p.span = (scores / grp - 4) & ~(kUnitBlocks - 1);
-    p.lds = (size_t)std::max(p.table_words + fixed + grp * gqa_score_stride(p.span), waves * 8 * kRedTile) * 4;
-    return p;
+    const auto plan = [&](int waves, int lds_words) {
+        const int fixed = waves * (kUnitWords + kTileWords) + gqa_state_words(waves);
+        GqaPlan p;
+        p.waves = waves;
+        const int round = std::min(units, waves) * kUnitBlocks;  // tokens that the wavefronts take at a time
+        p.both = wk + wv + fixed + grp * gqa_score_stride(round) <= lds_words;
+        p.table_words = p.both ? wk + wv : std::max(wk, wv);
+        const int scores = std::min(kGqaScoreWords, lds_words - p.table_words - fixed);
+        p.span = std::min((scores / grp - 4) & ~(kUnitBlocks - 1), units * kUnitBlocks);
+        if (p.span < units * kUnitBlocks && p.span > round) p.span -= p.span % round;
+        p.lds = (size_t)std::max(p.table_words + fixed + grp * gqa_score_stride(p.span), gqa_state_words(waves) + waves * 8 * kRedTile) * 4;
+        return p;
+    };
+    constexpr int kLdsWords = 160 * 1024 / 4;
+    if (lk || lv) return plan(12, kLdsWords);
+    const GqaPlan two = plan(8, kLdsWords / 2);
+    if (wgs > (size_t)cus && two.both) return two;
+    const auto rounds = [&](int waves) { return (units + waves - 1) / waves; };
+    const int waves = rounds(8) == rounds(16) ? 8 : rounds(12) == rounds(16) ? 12 : 16;
+    return plan(waves, kLdsWords);
 }
 
 // grid: (B * Hkv, n_splits).  The partial result of a split and query head is at
@@ -1045,75 +1053,59 @@ struct GqaArgs {
     float* ws;
     int Sk, Sv, B, Hq, Hkv, T_max, table_words, both, span;
 };
-typedef __attribute__((address_space(4))) const GqaArgs late_args;  // the arguments, read where they are used: all at once they exceed the scalar registers
 
 template <bool kLongK, bool kLongV, bool kWide, int kWaves>
 __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args) {
     constexpr int kThreads = kWaves * 64;
-    constexpr bool kLate = kLongK || kLongV;  // the decoder of long codes takes more scalar registers: more of the arguments are read late
-    constexpr int kItems = (48 + kWaves - 1) / kWaves;                       // pieces of the probabilities per wavefront (gqa_plan: at most 48)
     constexpr int kOutputs = (kGqaMaxGroup * kGroup + kThreads - 1) / kThreads;  // output elements per thread
-    // one register more than the 152 that these instantiations use: the amount of a 64-bit shift must not be the last
-    // register of the allocation (the build checks every kernel for it)
-    if (!kLongK && !kWide && (kLongV || kWaves == kGqaWaves)) asm volatile("" ::: "v152");
-    const int Sk = args.Sk, B = args.B, Hq = args.Hq, Hkv = args.Hkv, T_max = args.T_max, both = args.both, table_words = args.table_words, span_max = args.span;
-    const auto late = [] {
-        late_args* p = (late_args*)__builtin_amdgcn_kernarg_segment_ptr();
-        asm volatile("" : "+s"(p));
-        return p;
-    };
+    const int Sk = args.Sk, Sv = args.Sv, B = args.B, Hq = args.Hq, Hkv = args.Hkv, T_max = args.T_max, both = args.both, table_words = args.table_words, span_max = args.span;
     extern __shared__ __align__(16) uint32_t smem[];
     const int grp = Hq / Hkv, sstride = gqa_score_stride(span_max), n_splits = gridDim.y;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    uint32_t* wbuf = smem + table_words + wave * kUnitWords;
-    uint32_t* tile = smem + table_words + kWaves * kUnitWords + wave * kTileWords;
-    float* st_max = reinterpret_cast<float*>(smem + table_words + kWaves * (kUnitWords + kTileWords));  // [2][16]: before and after the span
-    float* st_den = st_max + 2 * kGqaMaxGroup;
-    float* st_alpha = st_den + kGqaMaxGroup;
-    float* wave_max = st_alpha + kGqaMaxGroup;                  // [wavefront][16]
-    float* item_den = wave_max + kWaves * kGqaMaxGroup;      // per piece of the probabilities
-    float* scores = item_den + 64;           // [grp][sstride], then FP16 probabilities at the same rows
-    uint32_t* v_tables = smem + (both ? decode_table_words(Sk, kLongK) : 0);
+    float* state = reinterpret_cast<float*>(smem);  // [wavefront][16] maxima, [wavefront][16] denominators
+    uint32_t* k_tables = smem + gqa_state_words(kWaves);
+    uint32_t* wbuf = k_tables + table_words + wave * kUnitWords;
+    uint32_t* tile = k_tables + table_words + kWaves * kUnitWords + wave * kTileWords;
+    float* scores = reinterpret_cast<float*>(k_tables + table_words + kWaves * (kUnitWords + kTileWords));  // [grp][sstride]
+    uint32_t* v_tables = k_tables + (both ? decode_table_words(Sk, kLongK) : 0);
     if (lane < kUnitBlocks) wbuf[lane * kStride + kBlockWords] = 0u;
     if (lane == 0) wbuf[kUnitBlocks * kStride] = 0u;
-    if (tid < kGqaMaxGroup) {
-        st_max[tid] = -INFINITY;
-        st_den[tid] = 0.0f;
-    }
 
     const int b = blockIdx.x / Hkv, hkv = blockIdx.x - b * Hkv, split = blockIdx.y, bkv = blockIdx.x;
-    int kept[3] = {bkv, split, n_splits};  // until the end
-    if (kLate) asm volatile("" : "+v"(kept[0]), "+v"(kept[1]), "+v"(kept[2]));
     const int T = max(0, min(args.seq_len[b], T_max));
     const int per_range = ((T + kUnitBlocks - 1) / kUnitBlocks + n_splits - 1) / n_splits;
     const int t_begin = min(T, split * per_range * kUnitBlocks), t_end = min(T, (split + 1) * per_range * kUnitBlocks);
-    const int n = lane & 15, slice = lane >> 4, half = slice & 1;   // matrix-core row or column and k slice; chain of this lane
-    const int tok = n + 16 * (lane >> 5);                          // its token of the unit
-    const int head = kWide ? n : n & 7;                             // head of this lane's column
-    const bool head_ok = head < grp, b_ok = head_ok && (kWide || (n >> 3) == (lane >> 5));
-    const size_t q_row = ((size_t)b * Hq + (size_t)hkv * grp + (head_ok ? head : 0)) * kGroup;
+    // the lane's place in a unit, formed in either pass: kept, what is derived from it would take registers through both
+    struct Place {
+        int lane, n, slice, half, tok;  // n: matrix-core row or column; slice: k slice; half: chain of the lane's token `tok` of the unit
+        __device__ Place() : lane(fresh_thread() & 63), n(lane & 15), slice(lane >> 4), half(slice & 1), tok(n + 16 * (lane >> 5)) {}
+    };
     const float inv_sqrt_d = 0.08838834764831845f;  // 1 / sqrt(128)
-    const uint32_t swap_sel = (lane & 1) ? 0x03020706u : 0x05040100u;  // odd lanes keep the high halves, even lanes the low halves
-    float4_t o[8];  // tile 4 h + s: dimensions 64 h + 16 s .. + 15 x heads
+    float4_t o[8];  // tile j: row r is dimension 64 (r / 8) + 8 j + r % 8, column the head
 #pragma unroll
     for (int j = 0; j < 8; ++j) o[j] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    float run_max = -INFINITY, run_den = 0.0f;  // of this wavefront and of head l % 16; the denominator of the lane's tokens
 
-    int parity = 0;
-    for (int s0 = t_begin; s0 < t_end; s0 += span_max, parity ^= 1) {
+    for (int s0 = t_begin; s0 < t_end; s0 += span_max) {
         const int span = min(span_max, t_end - s0);
         const int units = (span + kUnitBlocks - 1) / kUnitBlocks, unit0 = s0 / kUnitBlocks;  // s0 is a multiple of 32
         // ---- scores of the span, all query heads of the group
-        __syncthreads();
-        int u = wave;
         UnitLoad pre;
+        float mx = -INFINITY;
+        {
+        const Place P;
+        const int lane = P.lane, n = P.n, slice = P.slice, half = P.half, tok = P.tok;
+        const int head = kWide ? n : n & 7;                             // head of this lane's column
+        const bool head_ok = head < grp, b_ok = head_ok && (kWide || (n >> 3) == (lane >> 5));
+        const size_t q_row = ((size_t)b * Hq + (size_t)hkv * grp + (head_ok ? head : 0)) * kGroup;
+        int u = wave;
         const auto load_k = [&](int at) { pre = load_unit(args.k_blocks, args.k_meta, bkv, T_max, unit0 + min(at, units - 1), lane, tok); };
-        const bool first = s0 == t_begin;
         uint4 bq[kHalf / 8];  // B operands: the query of this lane's head, dimensions 64 * half + 8j .. + 7
         // requested behind the payload, so that it arrives during the builds; reloaded per span rather than kept alive across the V
         // phase (the pointer passes through an empty asm statement and is given its address space again)
         const auto load_q = [&] {
-            const uint4* qgen = reinterpret_cast<const uint4*>((kLate ? late()->q : args.q) + q_row + half * kHalf);
+            const uint4* qgen = reinterpret_cast<const uint4*>(args.q + q_row + half * kHalf);
             asm volatile("" : "+v"(qgen));
             const global_u4* qsrc = (const global_u4*)qgen;
 #pragma unroll
@@ -1122,29 +1114,28 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
                 bq[j] = make_uint4(v.x, v.y, v.z, v.w);
             }
         };
-        if (both && first) {  // both models' items, then the payload, then both builds
-            const uint32_t *dk = kLate ? late()->dev_k : args.dev_k, *dv = kLate ? late()->dev_v : args.dev_v;
-            const TableItems k_items = load_table_items(dk, kLongK ? fresh_size(Sk) : Sk), v_items = load_table_items(dv, kLongV ? fresh_size(args.Sv) : args.Sv);
+        if (!both) {
+            const TableItems items = load_table_items(args.dev_k, kLongK ? fresh_size(Sk) : Sk);
             load_k(u);
             load_q();
-            build_tables<kLongK>(smem, dk, kLongK ? fresh_size(Sk) : Sk, k_items);
-            build_tables<kLongV>(v_tables, dv, kLongV ? fresh_size(args.Sv) : args.Sv, v_items);
-        } else if (!both) {
-            const uint32_t* dk = kLate ? late()->dev_k : args.dev_k;
-            const TableItems items = load_table_items(dk, kLongK ? fresh_size(Sk) : Sk);
+            __syncthreads();  // the V tables of the span before have been read
+            build_tables<kLongK>(k_tables, args.dev_k, kLongK ? fresh_size(Sk) : Sk, items);
+            __syncthreads();
+        } else if (s0 == t_begin) {  // both models' items, then the payload, then both builds
+            const TableItems k_items = load_table_items(args.dev_k, kLongK ? fresh_size(Sk) : Sk), v_items = load_table_items(args.dev_v, kLongV ? fresh_size(Sv) : Sv);
             load_k(u);
             load_q();
-            build_tables<kLongK>(smem, dk, kLongK ? fresh_size(Sk) : Sk, items);
+            build_tables<kLongK>(k_tables, args.dev_k, kLongK ? fresh_size(Sk) : Sk, k_items);
+            build_tables<kLongV>(v_tables, args.dev_v, kLongV ? fresh_size(Sv) : Sv, v_items);
+            __syncthreads();
         } else {
             load_k(u);
             load_q();
         }
-        const Tables TK = table_pointers(smem, Sk);
-        __syncthreads();
+        const Tables TK = table_pointers(k_tables, Sk);
         {
 #pragma unroll
             for (int j = 0; j < kHalf / 8; ++j) bq[j] = b_ok ? bq[j] : make_uint4(0u, 0u, 0u, 0u);
-            float mx = -INFINITY;
             for (; u < units; u += kWaves) {
                 store_unit(wbuf, pre, lane);
                 // a slot past the range may hold anything: scale 0, so that its values are zeros (tokens m and 16 + m share a row
@@ -1185,90 +1176,42 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
                         v[i] = t0 + i < span ? acc[w][i] * inv_sqrt_d : -INFINITY;
                         mx = fmaxf(mx, v[i]);
                     }
-                    if (head_ok) *reinterpret_cast<float4_t*>(scores + head * sstride + t0) = v;
+                    if (head_ok) *reinterpret_cast<float4_t*>(scores + head * sstride + t0) = v;  // for this wavefront alone
                 }
             }
             // the wavefront's maximum per head: over the lanes of the column
             if (!kWide) mx = fmaxf(mx, __shfl_xor(mx, 8));
             mx = fmaxf(mx, __shfl_xor(mx, 16));
             mx = fmaxf(mx, __shfl_xor(mx, 32));
-            int at = lane;
-            if (kLate) asm volatile("" : "+v"(at));  // as in `fresh`
-            if (at < 16) wave_max[wave * kGqaMaxGroup + n] = mx;  // columns past the heads hold something, which nobody reads
         }
-        // the V tables' items and the first unit, requested here: they arrive during the softmax.  Together with both models' items and the query
-        // requested ahead of the builds, attention and merge over 8 sequences of 4096 tokens, 8 heads in groups of 4, 16 patterns, take 32.8 instead
-        // of 33.6 us, over 4 sequences of 300 tokens 15.0 instead of 15.7 us; under 64 patterns (tables in turn) 32.8 instead of 32.9 us and 16.1
-        // instead of 16.5 us, and over one sequence of 64 tokens, where there is no softmax to speak of, 12.7 where it was 12.5 us
-        u = wave;
-        const auto* av = late();
-        const uint4* v_blocks = av->v_blocks;
-        const uint32_t* v_meta = av->v_meta;
-        const int Sv = av->Sv;
-        const auto load_v = [&](int at) { pre = load_unit(v_blocks, v_meta, bkv, T_max, unit0 + min(at, units - 1), lane, tok); };
-        TableItems v_items{};
-        if (!both) v_items = load_table_items(av->dev_v, kLongV ? fresh_size(Sv) : Sv);
-        load_v(u);
-        __syncthreads();
-        // ---- running softmax: all wavefronts, 256 tokens of a head at a time
-        const int pieces = (units * kUnitBlocks + kItemTokens - 1) / kItemTokens, items = pieces * grp;
-        uint2 ph[kItems];
-        uint32_t ph_at[kItems];  // where they go, as a byte offset into the scores (in a vector register: the scalar ones are spent)
-#pragma unroll
-        for (int k = 0; k < kItems; ++k) {
-            ph_at[k] = 0xFFFFFFFFu;
-            const int it = wave + k * kWaves;
-            if (it < items) {  // uniform
-                const int g = it / pieces, t0 = (it - g * pieces) * kItemTokens + 4 * lane;
-                float m = n < kWaves ? wave_max[n * kGqaMaxGroup + g] : -INFINITY;
-                m = fmaxf(m, dpp_mov<0xB1>(m));
-                m = fmaxf(m, dpp_mov<0x4E>(m));
-                m = fmaxf(m, dpp_mov<0x141>(m));
-                m = fmaxf(m, dpp_mov<0x140>(m));
-                m = fmaxf(m, st_max[parity * kGqaMaxGroup + g]);
-                float4_t s = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-                if (t0 < units * kUnitBlocks) {
-                    s = *reinterpret_cast<const float4_t*>(scores + g * sstride + t0);
-                    ph_at[k] = (uint32_t)(g * sstride * 4 + t0 * 2);
-                }
-                float den = 0.0f;
-                half2_t p[2];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    p[i >> 1][i & 1] = (_Float16)__expf(s[i] - m);  // 0 for the tokens past the span
-                    den += (float)p[i >> 1][i & 1];
-                }
-                ph[k] = make_uint2(__builtin_bit_cast(uint32_t, p[0]), __builtin_bit_cast(uint32_t, p[1]));
-                den = wave_sum(den);
-                if (lane == 0) {
-                    item_den[it] = den;
-                    if (t0 == 0) st_max[(parity ^ 1) * kGqaMaxGroup + g] = m;
-                }
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < kItems; ++k) {
-            asm volatile("" : "+v"(ph_at[k]));
-            if (ph_at[k] != 0xFFFFFFFFu) *reinterpret_cast<uint2*>(reinterpret_cast<unsigned char*>(scores) + ph_at[k]) = ph[k];
-        }
-        if (tid < grp) {
-            const float before = st_max[parity * kGqaMaxGroup + tid], after = st_max[(parity ^ 1) * kGqaMaxGroup + tid];
-            const float alpha = before == -INFINITY ? 0.0f : __expf(before - after);
-            float den = 0.0f;
-            for (int c = 0; c < pieces; ++c) den += item_den[tid * pieces + c];
-            st_alpha[tid] = alpha;
-            st_den[tid] = st_den[tid] * alpha + den;
         }
         // ---- weighted sum of V over the span
-        if (!both) build_tables<kLongV>(v_tables, av->dev_v, kLongV ? fresh_size(Sv) : Sv, v_items);
+        const Place P;
+        const int lane = P.lane, n = P.n, slice = P.slice, half = P.half, tok = P.tok;
+        const uint32_t swap_sel = (lane & 1) ? 0x03020706u : 0x05040100u;  // odd lanes keep the high halves, even lanes the low halves
+        int u = wave;
+        const auto load_v = [&](int at) { pre = load_unit(args.v_blocks, args.v_meta, bkv, T_max, unit0 + min(at, units - 1), lane, tok); };
+        if (both) {
+            load_v(u);
+        } else {
+            const TableItems items = load_table_items(args.dev_v, kLongV ? fresh_size(Sv) : Sv);
+            load_v(u);
+            __syncthreads();
+            build_tables<kLongV>(v_tables, args.dev_v, kLongV ? fresh_size(Sv) : Sv, items);
+            __syncthreads();
+        }
         const Tables TV = table_pointers(v_tables, Sv);
-        __syncthreads();
         {
-            const float alpha = n < grp ? st_alpha[n] : 1.0f;  // every accumulator of a lane belongs to head l % 16
-            const _Float16* prob = reinterpret_cast<const _Float16*>(scores + min(n, grp - 1) * sstride) + 8 * slice;
+            const float before = run_max;
+            run_max = fmaxf(before, mx);
+            const float base = run_max == -INFINITY ? 0.0f : run_max;  // (a wavefront without units, or without a score above -inf)
+            if (s0 != t_begin) {  // every accumulator of a lane belongs to head l % 16
+                const float alpha = before == -INFINITY ? 0.0f : __expf(before - base);
+                run_den *= alpha;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) o[j] *= alpha;
+                for (int j = 0; j < 8; ++j) o[j] *= alpha;
+            }
+            const float* score = scores + min(n, grp - 1) * sstride + 8 * slice;
             for (; u < units; u += kWaves) {
                 store_unit(wbuf, pre, lane);
                 const uint32_t mw = (u * kUnitBlocks + tok < span) ? pre.meta : (pre.meta & 0xFFFF0000u);
@@ -1276,67 +1219,84 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
                 const Lane L = lane_setup(TV, mw, Sv);
                 const _Float16 sh16 = __builtin_bit_cast(_Float16, (unsigned short)(mw & 0xFFFFu));
                 const half2_t s2 = {sh16, sh16};
-                // B operand: probabilities of head l % 16 for tokens 8 * (l / 16) .. + 7 of the unit
-                const uint4 pb = n < grp ? *reinterpret_cast<const uint4*>(prob + u * kUnitBlocks) : make_uint4(0u, 0u, 0u, 0u);
-                uint32_t pk[8];
+                // B operand: probabilities of head l % 16 for tokens 8 * (l / 16) .. + 7 of the unit; 0 for the tokens past the span
+                half8_t pb;
+                {
+                    const float4_t s[2] = {reinterpret_cast<const float4_t*>(score + u * kUnitBlocks)[0], reinterpret_cast<const float4_t*>(score + u * kUnitBlocks)[1]};
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        pb[i] = n < grp ? (_Float16)__expf(s[i >> 2][i & 3] - base) : (_Float16)0.0f;
+                        run_den += (float)pb[i];
+                    }
+                }
+                uint32_t pk[4];
                 decode_chain<kLongV, kHalf>(wbuf + tok * kStride, half ? L.second_start : 0u, L, [&](int i, uint32_t e) {
                     if ((i & 1) == 0) {
-                        pk[(i >> 1) & 7] = e >> 16;
+                        pk[(i >> 1) & 3] = e >> 16;
                         return;
                     }
-                    pk[(i >> 1) & 7] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, pk[(i >> 1) & 7] | (e & 0xFFFF0000u)) * s2);
-                    if ((i & 15) != 15) return;
-                    // 16 values of this lane's token -> rows 16 * half + r of the tile (dimension 64 * half + 16 * (i / 16) + r);
+                    pk[(i >> 1) & 3] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, pk[(i >> 1) & 3] | (e & 0xFFFF0000u)) * s2);
+                    if ((i & 7) != 7) return;
+                    // 8 values of this lane's token -> rows 8 * half + r of the tile (dimension 64 * half + 8 * (i / 8) + r);
                     // an even lane takes dimension 2 r2 of its own and its neighbour's token, the odd neighbour dimension 2 r2 + 1
                     wave_lds_fence();
 #pragma unroll
-                    for (int r2 = 0; r2 < 8; ++r2) {
+                    for (int r2 = 0; r2 < 4; ++r2) {
                         const uint32_t other = (uint32_t)__builtin_amdgcn_mov_dpp((int)pk[r2], 0xB1, 0xF, 0xF, true);  // quad_perm [1,0,3,2]
-                        tile[(16 * half + 2 * r2 + (lane & 1)) * kTileStride + (tok >> 1)] = __builtin_amdgcn_perm(other, pk[r2], swap_sel);
+                        tile[(8 * half + 2 * r2 + (lane & 1)) * kTileStride + (tok >> 1)] = __builtin_amdgcn_perm(other, pk[r2], swap_sel);
                     }
                     wave_lds_fence();
                     const uint4 a0 = *reinterpret_cast<const uint4*>(tile + n * kTileStride + 4 * slice);
-                    const uint4 a1 = *reinterpret_cast<const uint4*>(tile + (16 + n) * kTileStride + 4 * slice);
-                    const half8_t bv = __builtin_bit_cast(half8_t, pb);
-                    o[i >> 4] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a0), bv, o[i >> 4], 0, 0, 0);
-                    o[4 + (i >> 4)] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a1), bv, o[4 + (i >> 4)], 0, 0, 0);
+                    o[i >> 3] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a0), pb, o[i >> 3], 0, 0, 0);
                 });
             }
         }
     }
-    // ---- sum over the wavefronts; everything else in LDS is dead once the state has been read
-    const auto* end = late();
-    float* out = end->out;
-    float* ws = end->ws;
-    const auto scalar = [](int v) { return kLate ? __builtin_amdgcn_readfirstlane(v) : v; };
-    const int bkv_end = scalar(kept[0]), split_end = scalar(kept[1]), n_splits_end = scalar(kept[2]);
-    const size_t heads = kLate ? (size_t)end->B * end->Hq : (size_t)B * Hq;
-    const size_t first_head = kLate ? (size_t)(bkv_end / end->Hkv) * end->Hq + (size_t)(bkv_end % end->Hkv) * grp : (size_t)b * Hq + (size_t)hkv * grp;
-    const size_t part = first_head * n_splits_end + split_end, total = heads * n_splits_end;  // of the group's first head
+    // ---- sum over the wavefronts; everything in LDS but the state is dead behind the first barrier
+    const Place P;
+    const int n = P.n, slice = P.slice;
+    float *out = args.out, *ws = args.ws;
+    const size_t first_head = (size_t)b * Hq + (size_t)hkv * grp;
+    const size_t part = first_head * n_splits + split, total = (size_t)B * Hq * n_splits;  // of the group's first head
+    run_den += __shfl_xor(run_den, 16);
+    run_den += __shfl_xor(run_den, 32);
+    if (lane < 16) state[wave * kGqaMaxGroup + lane] = run_max;
     __syncthreads();
-    float den[kOutputs];
+    float most = -INFINITY;
 #pragma unroll
-    for (int k = 0; k < kOutputs; ++k) den[k] = st_den[min((tid + k * kThreads) / kGroup, kGqaMaxGroup - 1)];
-    if (n_splits_end > 1 && tid < grp) {
-        const size_t at = total * kGroup + (part + (size_t)tid * n_splits_end) * 2;
-        ws[at] = st_max[parity * kGqaMaxGroup + tid];
-        ws[at + 1] = st_den[tid];
+    for (int w = 0; w < kWaves; ++w) most = fmaxf(most, state[w * kGqaMaxGroup + n]);
+    const float mine = run_max == -INFINITY ? 0.0f : __expf(run_max - most);
+    if (lane < 16) state[(kWaves + wave) * kGqaMaxGroup + lane] = run_den * mine;
+    float* red = reinterpret_cast<float*>(k_tables);  // [wavefront][8 tiles][4 slices][16 lanes][4]
+#pragma unroll
+    for (int j = 0; j < 8; ++j) *reinterpret_cast<float4_t*>(red + (wave * 8 + j) * kRedTile + slice * kRedRow + n * 4) = o[j] * mine;
+    __syncthreads();
+    const auto denominator = [&](int g) {
+        float den = 0.0f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) den += state[(kWaves + w) * kGqaMaxGroup + g];
+        return den;
+    };
+    if (n_splits > 1 && tid < grp) {  // (the first wavefront's lane of head `tid` holds that head's maximum)
+        const size_t at = total * kGroup + (part + (size_t)tid * n_splits) * 2;
+        ws[at] = most;
+        ws[at + 1] = denominator(tid);
     }
-    __syncthreads();
-    float* red = reinterpret_cast<float*>(smem);  // [wavefront][8 tiles][4 slices][16 lanes][4]
-#pragma unroll
-    for (int j = 0; j < 8; ++j) *reinterpret_cast<float4_t*>(red + (wave * 8 + j) * kRedTile + slice * kRedRow + n * 4) = o[j];
-    __syncthreads();
 #pragma unroll
     for (int k = 0; k < kOutputs; ++k) {
         const int e = tid + k * kThreads, g = e / kGroup, dim = e % kGroup;
         if (g < grp) {
-            const float* at = red + (dim >> 4) * kRedTile + ((dim & 15) >> 2) * kRedRow + g * 4 + (dim & 3);
+            const int row = 8 * (dim >> 6) + (dim & 7);
+            const float* at = red + ((dim & 63) >> 3) * kRedTile + (row >> 2) * kRedRow + g * 4 + (row & 3);
             float sum = 0.0f;
 #pragma unroll
             for (int w = 0; w < kWaves; ++w) sum += at[w * 8 * kRedTile];
-            if (n_splits_end == 1) out[(first_head + g) * kGroup + dim] = den[k] > 0.0f ? sum / den[k] : 0.0f;
-            else ws[(part + (size_t)g * n_splits_end) * kGroup + dim] = sum;
+            if (n_splits == 1) {
+                const float den = denominator(g);
+                out[(first_head + g) * kGroup + dim] = den > 0.0f ? sum / den : 0.0f;
+            } else {
+                ws[(part + (size_t)g * n_splits) * kGroup + dim] = sum;
+            }
         }
     }
 }
@@ -1557,14 +1517,14 @@ static int gqa_launch(const ecco_model* mk, const ecco_model* mv, const uint16_t
                       const int32_t* seq_len, int B, int Hq, int Hkv, int T_max, int n_splits, float* workspace,
                       float* out, void* stream) {
     const bool lk = mk->max_len > kPeekBits, lv = mv->max_len > kPeekBits;
-    const int waves = gqa_waves(lk || lv, ((T_max - 1) / kUnitBlocks + n_splits) / n_splits);  // units of a range: ceil(ceil(T_max / 32) / n_splits)
-    const GqaPlan plan = gqa_plan(mk->S, lk, mv->S, lv, Hq / Hkv, waves);
+    const int units = ((T_max - 1) / kUnitBlocks + n_splits) / n_splits;  // of a range: ceil(ceil(T_max / 32) / n_splits)
+    const GqaPlan plan = gqa_plan(mk->S, lk, mv->S, lv, Hq / Hkv, (size_t)B * Hkv * n_splits, units, cu_count(mk->device));
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int dev_id = mk->device;
     auto launch = [&](auto kernel) -> int {
         int rc = allow_lds(kernel, dev_id, plan.lds);
         if (rc != ECCO_OK) return rc;
-        hipLaunchKernelGGL(kernel, dim3(B * Hkv, n_splits), dim3(waves * 64), plan.lds, st,
+        hipLaunchKernelGGL(kernel, dim3(B * Hkv, n_splits), dim3(plan.waves * 64), plan.lds, st,
                            GqaArgs{mk->dev, mv->dev, q, static_cast<const uint4*>(k_blocks), k_meta, static_cast<const uint4*>(v_blocks), v_meta, seq_len,
                                    out, workspace, mk->S, mv->S, B, Hq, Hkv, T_max, plan.table_words, plan.both, plan.span});
         ECCO_HIP_CHECK(hipGetLastError());
@@ -1572,9 +1532,10 @@ static int gqa_launch(const ecco_model* mk, const ecco_model* mv, const uint16_t
     };
     const auto pick = [&](auto wide) -> int {
         constexpr bool kWide = decltype(wide)::value;
-        if (lk) return lv ? launch(kv_attend_gqa_kernel<true, true, kWide, kGqaWavesFew>) : launch(kv_attend_gqa_kernel<true, false, kWide, kGqaWavesFew>);
-        if (lv) return launch(kv_attend_gqa_kernel<false, true, kWide, kGqaWavesFew>);
-        return waves == kGqaWaves ? launch(kv_attend_gqa_kernel<false, false, kWide, kGqaWaves>) : launch(kv_attend_gqa_kernel<false, false, kWide, kGqaWavesFew>);
+        if (lk) return lv ? launch(kv_attend_gqa_kernel<true, true, kWide, 12>) : launch(kv_attend_gqa_kernel<true, false, kWide, 12>);
+        if (lv) return launch(kv_attend_gqa_kernel<false, true, kWide, 12>);
+        return plan.waves == 8 ? launch(kv_attend_gqa_kernel<false, false, kWide, 8>)
+                               : plan.waves == 12 ? launch(kv_attend_gqa_kernel<false, false, kWide, 12>) : launch(kv_attend_gqa_kernel<false, false, kWide, 16>);
     };
     const int rc = Hq / Hkv > 8 ? pick(std::true_type{}) : pick(std::false_type{});
     if (rc != ECCO_OK || n_splits == 1) return rc;

@@ -631,6 +631,44 @@ def test_gqa_unequal_lengths(dev, oracle, lengths, T, grp, n_splits):
     assert_attn_close(oracle, mv, ovb, ovm, seq, B, Hkv * grp, Hkv, T, out, want)
 
 
+# Wavefronts by the rounds over the units (32 tokens) of a range: sixteen where twelve take more, eight where they take as many; eight,
+# two workgroups per compute unit, where there are more workgroups than compute units and both models' tables fit half the LDS.
+@pytest.mark.parametrize("S,B,Hkv,grp,T,n_splits,lengths", [
+    (16, 2, 1, 4, 1000, 2, [1000, 513]),             # 16 units: sixteen
+    (16, 2, 1, 16, 1000, 2, [1000, 65]),             # more than eight heads: two products per unit; spans of a round
+    (64, 2, 1, 4, 1000, 2, [1000, 961]),             # tables in turn
+    (64, 2, 1, 12, 3500, 2, [3500, 1025]),           # and in spans
+    (40, 2, 1, 8, 4000, 1, [4000, 3999]),            # 40 patterns: both tables beside the scores of one round
+    (16, 100, 3, 2, 700, 1, [700, 1, 0, 32, 33]),    # two workgroups per compute unit
+    (16, 100, 3, 9, 2500, 1, [2500, 257, 0, 256]),   # in spans, two products per unit
+    (16, 50, 2, 3, 900, 3, [900, 1, 2, 65, 0]),      # with ranges to merge
+])
+def test_gqa_wavefronts(dev, oracle, S, B, Hkv, grp, T, n_splits, lengths):
+    """Against the oracle, and the same bits on a second launch.  The tokens are drawn from 512 encoded ones."""
+    n, Hq = 512, Hkv * grp
+    rng = np.random.default_rng(S + T)
+    k, v, mk, mv = _kv_setup(dev, oracle, 1, 1, n, S)
+    kb, km, okb, okm = enc_both(dev, oracle, mk, k); vb, vm, ovb, ovm = enc_both(dev, oracle, mv, v)
+    seq = np.array([lengths[b] if b < len(lengths) else 1 + b % 40 for b in range(B)], np.int32)
+    pick = rng.integers(0, n, (2, B * Hkv * T))
+    at = torch.from_numpy(pick).to(dev)
+    caches = [kb.view(n, 64)[at[0]], km.view(-1)[at[0]], vb.view(n, 64)[at[1]], vm.view(-1)[at[1]]]
+    q = W.activation(B * Hq, 128, 108).reshape(B, Hq, 128)
+    args = (mk, mv, t16(q, dev), *caches, ti32(seq, dev), B, Hq, Hkv, T)
+    first = E.ecco_kv_attend_gqa(*args, n_splits=n_splits)
+    assert torch.equal(first, E.ecco_kv_attend_gqa(*args, n_splits=n_splits))
+    out = first.cpu().numpy()
+    assert not out[seq == 0].any()
+    for b in range(min(B, 6)):  # sequences looked at one by one: those listed and one more
+        m = max(1, int(seq[b]))
+        ids = pick.reshape(2, B, Hkv, T)[:, b, :, :m]
+        one = [a.reshape(n, -1)[ids[i // 2].reshape(-1)] for i, a in enumerate((okb, okm, ovb, ovm))]
+        one = [one[0], one[1].reshape(-1), one[2], one[3].reshape(-1)]
+        want = oracle.kv_attend_gqa(mk.centroids, mk.code_lens, mv.centroids, mv.code_lens, np.ascontiguousarray(q[b:b + 1]).view(np.uint16), *one, seq[b:b + 1],
+                                    1, Hq, Hkv, m)
+        assert_attn_close(oracle, mv, one[2], one[3], seq[b:b + 1], 1, Hq, Hkv, m, out[b:b + 1], want, b)
+
+
 @pytest.mark.parametrize("long_k,long_v,S,grp,T,n_splits", [
     (True, False, 5, 9, 1500, 1),     # long codes under more than eight heads, two to four spans, six units per wavefront
     (False, True, 5, 9, 1500, 1),
