@@ -389,13 +389,16 @@ __global__ __launch_bounds__(kGemvThreads) void pb_gemv_kernel(const uint32_t* _
             uint32_t k[kIdxWords];
             const Walked b = walk_block(own, T, [&](int i, uint32_t word) { k[i] = word; });
             info[lane] = make_uint2(b.cent | (b.present << 16), __builtin_bit_cast(uint32_t, half_f(b.scale)));
-            // The padded entries, last one first: an earlier one at the same position does not count.  The last two (few blocks have
-            // more) are only multiplied with their activations at the end of the pass, so that nothing waits for those here.
+            // The padded entries, last one first: an earlier one at the same position does not count.  Of the last two (few blocks have
+            // more) only the codes are taken here; what they stand for follows when the indices lie in LDS, where a value's is one
+            // read (out of registers it is a tree of 15 selections), and the products with their activations at the end of the pass.
             const uint32_t entries = lane < count ? b.entries : 0u;
             const uint16_t* xb = reinterpret_cast<const uint16_t*>(x) + (size_t)((uint32_t)(at + min(lane, count - 1)) % (uint32_t)gpr) * kGroup;
-            const auto entry = [&](uint32_t j, uint32_t& pos) {  // entry j: its position, and what it adds to the value there
-                const uint32_t code = entry_code(own, b.end, j);
-                pos = code >> 8;
+            const auto place = [](uint32_t pos) { return 8u * (pos & 3u) + ((pos & 4u) ? 0u : 4u); };  // of a value's index in its word
+            const auto adds = [&](uint32_t code, uint32_t i) {  // what an entry adds to the value of index i
+                return fmaf(-half_f(lds_half(T.cent + b.cent + i * 2u)), half_f(b.scale), half_f(T.fp8[code & 0xFFu]));
+            };
+            const auto index_of = [&](uint32_t pos) {  // out of registers
                 uint32_t t[kIdxWords];  // word pos / 8 of the indices
 #pragma unroll
                 for (int i = 0; i < kIdxWords; ++i) t[i] = k[i];
@@ -407,20 +410,17 @@ __global__ __launch_bounds__(kGemvThreads) void pb_gemv_kernel(const uint32_t* _
 #pragma unroll
                     for (int i = 0; i < n; ++i) t[i] = (t[i] & ~upper) | (t[i + n] & upper);
                 }
-                const uint32_t i = (t[0] >> (8u * (pos & 3u) + ((pos & 4u) ? 0u : 4u))) & 15u;
-                return fmaf(-half_f(lds_half(T.cent + b.cent + i * 2u)), half_f(b.scale), half_f(T.fp8[code & 0xFFu]));
+                return (t[0] >> place(pos)) & 15u;
             };
-            float add = 0.0f, last[2] = {0.0f, 0.0f};
-            uint32_t last_x[2] = {0u, 0u};  // FP16 bits
-            if (__builtin_amdgcn_ballot_w64(entries != 0u) != 0ull) {
-                uint32_t pos[2];
+            float add = 0.0f;
+            uint32_t code[2] = {0u, 0u}, last_x[2] = {0u, 0u};  // of the last two; FP16 bits of their activations
+            const bool any = __builtin_amdgcn_ballot_w64(entries != 0u) != 0ull;
+            if (any) {
 #pragma unroll
-                for (uint32_t q = 0; q < 2; ++q) {
-                    last[q] = entry(entries - 1u - q, pos[q]);  // (of a block without: some position, and not used)
-                    last_x[q] = xb[pos[q]];
+                for (uint32_t q = 0; q < 2; ++q) {  // (of a block without: some position, and not used)
+                    code[q] = entry_code(own, b.end, entries - 1u - q);
+                    last_x[q] = xb[code[q] >> 8];
                 }
-                last[0] = entries > 0u ? last[0] : 0.0f;
-                last[1] = entries > 1u && pos[1] != pos[0] ? last[1] : 0.0f;
                 if (__builtin_amdgcn_ballot_w64(entries > 2u) != 0ull) {
                     uint64_t seen[2] = {0ull, 0ull};
                     const auto see = [&](uint32_t p) {  // whether p was there before
@@ -430,12 +430,12 @@ __global__ __launch_bounds__(kGemvThreads) void pb_gemv_kernel(const uint32_t* _
                         seen[1] |= high ? bit : 0ull;
                         return again;
                     };
-                    see(pos[0]);
-                    see(pos[1]);
+                    see(code[0] >> 8);
+                    see(code[1] >> 8);
                     for (uint32_t j = 2; __builtin_amdgcn_ballot_w64(j < entries) != 0ull; ++j)
                         if (j < entries) {
-                            uint32_t p;
-                            const float d = entry(entries - 1u - j, p), xv = half_f(xb[p]);
+                            const uint32_t c = entry_code(own, b.end, entries - 1u - j), p = c >> 8;
+                            const float d = adds(c, index_of(p)), xv = half_f(xb[p]);
                             if (!see(p)) add = fmaf(d, xv, add);
                         }
                 }
@@ -444,6 +444,13 @@ __global__ __launch_bounds__(kGemvThreads) void pb_gemv_kernel(const uint32_t* _
 #pragma unroll
             for (int i = 0; i < kIdxWords; ++i) own[i] = k[i];
             wave_lds_fence();
+            float last[2] = {0.0f, 0.0f};
+            if (any) {
+#pragma unroll
+                for (uint32_t q = 0; q < 2; ++q) last[q] = adds(code[q], (own[code[q] >> 11] >> place(code[q] >> 8)) & 15u);
+                last[0] = entries > 0u ? last[0] : 0.0f;
+                last[1] = entries > 1u && (code[0] ^ code[1]) > 0xFFu ? last[1] : 0.0f;  // not at the same position
+            }
             // sixteen blocks at a time, four per row of lanes: eight activations of each block's column group per lane, those of the
             // next sixteen requested while these are multiplied
             uint4 xs[kAhead];
@@ -518,7 +525,7 @@ int ecco_pb_decode_gemv(const ecco_pb_model* m, const void* blocks, int rows, in
     const int gpr = cols / kGroup, cus = ecco::cu_count(m->device);
     // a band of rows per workgroup and a workgroup per compute unit; the band in chunks whose sums fit the LDS
     const int band = (rows + cus - 1) / cus, grid = (rows + band - 1) / band;
-    const int chunk = std::min(band, gemv_part_floats(m->S) / gpr);
+    const int most = std::min(band, gemv_part_floats(m->S) / gpr), chunks = (band + most - 1) / most, chunk = (band + chunks - 1) / chunks;
     // as few wavefronts as hold the blocks 64 at a time, but four (one per SIMD): a chain takes as long for one lane as for 64, and
     // longer the more wavefronts read tables beside it (512 blocks per workgroup: 15.3 us on eight, 16.9 us on sixteen; 40 blocks: 10.4 us on
     // four, 11.1 us on two, 12.5 us on ten; by events around replayed graphs)
