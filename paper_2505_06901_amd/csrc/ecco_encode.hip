@@ -181,9 +181,13 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
     Coefs<kTiles> C;
     C.load(job.dev + DevLayout{S}.coef(), wave, tiles, lane);
     const EncTables T = stage_enc_tables<kSearchThreads, false>(smem, job.dev, S);
+    // Dealt out (rate_left) where there are more than 16 patterns: 131072 groups under 64 patterns 63.9 -> 60.3 us, 8192 groups 9.7 -> 8.4 us.
+    // Of up to 16 the most of four groups is 1.7 where the deal's share is 0.9: it does not pay for itself (44.0 -> 44.6 us, 6.7 -> 6.9 us).
+    constexpr bool kDeal = kTiles > 1;
     bool slack_set = false;
     if (l == 0) L.slack[wave * kWaveRows + row] = 0.0f;
     for (size_t b = blockIdx.x; b < batches; b += gridDim.x) {
+        __builtin_amdgcn_s_setprio(priority_hist(search_over(kTiles)));
         const uint32_t smax = row_max(lane_absmax(v));
         const float s = half_bits_f(smax);
         const half2_t s2 = splat_half(smax);
@@ -194,6 +198,7 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
         wave_fence();
         convert_hist(L.hist + wave * kWaveRows * kHistStride, lane);
         uint64_t left = patterns_left<kTiles, search_over(kTiles)>(L, C, tiles, wave, lane);
+        __builtin_amdgcn_s_setprio(kPriorityRate);
         // What the table of nearest centroids does not serve is rated value by value (scan_patterns), scales too small for it
         // from the start.  Of scale 0 all patterns are alike: the first wins with index 0.
         uint64_t later = 0;
@@ -203,43 +208,64 @@ __global__ __launch_bounds__(kSearchThreads) __attribute__((amdgpu_waves_per_eu(
         }
         uint32_t pattern = 0, idx = 0;
         float best = __builtin_inff();
-        int rated = 0;
-        while (__builtin_amdgcn_ballot_w64(left != 0) != 0ull) {  // the patterns left, ascending; a row that has none left repeats its last one
-            const uint32_t p = left != 0 ? (uint32_t)__builtin_ctzll(left) : pattern;
-            float sse;
-            uint32_t id;
-            const uint32_t marks = rate_pattern<true, true>(T.near + p * kSearchBins, T.pair + p * 64u, s2, v, -1, sse, id);
-            const uint64_t lanes = __builtin_amdgcn_ballot_w64((marks & ecco::kNearWide) != 0u);
-            if (lanes != 0ull && row_any(lanes, row)) {  // this pattern and those after it value by value
-                later |= left;
-                left = 0;
-            }
-            if (left != 0 && sse < best) {  // strict <: the lowest pattern wins a tie
-                best = sse;
-                pattern = p;
-                idx = id;
-            }
-            left &= left - 1ull;
-            if (++rated == kLookAfter && __builtin_amdgcn_ballot_w64(most_left(left, S)) != 0ull) {
-                later |= left;
-                left = 0;
+        if constexpr (kDeal) {
+            uint64_t crowded;
+            pattern = rate_left<false, 8>(L.hist + wave * kWaveRows * kHistStride, T.near, T.pair, v, smax, -1, left, S, lane, best, crowded);
+            later |= crowded;
+        } else {
+            int rated = 0;
+            while (__builtin_amdgcn_ballot_w64(left != 0) != 0ull) {  // the patterns left, ascending; a row that has none left repeats its last one
+                const uint32_t p = left != 0 ? (uint32_t)__builtin_ctzll(left) : pattern;
+                float sse;
+                uint32_t id;
+                const uint32_t marks = rate_pattern<true, true>(T.near + p * kSearchBins, T.pair + p * 64u, s2, v, -1, sse, id);
+                const uint64_t lanes = __builtin_amdgcn_ballot_w64((marks & ecco::kNearWide) != 0u);
+                if (lanes != 0ull && row_any(lanes, row)) {  // this pattern and those after it value by value
+                    later |= left;
+                    left = 0;
+                }
+                if (left != 0 && sse < best) {  // strict <: the lowest pattern wins a tie
+                    best = sse;
+                    pattern = p;
+                    idx = id;
+                }
+                left &= left - 1ull;
+                if (++rated == kLookAfter && __builtin_amdgcn_ballot_w64(most_left(left, S)) != 0ull) {
+                    later |= left;
+                    left = 0;
+                }
             }
         }
-        if (__builtin_amdgcn_ballot_w64(later != 0) != 0ull) {
-            bool won;
+        bool won = false;  // by the comparison value by value
+        if (__builtin_amdgcn_ballot_w64(later != 0) != 0ull)
             scan_patterns(reinterpret_cast<float*>(L.hist + wave * kWaveRows * kHistStride), smem + S * (kSearchBins / 4), v, smax, kGroup, later, lane,
                           best, pattern, won);
-            const uint32_t id = scan_indices(T.pair + pattern * 64u, s2, v, -1);
-            idx = won ? id : idx;
+        bool scan = won;  // whether the table gives no indices
+        if constexpr (kDeal) {
+            if (__builtin_amdgcn_ballot_w64(!won && smax != 0u) != 0ull) {
+                float none;
+                const uint32_t marks = rate_pattern<false, true>(T.near + pattern * kSearchBins, T.pair + pattern * 64u, s2, v, -1, none, idx);
+                scan = won || ((marks & ecco::kNearWide) != 0u && smax != 0u);
+                idx = smax == 0u ? 0u : idx;
+            }
         }
+        const uint64_t scans = __builtin_amdgcn_ballot_w64(scan);
+        if (scans != 0ull) {
+            const uint32_t id = scan_indices(T.pair + pattern * 64u, s2, v, -1);
+            idx = row_any(scans, row) ? id : idx;
+        }
+        __builtin_amdgcn_s_setprio(kPriorityPack);
         // the next group is requested here, when the search has given its registers back
-        load_values<kSearchBatch>(v, io.values(), io.groups(), b + gridDim.x, wave * kWaveRows + row, l);
+        int last = threadIdx.x & 63;  // the lane taken afresh: what is derived from it is formed here, not kept through the search
+        asm volatile("" : "+v"(last));
+        const int place = last & 15, group = wave * kWaveRows + (last >> 4);
+        load_values<kSearchBatch>(v, io.values(), io.groups(), b + gridDim.x, group, place);
         uint32_t mw;
-        const uint32_t word = pack_row<kLong>(T.enc + pattern * (kK * 4u), hist, idx, l, smax, pattern, mw);
+        const uint32_t word = pack_row<kLong>(T.enc + pattern * (kK * 4u), L.hist + group * kHistStride, idx, place, smax, pattern, mw);
         size_t at;
-        if (io.place(b * kSearchBatch + (uint32_t)(wave * kWaveRows + row), at)) {
-            io.blocks[at * kBlockWords + l] = word;
-            if (l == 0) io.meta[at] = mw;
+        if (io.place(b * kSearchBatch + (uint32_t)group, at)) {
+            io.blocks[at * kBlockWords + place] = word;
+            if (place == 0) io.meta[at] = mw;
         }
     }
 }

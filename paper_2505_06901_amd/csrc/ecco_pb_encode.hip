@@ -92,6 +92,7 @@ void pb_encode_kernel(const uint32_t* __restrict__ dev, int S, float inv_tscale,
         asm volatile("" : "+v"(at));
         const int lane = at, l = lane & 15, row = lane >> 4;
         uint32_t* hist = L.hist + (wave * kWaveRows + row) * kHistStride;
+        __builtin_amdgcn_s_setprio(priority_hist(false));
         // the element of largest magnitude, first position on ties: the least (position, value) of those that have it
         const uint32_t mag = row_max(lane_absmax(v));
         uint32_t first = 0xFFFFFFFFu;
@@ -115,6 +116,7 @@ void pb_encode_kernel(const uint32_t* __restrict__ dev, int S, float inv_tscale,
         wave_fence();
         convert_hist(L.hist + wave * kWaveRows * kHistStride, lane);
         uint64_t left = patterns_left<kTiles, true>(L, C, tiles, wave, lane0);
+        __builtin_amdgcn_s_setprio(kPriorityRate);
         // What the table of nearest centroids does not serve is rated value by value (scan_patterns): from the start scales too
         // small for it, and all patterns where the scale was rounded so far that values lie beyond the bins (which reach 1.09
         // scales).  Of scale 0 all patterns are alike: the first wins with index 0.
@@ -126,34 +128,10 @@ void pb_encode_kernel(const uint32_t* __restrict__ dev, int S, float inv_tscale,
             later = s == 0.0f ? 0ull : !beyond ? left : S == 64 ? ~0ull : (1ull << S) - 1ull;
             left = 0;
         }
-        // A single pattern left has won; several are rated, ascending (a row that has none left repeats its last one), by their errors
-        // alone, all eight values of a lane in flight; the winner's indices follow.  (Errors and indices together, four values at a
-        // time: 108.5 us for encoding and decoding 131072 groups at 64 patterns, 105.0 us so.  The two-chain encoder, with fewer
-        // registers taken and nothing to leave out of the sums, does not gain: 64.1 us, 64.5 us so.)
-        uint32_t pattern = left != 0 ? (uint32_t)__builtin_ctzll(left) : 0u;
-        if ((left & (left - 1ull)) == 0ull) left = 0;
-        float best = __builtin_inff();
-        int rated = 0;
-        while (__builtin_amdgcn_ballot_w64(left != 0) != 0ull) {
-            const uint32_t p = left != 0 ? (uint32_t)__builtin_ctzll(left) : pattern;
-            float sse;
-            uint32_t none;
-            const uint32_t marks = rate_pattern<true, false, 8>(near + p * ecco::kSearchBins, pair + p * 64u, s2, v, skip, sse, none);
-            const uint64_t lanes = __builtin_amdgcn_ballot_w64((marks & ecco::kNearWide) != 0u);
-            if (lanes != 0ull && row_any(lanes, row)) {  // this pattern and those after it value by value
-                later |= left;
-                left = 0;
-            }
-            if (left != 0 && sse < best) {  // strict <: the lowest pattern wins a tie
-                best = sse;
-                pattern = p;
-            }
-            left &= left - 1ull;
-            if (++rated == kLookAfter && __builtin_amdgcn_ballot_w64(most_left(left, S)) != 0ull) {
-                later |= left;
-                left = 0;
-            }
-        }
+        float best;
+        uint64_t crowded;
+        uint32_t pattern = rate_left<true, 8>(L.hist + wave * kWaveRows * kHistStride, near, pair, v, smag, skip, left, S, lane, best, crowded);
+        later |= crowded;
         bool won = false;  // by the comparison value by value
         if (__builtin_amdgcn_ballot_w64(later != 0) != 0ull)
             scan_patterns(reinterpret_cast<float*>(L.hist + wave * kWaveRows * kHistStride), pair_at, v, __builtin_bit_cast(uint32_t, s2) & 0xFFFFu,
@@ -173,6 +151,7 @@ void pb_encode_kernel(const uint32_t* __restrict__ dev, int S, float inv_tscale,
         }
         if (s == 0.0f) idx = skip_again < 0 ? 0u : 15u << (28 - 4 * skip_again);
 
+        __builtin_amdgcn_s_setprio(kPriorityPack);
         // the codebook of least total length, lowest on ties
         uint32_t sum = 0;  // four bytes, at most 8 x 8 each
 #pragma unroll

@@ -220,7 +220,7 @@ __device__ __forceinline__ uint32_t rate_pattern(const uint8_t* near, uint32_t p
 
 // A rating by the table takes 500 to 1000 cycles for the four rows of a wavefront, by how many third candidates have to be looked
 // at; value by value it is 160 for one row, and about 3000 to begin with.  So a wavefront goes on that way where the bounds
-// have told hardly any patterns apart, which is looked at after this many ratings.
+// have told hardly any patterns apart, which is looked at after this many ratings (ahead of them where the patterns are dealt out).
 constexpr int kLookAfter = 4;
 __device__ __forceinline__ bool most_left(uint64_t left, int S) { return 4 * (__builtin_popcountll(left) + kLookAfter) > 3 * S; }
 // whether `lanes` (a ballot) holds a lane of row `row`
@@ -369,6 +369,98 @@ __device__ __forceinline__ void scan_patterns(float* recon, const uint32_t* pair
     wave_fence();
 }
 
+// ---- the patterns left over from the bounds ----------------------------------------------------------------------------
+// Rates the patterns `left` of the wavefront's four groups (a bit each; one alone has won and is not looked at) and returns each row's
+// best; `later` receives those that the table of nearest centroids does not serve.  A group has 1.3 to 2.1 patterns left on average
+// and the most of four groups 1.9 to 3.6, the most of a workgroup's 3.2 to 6, for which all others would wait at the next barrier: so the
+// patterns of the four groups are dealt out to the four rows of lanes, one after the other, whosever they are (1.5 to 2.1 rounds).
+// The values, bins and scales wait in LDS for this, with a list of (group, pattern); the least error of a group, the lowest
+// pattern on a tie, is kept by an atomic minimum.  at: kDealWords words of LDS of the wavefront.  131072 groups, 64 patterns: 63.9 -> 60.3
+// us, self-contained blocks encoded and decoded 102.0 -> 99.3 us; 8192 groups 9.7 -> 8.4 us.
+constexpr int kDealWords = 64 * 4 + 64 * 2 + kWaveRows * 2 + kWaveRows * 4 + kWaveRows * 64;
+static_assert(kDealWords <= kWaveRows * kHistStride, "over the wavefront's part of the histogram");
+template <bool kSkip, int kAtOnce>
+__device__ __forceinline__ uint32_t rate_left(uint32_t* at, const uint8_t* near, uint32_t pair, RowValues& v, uint32_t smax, int skip, uint64_t left, int S, int lane,
+                                              float& least, uint64_t& later) {
+    asm volatile("" : "+v"(lane));  // what is derived from the lane is formed here, not kept through the search
+    const int row = lane >> 4, l = lane & 15;
+    uint4* values = reinterpret_cast<uint4*>(at);
+    uint2* bins = reinterpret_cast<uint2*>(at + 256);
+    uint2* about = reinterpret_cast<uint2*>(at + 384);                        // per group: scale, place that counts as without error
+    unsigned long long* best = reinterpret_cast<unsigned long long*>(at + 392);  // per group: (error, pattern)
+    unsigned long long* wide = best + kWaveRows;                              // per group: patterns for a comparison value by value
+    uint32_t* list = at + 408;
+    uint32_t pattern = left != 0 ? (uint32_t)__builtin_ctzll(left) : 0u;
+    least = __builtin_inff();
+    if ((left & (left - 1ull)) == 0ull) left = 0;
+    // hardly any told apart in one of the groups: value by value is the faster way (kLookAfter)
+    const int count = __builtin_popcountll(left);
+    const bool most = __builtin_amdgcn_ballot_w64(count > kLookAfter && 4 * count > 3 * S) != 0ull && count > kLookAfter;
+    later = most ? left : 0ull;
+    left = most ? 0ull : left;
+    if (__builtin_amdgcn_ballot_w64(left != 0ull) == 0ull) return pattern;
+    wave_fence();
+    values[lane] = make_uint4(v.x[0], v.x[1], v.x[2], v.x[3]);
+    bins[lane] = make_uint2(v.bins[0], v.bins[1]);
+    if (l == 0) {
+        about[row].x = smax;
+        best[row] = ~0ull;
+        wide[row] = 0ull;
+    }
+    if (kSkip && skip >= 0) about[row].y = (uint32_t)(8 * l + skip);
+    uint32_t total = 0;
+#pragma unroll
+    for (int g = 0; g < kWaveRows; ++g) {  // lane p writes group g's pattern p
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)left, 16 * g), hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(left >> 32), 16 * g);
+        const uint32_t to = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, total));
+        const uint64_t m = ((uint64_t)hi << 32) | lo;
+        if ((m >> lane) & 1ull) list[to] = ((uint32_t)g << 8) | (uint32_t)lane;
+        total += (uint32_t)__builtin_popcountll(m);
+    }
+    wave_fence();
+    for (uint32_t i = 0; i < total; i += kWaveRows) {  // uniform; a row that has none left repeats the last one
+        const uint32_t item = list[min(i + (uint32_t)row, total - 1u)], g = item >> 8, p = item & 0xFFu;
+        const uint4 x = values[g * kRowLanes + l];
+        const uint2 b = bins[g * kRowLanes + l], a = about[g];
+        RowValues w;
+        w.x[0] = x.x; w.x[1] = x.y; w.x[2] = x.z; w.x[3] = x.w;
+        w.bins[0] = b.x; w.bins[1] = b.y;
+        float sse;
+        uint32_t none;
+        const uint32_t marks = rate_pattern<true, false, kAtOnce>(near + p * ecco::kSearchBins, pair + p * 64u, splat_half(a.x), w,
+                                                                  kSkip ? (int)a.y - 8 * l : -1, sse, none);
+        const uint64_t lanes = __builtin_amdgcn_ballot_w64((marks & ecco::kNearWide) != 0u);
+        const bool served = lanes == 0ull || !row_any(lanes, row);
+        if (l == 0) {
+            if (served) atomicMin(&best[g], ((unsigned long long)__builtin_bit_cast(uint32_t, sse) << 32) | p);
+            else atomicOr(&wide[g], 1ull << p);
+        }
+    }
+    wave_fence();
+    const unsigned long long found = best[row];
+    later |= wide[row];
+    // read again: kept, they would take six registers through the ratings
+    const uint4 x = values[lane];
+    const uint2 b = bins[lane];
+    v.x[0] = x.x; v.x[1] = x.y; v.x[2] = x.z; v.x[3] = x.w;
+    v.bins[0] = b.x; v.bins[1] = b.y;
+    wave_fence();
+    if (found != ~0ull) {
+        least = __builtin_bit_cast(float, (uint32_t)(found >> 32));
+        pattern = (uint32_t)found;
+    }
+    return pattern;
+}
+
+// Priority of a wavefront's instructions on its SIMD in the phases of a full search.  The workgroups of a compute unit start together and would
+// stay in step: all wait for table reads in the ratings, all meet at the barriers of the bounds.  With the ratings ahead of the histogram
+// and that ahead of the bounds, whose waits at barriers cost nobody else anything, one workgroup's ratings fill the other's waits: 131072
+// groups, 64 patterns 60.2 -> 54.5 us, 16 patterns 43.9 -> 39.9 us, self-contained blocks encoded and decoded 99.4 -> 91.2 us.  (Ratings in front and
+// all else alike 56.3 us, histogram in front 58.7 us; packing like the ratings 55.0 us.)  With three workgroups per compute unit (up to
+// 16 patterns) the histogram goes with the ratings: behind them, the last of one to two batches per workgroup waits (32768 groups 12.9 us, 13.2 us).
+constexpr int kPriorityBounds = 0, kPriorityPack = 1, kPriorityRate = 2;
+constexpr int priority_hist(bool three) { return three ? 2 : 1; }
+
 // ---- bounds on every pattern's error, and the patterns that can be the best ------------------------------------------
 // Workgroup-wide LDS of the bounds: histogram, partial sums of the matrix product, the pattern tiles' least upper bounds,
 // the groups' slack, the patterns left per group.  kOver: the partial sums lie over the histogram, at the price of a barrier,
@@ -464,6 +556,7 @@ __device__ __forceinline__ uint64_t patterns_left(const SearchLds& L, const Coef
     const int tile = wave / kParts, part = wave % kParts;
     float4_t sum[2], err[2];  // of groups 0..15 and 16..31
     __syncthreads();
+    __builtin_amdgcn_s_setprio(kPriorityBounds);
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
         sum[m] = float4_t{0.0f, 0.0f, 0.0f, 0.0f};

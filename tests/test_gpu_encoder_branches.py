@@ -149,6 +149,37 @@ def test_value_by_value(dev, S, n):
     assert np.array_equal(E.ecco_pb_encode(pm, t).cpu().numpy(), P.encode(om, x.view(np.uint16)))
 
 
+@pytest.mark.parametrize("S,alike,n", [(17, 3, 1003), (33, 16, 2001), (64, 2, 1501), (64, 16, 2113), (64, 40, 999), (64, 64, 515)])
+def test_patterns_dealt_out(dev, S, alike, n):
+    """Patterns of which up to `alike` are the same, so that as many are left over from the bounds and tie, the lowest of them wins,
+    beside groups with one left, none (all zero) and scales the tables do not serve: the patterns of a wavefront's four groups are
+    rated by whichever row is free."""
+    from oracle import oracle as O
+    from oracle import paper_block as P
+    rng = np.random.default_rng(S + alike)
+    some = np.sort(rng.standard_normal((S, 16)) / 3, axis=1)
+    some[:, 0], some[:, 15] = -1, 1
+    some = np.sort(np.clip(some, -1, 1), axis=1).astype(np.float16)
+    cent = some[np.minimum(np.arange(S), np.maximum(0, np.arange(S) - alike + 1))][rng.permutation(S)]  # the first one `alike` times
+    lens = np.full((S, 16), 4, np.uint8)
+    x = rng.standard_normal((n, 128)) * 0.02
+    own = rng.random(n) < 0.5
+    x[own] = some[0].astype(np.float64)[rng.integers(0, 16, (own.sum(), 128))] * 0.07 * (1 + 0.001 * rng.standard_normal((own.sum(), 128)))
+    x[rng.random(n) < 0.1] = 0.0
+    x[rng.random(n) < 0.1] *= 2.0 ** -9
+    x = x.astype(np.float16)
+    t = torch.from_numpy(x).to(dev)
+    m = E.ecco_model_to_device(E.ecco_model_create(cent, lens), 0)
+    want = O.encode(cent.view(np.uint16), lens, x.view(np.uint16))
+    blocks, meta = E.ecco_encode(m, t)
+    assert np.array_equal(meta.cpu().numpy().view(np.uint32), want[1])
+    assert np.array_equal(blocks.cpu().numpy(), want[0])
+    om = pb_model(P, S=S, texp=-9, seed=S)
+    om.cent[:] = cent[:, :15].view(np.uint16)
+    pm = E.ecco_pb_model_to_device(E.ecco_pb_model_create(om.cent, om.lens, om.kp_lens, om.texp), 0)
+    assert np.array_equal(E.ecco_pb_encode(pm, t).cpu().numpy(), P.encode(om, x.view(np.uint16)))
+
+
 def test_no_input_is_far_slower(dev):
     """Encoding must not collapse on padding (all-zero groups), on tiny scales or on groups that one value dominates: against
     ordinary weights at most 3 times for zeros (as fast, when measured) and 15 times where every value is compared with every
