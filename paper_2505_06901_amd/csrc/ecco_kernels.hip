@@ -194,6 +194,13 @@ typedef __attribute__((address_space(3))) uint32_t lds_u32;  // a 32-bit word in
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) u32x4 global_u4;   // sixteen bytes in global memory
 
+// Priority of a wavefront's instructions on its SIMD while it decodes (0 otherwise), in the batch-1 product and the plain attention:
+// wavefronts that store and request units, add up or meet at barriers then do so in the gaps of the others' table reads.  8192 x 28672
+// 64.9 -> 63.5 us, attention over 16 x 32 sequences and heads of 1000 tokens 66.3 -> 64.4 us (64 patterns), 48.1 -> 46.3 us (16).  The batched
+// product (11008 x 4096, batch 8: 18.0 -> 18.5 us), the standalone decoder (131072 groups 12.65 -> 12.87 us) and the grouped-query
+// attention (1024 tokens 20.6 -> 20.9 us) lose by it and go without.
+constexpr int kPriorityDecode = 1;
+
 // ---- the chain decoder ----------------------------------------------------------------------------------
 // Decodes kCount values starting at stream bit `start` of the staged block `w` (16 words, a zero
 // word, then two more readable words), calling sink(i, entry) with the table entry of each (length,
@@ -439,6 +446,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_kernel(const uint32_t* __re
         if (un < u_end) pre = load_unit(blocks, meta, row0 + un % band_rows, gpr, un / band_rows, lane);
         const Lane L = lane_setup(T, mw, S);
         float acc = 0.0f;
+        __builtin_amdgcn_s_setprio(kPriorityDecode);
         decode_chain<kLong, kHalf>(wbuf + blk * kStride, half ? L.second_start : 0u, L, [&](int i, uint32_t e) {
             const uint32_t xp = xs[i >> 1];
             const float xv = half_bits_f((i & 1) ? (xp >> 16) : (xp & 0xFFFFu));
@@ -447,6 +455,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_kernel(const uint32_t* __re
             // chain and all 64 table entries stay in registers
             if ((i & 3) == 3) asm volatile("" : "+v"(acc));
         });
+        __builtin_amdgcn_s_setprio(0);
         const float t = wave_sum(cg < gpr ? acc * L.scale : 0.0f);
         if (lane == 0) {
             if (col_tiles == 1) y[row0 + r] = t;
@@ -854,6 +863,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(kWa
                 const half2_t s2 = {sh, sh};
                 uint32_t pk = 0;
                 float acc = 0.0f;
+                __builtin_amdgcn_s_setprio(kPriorityDecode);
                 decode_chain<kLongK, kHalf>(wbuf + blk * kStride, half ? L.second_start : 0u, L, [&](int i, uint32_t e) {
                     if ((i & 1) == 0) {
                         pk = e >> 16;
@@ -865,6 +875,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(kWa
                         if ((i & 3) == 3) asm volatile("" : "+v"(acc));  // keeps the multiply-adds next to their table reads
                     }
                 });
+                __builtin_amdgcn_s_setprio(0);
                 acc += __shfl_xor(acc, 32);
                 const int t = u * kUnitBlocks + blk;
                 const float sc = t < span ? acc * inv_sqrt_d : -INFINITY;
@@ -905,6 +916,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(kWa
                 const float p = __expf(scores[u * kUnitBlocks + blk] - base);  // 0 for the tokens past the span
                 den += p;
                 uint32_t pk = 0;
+                __builtin_amdgcn_s_setprio(kPriorityDecode);
                 decode_chain<kLongV, kHalf>(wbuf + blk * kStride, half ? L.second_start : 0u, L, [&](int i, uint32_t e) {
                     if ((i & 1) == 0) {
                         pk = e >> 16;
@@ -915,6 +927,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(kWa
                         if ((i & 3) == 3) asm volatile("" : "+v"(o[i - 3]), "+v"(o[i - 2]), "+v"(o[i - 1]), "+v"(o[i]));  // as above
                     }
                 });
+                __builtin_amdgcn_s_setprio(0);
             }
             // The span's sums over the rows of 16 lanes (rows 0 and 1 hold values 0..63, rows 2 and 3 values 64..127).  At the first two
             // levels a lane keeps the values that match its own lane bit and sends the others to its partner, so that lane l of a row ends
