@@ -202,28 +202,32 @@ typedef __attribute__((address_space(1))) u32x4 global_u4;   // sixteen bytes in
 constexpr int kPriorityDecode = 1;
 
 // ---- the chain decoder ----------------------------------------------------------------------------------
-// Decodes kCount values starting at stream bit `start` of the staged block `w` (16 words, a zero
-// word, then two more readable words), calling sink(i, entry) with the table entry of each (length,
-// index, centroid).  Values are taken in runs of 4 (2 when the model has codes longer than 8 bits:
-// kLong).  A run works on a left-aligned 64-bit window made of the two words around its bit
-// position: at least 33 valid bits, enough for the longest run of codes plus the last peek, so
-// there is no refill test and no branch inside a run.  A run consumes at most 32 bits, so the next
-// run needs the same two words or the next two: the third word is requested one run ahead and the
-// window is rebuilt with two selects, which keeps the LDS latency of the stream itself off the
-// dependent chain (only the table reads remain on it).  The position is clamped to 512, where the
-// window's upper half is the zero word: bits past the block read as zero and arbitrary bytes decode
-// without touching other memory (the lower half of that last window is never looked at).
+// Decodes kCount values starting at stream bit `start` of the staged block `w` (16 words and a zero word), calling sink(i, entry)
+// with the table entry of each (length, index, centroid).  Values are taken in runs of 4 (2 when the model has codes longer than
+// 8 bits: kLong) out of a left-aligned 64-bit window, so there is no refill test and no branch inside a run.  A run consumes at
+// most 32 bits: its upper half is whole again when the run ends, and only the lower half is filled anew, from the words that
+// follow.  The next run's first table read and shift need the upper half alone, so the refill passes in the shadow of that read and the
+// dependent chain holds the table reads, a shift and two address instructions each.  (With the whole window rebuilt at the end of a
+// run, seven more dependent instructions per run: 8192 x 28672 64.1 -> 63.2 us, 4096 x 4096 7.55 -> 7.50 us, batch 8 over 11008 x 4096 18.4 -> 18.3 us,
+// append and attention over 8 x 32 sequences and heads of 4096 tokens 92.1 -> 91.0 us.  A shift of either half by v_alignbit, with 32 - length
+// in the table, costs an instruction per value: 65.0, 7.65, 19.5 and 94.1 us.)  The word after next is requested a run ahead: a run
+// moves by one word at most.  From the block's end on every word is the zero word: arbitrary bytes decode without touching other memory.
 template <bool kLong, int kCount, class Sink>
 __device__ __forceinline__ void decode_chain(const uint32_t* w, uint32_t start, const Lane& L, Sink&& sink) {
     constexpr int kRun = kLong ? 2 : 4;
     static_assert(kCount % kRun == 0, "chain length");
     static_assert(kRun * (kLong ? kMaxLen : kPeekBits) <= 32, "a run stays inside two words");
-    uint32_t pos = start;  // <= 511
-    uint32_t wi = pos >> 5;
-    uint32_t w0 = w[wi], w1 = w[wi + 1], w2 = w[wi + 2];
+    // The lower half of the window comes from the words w1 and w2, w1 being the first that begins at the position or behind it: with
+    // the position counted down from 0, the position itself is the shift count, also on a word's border.
+    int32_t down = -(int32_t)start;  // start <= 511
+    int32_t next = down >> 5;        // index of w1, negated
+    const auto word = [&](int32_t i) { return w[min((uint32_t)i, (uint32_t)kBlockWords)]; };
+    const uint32_t wi = start >> 5;
+    uint32_t w1 = word(-next), w2 = word(1 - next), w3 = word(2 - next);
+    uint64_t win = ((((uint64_t)w[wi] << 32) | (uint64_t)w[wi + 1]) << (start & 31u)) & 0xFFFFFFFF00000000ull;
+    win |= __builtin_amdgcn_alignbit(w1, w2, (uint32_t)down);
 #pragma unroll
     for (int i0 = 0; i0 < kCount; i0 += kRun) {
-        uint64_t win = (((uint64_t)w0 << 32) | (uint64_t)w1) << (pos & 31u);
         uint32_t used = 0;  // sum of the run's entries; its low byte is the number of bits consumed (at most 4 x 8 or 2 x 12)
 #pragma unroll
         for (int j = 0; j < kRun; ++j) {
@@ -250,13 +254,14 @@ __device__ __forceinline__ void decode_chain(const uint32_t* w, uint32_t start, 
             win <<= (e & 0xFFu);
         }
         if (i0 + kRun < kCount) {
-            pos = min(pos + (used & 0xFFu), (uint32_t)(kBlockWords * 32));
-            const uint32_t nwi = pos >> 5;  // wi or wi + 1
-            const bool adv = nwi != wi;
-            w0 = adv ? w1 : w0;
+            down -= (int32_t)(used & 0xFFu);
+            const int32_t now = down >> 5;  // next or next - 1
+            const bool adv = now != next;
             w1 = adv ? w2 : w1;
-            w2 = w[nwi + 2];  // used one run later at the earliest
-            wi = nwi;
+            w2 = adv ? w3 : w2;
+            w3 = word(2 - now);  // used one run later at the earliest
+            win = (win & 0xFFFFFFFF00000000ull) | (uint64_t)__builtin_amdgcn_alignbit(w1, w2, (uint32_t)down);
+            next = now;
         }
     }
 }
@@ -280,7 +285,7 @@ constexpr int kGemvThreads = 1024;
 // partial sums of a row's column tiles meet in LDS and are added in a fixed order.
 constexpr int kUnitBlocks = 32;
 constexpr int kWaves = kGemvThreads / 64;
-constexpr int kUnitWords = kUnitBlocks * kStride + 4;  // private payload buffer of a wavefront (+ the two words a chain may read past the last slot)
+constexpr int kUnitWords = kUnitBlocks * kStride + 4;  // private payload buffer of a wavefront, in whole pieces of 16 bytes
 constexpr int kXGroupWords = kGroup / 2 + 4;           // words per column group of x in LDS (skewed against bank conflicts)
 constexpr int kXLdsGroups = 128;                       // x is staged in LDS up to this many column groups, read from L2 beyond
 constexpr int kMaxBandRows = 128;
@@ -631,6 +636,8 @@ __global__ __launch_bounds__(kGemvThreads) void gemm_kernel(const uint32_t* __re
                                                             const uint4* __restrict__ blocks, const uint32_t* __restrict__ meta,
                                                             int rows, int gpr, int rb_per_wg, int batch,
                                                             const uint16_t* __restrict__ x, float* __restrict__ y) {
+    // (one more register than the allocation the body ends in: none of its 64-bit shifts may have its amount in the last one, see build.py)
+    asm volatile("" ::: "v97");
     extern __shared__ __align__(16) uint32_t smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -796,6 +803,8 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(kWa
     const uint32_t* __restrict__ dev_k, int Sk, const uint32_t* __restrict__ dev_v, int Sv, const uint16_t* __restrict__ q,
     const uint4* __restrict__ k_blocks, const uint32_t* __restrict__ k_meta, const uint4* __restrict__ v_blocks, const uint32_t* __restrict__ v_meta,
     const int32_t* __restrict__ seq_len, int H, int T_max, int table_words, int both, int span_max, float* __restrict__ out) {
+    // (one more register than the allocation the body ends in: none of its 64-bit shifts may have its amount in the last one, see build.py)
+    asm volatile("" ::: "v113");
     extern __shared__ __align__(16) uint32_t smem[];
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1071,6 +1080,8 @@ template <bool kLongK, bool kLongV, bool kWide, int kWaves>
 __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args) {
     constexpr int kThreads = kWaves * 64;
     constexpr int kOutputs = (kGqaMaxGroup * kGroup + kThreads - 1) / kThreads;  // output elements per thread
+    // (one more register than the allocation the body ends in: none of its 64-bit shifts may have its amount in the last one, see build.py)
+    asm volatile("" ::: "v121");
     const int Sk = args.Sk, Sv = args.Sv, B = args.B, Hq = args.Hq, Hkv = args.Hkv, T_max = args.T_max, both = args.both, table_words = args.table_words, span_max = args.span;
     extern __shared__ __align__(16) uint32_t smem[];
     const int grp = Hq / Hkv, sstride = gqa_score_stride(span_max), n_splits = gridDim.y;

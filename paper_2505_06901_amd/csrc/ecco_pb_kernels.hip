@@ -121,18 +121,22 @@ struct Walked {
     uint32_t end;      // where they start
 };
 // Step 1: walks the block staged in this lane's slot; put(i, word) receives the indices of values 8 i .. 8 i + 7.  Values are taken
-// in runs of four out of a 64-bit window (at least 33 valid bits); the words of the next run's window are requested before the
-// run, so that the dependent chain holds only the table reads.  A value is present iff its code ends inside the block; the
-// position stops at bit 512, where the window is zero.
+// in runs of four out of a 64-bit window whose upper half is whole again when a run ends (it consumes at most 32 bits); the lower
+// half is then filled from the words that follow, in the shadow of the next run's first table read, so that the dependent chain
+// holds only the table reads, a mask, a shift and an addition each (whole window rebuilt: seven more dependent instructions per run; 4096 x 4096
+// 14.0 -> 13.7 us).  A value is present iff its code ends inside the block; from its end on the stream is zero.
 template <class Put>
 __device__ __forceinline__ Walked walk_block(const uint32_t* w, const Tables& T, Put&& put) {
     const uint32_t first = w[0];
     const uint32_t kpe = T.kplut[(first >> 14) & 0xFFu], p = kpe >> 8;
     const uint32_t sv = T.fp8[first >> 24];  // the signed scale, FP16 bits
     const uint8_t* tab = T.lut + (p * kBooks + ((first >> 22) & 3u)) * 256u;
-    uint32_t fetch = 10u + (kpe & 0xFFu);    // where the next run is fetched from; stops at 512
-    uint32_t reach = fetch;                   // where the codes read so far end; keeps counting past 512
-    uint32_t wi = 0, w0 = first, w1 = w[1], w2 = w[2];
+    uint32_t reach = 10u + (kpe & 0xFFu);     // where the codes read so far end; below 32 to begin with
+    // the window's bits 0..31 are carried along, bits 32..63 come from the words w1, w2; `next` is the first of them, negated
+    int32_t next = -1;
+    uint32_t w1 = w[1], w2 = w[2], w3 = w[3];
+    uint64_t win = ((((uint64_t)first << 32) | (uint64_t)w1) << reach) & 0xFFFFFFFF00000000ull;
+    win |= __builtin_amdgcn_alignbit(w1, w2, 0u - reach);
     // of the last run that starts inside the block: how many came before it, where it starts, its table bytes
     uint32_t runs = 0, last_start = 0, last_run = 0;
 #pragma unroll
@@ -140,7 +144,6 @@ __device__ __forceinline__ Walked walk_block(const uint32_t* w, const Tables& T,
         uint32_t packed[2];  // four table bytes each
 #pragma unroll
         for (int h = 0; h < 8; h += 4) {
-            uint64_t win = (((uint64_t)w0 << 32) | (uint64_t)w1) << (fetch & 31u);
             uint32_t e[4], len[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -158,13 +161,13 @@ __device__ __forceinline__ Walked walk_block(const uint32_t* w, const Tables& T,
             const uint32_t used = (len[0] + len[1]) + (len[2] + len[3]);
             reach += used;
             if (i0 + h + 4 < kGroup) {
-                fetch = min(fetch + used, (uint32_t)kBlockBits);
-                const uint32_t nwi = fetch >> 5;  // wi or wi + 1
-                const bool adv = nwi != wi;
-                w0 = adv ? w1 : w0;
+                const int32_t now = -(int32_t)reach >> 5;  // next or next - 1
+                const bool adv = now != next;
                 w1 = adv ? w2 : w1;
-                w2 = w[nwi + 2u];  // used one run later at the earliest; past the pad it is never looked at
-                wi = nwi;
+                w2 = adv ? w3 : w2;
+                w3 = w[min(2u - (uint32_t)now, (uint32_t)kBlockWords)];  // used one run later at the earliest; from the pad on zero
+                win = (win & 0xFFFFFFFF00000000ull) | (uint64_t)__builtin_amdgcn_alignbit(w1, w2, 0u - reach);
+                next = now;
             }
         }
         uint32_t word = (packed[0] & 0xF0F0F0F0u) | ((packed[1] >> 4) & 0x0F0F0F0Fu);
