@@ -17,6 +17,7 @@
 #include <cstdint>
 
 #include "ecco.h"
+#include "ecco_stream.h"
 
 namespace {
 
@@ -54,6 +55,8 @@ __device__ __forceinline__ uint32_t dequant_pair(uint32_t d, half2_t s2, half2_t
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(q2, s2, z2));
 }
 
+// kStream, here and below: the FP16 values pass the caches by (ecco_stream.h says when)
+template <bool kStream>
 __global__ __launch_bounds__(kActThreads) void act_decode_kernel(const uint2* __restrict__ blocks, size_t n_pieces,
                                                                   uint4* __restrict__ dst) {
     const size_t stride = (size_t)gridDim.x * kActThreads;
@@ -74,7 +77,7 @@ __global__ __launch_bounds__(kActThreads) void act_decode_kernel(const uint2* __
         d = w.y ^ 0x40404040u;
         o.z = dequant_pair<0x0C010C00u>(d, s2, z2);
         o.w = dequant_pair<0x0C030C02u>(d, s2, z2);
-        dst[i] = o;
+        ecco_stream::store<kStream>(dst + i, o);
     }
 }
 
@@ -85,11 +88,12 @@ __device__ __forceinline__ uint32_t to_half_bits(float f) {
     return (uint32_t)__builtin_bit_cast(unsigned short, h);
 }
 
+template <bool kStream>
 __global__ __launch_bounds__(kActThreads) void act_encode_kernel(const uint4* __restrict__ src, size_t n_pieces,
                                                                  uint2* __restrict__ blocks) {
     const size_t stride = (size_t)gridDim.x * kActThreads;
     for (size_t i = (size_t)blockIdx.x * kActThreads + threadIdx.x; i < n_pieces; i += stride) {  // whole groups of 8 lanes pass or fail
-        const uint4 a = src[i];
+        const uint4 a = ecco_stream::load<kStream>(src + i);
         const uint32_t raw[4] = {a.x, a.y, a.z, a.w};
         float x[8];
 #pragma unroll
@@ -193,7 +197,7 @@ int ecco_act_encode(const uint16_t* src, size_t n_groups, void* blocks, void* st
     if (n_groups > ((size_t)1 << 40)) return ECCO_ESHAPE;
     if (!aligned(src, 16) || !aligned(blocks, 64)) return ECCO_EALIGN;
     const size_t n_pieces = n_groups * kPiecesPerBlock;
-    hipLaunchKernelGGL(act_encode_kernel, dim3(act_grid(n_pieces)), dim3(kActThreads), 0, static_cast<hipStream_t>(stream),
+    hipLaunchKernelGGL(ecco_stream::encoder_input(n_pieces * 16) ? act_encode_kernel<true> : act_encode_kernel<false>, dim3(act_grid(n_pieces)), dim3(kActThreads), 0, static_cast<hipStream_t>(stream),
                        reinterpret_cast<const uint4*>(src), n_pieces, static_cast<uint2*>(blocks));
     ECCO_HIP_CHECK(hipGetLastError());
     return ECCO_OK;
@@ -224,7 +228,7 @@ int ecco_act_decode(const void* blocks, size_t n_groups, uint16_t* dst, void* st
     if (n_groups > ((size_t)1 << 40)) return ECCO_ESHAPE;
     if (!aligned(blocks, 64) || !aligned(dst, 16)) return ECCO_EALIGN;
     const size_t n_pieces = n_groups * kPiecesPerBlock;
-    hipLaunchKernelGGL(act_decode_kernel, dim3(act_grid(n_pieces)), dim3(kActThreads), 0, static_cast<hipStream_t>(stream),
+    hipLaunchKernelGGL(ecco_stream::activations(dst, n_pieces * 16) ? act_decode_kernel<true> : act_decode_kernel<false>, dim3(act_grid(n_pieces)), dim3(kActThreads), 0, static_cast<hipStream_t>(stream),
                        static_cast<const uint2*>(blocks), n_pieces, reinterpret_cast<uint4*>(dst));
     ECCO_HIP_CHECK(hipGetLastError());
     return ECCO_OK;

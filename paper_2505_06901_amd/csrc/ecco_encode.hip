@@ -11,9 +11,11 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "ecco_launch.h"
 #include "ecco_rows.h"
+#include "ecco_stream.h"
 
 using namespace ecco;
 using namespace ecco_rows;
@@ -26,6 +28,7 @@ constexpr int kMinmaxBatch = kMinmaxThreads / 64 * kWaveRows;
 
 // where a kernel finds group i and where its block goes
 struct BulkIo {
+    static constexpr bool kDense = true;  // blocks are written one behind the other
     const uint32_t* src;
     uint32_t* blocks;
     uint32_t* meta;
@@ -39,6 +42,7 @@ struct BulkIo {
 };
 // one new token per sequence and head: group (b, h) goes to the slot seq_len[b] of its cache, if there is one
 struct AppendIo {
+    static constexpr bool kDense = false;
     const uint32_t* src;
     uint32_t* blocks;
     uint32_t* meta;
@@ -462,7 +466,8 @@ __device__ __forceinline__ uint32_t fine_indices(uint32_t fine, uint32_t pair, h
     return marks;
 }
 
-template <bool kFine, bool kLong, class Io>
+// kStream: the payloads are stored past the caches (ecco_stream.h says when)
+template <bool kFine, bool kLong, bool kStream, class Io>
 __global__ __launch_bounds__(kMinmaxThreads) void encode_minmax_kernel(Job<Io> j0, Job<Io> j1) {
     extern __shared__ __align__(16) uint32_t smem[];
     const Job<Io>& job = blockIdx.y ? j1 : j0;
@@ -508,7 +513,7 @@ __global__ __launch_bounds__(kMinmaxThreads) void encode_minmax_kernel(Job<Io> j
         const uint32_t word = pack_row<kLong>(T.enc + pattern * (kK * 4u), image, idx, l, smax, pattern, mw);
         size_t at;
         if (io.place(g, at)) {
-            io.blocks[at * kBlockWords + l] = word;
+            ecco_stream::store<kStream>(io.blocks + at * kBlockWords + l, word);
             if (l == 0) io.meta[at] = mw;
         }
 #pragma unroll
@@ -553,8 +558,13 @@ int launch_encode(bool minmax, const ecco_model* m0, const Io& io0, const ecco_m
         const size_t lds = minmax_lds_bytes(S, fine);
         const int per_cu = (int)std::min<size_t>(8, 160 * 1024 / lds);  // at 64 patterns six fit; at 16 eight took 38.8 us for 262144 groups, six 39.8 us
         const auto minmax_run = [&](auto kernel) { return run(kernel, lds, kMinmaxBatch, kMinmaxThreads, per_cu); };
-        if (fine) rc = lng ? minmax_run(encode_minmax_kernel<true, true, Io>) : minmax_run(encode_minmax_kernel<true, false, Io>);
-        else rc = lng ? minmax_run(encode_minmax_kernel<false, true, Io>) : minmax_run(encode_minmax_kernel<false, false, Io>);
+        const auto pick = [&](auto stream_tag) -> int {
+            constexpr bool kStream = decltype(stream_tag)::value;
+            if (fine) return lng ? minmax_run(encode_minmax_kernel<true, true, kStream, Io>) : minmax_run(encode_minmax_kernel<true, false, kStream, Io>);
+            return lng ? minmax_run(encode_minmax_kernel<false, true, kStream, Io>) : minmax_run(encode_minmax_kernel<false, false, kStream, Io>);
+        };
+        if constexpr (Io::kDense) rc = ecco_stream::encoded(groups * ECCO_BLOCK_BYTES) ? pick(std::true_type{}) : pick(std::false_type{});
+        else rc = pick(std::false_type{});
     } else {
         const size_t lds = search_lds_bytes(S);
         switch (search_tiles(S)) {

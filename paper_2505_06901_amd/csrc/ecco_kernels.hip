@@ -24,6 +24,7 @@
 #include <vector>
 
 #include "ecco_launch.h"
+#include "ecco_stream.h"
 
 using namespace ecco;
 
@@ -505,7 +506,8 @@ struct DecCfg {
 };
 inline size_t decode_lds_bytes(int S) { return (table_words(S) + (size_t)kDecWaves * DecCfg::kWaveWords) * 4; }
 
-template <bool kLong, bool kIndices>
+// kStream: the values are stored past the caches (ecco_stream.h says when)
+template <bool kLong, bool kIndices, bool kStream>
 __global__ __launch_bounds__(kDecWaves * 64) void decode_kernel(const uint32_t* __restrict__ dev, int S,
                                                               const uint4* __restrict__ blocks, const uint32_t* __restrict__ meta,
                                                               int n_groups, int units_per_wg, void* __restrict__ dst) {
@@ -590,7 +592,7 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_kernel(const uint32_t* 
                     const int row = (lane >> 3) + 8 * r, part = lane & 7;
                     const uint4 v = image[row * Cfg::kLinePieces + (part ^ (row & 7))];
                     if (u * kUnitBlocks + row < n_groups)
-                        *reinterpret_cast<uint4*>(obase + row * (kGroup * 2) + h * (kHalf * 2) + part * 16) = v;
+                        ecco_stream::store<kStream>(reinterpret_cast<uint4*>(obase + row * (kGroup * 2) + h * (kHalf * 2) + part * 16), v);
                 }
             }
         }
@@ -1457,8 +1459,9 @@ static int decode_common(const ecco_model* m, const void* blocks, const uint32_t
         ECCO_HIP_CHECK(hipGetLastError());
         return ECCO_OK;
     };
-    if (indices) return lng ? launch(decode_kernel<true, true>) : launch(decode_kernel<false, true>);
-    return lng ? launch(decode_kernel<true, false>) : launch(decode_kernel<false, false>);
+    if (indices) return lng ? launch(decode_kernel<true, true, false>) : launch(decode_kernel<false, true, false>);
+    if (ecco_stream::decoded(dst, n_groups * kGroup * 2)) return lng ? launch(decode_kernel<true, false, true>) : launch(decode_kernel<false, false, true>);
+    return lng ? launch(decode_kernel<true, false, false>) : launch(decode_kernel<false, false, false>);
 }
 
 int ecco_decode(const ecco_model* m, const void* blocks, const uint32_t* meta, size_t n_groups, uint16_t* dst, void* stream) {

@@ -18,6 +18,7 @@
 #include <type_traits>
 
 #include "ecco_pb_launch.h"
+#include "ecco_stream.h"
 
 namespace {
 
@@ -245,6 +246,8 @@ constexpr uint32_t kEntriesAtOnce = 4;
 constexpr int kDecodeWaveWords = kInfoWords + kPayWords + kUnit * kDecodeIdxStride;  // private LDS of a wavefront
 inline size_t decode_lds_bytes(int S) { return (table_words(S) + (size_t)kDecodeWaves * kDecodeWaveWords) * 4; }
 
+// kStream: the values are stored past the caches (ecco_stream.h says when)
+template <bool kStream>
 __global__ __launch_bounds__(kDecodeThreads) void pb_decode_kernel(const uint32_t* __restrict__ dev, int S, const uint4* __restrict__ blocks, size_t n_groups,
                                                                    int unit, uint4* __restrict__ dst) {
     extern __shared__ __align__(16) uint32_t smem[];
@@ -293,7 +296,7 @@ __global__ __launch_bounds__(kDecodeThreads) void pb_decode_kernel(const uint32_
                 for (int i = 0; i < 4; ++i)  // each product rounds once
                     v[i] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, r[q].c[2 * i] | (r[q].c[2 * i + 1] << 16)) * s2);
                 const int blk = b0 + q * kRows + row;
-                if (blk < count) out[blk * (kGroup / 8) + l] = make_uint4(v[0], v[1], v[2], v[3]);
+                if (blk < count) ecco_stream::store<kStream>(out + blk * (kGroup / 8) + l, make_uint4(v[0], v[1], v[2], v[3]));
             }
         }
         // The padded entries, a block per lane again, over the values just written, in the order of the stream: a later one at the
@@ -554,13 +557,14 @@ int ecco_pb_decode(const ecco_pb_model* m, const void* blocks, size_t n_groups, 
     if (!aligned(blocks, 64) || !aligned(dst, 16)) return ECCO_EALIGN;
     if (model_ready(m) != ECCO_OK) return ECCO_EINVAL;
     const size_t lds = decode_lds_bytes(m->S);
-    const int rc = ecco::allow_lds(pb_decode_kernel, m->device, lds);
+    const auto kernel = ecco_stream::decoded(dst, n_groups * kGroup * 2) ? pb_decode_kernel<true> : pb_decode_kernel<false>;
+    const int rc = ecco::allow_lds(kernel, m->device, lds);
     if (rc != ECCO_OK) return rc;
     const size_t cus = (size_t)ecco::cu_count(m->device);
     const int unit = unit_of(n_groups, cus * kDecodeWaves);
     const size_t units = (n_groups + unit - 1) / unit;
     const int grid = (int)std::min<size_t>((units + kDecodeWaves - 1) / kDecodeWaves, cus);
-    hipLaunchKernelGGL(pb_decode_kernel, dim3(grid), dim3(kDecodeThreads), lds, static_cast<hipStream_t>(stream), m->dev, m->S, static_cast<const uint4*>(blocks), n_groups,
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kDecodeThreads), lds, static_cast<hipStream_t>(stream), m->dev, m->S, static_cast<const uint4*>(blocks), n_groups,
                        unit, reinterpret_cast<uint4*>(dst));
     ECCO_HIP_CHECK(hipGetLastError());
     return ECCO_OK;

@@ -1,0 +1,80 @@
+"""Large outputs are stored past the caches; sizes and alignments around the lines where that begins and ends give what
+the ordinary stores of smaller calls over the same groups give, byte for byte."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+GROUP = 128
+
+
+def _weights(n, seed):
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    w = torch.randn(n, GROUP, device="cuda", generator=gen).mul_(0.02)
+    w[torch.rand(n, GROUP, device="cuda", generator=gen) < 1e-3] *= 10.0
+    w[::7, 9:] = 0.0  # mostly zero: short codes, and many padded entries in the self-contained format
+    return w.to(torch.float16)
+
+
+def _out(n, values, skip):
+    """n x values FP16 that begin `skip` values behind a line of memory, filled with a pattern no decoder leaves."""
+    import torch
+    return torch.full((n * values + skip + 64,), float("nan"), dtype=torch.float16, device="cuda")[skip:skip + n * values].view(n, values)
+
+
+def _same(a, b):
+    import torch
+    return torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+# 8 MiB and 128 MiB of FP16 are 32768 and 524288 groups; the pieces decoded for comparison lie on the other side of the line
+@pytest.mark.parametrize("n,piece,skip", [(32767, 32767, 0), (32768, 8192, 0), (33001, 9001, 0), (33001, 9001, 8), (524288, 30011, 0), (524291, 262144, 0)])
+def test_decoded_values(n, piece, skip):
+    import paper_2505_06901_amd as E
+    from paper_2505_06901_amd import workloads as W
+    fit = W.weight_matrix(2048, GROUP, 0.02, 1e-3, 10.0, 1)
+    w = _weights(n, n)
+    m = E.ecco_model_to_device(E.ecco_fit_patterns(fit, 16, 4, 1), 0)
+    blocks, meta = E.ecco_encode(m, w)
+    got = E.ecco_decode(m, blocks, meta, _out(n, GROUP, skip))
+    p = E.ecco_pb_model_to_device(E.ecco_pb_fit(fit, 16, 1), 0)
+    pb_blocks = E.ecco_pb_encode(p, w)
+    pb_got = E.ecco_pb_decode(p, pb_blocks, _out(n, GROUP, skip))
+    for i in range(0, n, piece):
+        e = min(i + piece, n)
+        assert _same(got[i:e], E.ecco_decode(m, blocks[i:e], meta[i:e], _out(e - i, GROUP, 0))), i
+        assert _same(pb_got[i:e], E.ecco_pb_decode(p, pb_blocks[i:e], _out(e - i, GROUP, 0))), i
+
+
+# 8 MiB of FP16 are 65536 groups of 64, 128 MiB 1048576
+@pytest.mark.parametrize("n,piece,skip", [(65535, 65535, 0), (65536, 8192, 0), (65541, 20003, 0), (65541, 20003, 8), (1048579, 65535, 0)])
+def test_activations(n, piece, skip):
+    import torch
+    import paper_2505_06901_amd as E
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randn(n, 64, device="cuda", generator=gen).mul_(10.0 ** (2.0 * torch.rand(64, device="cuda", generator=gen) - 1.0)).to(torch.float16)
+    blocks = E.ecco_act_encode(x)
+    got = E.ecco_act_decode(blocks, _out(n, 64, skip))
+    for i in range(0, n, piece):
+        e = min(i + piece, n)
+        assert torch.equal(blocks[i:e], E.ecco_act_encode(x[i:e])), i
+        assert _same(got[i:e], E.ecco_act_decode(blocks[i:e], _out(e - i, 64, 0))), i
+
+
+# 4 MiB of blocks are 65536 groups; models of both kinds of bins
+@pytest.mark.parametrize("n,piece", [(65535, 65535), (65536, 8192), (65551, 20003)])
+@pytest.mark.parametrize("offset", [0.0, 1.0])
+def test_minmax_blocks(n, piece, offset):
+    import torch
+    import paper_2505_06901_amd as E
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    x = (offset + torch.randn(n, GROUP, device="cuda", generator=gen).mul_(0.1)).to(torch.float16)
+    m = E.ecco_model_to_device(E.ecco_fit_patterns(x[:2048].cpu().numpy(), 16, 4, 1), 0)
+    blocks, meta = E.ecco_encode_minmax(m, x)
+    for i in range(0, n, piece):
+        e = min(i + piece, n)
+        b, mw = E.ecco_encode_minmax(m, x[i:e])
+        assert torch.equal(blocks[i:e], b) and torch.equal(meta[i:e], mw), i
+    assert _same(E.ecco_decode(m, blocks[:4096], meta[:4096]), E.ecco_decode(m, *E.ecco_encode_minmax(m, x[:4096])))
+    assert np.isfinite(E.ecco_decode(m, blocks, meta).float().cpu().numpy()).all()
