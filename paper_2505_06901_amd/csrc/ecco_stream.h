@@ -18,12 +18,14 @@ constexpr size_t kMiB = (size_t)1 << 20;
 // Outputs of the decoders may begin in the middle of a 128-byte line; a store of part of a line is better left to the cache.
 inline bool whole_lines(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 127u) == 0; }
 
-// Decoders of weights (both formats): 8 to 128 MiB of FP16.  Two-chain format: 4096 groups 5.6 -> 5.6 (8.2 -> 8.4), 32768 8.1 -> 7.2 (11.4 -> 11.0),
+// Decoders of weights (both formats): 8 to 128 MiB of FP16, and from 400 MiB on.  Two-chain format: 4096 groups 5.6 -> 5.6 (8.2 -> 8.4), 32768 8.1 -> 7.2 (11.4 -> 11.0),
 // 131072 14.9 -> 12.8 (21.4 -> 20.7), 352256 29.8 -> 25.2 (44.4 -> 44.8), 524288 43.2 -> 36.3 (65.9 -> 65.6); beyond, the reader
-// misses what the cache would have held for it: 786432 62.8 -> 51.2 (91.3 -> 98.3), 1048576 81.5 -> 64.2 (117 -> 125).
+// misses what the cache would have held for it: 786432 62.8 -> 51.2 (91.3 -> 98.3), 1048576 81.5 -> 64.2 (117 -> 125), 1572864 118 -> 121 (186 -> 188);
+// of what is far larger than the cache it holds nothing for a reader, who only waits for its write-back: 1835008 134 -> 133 (226 -> 211), 2097152 149 -> 147
+// (258 -> 236).
 // Self-contained blocks: 16384 10.4 -> 10.2 (13.2 -> 13.2), 65536 14.9 -> 12.6 (19.7 -> 18.1), 131072 19.4 -> 17.3 (26.4 -> 25.7),
-// 262144 30.8 -> 27.7 (41.2 -> 41.4), 524288 54.0 -> 50.5 (74.3 -> 75.9).
-inline bool decoded(const void* to, size_t bytes) { return bytes >= 8 * kMiB && bytes <= 128 * kMiB && whole_lines(to); }
+// 262144 30.8 -> 27.7 (41.2 -> 41.4), 524288 54.0 -> 50.5 (74.3 -> 75.9), 1835008 159 -> 154 (278 -> 243).
+inline bool decoded(const void* to, size_t bytes) { return whole_lines(to) && bytes >= 8 * kMiB && (bytes <= 128 * kMiB || bytes >= 400 * kMiB); }
 
 // Activation decoder: from 8 MiB of FP16 on.  65536 groups 4.5 -> 3.4 (7.8 -> 7.7), 131072 7.7 -> 5.4 (12.2 -> 11.8), 262144 12.7 -> 9.3 (18.4 -> 19.0),
 // 524288 21.9 -> 17.1 (31.2 -> 33.3), 1048576 39.6 -> 32.8 (59.8 -> 61.3), 2097152 76.1 -> 64.7 (117 -> 117).  Between 32 and 128 MiB the

@@ -28,8 +28,8 @@ def _same(a, b):
     return torch.equal(a.view(torch.int16), b.view(torch.int16))
 
 
-# 8 MiB and 128 MiB of FP16 are 32768 and 524288 groups; the pieces decoded for comparison lie on the other side of the line
-@pytest.mark.parametrize("n,piece,skip", [(32767, 32767, 0), (32768, 8192, 0), (33001, 9001, 0), (33001, 9001, 8), (524288, 30011, 0), (524291, 262144, 0)])
+# 8, 128 and 400 MiB of FP16 are 32768, 524288 and 1638400 groups; the pieces decoded for comparison lie on the other side of the line
+@pytest.mark.parametrize("n,piece,skip", [(32767, 32767, 0), (32768, 8192, 0), (33001, 9001, 0), (33001, 9001, 8), (524288, 30011, 0), (524291, 262144, 0), (1638403, 600001, 0)])
 def test_decoded_values(n, piece, skip):
     import paper_2505_06901_amd as E
     from paper_2505_06901_amd import workloads as W
