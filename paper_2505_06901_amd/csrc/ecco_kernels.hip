@@ -7,7 +7,7 @@
 // consumer -- the activation x[i] in the fused GEMV, the query q[i] in attention -- a register with
 // a static index.  Per value a lane does: peek 8 bits of its 64-bit window, one LDS table read that
 // returns code length, index and the centroid as FP16, the consumer's multiply-add, one 64-bit
-// shift; every four values the window is rebuilt from LDS at the chain's bit position.  Raw-mode
+// shift; every four values the window's lower half is filled anew from LDS.  Raw-mode
 // blocks run the same instructions against a 16-entry table with a 4-bit peek.  All kernels work
 // in units of 32 blocks per wavefront: 2 KB of payload fetched with coalesced 16-byte loads one
 // unit ahead, kept in a per-wavefront LDS buffer with a 17-word stride per block (word 16 is a

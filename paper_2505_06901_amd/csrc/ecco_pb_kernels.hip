@@ -7,10 +7,10 @@
 // activations come and the decoded values leave in whole lines.  (With the lanes of a matrix-core operand, 16 blocks at a time, the
 // reads of one instruction fall into 16 patterns' tables and cost twice as much: 16.8 us where this takes 15.7.)  The padded entries
 // are few (one block in ten has any) and are taken up a block per lane, not by the rows.
-// What bounds it: step 1 is a serial chain of 128 table reads per lane, 97 cycles each when nothing else is in the way (56 of the
-// read, 8.5 for each of the three dependent instructions, the window), 5.2 us; step 2 the vector instructions.  Product over
-// 4096 x 4096, one pass per wavefront, by events around replayed graphs: 4.6 us launch, tables and payload, 6 us walk, 2 us padded
-// entries, 3 us values, 15.6 us together; 18.1 us with the entries taken up by the rows and the index image beside the payload.
+// What bounds it: step 1 is a serial chain of 128 table reads per lane, about 82 cycles each when nothing else is in the way (56 of the
+// read, 8.5 for each of the three dependent instructions; 97 while the window was rebuilt on the chain); step 2 the vector instructions.  Product
+// over 4096 x 4096, one pass per wavefront, by events around replayed graphs, before that: 4.6 us launch, tables and payload, 6 us walk, 2 us
+// padded entries, 3 us values, 15.6 us together; 18.1 us with the entries taken up by the rows and the index image beside the payload.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
