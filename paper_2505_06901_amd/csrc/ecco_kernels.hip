@@ -24,13 +24,13 @@
 #include <vector>
 
 #include "ecco_launch.h"
+#include "ecco_plan.h"
 #include "ecco_stream.h"
 
 using namespace ecco;
 
 namespace {
 
-constexpr int kStride = kBlockWords + 1;  // LDS words per staged block (last one is a zero pad)
 constexpr int kHalf = kGroup / 2;         // values per chain
 
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
@@ -53,8 +53,6 @@ struct Tables {
     const __half* cent;       // [S][16]
 };
 __host__ __device__ constexpr size_t table_words(int S) { return (size_t)S * (kPeekEntries + kK + kK + kK / 2); }  // LDS words of a model's decode tables
-// LDS words of the decode tables: the long-code lists and the centroids are only copied for models that need them
-__host__ __device__ constexpr int decode_table_words(int S, bool lng) { return S * (kPeekEntries + kK + (lng ? kK + kK / 2 : 0)); }
 
 // copies `words` (a multiple of 4; both sides 16-byte aligned) from global memory to LDS with all
 // threads of the workgroup, four 16-byte loads in flight per thread
@@ -284,9 +282,7 @@ constexpr int kGemvThreads = 1024;
 // lane keeps the 64 activations of its chain in registers across those units, so a value costs one
 // mixed-precision FMA.  Rows are never split over workgroups:
 // partial sums of a row's column tiles meet in LDS and are added in a fixed order.
-constexpr int kUnitBlocks = 32;
 constexpr int kWaves = kGemvThreads / 64;
-constexpr int kUnitWords = kUnitBlocks * kStride + 4;  // private payload buffer of a wavefront, in whole pieces of 16 bytes
 constexpr int kXGroupWords = kGroup / 2 + 4;           // words per column group of x in LDS (skewed against bank conflicts)
 constexpr int kXLdsGroups = 128;                       // x is staged in LDS up to this many column groups, read from L2 beyond
 constexpr int kMaxBandRows = 128;
@@ -764,42 +760,6 @@ __global__ __launch_bounds__(kGemvThreads) void gemm_kernel(const uint32_t* __re
 // span (builds, sums, waits at barriers) is what this form cuts.  Append and attention, 8 x 32 sequences and heads, 64 patterns:
 // 4096 tokens 95.4 -> 91.9 us, 512 tokens 26.8 -> 24.7 us; 16 patterns: 4096 tokens 89.5 -> 84.7 us, 512 tokens 22.5 -> 20.5 us.  K and V enter as fp16(centroid * scale), formed two at a time by a packed FP16 multiply, which rounds exactly like the
 // FP32-multiply-then-round rule.
-constexpr int kSpanMax = 8192, kSpanLeast = 2048;
-
-// Two workgroups of eight wavefronts share a compute unit where there are workgroups for it and both models' tables fit half its
-// LDS: each decodes while the other builds or sums (16 patterns, 16 x 32 sequences and heads of 1024 tokens 59.2 -> 48.1 us).  Otherwise
-// one of as few wavefronts as take the fewest rounds over the units of a span: a table read costs less the more wavefronts
-// wait for theirs (one workgroup, 8192 tokens: 166.7 us with sixteen, 177.9 us with twelve), barriers and sums the more the more
-// meet (64 patterns, ten units: 21.5 us with twelve, 22.2 us with sixteen; two units: 15.8 us with eight, 16.5 us with twelve).  The
-// decoders of long codes need the registers of twelve.
-struct AttnPlan {
-    int waves;
-    int table_words;  // LDS words of the tables: both models', or the larger one's
-    int both;         // the V tables have their own place, behind those of K
-    int span;         // tokens per span, a multiple of 32
-    size_t lds;
-};
-inline AttnPlan attn_plan(int Sk, bool lk, int Sv, bool lv, size_t wgs, int T_max, int cus) {
-    const int wk = decode_table_words(Sk, lk), wv = decode_table_words(Sv, lv), units = (T_max + kUnitBlocks - 1) / kUnitBlocks;
-    const auto plan = [&](int waves, int lds_words) {
-        AttnPlan p;
-        const int fixed = waves * (kUnitWords + 2);
-        p.waves = waves;
-        p.both = wk + wv + fixed + std::min(kSpanLeast, units * kUnitBlocks) <= lds_words;
-        p.table_words = p.both ? wk + wv : std::max(wk, wv);
-        p.span = std::min({kSpanMax, units * kUnitBlocks, (lds_words - p.table_words - fixed) / kUnitBlocks * kUnitBlocks});
-        p.lds = (size_t)(p.table_words + fixed + p.span) * 4;
-        return p;
-    };
-    constexpr int kLdsWords = 160 * 1024 / 4;
-    if (lk || lv) return plan(12, kLdsWords);
-    const AttnPlan two = plan(8, kLdsWords / 2);
-    if (wgs > (size_t)cus && two.both) return two;
-    const auto rounds = [&](int waves) { return (units + waves - 1) / waves; };
-    const int waves = rounds(8) == rounds(16) ? 8 : rounds(12) == rounds(16) ? 12 : 16;
-    return plan(waves, kLdsWords);
-}
-
 template <bool kLongK, bool kLongV, int kWaves>
 __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(kWaves == 12 ? 3 : 4))) void kv_attend_kernel(
     const uint32_t* __restrict__ dev_k, int Sk, const uint32_t* __restrict__ dev_v, int Sv, const uint16_t* __restrict__ q,
@@ -1019,48 +979,6 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(kWa
 // 4096 tokens 34.9 us with a softmax of the workgroup between the passes, 33.3 us so; groups of 8, 1024 tokens 19.1 -> 17.9 us); otherwise the V tables replace the K tables in every span.  With one
 // range per sequence the result is normalised and written; otherwise (maximum, denominator, unnormalised output) of the range go to the
 // caller's workspace and kv_attend_combine_kernel merges them.
-constexpr int kGqaMaxGroup = 16;
-constexpr int kTileStride = 20;                 // words per row of the transposition tile: 32 tokens (16 words) + 4 of padding
-constexpr int kTileWords = 16 * kTileStride;
-constexpr int kGqaScoreWords = 7936;            // query heads x tokens of a span kept in LDS, at most
-constexpr int kRedTile = 276, kRedRow = 68;     // words of a tile, and of 16 lanes of it, in the sum over wavefronts (skewed over the banks)
-constexpr int gqa_state_words(int waves) { return 2 * waves * kGqaMaxGroup; }  // per wavefront and head: maximum, denominator
-
-__host__ __device__ constexpr int gqa_score_stride(int span) { return span + 4; }   // words: 16-byte aligned, and 4 modulo 32 so that heads fall on different banks
-// Two workgroups of eight wavefronts share a compute unit where there are workgroups for it and both models' tables fit half its
-// LDS (16 patterns, 16 x 32 heads in groups of 2, 1000 tokens: 57.4 -> 44.9 us).  Otherwise one of as few wavefronts as take the fewest
-// rounds over the units of a range (with 16 patterns: 16 units 23.6 us with sixteen, 24.6 us with twelve; 8 units 17.9 us with eight,
-// 19.3 us with twelve, 20.6 us with sixteen).  The decoders of long codes need the registers of twelve.
-struct GqaPlan {
-    int waves;
-    int table_words;  // LDS words of the tables: both models', or the larger one's
-    int both;         // the V tables have their own place, behind those of K
-    int span;         // tokens per span, a multiple of 32
-    size_t lds;
-};
-inline GqaPlan gqa_plan(int Sk, bool lk, int Sv, bool lv, int grp, size_t wgs, int units, int cus) {
-    const int wk = decode_table_words(Sk, lk), wv = decode_table_words(Sv, lv);
-    const auto plan = [&](int waves, int lds_words) {
-        const int fixed = waves * (kUnitWords + kTileWords) + gqa_state_words(waves);
-        GqaPlan p;
-        p.waves = waves;
-        const int round = std::min(units, waves) * kUnitBlocks;  // tokens that the wavefronts take at a time
-        p.both = wk + wv + fixed + grp * gqa_score_stride(round) <= lds_words;
-        p.table_words = p.both ? wk + wv : std::max(wk, wv);
-        const int scores = std::min(kGqaScoreWords, lds_words - p.table_words - fixed);
-        p.span = std::min((scores / grp - 4) & ~(kUnitBlocks - 1), units * kUnitBlocks);
-        if (p.span < units * kUnitBlocks && p.span > round) p.span -= p.span % round;
-        p.lds = (size_t)std::max(p.table_words + fixed + grp * gqa_score_stride(p.span), gqa_state_words(waves) + waves * 8 * kRedTile) * 4;
-        return p;
-    };
-    constexpr int kLdsWords = 160 * 1024 / 4;
-    if (lk || lv) return plan(12, kLdsWords);
-    const GqaPlan two = plan(8, kLdsWords / 2);
-    if (wgs > (size_t)cus && two.both) return two;
-    const auto rounds = [&](int waves) { return (units + waves - 1) / waves; };
-    const int waves = rounds(8) == rounds(16) ? 8 : rounds(12) == rounds(16) ? 12 : 16;
-    return plan(waves, kLdsWords);
-}
 
 // grid: (B * Hkv, n_splits).  The partial result of a split and query head is at
 // index (sequence * Hq + query head) * n_splits + split of the workspace: 128 outputs each, then (maximum, denominator) pairs.

@@ -554,6 +554,25 @@ def test_kv_attend_variants(dev, oracle, S, B, H, T, lengths):
         assert_attn_close(oracle, mv, one[2], one[3], seq[b:b + 1], 1, H, H, m, out[b:b + 1], want, b)
 
 
+@pytest.mark.parametrize("T_max", [2 ** 31 - 33, 2 ** 31 - 1])
+def test_largest_capacity(dev, oracle, T_max):
+    """One cache whose capacity is the largest an int holds (a stride that one sequence and head never multiplies): only the slots of
+    the units that seq_len reaches are there."""
+    n, T = 96, 70
+    k, v, mk, mv = _kv_setup(dev, oracle, 1, 1, n, 16)
+    kb, km, okb, okm = enc_both(dev, oracle, mk, k); vb, vm, ovb, ovm = enc_both(dev, oracle, mv, v)
+    q = W.activation(4, 128, 110).reshape(1, 4, 128)
+    seq = np.array([T], np.int32)
+    args = (mk.centroids, mk.code_lens, mv.centroids, mv.code_lens)
+    out = E.ecco_kv_attend(mk, mv, t16(q[:, :1], dev), kb, km, vb, vm, ti32(seq, dev), 1, 1, T_max).cpu().numpy()
+    want = oracle.kv_attend(*args, np.ascontiguousarray(q[:, :1]).view(np.uint16), okb, okm, ovb, ovm, seq, 1, 1, n)
+    assert_attn_close(oracle, mv, ovb, ovm, seq, 1, 1, 1, n, out, want)
+    want = oracle.kv_attend_gqa(*args, q.view(np.uint16), okb, okm, ovb, ovm, seq, 1, 4, 1, n)
+    for n_splits in (1, 3):
+        out = E.ecco_kv_attend_gqa(mk, mv, t16(q, dev), kb, km, vb, vm, ti32(seq, dev), 1, 4, 1, T_max, n_splits=n_splits).cpu().numpy()
+        assert_attn_close(oracle, mv, ovb, ovm, seq, 1, 4, 1, n, out, want, n_splits)
+
+
 def test_attend_ignores_cache_behind_seq_len(dev, oracle):
     """Slots at or behind seq_len may hold anything, NaN scales included: both attention kernels must not read them into the result."""
     B, H, T = 2, 2, 100
