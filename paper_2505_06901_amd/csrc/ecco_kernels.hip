@@ -956,9 +956,9 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(kWa
 
 // ---- grouped-query attention over compressed K / V, split over the tokens ---------------------------------
 // Several query heads share one key/value head (Section 5.3: with grouped-query attention the batched
-// matrix-vector products become small matrix products).  One workgroup per (sequence, key/value head, token range) decodes every K and V block of its range once and serves all grp = Hq / Hkv query heads of the group
-// with it, on the matrix cores, in 16 x 16 tiles (v_mfma_f32_16x16x32_f16): a lane's four accumulator registers per tile
-// leave room for four wavefronts per SIMD, where 32 x 32 tiles, half of whose columns no group of at most 16 heads can use,
+// matrix-vector products become small matrix products).  One workgroup per (sequence, key/value head, token range) decodes every K
+// and V block of its range once and serves all grp = Hq / Hkv query heads of the group with it, on the matrix cores, in 16 x 16 tiles (v_mfma_f32_16x16x32_f16): a lane's four accumulator registers per tile
+// leave room for three wavefronts per SIMD, four where workgroups share a compute unit, where 32 x 32 tiles, half of whose columns no group of at most 16 heads can use,
 // left two.
 // A unit is 32 tokens; lane l decodes chain (l / 16) % 2 of token l % 16 + 16 (l / 32).
 //   scores  S[token][head] = sum_dim K[token][dim] q[head][dim]: eight decoded values of a lane are its A operand (row
@@ -993,7 +993,7 @@ struct GqaArgs {
     const int32_t* seq_len;
     float* out;
     float* ws;
-    int Sk, Sv, B, Hq, Hkv, T_max, table_words, both, span;
+    int Sk, Sv, B, Hq, Hkv, T_max, table_words, both, span, step;
 };
 
 template <bool kLongK, bool kLongV, bool kWide, int kWaves>
@@ -1002,9 +1002,9 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
     constexpr int kOutputs = (kGqaMaxGroup * kGroup + kThreads - 1) / kThreads;  // output elements per thread
     // (one more register than the allocation the body ends in: none of its 64-bit shifts may have its amount in the last one, see build.py)
     asm volatile("" ::: "v121");
-    const int Sk = args.Sk, Sv = args.Sv, B = args.B, Hq = args.Hq, Hkv = args.Hkv, T_max = args.T_max, both = args.both, table_words = args.table_words, span_max = args.span;
+    const int Sk = args.Sk, Sv = args.Sv, B = args.B, Hq = args.Hq, Hkv = args.Hkv, T_max = args.T_max, both = args.both, table_words = args.table_words;
     extern __shared__ __align__(16) uint32_t smem[];
-    const int grp = Hq / Hkv, sstride = gqa_score_stride(span_max), n_splits = gridDim.y;
+    const int grp = Hq / Hkv, sstride = gqa_score_stride(args.span), n_splits = gridDim.y;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     float* state = reinterpret_cast<float*>(smem);  // [wavefront][16] maxima, [wavefront][16] denominators
@@ -1020,6 +1020,7 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
     const int T = max(0, min(args.seq_len[b], T_max));
     const int per_range = ((T + kUnitBlocks - 1) / kUnitBlocks + n_splits - 1) / n_splits;
     const int t_begin = min(T, split * per_range * kUnitBlocks), t_end = min(T, (split + 1) * per_range * kUnitBlocks);
+    const int span_max = t_end - t_begin <= args.span ? args.span : args.step;  // a range that one span holds is not cut
     // the lane's place in a unit, formed in either pass: kept, what is derived from it would take registers through both
     struct Place {
         int lane, n, slice, half, tok;  // n: matrix-core row or column; slice: k slice; half: chain of the lane's token `tok` of the unit
@@ -1471,7 +1472,7 @@ static int gqa_launch(const ecco_model* mk, const ecco_model* mv, const uint16_t
         if (rc != ECCO_OK) return rc;
         hipLaunchKernelGGL(kernel, dim3(B * Hkv, n_splits), dim3(plan.waves * 64), plan.lds, st,
                            GqaArgs{mk->dev, mv->dev, q, static_cast<const uint4*>(k_blocks), k_meta, static_cast<const uint4*>(v_blocks), v_meta, seq_len,
-                                   out, workspace, mk->S, mv->S, B, Hq, Hkv, T_max, plan.table_words, plan.both, plan.span});
+                                   out, workspace, mk->S, mv->S, B, Hq, Hkv, T_max, plan.table_words, plan.both, plan.span, plan.step});
         ECCO_HIP_CHECK(hipGetLastError());
         return ECCO_OK;
     };
@@ -1479,8 +1480,7 @@ static int gqa_launch(const ecco_model* mk, const ecco_model* mv, const uint16_t
         constexpr bool kWide = decltype(wide)::value;
         if (lk) return lv ? launch(kv_attend_gqa_kernel<true, true, kWide, 12>) : launch(kv_attend_gqa_kernel<true, false, kWide, 12>);
         if (lv) return launch(kv_attend_gqa_kernel<false, true, kWide, 12>);
-        return plan.waves == 8 ? launch(kv_attend_gqa_kernel<false, false, kWide, 8>)
-                               : plan.waves == 12 ? launch(kv_attend_gqa_kernel<false, false, kWide, 12>) : launch(kv_attend_gqa_kernel<false, false, kWide, 16>);
+        return plan.waves == 8 ? launch(kv_attend_gqa_kernel<false, false, kWide, 8>) : launch(kv_attend_gqa_kernel<false, false, kWide, 12>);
     };
     const int rc = Hq / Hkv > 8 ? pick(std::true_type{}) : pick(std::false_type{});
     if (rc != ECCO_OK || n_splits == 1) return rc;

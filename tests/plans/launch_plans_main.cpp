@@ -1,6 +1,7 @@
 // Walks the launch plans of the attention kernels (csrc/ecco_plan.h) over their whole range of sizes and prints the first one that
 // the kernels could not run: spans are positive multiples of 32 that make progress, everything fits the LDS that the plan asks for.
 #include <cstdio>
+#include <cstdlib>
 #include <vector>
 
 #include "ecco_plan.h"
@@ -40,14 +41,27 @@ int main() {
                                     const int units = ((T - 1) / kUnitBlocks + n_splits) / n_splits;
                                     const GqaPlan g = gqa_plan(S, lk, Sv, lv, grp, wgs, units, 256);
                                     const auto checkg = [&](bool ok, const char* what) { expect(ok, what, "grouped", S, lng, grp, wgs, (long long)units * 32, g.waves, g.span, g.lds); };
-                                    checkg(lng ? g.waves == 12 : g.waves == 8 || g.waves == 12 || g.waves == 16, "wavefronts");
+                                    checkg(g.waves == 12 || (!lng && g.waves == 8), "wavefronts");
                                     checkg(g.span >= kUnitBlocks && g.span % kUnitBlocks == 0, "span");
+                                    checkg(g.step >= kUnitBlocks && g.step % kUnitBlocks == 0 && g.step <= g.span, "step");
                                     checkg(g.table_words >= (g.both ? wk + wv : std::max(wk, wv)), "tables");
                                     checkg(g.lds <= 160 * 1024, "limit");
                                     checkg(g.lds >= 4 * ((size_t)g.table_words + (size_t)g.waves * (kUnitWords + kTileWords) + gqa_state_words(g.waves) + (size_t)grp * gqa_score_stride(g.span)), "room");
                                     checkg(g.lds >= 4 * ((size_t)gqa_state_words(g.waves) + (size_t)g.waves * 8 * kRedTile), "room of the sums");
                                 }
                         }
+    // Two workgroups share a compute unit (half of its LDS each) where no single sequence can outlast the work of
+    // a compute unit otherwise, not where a few long ones decide.
+    struct Shared { size_t wgs; int tokens; bool shared; };
+    for (const Shared c : {Shared{256, 512, false}, {257, 512, true}, {257, 513, false}, {288, 4096, false}, {384, 1024, false}, {512, 1024, true}, {1024, 4096, false}, {2048, 4096, true}, {2048, 500, true}}) {
+        const AttnPlan p = attn_plan(16, false, 16, false, c.wgs, c.tokens, 256);
+        expect((p.lds <= 80 * 1024 && p.waves == 8 && p.both) == c.shared, "sharing", "plain", 16, false, 1, c.wgs, c.tokens, p.waves, p.span, p.lds);
+        const GqaPlan g = gqa_plan(16, false, 16, false, 4, c.wgs, units_of(c.tokens), 256);
+        expect((g.lds <= 80 * 1024 && g.waves == 8 && g.both) == c.shared, "sharing", "grouped", 16, false, 4, c.wgs, c.tokens, g.waves, g.span, g.lds);
+    }
+    // a range that the LDS holds whole is one span, however long the capacity is; of longer ones every span but the last is whole rounds
+    const GqaPlan g = gqa_plan(64, false, 64, false, 8, 256, 32, 256);
+    expect(g.span >= 928 && g.step % (g.waves * kUnitBlocks) == 0, "spans", "grouped", 64, false, 8, 256, 1024, g.waves, g.span, g.lds);
     std::printf("%ld conditions hold\n", checked);
     return 0;
 }

@@ -515,8 +515,8 @@ def test_kv_attend_matches_oracle(dev, oracle):
 
 
 # Units are 32 tokens.  The wavefronts of a workgroup: eight where twelve or sixteen take as many rounds over the capacity's units or
-# where two workgroups share a compute unit (more workgroups than compute units, tables of both models in half the LDS), else twelve
-# where sixteen take as many, else sixteen; tables side by side (16 patterns) or in turn (64); spans of up to 8192 tokens.
+# where two workgroups share a compute unit (more workgroups than compute units and no more than 16 units for each that a compute unit
+# gets; tables of both models in half the LDS), else twelve where sixteen take as many, else sixteen; tables side by side (16 patterns) or in turn (64); spans of up to 8192 tokens.
 @pytest.mark.parametrize("S,B,H,T,lengths", [
     (16, 3, 2, 97, [97, 32, 1]),                # four units: eight wavefronts, some without units
     (16, 2, 2, 300, [300, 289]),                # ten: twelve
@@ -526,7 +526,8 @@ def test_kv_attend_matches_oracle(dev, oracle):
     (64, 2, 1, 8900, [8900, 8192]),             # and in each of two spans
     (40, 2, 1, 700, [700, 699]),                # 40 patterns: both tables fit one workgroup's LDS
     (16, 150, 2, 100, [100, 1, 0, 64, 65]),     # more workgroups than compute units: two per unit
-    (16, 150, 2, 7500, [7500, 7361, 33, 0, 7]), # two spans of such
+    (16, 150, 2, 7500, [7500, 7361, 33, 0, 7]), # as many of longer sequences: one per unit
+    (25, 640, 2, 2500, [2500, 2465, 33, 0, 7]), # five for each: two per unit, in two spans
 ])
 def test_kv_attend_variants(dev, oracle, S, B, H, T, lengths):
     """Against the oracle, and the same bits on a second launch.  The tokens are drawn from 512 encoded ones."""
@@ -650,17 +651,20 @@ def test_gqa_unequal_lengths(dev, oracle, lengths, T, grp, n_splits):
     assert_attn_close(oracle, mv, ovb, ovm, seq, B, Hkv * grp, Hkv, T, out, want)
 
 
-# Wavefronts by the rounds over the units (32 tokens) of a range: sixteen where twelve take more, eight where they take as many; eight,
-# two workgroups per compute unit, where there are more workgroups than compute units and both models' tables fit half the LDS.
+# Wavefronts by the units (32 tokens) of a range: eight up to eight, twelve beyond; eight, two workgroups per compute unit, where there are
+# more workgroups than compute units, no more than 16 units for each that a compute unit gets, and both models' tables fit half the LDS.
 @pytest.mark.parametrize("S,B,Hkv,grp,T,n_splits,lengths", [
-    (16, 2, 1, 4, 1000, 2, [1000, 513]),             # 16 units: sixteen
-    (16, 2, 1, 16, 1000, 2, [1000, 65]),             # more than eight heads: two products per unit; spans of a round
+    (16, 2, 1, 4, 1000, 2, [1000, 513]),             # 16 units: two rounds of twelve
+    (16, 2, 1, 16, 1000, 2, [1000, 65]),             # more than eight heads: two products per unit; spans of a round of twelve
     (64, 2, 1, 4, 1000, 2, [1000, 961]),             # tables in turn
     (64, 2, 1, 12, 3500, 2, [3500, 1025]),           # and in spans
     (40, 2, 1, 8, 4000, 1, [4000, 3999]),            # 40 patterns: both tables beside the scores of one round
-    (16, 100, 3, 2, 700, 1, [700, 1, 0, 32, 33]),    # two workgroups per compute unit
-    (16, 100, 3, 9, 2500, 1, [2500, 257, 0, 256]),   # in spans, two products per unit
-    (16, 50, 2, 3, 900, 3, [900, 1, 2, 65, 0]),      # with ranges to merge
+    (16, 100, 3, 2, 700, 1, [700, 1, 0, 32, 33]),    # more workgroups than compute units, of 22 units: one per unit
+    (16, 100, 3, 2, 500, 1, [500, 1, 0, 32, 33]),    # of 16: two per unit
+    (16, 100, 3, 9, 2500, 1, [2500, 257, 0, 256]),   # longer ranges: one per unit; in spans, two products per unit
+    (16, 256, 3, 9, 1100, 1, [1100, 257, 0, 512]),   # three for each: two per unit; in spans, two products per unit
+    (64, 4, 1, 8, 2000, 2, [2000, 1921, 1920, 1790]),  # ranges that one span just holds, and just not
+    (16, 50, 2, 3, 900, 3, [900, 1, 2, 65, 0]),      # two per unit, with ranges to merge
 ])
 def test_gqa_wavefronts(dev, oracle, S, B, Hkv, grp, T, n_splits, lengths):
     """Against the oracle, and the same bits on a second launch.  The tokens are drawn from 512 encoded ones."""
