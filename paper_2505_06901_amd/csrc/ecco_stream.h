@@ -18,12 +18,8 @@ constexpr size_t kMiB = (size_t)1 << 20;
 // Outputs of the decoders may begin in the middle of a 128-byte line; a store of part of a line is better left to the cache.
 inline bool whole_lines(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 127u) == 0; }
 
-// Decoders of weights (both formats): 8 to 128 MiB of FP16, and from 400 MiB on.  Two-chain format: 4096 groups 5.6 -> 5.6 (8.2 -> 8.4), 32768 8.1 -> 7.2 (11.4 -> 11.0),
-// 131072 14.9 -> 12.8 (21.4 -> 20.7), 352256 29.8 -> 25.2 (44.4 -> 44.8), 524288 43.2 -> 36.3 (65.9 -> 65.6); beyond, the reader
-// misses what the cache would have held for it: 786432 62.8 -> 51.2 (91.3 -> 98.3), 1048576 81.5 -> 64.2 (117 -> 125), 1572864 118 -> 121 (186 -> 188);
-// of what is far larger than the cache it holds nothing for a reader, who only waits for its write-back: 1835008 134 -> 133 (226 -> 211), 2097152 149 -> 147
-// (258 -> 236).
-// Self-contained blocks: 16384 10.4 -> 10.2 (13.2 -> 13.2), 65536 14.9 -> 12.6 (19.7 -> 18.1), 131072 19.4 -> 17.3 (26.4 -> 25.7),
+// Decoder of self-contained blocks: 8 to 128 MiB of FP16, and from 400 MiB on.
+// 16384 10.4 -> 10.2 (13.2 -> 13.2), 65536 14.9 -> 12.6 (19.7 -> 18.1), 131072 19.4 -> 17.3 (26.4 -> 25.7),
 // 262144 30.8 -> 27.7 (41.2 -> 41.4), 524288 54.0 -> 50.5 (74.3 -> 75.9), 1835008 159 -> 154 (278 -> 243).
 inline bool decoded(const void* to, size_t bytes) { return whole_lines(to) && bytes >= 8 * kMiB && (bytes <= 128 * kMiB || bytes >= 400 * kMiB); }
 

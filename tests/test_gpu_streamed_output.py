@@ -78,3 +78,51 @@ def test_minmax_blocks(n, piece, offset):
         assert torch.equal(blocks[i:e], b) and torch.equal(meta[i:e], mw), i
     assert _same(E.ecco_decode(m, blocks[:4096], meta[:4096]), E.ecco_decode(m, *E.ecco_encode_minmax(m, x[:4096])))
     assert np.isfinite(E.ecco_decode(m, blocks, meta).float().cpu().numpy()).all()
+
+
+def _time(fns, rounds=9):
+    """us per call of fns, as a graph replayed several times; the median."""
+    import torch
+    torch.cuda.synchronize()
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        for f in fns:
+            f()
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=st):
+            for f in fns:
+                f()
+        times = []
+        for _ in range(rounds + 1):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record(st)
+            g.replay()
+            b.record(st)
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b) * 1000 / len(fns))
+    return sorted(times[1:])[rounds // 2]
+
+
+@pytest.mark.parametrize("kind,groups", [("weights", 524288)])
+def test_reader_is_not_left_with_the_stores(kind, groups):
+    """A decoder and a plain reader of its output behind it take no longer than the decoder alone and the reader behind a fill of as many
+    bytes, which leaves them in the last-level cache.  Measured: 1.00; 1.15 when the output was stored past the caches.
+    Rotating over 900 MB, so that nothing is found there from the round before."""
+    import torch
+    import paper_2505_06901_amd as E
+    from paper_2505_06901_amd import workloads as W
+    n = 6
+    fit = W.weight_matrix(2048, GROUP, 0.02, 1e-3, 10.0, 1)
+    m = E.ecco_model_to_device(E.ecco_fit_patterns(fit, 64, 12, 1), 0)
+    blocks, meta = E.ecco_encode(m, _weights(groups, 1))
+    sets = [(blocks.clone(), meta.clone(), torch.empty((groups, GROUP), dtype=torch.float16, device="cuda")) for _ in range(n)]
+    decode = [lambda s=s: E.ecco_decode(m, *s) for s in sets]
+    sink = torch.empty(256, dtype=torch.int32, device="cuda")
+    read = [lambda s=s: E.ecco_read_stream(s[-1], sink) for s in sets]
+    fill = [lambda s=s: s[-1].fill_(0.5) for s in sets]
+    both = lambda x, y: [lambda f=f, g=g: (f(), g()) for f, g in zip(x, y)]
+    alone, together = _time(decode), _time(both(decode, read))
+    reader = _time(both(fill, read)) - _time(fill)
+    print("%s %d: decoder %.1f, reader behind a fill %.1f, decoder and reader %.1f us" % (kind, groups, alone, reader, together))
+    assert together <= 1.06 * (alone + reader)
