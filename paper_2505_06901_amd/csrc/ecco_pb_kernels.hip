@@ -300,7 +300,8 @@ __global__ __launch_bounds__(kDecodeThreads) void pb_decode_kernel(const uint32_
             }
         }
         // The padded entries, a block per lane again, over the values just written, in the order of the stream: a later one at the
-        // same position wins.  (A wavefront's stores to one address arrive in the order they were issued.)
+        // same position wins.  (A wavefront's stores to one address arrive in the order they were issued, those past the caches among them:
+        // the hint concerns where a line is kept, and the fence keeps the compiler from exchanging them.)
         wave_lds_fence();
         uint16_t* values = reinterpret_cast<uint16_t*>(out) + lane * kGroup;
         const uint32_t entries = lane < count ? b.entries : 0u;

@@ -1,10 +1,11 @@
 // Outputs and inputs that pass the caches by (non-temporal accesses), for gfx950, and from which size on.
 //
 // What a kernel stores the ordinary way stays in the L2 (4 MB for each of eight dies) and is written back when the kernel ends, and it takes the
-// place of other data in the last-level cache (256 MB).  Whole lines that are stored once can go to memory as they are
-// produced.  A reader that follows then finds them in memory instead of a cache, so the lines are drawn where the kernel and a plain
-// read of its whole output behind it take no longer together than before (within what runs differ by, but where stated).  All
-// times in us, graph replay over rotating buffers of 700 MB or more: ordinary -> streamed, in brackets with the reader.
+// place of other data in the last-level cache (256 MB).  Whole lines that are stored once can go to memory as they are produced, and the
+// kernel is done sooner; but a reader that follows then finds them in memory instead of a cache.  So the lines are drawn where the
+// kernel and what reads its output behind it take no longer together than before (where one such reader loses, it is said).  All
+// times in us, ordinary -> streamed, graphs of several launches, each replayed once untimed: a graph that follows another writes back
+// what that one has left dirty.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -18,10 +19,11 @@ constexpr size_t kMiB = (size_t)1 << 20;
 // Outputs of the decoders may begin in the middle of a 128-byte line; a store of part of a line is better left to the cache.
 inline bool whole_lines(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 127u) == 0; }
 
-// Decoder of self-contained blocks: 8 to 128 MiB of FP16, and from 400 MiB on.
-// 16384 10.4 -> 10.2 (13.2 -> 13.2), 65536 14.9 -> 12.6 (19.7 -> 18.1), 131072 19.4 -> 17.3 (26.4 -> 25.7),
-// 262144 30.8 -> 27.7 (41.2 -> 41.4), 524288 54.0 -> 50.5 (74.3 -> 75.9), 1835008 159 -> 154 (278 -> 243).
-inline bool decoded(const void* to, size_t bytes) { return whole_lines(to) && bytes >= 8 * kMiB && (bytes <= 128 * kMiB || bytes >= 400 * kMiB); }
+// Decoder of self-contained blocks: from 400 MiB of FP16 on.  Alone / with a plain reader / with products of 16 and 512 rows behind it, into one buffer used again
+// and again: 1835008 groups 157 -> 152 / 276 -> 238 / 273 -> 267, 368 -> 356.  What the cache holds is better left there: 131072
+// 18.5 -> 16.8 / 32.6 -> 32.3 / 31.8 -> 35.0, 46.4 -> 48.1; 352256 38.5 -> 36.9 / 53.9 -> 55.1 / 55.8 -> 60.9, 87.5 -> 91.4; 1048576 95.3 -> 90.2 / 136 -> 139 /
+// 155 -> 157, 207 -> 204.
+inline bool decoded(const void* to, size_t bytes) { return whole_lines(to) && bytes >= 400 * kMiB; }
 
 // Activation decoder: from 8 MiB of FP16 on.  65536 groups 4.5 -> 3.4 (7.8 -> 7.7), 131072 7.7 -> 5.4 (12.2 -> 11.8), 262144 12.7 -> 9.3 (18.4 -> 19.0),
 // 524288 21.9 -> 17.1 (31.2 -> 33.3), 1048576 39.6 -> 32.8 (59.8 -> 61.3), 2097152 76.1 -> 64.7 (117 -> 117).  Between 32 and 128 MiB the
