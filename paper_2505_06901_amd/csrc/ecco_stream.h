@@ -25,17 +25,18 @@ inline bool whole_lines(const void* p) { return (reinterpret_cast<uintptr_t>(p) 
 // 155 -> 157, 207 -> 204.
 inline bool decoded(const void* to, size_t bytes) { return whole_lines(to) && bytes >= 400 * kMiB; }
 
-// Activation decoder: from 8 MiB of FP16 on.  65536 groups 4.5 -> 3.4 (7.8 -> 7.7), 131072 7.7 -> 5.4 (12.2 -> 11.8), 262144 12.7 -> 9.3 (18.4 -> 19.0),
-// 524288 21.9 -> 17.1 (31.2 -> 33.3), 1048576 39.6 -> 32.8 (59.8 -> 61.3), 2097152 76.1 -> 64.7 (117 -> 117).  Between 32 and 128 MiB the
-// reader alone loses by it, but the codec's blocks stay in the cache: encoded and decoded 524288 groups 41.3 -> 38.1, 1048576 80.4 -> 69.8,
-// and with a writer of the input and a reader of the output around them 76.7 -> 71.7 and 148 -> 139.
-inline bool activations(const void* to, size_t bytes) { return bytes >= 8 * kMiB && whole_lines(to); }
+// Activation decoder: from 256 MiB of FP16 on.  Alone / with a plain reader / with a product of 256 columns behind it, into one buffer used again and again:
+// 2097152 groups 72.7 -> 69.4 / 111 -> 114 / 152 -> 144, over several buffers 74.9 -> 63.1 / 115 -> 119 / 154 -> 152, 3145728 113 -> 108 / 194 -> 177 / 233 ->
+// 233; encoded and decoded 157 -> 138 and 236 -> 226, with a writer in front and a plain reader behind, and the encoder's input streamed as well, 286 -> 278 and 460 ->
+// 429.  (A program that only decodes and reads 256 MiB loses 3 %.)  Below, readers lose: one buffer, 262144 11.0 -> 10.2 / 20.0 -> 22.7 / 35.5 -> 40.7, 524288
+// 17.3 -> 17.0 / 29.4 -> 30.3 / 54.4 -> 56.0, 1048576 34.2 -> 31.2 / 56.1 -> 59.2 / 78.5 -> 86.2.
+inline bool activations(const void* to, size_t bytes) { return bytes >= 256 * kMiB && whole_lines(to); }
 
-// Activation encoder's input: from 64 MiB on, so that it does not take the place of the blocks.  32768 groups 3.55 -> 3.85 and 262144
-// 13.0 -> 13.2 (not taken), 524288 22.2 -> 22.1, 1048576 41.5 -> 40.7, 1572864 61.3 -> 58.4, 2097152 81.3 -> 73.7; with a writer of the input in
-// front 22.7 -> 23.4 at 262144, then 41.2 -> 41.2, 92.8 -> 84.9, 133 -> 130, 176 -> 168.  (Writer, encoder, decoder and reader of 524288 groups take
-// 79.3 if only the decoder streams.)
-constexpr bool encoder_input(size_t bytes) { return bytes >= 64 * kMiB; }
+// Activation encoder's input: from 256 MiB on, so that it does not take the place of the blocks.  Alone / with a writer of the input in front / and a
+// reader of the blocks behind: 2097152 groups 77.9 -> 72.0 / 174 -> 171 / 195 -> 188, 4194304 176 -> 160 / 386 -> 361 / 423 -> 393.  Below, it depends on what is beside it:
+// 524288 21.5 -> 21.3 / 38.5 -> 39.6 / 45.2 -> 46.4; 786432 30.7 -> 30.8 / 69.6 -> 56.6 / 76.9 -> 67.7, but with the decoder and a product behind 92.7 -> 111;
+// 1048576 40.3 -> 39.4 / 89.7 -> 81.6 / 99.0 -> 99.5.
+constexpr bool encoder_input(size_t bytes) { return bytes >= 256 * kMiB; }
 
 // Blocks of the min/max encoder: from 4 MiB on.  16384 groups 4.9 -> 4.9 (7.3 -> 7.5), 65536 11.1 -> 10.6 (13.7 -> 13.6), 131072
 // 18.4 -> 17.6 (21.7 -> 21.3), 524288 62.1 -> 60.8 (68.2 -> 68.1).  The full search gains 1 % and goes without.

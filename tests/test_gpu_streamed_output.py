@@ -47,8 +47,8 @@ def test_decoded_values(n, piece, skip):
         assert _same(pb_got[i:e], E.ecco_pb_decode(p, pb_blocks[i:e], _out(e - i, GROUP, 0))), i
 
 
-# 8 MiB of FP16 are 65536 groups of 64, 128 MiB 1048576
-@pytest.mark.parametrize("n,piece,skip", [(65535, 65535, 0), (65536, 8192, 0), (65541, 20003, 0), (65541, 20003, 8), (1048579, 65535, 0)])
+# 8 MiB of FP16 are 65536 groups of 64, 128 MiB 1048576, 256 MiB 2097152
+@pytest.mark.parametrize("n,piece,skip", [(65535, 65535, 0), (65536, 8192, 0), (65541, 20003, 0), (65541, 20003, 8), (1048579, 65535, 0), (2097152, 1000003, 0), (2097157, 262144, 0), (2097157, 262144, 8)])
 def test_activations(n, piece, skip):
     import torch
     import paper_2505_06901_amd as E
@@ -104,7 +104,7 @@ def _time(fns, rounds=9):
     return sorted(times[1:])[rounds // 2]
 
 
-@pytest.mark.parametrize("kind,groups", [("weights", 524288), ("self-contained", 352256)])
+@pytest.mark.parametrize("kind,groups", [("weights", 524288), ("self-contained", 352256), ("activations", 1048576)])
 def test_reader_is_not_left_with_the_stores(kind, groups):
     """A decoder and a plain reader of its output behind it take no longer than the decoder alone and the reader behind a fill of as many
     bytes, which leaves them in the last-level cache.  Measured: 1.00 to 1.01; 1.10 to 1.17 when
@@ -117,6 +117,9 @@ def test_reader_is_not_left_with_the_stores(kind, groups):
     if kind == "weights":
         m = E.ecco_model_to_device(E.ecco_fit_patterns(fit, 64, 12, 1), 0)
         inputs, run, values = E.ecco_encode(m, _weights(groups, 1)), lambda s: E.ecco_decode(m, *s), GROUP
+    elif kind == "activations":
+        x = _weights(groups // 2, 1).view(groups, 64)
+        inputs, run, values = (E.ecco_act_encode(x),), lambda s: E.ecco_act_decode(*s), 64
     else:
         m = E.ecco_pb_model_to_device(E.ecco_pb_fit(fit, 64, 1), 0)
         inputs, run, values = (E.ecco_pb_encode(m, _weights(groups, 1)),), lambda s: E.ecco_pb_decode(m, *s), GROUP
