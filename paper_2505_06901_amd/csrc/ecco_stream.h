@@ -38,9 +38,10 @@ inline bool activations(const void* to, size_t bytes) { return bytes >= 256 * kM
 // 1048576 40.3 -> 39.4 / 89.7 -> 81.6 / 99.0 -> 99.5.
 constexpr bool encoder_input(size_t bytes) { return bytes >= 256 * kMiB; }
 
-// Blocks of the min/max encoder: from 4 MiB on.  16384 groups 4.9 -> 4.9 (7.3 -> 7.5), 65536 11.1 -> 10.6 (13.7 -> 13.6), 131072
-// 18.4 -> 17.6 (21.7 -> 21.3), 524288 62.1 -> 60.8 (68.2 -> 68.1).  The full search gains 1 % and goes without.
-constexpr bool encoded(size_t bytes) { return bytes >= 4 * kMiB; }
+// Blocks of the min/max encoder: from 8 to 16 MiB.  Alone / with a plain reader / with the decoder behind it, 16 patterns: 131072 groups 18.5 -> 18.1 / 21.0 -> 20.6 /
+// 30.6 -> 30.2, 262144 32.6 -> 31.7 / 34.9 -> 35.1 / 50.7 -> 50.2; not taken: 65536 11.3 -> 10.9 / 13.4 -> 13.4 / 19.2 -> 19.4, 524288 60.5 -> 60.9 / 63.7 -> 63.8 /
+// 91.0 -> 97.0.  The full search gains 1 % and goes without.
+constexpr bool encoded(size_t bytes) { return bytes >= 8 * kMiB && bytes <= 16 * kMiB; }
 
 typedef uint32_t word4_t __attribute__((ext_vector_type(4)));
 

@@ -62,8 +62,8 @@ def test_activations(n, piece, skip):
         assert _same(got[i:e], E.ecco_act_decode(blocks[i:e], _out(e - i, 64, 0))), i
 
 
-# 4 MiB of blocks are 65536 groups; models of both kinds of bins
-@pytest.mark.parametrize("n,piece", [(65535, 65535), (65536, 8192), (65551, 20003)])
+# 4 MiB of blocks are 65536 groups, 8 and 16 MiB 131072 and 262144; models of both kinds of bins
+@pytest.mark.parametrize("n,piece", [(65535, 65535), (65536, 8192), (65551, 20003), (131071, 50021), (131072, 60013), (262144, 130001), (262147, 131072)])
 @pytest.mark.parametrize("offset", [0.0, 1.0])
 def test_minmax_blocks(n, piece, offset):
     import torch
