@@ -73,6 +73,20 @@ __device__ inline void stage_vec(uint32_t* dst, const uint32_t* __restrict__ src
     }
 }
 
+// The thread's index, taken afresh: in a kernel that stages tables in every span, what is derived from it is then formed there and
+// does not take registers through the decode loops.
+__device__ __forceinline__ int fresh_thread() {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    return tid;
+}
+// A model's size, likewise: what the staging of a model with long codes derives from it (masks, addresses) would otherwise be formed
+// once for all spans and take scalar registers throughout
+__device__ __forceinline__ int fresh_size(int S) {
+    asm volatile("" : "+s"(S));
+    return S;
+}
+
 // Building the decode tables of a model in LDS from the compact tables in global memory.  Item
 // (p, k) is index k of pattern p: its code of length l <= 8 is the prefix of 2^(8-l) consecutive
 // 8-bit peeks, which all get the entry (centroid, index, length); a longer code marks its single
@@ -128,22 +142,9 @@ __device__ __forceinline__ Tables table_pointers(uint32_t* base, int S) {
 // beyond the items repeating the last one -- the build does not wait for the payload.  The lists of the long
 // codes and the centroids are copied only for a model that needs them (behind the payload, then).  The caller
 // synchronises afterwards.
-// A model's size, likewise: what the staging of a model with long codes derives from it (masks, addresses) would otherwise be formed
-// once for all spans and take scalar registers throughout
-__device__ __forceinline__ int fresh_size(int S) {
-    asm volatile("" : "+s"(S));
-    return S;
-}
 struct TableItems {
     TableItem item[2];
 };
-// The thread's index, taken afresh: in a kernel that stages tables in every span, what is derived from it is then formed there and
-// does not take registers through the decode loops.
-__device__ __forceinline__ int fresh_thread() {
-    int tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));
-    return tid;
-}
 __device__ __forceinline__ TableItems load_table_items(const uint32_t* __restrict__ dev, int S) {
     const int n = S * kK, tid = fresh_thread();
     TableItems t;
@@ -788,6 +789,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(kWa
     const uint32_t* __restrict__ dev_k, int Sk, const uint32_t* __restrict__ dev_v, int Sv, const uint16_t* __restrict__ q,
     const uint4* __restrict__ k_blocks, const uint32_t* __restrict__ k_meta, const uint4* __restrict__ v_blocks, const uint32_t* __restrict__ v_meta,
     const int32_t* __restrict__ seq_len, int H, int T_max, int table_words, int both, int span_max, float* __restrict__ out) {
+    static_assert(2 * kWaves * 64 >= kMaxS * kK, "load_table_items: two table items per thread cover every model");
     // (one more register than the allocation the body ends in: none of its 64-bit shifts may have its amount in the last one, see build.py)
     asm volatile("" ::: "v113");
     extern __shared__ __align__(16) uint32_t smem[];
@@ -1022,6 +1024,7 @@ struct GqaArgs {
 template <bool kLongK, bool kLongV, bool kWide, int kWaves>
 __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args) {
     constexpr int kThreads = kWaves * 64;
+    static_assert(2 * kThreads >= kMaxS * kK, "load_table_items: two table items per thread cover every model");
     constexpr int kOutputs = (kGqaMaxGroup * kGroup + kThreads - 1) / kThreads;  // output elements per thread
     // (one more register than the allocation the body ends in: none of its 64-bit shifts may have its amount in the last one, see build.py)
     asm volatile("" ::: "v121");
