@@ -521,11 +521,13 @@ __global__ __launch_bounds__(kMinmaxThreads) void encode_minmax_kernel(Job<Io> j
     }
 }
 
-// Whether a workgroup per group is the faster way.  On 256 compute units it takes 2.9 us + 6.4 ns per group for the full
-// search at S = 64, 2.7 us + 2.1 ns at S = 16, 2.1 us + 1.2 ns with the min/max selector, where the bulk kernels start at
-// 8.5, 6.5 and 3.9 us: the lines cross at 860, 1800 and 1500 groups.
+// Whether a workgroup per group is the faster way.  For the full search on 256 compute units it takes, in us at 512 / 768 / 1025 / 1537 groups, with up to 16
+// patterns 3.7 / 4.3 / 4.8 / 5.9, 32 4.6 / 5.5 / 6.8 / 8.7, 48 5.5 / 6.8 / 8.8 / 11.7, 64 6.3 / 8.1 / 11.1 / 14.6 (a sum per tile of patterns and per
+// group that a compute unit gets); the bulk kernel 6.2, 6.7, 7.4 and 7.6 over all of them: the lines cross at about 1700, 1050, 780 and 560 groups, seven, four, three
+// and two for each compute unit.  With the min/max selector 2.1 us + 1.2 ns per group and 3.9 us: 1500 groups.
 bool few_groups(bool minmax, size_t groups, int S, int cus) {
-    return minmax ? groups <= (size_t)cus * 6 : groups * (size_t)(S + 24) <= (size_t)cus * 288;
+    constexpr int kMost[] = {7, 4, 3, 2};  // by tiles of 16 patterns
+    return groups <= (size_t)cus * (minmax ? 6 : kMost[search_tiles(S) - 1]);
 }
 
 // ---- host side -----------------------------------------------------------------------------------------------------------

@@ -55,7 +55,10 @@ def groups(cent, n, seed):
 
 
 @pytest.mark.parametrize("S,n,long_codes", [(1, 1, False), (3, 47, True), (16, 31, False), (16, 4001, False), (17, 2405, True), (33, 3000, False),
-                                            (48, 33, False), (64, 1201, True), (64, 2113, False), (64, 20011, False)])
+                                            (48, 33, False), (64, 1201, True), (64, 2113, False), (64, 20011, False),
+                                            # a workgroup per group up to 7, 4, 3 and 2 of them for each of 256 compute units
+                                            (8, 1792, True), (8, 1793, False), (20, 1024, False), (20, 1025, True), (40, 768, False), (40, 769, False), (64, 512, False),
+                                            (64, 513, True)])
 def test_encode_and_minmax(dev, S, n, long_codes):
     from oracle import oracle as O
     cent, lens = model_tables(S, S, long_codes)
@@ -68,7 +71,7 @@ def test_encode_and_minmax(dev, S, n, long_codes):
         assert np.array_equal(blocks.cpu().numpy(), want[0]), name
 
 
-@pytest.mark.parametrize("B,H,Sk,Sv", [(3, 5, 16, 64), (7, 37, 33, 16), (16, 64, 64, 16), (16, 96, 3, 17)])
+@pytest.mark.parametrize("B,H,Sk,Sv", [(3, 5, 16, 64), (7, 37, 33, 16), (16, 64, 64, 16), (16, 96, 3, 17), (8, 32, 64, 5), (9, 32, 64, 48)])
 @pytest.mark.parametrize("minmax", [False, True])
 def test_append_with_unlike_models(dev, B, H, Sk, Sv, minmax):
     """Keys and values under models of different sizes; sequences whose position lies outside the cache write nothing."""
