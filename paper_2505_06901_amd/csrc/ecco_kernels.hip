@@ -431,7 +431,6 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_kernel(const uint32_t* __re
         if (i1 < gpr * 16) *reinterpret_cast<uint4*>(xt + (i1 >> 4) * kXGroupWords + (i1 & 15) * 4) = xp1;
     }
     if (lane < kUnitBlocks) wbuf[lane * kStride + kBlockWords] = 0u;  // zero pads of the private buffer
-    if (lane == 0) wbuf[kUnitBlocks * kStride] = 0u;
     const Tables T = table_pointers(smem, S);
     __syncthreads();
 
@@ -561,7 +560,6 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_kernel(const uint32_t* 
     for (; u < u_end; u += kDecWaves) {
         store_unit(wbuf, pre, lane);  // fenced: the previous unit's image has been read
         if (lane < kUnitBlocks) wbuf[lane * kStride + kBlockWords] = 0u;  // zero pads of the payload buffer (the image lay over them)
-        if (lane == 0) wbuf[kUnitBlocks * kStride] = 0u;
         wave_lds_fence();
         const uint32_t mw = pre.meta;
         if (u + kDecWaves < u_end) pre = load_unit(blocks, meta, 0, n_groups, u + kDecWaves, lane);
@@ -681,7 +679,6 @@ __global__ __launch_bounds__(kGemvThreads) void gemm_kernel(const uint32_t* __re
         for (int i = tid; i < S * kK / 2; i += kGemvThreads) smem[S * (kPeekEntries + 2 * kK) + i] = dev[D.cent() + i];
     }
     if (lane < kUnitBlocks) wbuf[lane * kStride + kBlockWords] = 0u;
-    if (lane == 0) wbuf[kUnitBlocks * kStride] = 0u;
     const Tables T = table_pointers(smem, S);
     __syncthreads();
 
@@ -815,7 +812,6 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(kWa
         {
             const int lane = fresh_thread() & 63, blk = lane & (kUnitBlocks - 1), half = lane >> 5;
             if (lane < kUnitBlocks) wbuf[lane * kStride + kBlockWords] = 0u;  // zero pads of the private buffer (the sums lay over it)
-            if (lane == 0) wbuf[kUnitBlocks * kStride] = 0u;
             int u = wave;
             const auto load_k = [&](int at) { pre = load_unit(k_blocks, k_meta, bh, T_max, unit0 + min(at, units - 1), lane); };
             if (!both) {
@@ -1040,7 +1036,6 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
     float* scores = reinterpret_cast<float*>(k_tables + table_words + kWaves * (kUnitWords + kTileWords));  // [grp][sstride]
     uint32_t* v_tables = k_tables + (both ? decode_table_words(Sk, kLongK) : 0);
     if (lane < kUnitBlocks) wbuf[lane * kStride + kBlockWords] = 0u;
-    if (lane == 0) wbuf[kUnitBlocks * kStride] = 0u;
 
     const int b = blockIdx.x / Hkv, hkv = blockIdx.x - b * Hkv, split = blockIdx.y, bkv = blockIdx.x;
     const int T = max(0, min(args.seq_len[b], T_max));

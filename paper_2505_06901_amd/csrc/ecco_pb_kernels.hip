@@ -265,7 +265,6 @@ __global__ __launch_bounds__(kDecodeThreads) void pb_decode_kernel(const uint32_
     PieceLoad pre;
     const Tables T = stage_tables<kDecodeThreads>(smem, dev, S, [&] { pre = load(u); });
     pay[lane * kSlot + kBlockWords] = 0u;
-    if (lane < 4) pay[kUnit * kSlot + lane] = 0u;
     __syncthreads();
 
     for (; u < n_units; u += step) {
@@ -377,7 +376,6 @@ __global__ __launch_bounds__(kGemvThreads) void pb_gemv_kernel(const uint32_t* _
     };
     const Tables T = stage_tables<kGemvThreads>(smem, dev, S, [&] { load(blocks + (size_t)band0 * gpr * 4, min(chunk, band1 - band0) * gpr, wave * unit); });
     pay[lane * kSlot + kBlockWords] = 0u;
-    if (lane < 4) pay[kUnit * kSlot + lane] = 0u;
     __syncthreads();
 
     constexpr int kAhead = 4;
