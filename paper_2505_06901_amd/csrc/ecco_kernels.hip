@@ -25,6 +25,7 @@
 
 #include "ecco_launch.h"
 #include "ecco_plan.h"
+#include "ecco_stream.h"
 
 using namespace ecco;
 
@@ -513,11 +514,6 @@ __global__ __launch_bounds__(kGemvThreads) void gemv_kernel(const uint32_t* __re
 // lies over the wavefront's 2.2 KB payload buffer, which is dead once both chains are decoded (the
 // values wait in registers meanwhile), so sixteen wavefronts fit 160 KB of LDS next to the S = 64
 // tables; the zero words that bound each block's stream are rewritten with every unit.
-// The values are stored the ordinary way: what reads them next -- in prefill a matrix product -- finds them in the last-level cache.  Past the
-// caches (non-temporal), into one buffer used again and again, in us alone / with a plain reader / with products of 16 and 512 rows behind the kernel: 32768
-// groups 7.6 -> 7.4 / 12.8 -> 12.2 / 18.1 -> 20.3, 25.5 -> 26.5; 131072 13.0 -> 12.3 / 29.8 -> 28.7 / 27.0 -> 29.6, 40.4 -> 44.9; 352256 25.6 -> 26.3 /
-// 40.6 -> 42.8 / 43.4 -> 47.9, 73.2 -> 80.5; 1048576 73.3 -> 74.3 / 106 -> 119 / 126 -> 133, 182 -> 184.  Beyond the cache readers gain (1835008 130 -> 130 /
-// 221 -> 206 / 238 -> 229, 329 -> 323), but a step of other kernels between two decodings does not (0.436 -> 0.450 ms).
 constexpr int kDecWaves = 16;
 struct DecCfg {
     static constexpr int kLinePieces = kHalf / 8;                  // 16-byte pieces of a chain's 128 output bytes
@@ -526,7 +522,8 @@ struct DecCfg {
 };
 inline size_t decode_lds_bytes(int S) { return (table_words(S) + (size_t)kDecWaves * DecCfg::kWaveWords) * 4; }
 
-template <bool kLong, bool kIndices>
+// kThrough: the values are written through (ecco_stream.h says when and why)
+template <bool kLong, bool kIndices, bool kThrough>
 __global__ __launch_bounds__(kDecWaves * 64) void decode_kernel(const uint32_t* __restrict__ dev, int S,
                                                               const uint4* __restrict__ blocks, const uint32_t* __restrict__ meta,
                                                               int n_groups, int units_per_wg, void* __restrict__ dst) {
@@ -609,7 +606,9 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_kernel(const uint32_t* 
                 for (int r = 0; r < 4; ++r) {
                     const int row = (lane >> 3) + 8 * r, part = lane & 7;
                     const uint4 v = image[row * Cfg::kLinePieces + (part ^ (row & 7))];
-                    if (u * kUnitBlocks + row < n_groups)
+                    if constexpr (kThrough)
+                        ecco_stream::store_through(obase, (uint32_t)min(n_groups - u * kUnitBlocks, kUnitBlocks) * (kGroup * 2), row * (kGroup * 2) + h * (kHalf * 2) + part * 16, v);
+                    else if (u * kUnitBlocks + row < n_groups)
                         *reinterpret_cast<uint4*>(obase + row * (kGroup * 2) + h * (kHalf * 2) + part * 16) = v;
                 }
             }
@@ -1399,8 +1398,9 @@ static int decode_common(const ecco_model* m, const void* blocks, const uint32_t
         ECCO_HIP_CHECK(hipGetLastError());
         return ECCO_OK;
     };
-    if (indices) return lng ? launch(decode_kernel<true, true>) : launch(decode_kernel<false, true>);
-    return lng ? launch(decode_kernel<true, false>) : launch(decode_kernel<false, false>);
+    if (indices) return lng ? launch(decode_kernel<true, true, false>) : launch(decode_kernel<false, true, false>);
+    if (ecco_stream::weights(dst, n_groups * kGroup * 2) == ecco_stream::Stores::kThrough) return lng ? launch(decode_kernel<true, false, true>) : launch(decode_kernel<false, false, true>);
+    return lng ? launch(decode_kernel<true, false, false>) : launch(decode_kernel<false, false, false>);
 }
 
 int ecco_decode(const ecco_model* m, const void* blocks, const uint32_t* meta, size_t n_groups, uint16_t* dst, void* stream) {

@@ -246,8 +246,9 @@ constexpr uint32_t kEntriesAtOnce = 4;
 constexpr int kDecodeWaveWords = kInfoWords + kPayWords + kUnit * kDecodeIdxStride;  // private LDS of a wavefront
 inline size_t decode_lds_bytes(int S) { return (table_words(S) + (size_t)kDecodeWaves * kDecodeWaveWords) * 4; }
 
-// kStream: the values are stored past the caches (ecco_stream.h says when)
-template <bool kStream>
+// kStores: how the values are stored (ecco_stream.h says when and why)
+using ecco_stream::Stores;
+template <Stores kStores>
 __global__ __launch_bounds__(kDecodeThreads) void pb_decode_kernel(const uint32_t* __restrict__ dev, int S, const uint4* __restrict__ blocks, size_t n_groups,
                                                                    int unit, uint4* __restrict__ dst) {
     extern __shared__ __align__(16) uint32_t smem[];
@@ -295,12 +296,14 @@ __global__ __launch_bounds__(kDecodeThreads) void pb_decode_kernel(const uint32_
                 for (int i = 0; i < 4; ++i)  // each product rounds once
                     v[i] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, r[q].c[2 * i] | (r[q].c[2 * i + 1] << 16)) * s2);
                 const int blk = b0 + q * kRows + row;
-                if (blk < count) ecco_stream::store<kStream>(out + blk * (kGroup / 8) + l, make_uint4(v[0], v[1], v[2], v[3]));
+                const uint4 v4 = make_uint4(v[0], v[1], v[2], v[3]);
+                if constexpr (kStores == Stores::kThrough) ecco_stream::store_through(out, (uint32_t)count * (kGroup * 2), (uint32_t)(blk * (kGroup * 2) + l * 16), v4);
+                else if (blk < count) ecco_stream::store<kStores == Stores::kPast>(out + blk * (kGroup / 8) + l, v4);
             }
         }
         // The padded entries, a block per lane again, over the values just written, in the order of the stream: a later one at the
-        // same position wins.  (A wavefront's stores to one address arrive in the order they were issued, those past the caches among them:
-        // the hint concerns where a line is kept, and the fence keeps the compiler from exchanging them.)
+        // same position wins.  (A wavefront's stores to one address arrive in the order they were issued, those that are written
+        // through or past the caches among them: that says where a line is kept, and the fence keeps the compiler from exchanging them.)
         wave_lds_fence();
         uint16_t* values = reinterpret_cast<uint16_t*>(out) + lane * kGroup;
         const uint32_t entries = lane < count ? b.entries : 0u;
@@ -556,7 +559,8 @@ int ecco_pb_decode(const ecco_pb_model* m, const void* blocks, size_t n_groups, 
     if (!aligned(blocks, 64) || !aligned(dst, 16)) return ECCO_EALIGN;
     if (model_ready(m) != ECCO_OK) return ECCO_EINVAL;
     const size_t lds = decode_lds_bytes(m->S);
-    const auto kernel = ecco_stream::decoded(dst, n_groups * kGroup * 2) ? pb_decode_kernel<true> : pb_decode_kernel<false>;
+    const Stores stores = ecco_stream::self_contained(dst, n_groups * kGroup * 2);
+    const auto kernel = stores == Stores::kPast ? pb_decode_kernel<Stores::kPast> : stores == Stores::kThrough ? pb_decode_kernel<Stores::kThrough> : pb_decode_kernel<Stores::kCached>;
     const int rc = ecco::allow_lds(kernel, m->device, lds);
     if (rc != ECCO_OK) return rc;
     const size_t cus = (size_t)ecco::cu_count(m->device);

@@ -1,11 +1,12 @@
-// Outputs and inputs that pass the caches by (non-temporal accesses), for gfx950, and from which size on.
+// Outputs that are written through, and outputs and inputs that pass the caches by (non-temporal accesses), for gfx950, by sizes.
 //
-// What a kernel stores the ordinary way stays in the L2 (4 MB for each of eight dies) and is written back when the kernel ends, and it takes the
-// place of other data in the last-level cache (256 MB).  Whole lines that are stored once can go to memory as they are produced, and the
-// kernel is done sooner; but a reader that follows then finds them in memory instead of a cache.  So the lines are drawn where the
-// kernel and what reads its output behind it take no longer together than before (where one such reader loses, it is said).  All
-// times in us, ordinary -> streamed, graphs of several launches, each replayed once untimed: a graph that follows another writes back
-// what that one has left dirty.
+// What a kernel stores the ordinary way stays in the L2 (4 MB for each of eight dies) and is written back when the kernel ends; the last-level
+// cache (256 MB) then holds it for a reader.  Whole lines that are stored once can be written through as they are produced (a store of
+// device scope): the kernel does not end with the write-back, and the reader finds them where it did before.  Past the caches the kernel is done sooner
+// still, but a reader finds its lines in memory: that is for outputs that the last-level cache would not hold anyway.  The lines are drawn
+// where the kernel and what reads its output behind it take no longer together than with ordinary stores (where one such reader loses, it
+// is said).  All times in us, graphs of several launches, each replayed once untimed: a graph that follows another writes back what that
+// one has left dirty.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -19,11 +20,22 @@ constexpr size_t kMiB = (size_t)1 << 20;
 // Outputs of the decoders may begin in the middle of a 128-byte line; a store of part of a line is better left to the cache.
 inline bool whole_lines(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 127u) == 0; }
 
-// Decoder of self-contained blocks: from 400 MiB of FP16 on.  Alone / with a plain reader / with products of 16 and 512 rows behind it, into one buffer used again
-// and again: 1835008 groups 157 -> 152 / 276 -> 238 / 273 -> 267, 368 -> 356.  What the cache holds is better left there: 131072
-// 18.5 -> 16.8 / 32.6 -> 32.3 / 31.8 -> 35.0, 46.4 -> 48.1; 352256 38.5 -> 36.9 / 53.9 -> 55.1 / 55.8 -> 60.9, 87.5 -> 91.4; 1048576 95.3 -> 90.2 / 136 -> 139 /
-// 155 -> 157, 207 -> 204.
-inline bool decoded(const void* to, size_t bytes) { return whole_lines(to) && bytes >= 400 * kMiB; }
+enum class Stores { kCached, kThrough, kPast };
+
+// Decoder of two-chain blocks: written through from 4 to 96 MiB of FP16.  Ordinary -> through, into one buffer used again and again, alone / with a plain reader /
+// with products of 16 and 512 rows behind it: 32768 groups 7.6 -> 6.9 / 13.2 -> 12.6 / 18.0 -> 17.2, 25.4 -> 24.7; 131072 13.1 -> 11.6 / 28.9 -> 28.0 /
+// 26.7 -> 25.6, 41.3 -> 40.3; 352256 23.4 -> 22.3 / 38.6 -> 37.8 / 40.9 -> 40.1, 76.3 -> 75.4; not taken: 4096 5.7 -> 5.7, 524288 42.0 -> 43.2 / 63.9 -> 64.8 /
+// 64.8 -> 65.7, 103 -> 103.  Past the caches every product loses up to 256 MiB (352256 25.9 / 40.7 / 46.0, 81.2), and beyond, a step of other kernels between two
+// decodings (0.436 -> 0.450 ms for 448 MiB).
+inline Stores weights(const void* to, size_t bytes) { return whole_lines(to) && bytes >= 4 * kMiB && bytes <= 96 * kMiB ? Stores::kThrough : Stores::kCached; }
+
+// Decoder of self-contained blocks: written through below 400 MiB, past the caches from there on.  Ordinary -> through, as above: 4096 groups 9.7 -> 9.8,
+// 32768 11.8 -> 10.8 / 17.2 -> 16.1 / 22.0 -> 20.5, 30.6 -> 29.1; 131072 18.2 -> 15.5 / 30.3 -> 30.2 / 31.3 -> 30.2, 46.5 -> 44.8; 352256 38.0 -> 34.5 / 54.8 -> 51.3 /
+// 55.4 -> 53.6, 87.8 -> 85.4; 1048576 96.6 -> 91.6 / 141 -> 137 / 159 -> 156, 221 -> 219.  Ordinary -> past: 1835008 157 -> 144 / 276 -> 235 / 288 -> 269, 368 -> 349, but
+// 131072 18.2 -> 16.4 / 30.3 -> 30.6 / 31.3 -> 34.1, 46.5 -> 48.5.
+inline Stores self_contained(const void* to, size_t bytes) {
+    return !whole_lines(to) || bytes < 4 * kMiB ? Stores::kCached : bytes < 400 * kMiB ? Stores::kThrough : Stores::kPast;
+}
 
 // Activation decoder: from 256 MiB of FP16 on.  Alone / with a plain reader / with a product of 256 columns behind it, into one buffer used again and again:
 // 2097152 groups 72.7 -> 69.4 / 111 -> 114 / 152 -> 144, over several buffers 74.9 -> 63.1 / 115 -> 119 / 154 -> 152, 3145728 113 -> 108 / 194 -> 177 / 233 ->
@@ -50,6 +62,12 @@ template <bool kStream>
 __device__ __forceinline__ void store(uint4* to, uint4 v) {
     if constexpr (kStream) __builtin_nontemporal_store(word4_t{v.x, v.y, v.z, v.w}, reinterpret_cast<word4_t*>(to));
     else *to = v;
+}
+// Sixteen bytes at byte `at` of the `bytes` behind `base` (both the same for the wavefront's lanes) that are written through to memory; nothing is
+// stored beyond them.  The descriptor's last word says raw 32-bit elements, the operand 16 device scope (sc1).
+__device__ __forceinline__ void store_through(void* base, uint32_t bytes, uint32_t at, uint4 v) {
+    const auto r = __builtin_amdgcn_make_buffer_rsrc(base, 0, (int)bytes, 0x00020000);
+    __builtin_amdgcn_raw_buffer_store_b128(word4_t{v.x, v.y, v.z, v.w}, r, (int)at, 0, 16);
 }
 template <bool kStream>
 __device__ __forceinline__ void store(uint32_t* to, uint32_t v) {

@@ -1,5 +1,5 @@
-"""Large outputs are stored past the caches; sizes and alignments around the lines where that begins and ends give what
-the ordinary stores of smaller calls over the same groups give, byte for byte."""
+"""Outputs are written through or stored past the caches by their sizes; sizes and alignments around the lines where that begins and ends
+give what the ordinary stores of smaller calls over the same groups give, byte for byte, and nothing beside the output is written."""
 import numpy as np
 import pytest
 
@@ -17,10 +17,21 @@ def _weights(n, seed):
     return w.to(torch.float16)
 
 
+BEHIND = 4096  # values behind an output: more than a unit of any decoder
+
+
 def _out(n, values, skip):
-    """n x values FP16 that begin `skip` values behind a line of memory, filled with a pattern no decoder leaves."""
+    """n x values FP16 that begin `skip` values behind a line of memory, filled with a pattern no decoder leaves, as everything around them is."""
     import torch
-    return torch.full((n * values + skip + 64,), float("nan"), dtype=torch.float16, device="cuda")[skip:skip + n * values].view(n, values)
+    return torch.full((64 + skip + n * values + BEHIND,), float("nan"), dtype=torch.float16, device="cuda")[64 + skip:64 + skip + n * values].view(n, values)
+
+
+def _guarded(t):
+    """Whether what lies around the output (its storage beyond it) still holds the pattern."""
+    import torch
+    whole = torch.tensor([], dtype=t.dtype, device=t.device).set_(t.untyped_storage())
+    first = t.storage_offset()
+    return bool(whole[:first].isnan().all()) and bool(whole[first + t.numel():].isnan().all())
 
 
 def _same(a, b):
@@ -28,8 +39,9 @@ def _same(a, b):
     return torch.equal(a.view(torch.int16), b.view(torch.int16))
 
 
-# 8, 128 and 400 MiB of FP16 are 32768, 524288 and 1638400 groups; the pieces decoded for comparison lie on the other side of the line
-@pytest.mark.parametrize("n,piece,skip", [(32767, 32767, 0), (32768, 8192, 0), (33001, 9001, 0), (33001, 9001, 8), (524288, 30011, 0), (524291, 262144, 0), (1638403, 600001, 0)])
+# 4, 8, 96, 128 and 400 MiB of FP16 are 16384, 32768, 393216, 524288 and 1638400 groups; the pieces decoded for comparison lie on the other
+# side of the line (ordinary stores), or are others
+@pytest.mark.parametrize("n,piece,skip", [(16383, 16000, 0), (16384, 16383, 0), (16385, 16001, 0), (16411, 15999, 8), (32767, 16383, 0), (32768, 8192, 0), (33001, 9001, 0), (33001, 9001, 8), (393216, 16383, 0), (393217, 16379, 0), (524288, 30011, 0), (524291, 262144, 0), (1638399, 600001, 0), (1638403, 600001, 0)])
 def test_decoded_values(n, piece, skip):
     import paper_2505_06901_amd as E
     from paper_2505_06901_amd import workloads as W
@@ -41,6 +53,7 @@ def test_decoded_values(n, piece, skip):
     p = E.ecco_pb_model_to_device(E.ecco_pb_fit(fit, 16, 1), 0)
     pb_blocks = E.ecco_pb_encode(p, w)
     pb_got = E.ecco_pb_decode(p, pb_blocks, _out(n, GROUP, skip))
+    assert _guarded(got) and _guarded(pb_got)
     for i in range(0, n, piece):
         e = min(i + piece, n)
         assert _same(got[i:e], E.ecco_decode(m, blocks[i:e], meta[i:e], _out(e - i, GROUP, 0))), i
@@ -48,7 +61,7 @@ def test_decoded_values(n, piece, skip):
 
 
 # 8 MiB of FP16 are 65536 groups of 64, 128 MiB 1048576, 256 MiB 2097152
-@pytest.mark.parametrize("n,piece,skip", [(65535, 65535, 0), (65536, 8192, 0), (65541, 20003, 0), (65541, 20003, 8), (1048579, 65535, 0), (2097152, 1000003, 0), (2097157, 262144, 0), (2097157, 262144, 8)])
+@pytest.mark.parametrize("n,piece,skip", [(65535, 60001, 0), (65536, 8192, 0), (65541, 20003, 0), (65541, 20003, 8), (1048579, 65535, 0), (2097152, 1000003, 0), (2097157, 262144, 0), (2097157, 262144, 8)])
 def test_activations(n, piece, skip):
     import torch
     import paper_2505_06901_amd as E
@@ -56,6 +69,7 @@ def test_activations(n, piece, skip):
     x = torch.randn(n, 64, device="cuda", generator=gen).mul_(10.0 ** (2.0 * torch.rand(64, device="cuda", generator=gen) - 1.0)).to(torch.float16)
     blocks = E.ecco_act_encode(x)
     got = E.ecco_act_decode(blocks, _out(n, 64, skip))
+    assert _guarded(got)
     for i in range(0, n, piece):
         e = min(i + piece, n)
         assert torch.equal(blocks[i:e], E.ecco_act_encode(x[i:e])), i
@@ -63,7 +77,7 @@ def test_activations(n, piece, skip):
 
 
 # 4 MiB of blocks are 65536 groups, 8 and 16 MiB 131072 and 262144; models of both kinds of bins
-@pytest.mark.parametrize("n,piece", [(65535, 65535), (65536, 8192), (65551, 20003), (131071, 50021), (131072, 60013), (262144, 130001), (262147, 131072)])
+@pytest.mark.parametrize("n,piece", [(65535, 60001), (65536, 8192), (65551, 20003), (131071, 50021), (131072, 60013), (262144, 130001), (262147, 131072)])
 @pytest.mark.parametrize("offset", [0.0, 1.0])
 def test_minmax_blocks(n, piece, offset):
     import torch
@@ -76,7 +90,6 @@ def test_minmax_blocks(n, piece, offset):
         e = min(i + piece, n)
         b, mw = E.ecco_encode_minmax(m, x[i:e])
         assert torch.equal(blocks[i:e], b) and torch.equal(meta[i:e], mw), i
-    assert _same(E.ecco_decode(m, blocks[:4096], meta[:4096]), E.ecco_decode(m, *E.ecco_encode_minmax(m, x[:4096])))
     assert np.isfinite(E.ecco_decode(m, blocks, meta).float().cpu().numpy()).all()
 
 
@@ -104,10 +117,10 @@ def _time(fns, rounds=9):
     return sorted(times[1:])[rounds // 2]
 
 
-@pytest.mark.parametrize("kind,groups", [("weights", 524288), ("self-contained", 352256), ("activations", 1048576)])
+@pytest.mark.parametrize("kind,groups", [("weights", 262144), ("weights", 524288), ("self-contained", 352256), ("activations", 1048576)])
 def test_reader_is_not_left_with_the_stores(kind, groups):
     """A decoder and a plain reader of its output behind it take no longer than the decoder alone and the reader behind a fill of as many
-    bytes, which leaves them in the last-level cache.  Measured: 1.00 to 1.01; 1.10 to 1.17 when
+    bytes, which leaves them in the last-level cache.  Measured: 0.98 to 1.02; 1.10 to 1.17 when
     the output was stored past the caches.  Rotating over 650 MB, so that nothing is found there from the round before."""
     import torch
     import paper_2505_06901_amd as E
