@@ -555,6 +555,44 @@ def test_kv_attend_variants(dev, oracle, S, B, H, T, lengths):
         assert_attn_close(oracle, mv, one[2], one[3], seq[b:b + 1], 1, H, H, m, out[b:b + 1], want, b)
 
 
+@pytest.mark.parametrize("long_k,long_v", [(True, False), (False, True), (True, True)])
+@pytest.mark.parametrize("S,T,lengths", [
+    (5, 1000, [1000, 500, 333]),     # tables of both models side by side
+    (64, 1000, [1000, 500, 333]),    # in turn
+    (64, 8900, [8900, 8193, 1]),     # in each of two spans
+])
+def test_kv_attend_long_codes_variants(dev, oracle, long_k, long_v, S, T, lengths):
+    """Codes of up to 12 bits in K, in V and in both: against the oracle, and the same bits on every one of several launches.  The tokens
+    are drawn from 512 encoded ones."""
+    n, B = 512, len(lengths)
+    rng = np.random.default_rng(S + T)
+    k, v, mk, mv = _kv_setup(dev, oracle, 1, 1, n, S)
+    cent, lens, probs = _skewed_model(oracle, S, 3)
+    long_m = E.ecco_model_to_device(E.ecco_model_create(cent, lens), 0)
+    if long_k:
+        mk, k = long_m, _skewed_data(cent, probs, n, 11).reshape(1, 1, n, 128)
+    if long_v:
+        mv, v = long_m, _skewed_data(cent, probs, n, 12).reshape(1, 1, n, 128)
+    kb, km, okb, okm = enc_both(dev, oracle, mk, k); vb, vm, ovb, ovm = enc_both(dev, oracle, mv, v)
+    seq = np.array(lengths, np.int32)
+    pick = rng.integers(0, n, (2, B * T))
+    at = torch.from_numpy(pick).to(dev)
+    caches = [kb.view(n, 64)[at[0]], km.view(-1)[at[0]], vb.view(n, 64)[at[1]], vm.view(-1)[at[1]]]
+    q = W.activation(B, 128, 111).reshape(B, 1, 128)
+    args = (mk, mv, t16(q, dev), *caches, ti32(seq, dev), B, 1, T)
+    first = E.ecco_kv_attend(*args)
+    for _ in range(5):
+        assert torch.equal(first, E.ecco_kv_attend(*args))
+    out = first.cpu().numpy()
+    for b in range(B):
+        m = int(seq[b])
+        ids = pick.reshape(2, B, 1, T)[:, b, :, :m]
+        one = [a.reshape(n, -1)[ids[i // 2].reshape(-1)] for i, a in enumerate((okb, okm, ovb, ovm))]
+        one = [one[0], one[1].reshape(-1), one[2], one[3].reshape(-1)]
+        want = oracle.kv_attend(mk.centroids, mk.code_lens, mv.centroids, mv.code_lens, np.ascontiguousarray(q[b:b + 1]).view(np.uint16), *one, seq[b:b + 1], 1, 1, m)
+        assert_attn_close(oracle, mv, one[2], one[3], seq[b:b + 1], 1, 1, 1, m, out[b:b + 1], want, b)
+
+
 @pytest.mark.parametrize("T_max", [2 ** 31 - 33, 2 ** 31 - 1])
 def test_largest_capacity(dev, oracle, T_max):
     """One cache whose capacity is the largest an int holds (a stride that one sequence and head never multiplies): only the slots of
