@@ -37,18 +37,15 @@ inline Stores self_contained(const void* to, size_t bytes) {
     return !whole_lines(to) || bytes < 4 * kMiB ? Stores::kCached : bytes < 400 * kMiB ? Stores::kThrough : Stores::kPast;
 }
 
-// Activation decoder: from 256 MiB of FP16 on.  Alone / with a plain reader / with a product of 256 columns behind it, into one buffer used again and again:
-// 2097152 groups 72.7 -> 69.4 / 111 -> 114 / 152 -> 144, over several buffers 74.9 -> 63.1 / 115 -> 119 / 154 -> 152, 3145728 113 -> 108 / 194 -> 177 / 233 ->
-// 233; encoded and decoded 157 -> 138 and 236 -> 226, with a writer in front and a plain reader behind, and the encoder's input streamed as well, 286 -> 278 and 460 ->
-// 429.  (A program that only decodes and reads 256 MiB loses 3 %.)  Below, readers lose: one buffer, 262144 11.0 -> 10.2 / 20.0 -> 22.7 / 35.5 -> 40.7, 524288
-// 17.3 -> 17.0 / 29.4 -> 30.3 / 54.4 -> 56.0, 1048576 34.2 -> 31.2 / 56.1 -> 59.2 / 78.5 -> 86.2.
-inline bool activations(const void* to, size_t bytes) { return bytes >= 256 * kMiB && whole_lines(to); }
-
-// Activation encoder's input: from 256 MiB on, so that it does not take the place of the blocks.  Alone / with a writer of the input in front / and a
-// reader of the blocks behind: 2097152 groups 77.9 -> 72.0 / 174 -> 171 / 195 -> 188, 4194304 176 -> 160 / 386 -> 361 / 423 -> 393.  Below, it depends on what is beside it:
-// 524288 21.5 -> 21.3 / 38.5 -> 39.6 / 45.2 -> 46.4; 786432 30.7 -> 30.8 / 69.6 -> 56.6 / 76.9 -> 67.7, but with the decoder and a product behind 92.7 -> 111;
-// 1048576 40.3 -> 39.4 / 89.7 -> 81.6 / 99.0 -> 99.5.
-constexpr bool encoder_input(size_t bytes) { return bytes >= 256 * kMiB; }
+// Activation decoder and the FP16 input of the activation encoder: past the caches from 192 MiB on.  Together they are what the last-level cache would hold little of, and
+// the blocks stay in it.  Ordinary -> past, over several buffers (in brackets into one), decoder with a product of 256 columns behind it / encoder and decoder / with a product
+// behind / with a writer in front and a plain reader behind: 1572864 groups 133 -> 123 (127 -> 116) / 129 -> 99 / 198 -> 172 / 215 -> 206; 2097152 158 -> 154 (160 -> 143) /
+// 156 -> 132 / 237 -> 224 / 286 -> 278; encoder alone 59 -> 56, 78 -> 72, 176 -> 160 for 4194304.  A program that only decodes and reads once over loses: 87 -> 89 (81 -> 88), 115 ->
+// 118 (113 -> 114).  Not taken: 1048576 100 -> 88 (79 -> 88) / 78 -> 69 / 139 -> 122 / 147 -> 138, reader 59 -> 60 (56 -> 59); 700000 64 -> 72 (62 -> 71) / 49 -> 48 / 85 -> 96 /
+// 98 -> 97; 262144 30 -> 34 (34 -> 39) / 23 -> 21 / 40 -> 43 / 38 -> 38.  Written through as the weights are, readers of up to 64 MiB lose 5 to 16 % where one buffer is used again and
+// again, and nothing gains more than 5 %.
+inline bool activations(const void* to, size_t bytes) { return bytes >= 192 * kMiB && whole_lines(to); }
+constexpr bool encoder_input(size_t bytes) { return bytes >= 192 * kMiB; }
 
 // Blocks of the min/max encoder: from 8 to 16 MiB.  Alone / with a plain reader / with the decoder behind it, 16 patterns: 131072 groups 18.5 -> 18.1 / 21.0 -> 20.6 /
 // 30.6 -> 30.2, 262144 32.6 -> 31.7 / 34.9 -> 35.1 / 50.7 -> 50.2; not taken: 65536 11.3 -> 10.9 / 13.4 -> 13.4 / 19.2 -> 19.4, 524288 60.5 -> 60.9 / 63.7 -> 63.8 /

@@ -60,8 +60,8 @@ def test_decoded_values(n, piece, skip):
         assert _same(pb_got[i:e], E.ecco_pb_decode(p, pb_blocks[i:e], _out(e - i, GROUP, 0))), i
 
 
-# 8 MiB of FP16 are 65536 groups of 64, 128 MiB 1048576, 256 MiB 2097152
-@pytest.mark.parametrize("n,piece,skip", [(65535, 60001, 0), (65536, 8192, 0), (65541, 20003, 0), (65541, 20003, 8), (1048579, 65535, 0), (2097152, 1000003, 0), (2097157, 262144, 0), (2097157, 262144, 8)])
+# 8 MiB of FP16 are 65536 groups of 64, 128 MiB 1048576, 192 MiB 1572864, 256 MiB 2097152
+@pytest.mark.parametrize("n,piece,skip", [(65535, 60001, 0), (65536, 8192, 0), (65541, 20003, 0), (65541, 20003, 8), (1048579, 65535, 0), (1572863, 500009, 0), (1572864, 1000003, 0), (2097152, 1000003, 0), (2097157, 262144, 0), (2097157, 262144, 8)])
 def test_activations(n, piece, skip):
     import torch
     import paper_2505_06901_amd as E
