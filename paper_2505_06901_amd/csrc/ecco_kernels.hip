@@ -678,6 +678,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemm_kernel(const uint32_t* __re
         for (int i = tid; i < S * kK / 2; i += kGemvThreads) smem[S * (kPeekEntries + 2 * kK) + i] = dev[D.cent() + i];
     }
     if (lane < kUnitBlocks) wbuf[lane * kStride + kBlockWords] = 0u;
+    if (kLong && lane < 2) wbuf[kUnitBlocks * kStride + lane] = 0u;  // read behind the last slot's zero word, though not used
     const Tables T = table_pointers(smem, S);
     __syncthreads();
 
