@@ -768,19 +768,18 @@ __global__ __launch_bounds__(kGemvThreads) void gemm_kernel(const uint32_t* __re
 }
 
 // ---- single-query attention over compressed K / V ----------------------------------------------------
-// One workgroup per (sequence, head).  The cache of a head is a band of T blocks, so the kernel reuses the streaming scheme of
-// the batch-1 GEMV: a unit is 32 consecutive tokens (2 KB of payload), lane l of a wavefront decodes chain l / 32 of token
-// l % 32, units are prefetched into registers and decoded out of the wavefront's private LDS buffer.  The sequence is walked in
-// spans whose scores fit LDS.  Per span a wavefront takes its units twice.  With the K tables it forms the scores q.K_t / sqrt(128)
-// (the lane keeps the 64 query elements of its chain in registers), which wait in LDS; with the V tables every lane adds p_t * V_t of
-// its chain into 64 private FP32 accumulators (a static register per value position, nothing shared).  The softmax is the wavefront's
-// own: p_t is relative to the largest score of its units, and maxima, denominators and outputs of the wavefronts meet at the end of
-// the span, once.  (A maximum and a denominator common to the workgroup took four more barriers and a loop over the scores
-// between the passes.)  Where both models' tables fit they are built together, and a wavefront passes from K to V on its own;
-// otherwise the V tables replace those of K in between, behind a barrier.  The decoding is bound by the table reads; what is fixed per
-// span (builds, sums, waits at barriers) is what this form cuts.  Append and attention, 8 x 32 sequences and heads, 64 patterns:
-// 4096 tokens 95.4 -> 91.9 us, 512 tokens 26.8 -> 24.7 us; 16 patterns: 4096 tokens 89.5 -> 84.7 us, 512 tokens 22.5 -> 20.5 us.  K and V enter as fp16(centroid * scale), formed two at a time by a packed FP16 multiply, which rounds exactly like the
-// FP32-multiply-then-round rule.
+// One workgroup per (sequence, head).  The cache of a head is a band of T blocks, so the kernel reuses the streaming scheme of the batch-1 GEMV: a
+// unit is 32 consecutive tokens (2 KB of payload), lane l of a wavefront decodes chain l / 32 of token l % 32, units are prefetched into registers
+// and decoded out of the wavefront's private LDS buffer.  The sequence is walked in spans whose scores fit LDS.  Per span a wavefront takes its units
+// twice.  With the K tables it forms the scores q.K_t / sqrt(128) (the lane keeps the 64 query elements of its chain in registers), which wait in
+// LDS; with the V tables every lane adds p_t * V_t of its chain into 64 private FP32 accumulators (a static register per value position, nothing
+// shared).  The softmax is the wavefront's own: p_t is relative to the largest score of its units, and maxima, denominators and outputs of the
+// wavefronts meet at the end of the span, once.  (A maximum and a denominator common to the workgroup took four more barriers and a loop over the
+// scores between the passes.)  Where both models' tables fit they are built together, and a wavefront passes from K to V on its own; otherwise the V
+// tables replace those of K in between, behind a barrier.  The decoding is bound by the table reads; what is fixed per span (builds, sums, waits at
+// barriers) is what this form cuts.  Append and attention, 8 x 32 sequences and heads, 64 patterns: 4096 tokens 95.4 -> 91.9 us, 512 tokens 26.8 ->
+// 24.7 us; 16 patterns: 4096 tokens 89.5 -> 84.7 us, 512 tokens 22.5 -> 20.5 us.  K and V enter as fp16(centroid * scale), formed two at a time by a
+// packed FP16 multiply, which rounds exactly like the FP32-multiply-then-round rule.
 template <bool kLongK, bool kLongV, int kWaves>
 __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(kWaves == 12 ? 3 : 4))) void kv_attend_kernel(
     const uint32_t* __restrict__ dev_k, int Sk, const uint32_t* __restrict__ dev_v, int Sv, const uint16_t* __restrict__ q,
@@ -976,12 +975,11 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(kWa
 }
 
 // ---- grouped-query attention over compressed K / V, split over the tokens ---------------------------------
-// Several query heads share one key/value head (Section 5.3: with grouped-query attention the batched
-// matrix-vector products become small matrix products).  One workgroup per (sequence, key/value head, token range) decodes every K
-// and V block of its range once and serves all grp = Hq / Hkv query heads of the group with it, on the matrix cores, in 16 x 16 tiles (v_mfma_f32_16x16x32_f16): a lane's four accumulator registers per tile
-// leave room for three wavefronts per SIMD, four where workgroups share a compute unit, where 32 x 32 tiles, half of whose columns no group of at most 16 heads can use,
-// left two.
-// A unit is 32 tokens; lane l decodes chain (l / 16) % 2 of token l % 16 + 16 (l / 32).
+// Several query heads share one key/value head (Section 5.3: with grouped-query attention the batched matrix-vector products become small matrix
+// products).  One workgroup per (sequence, key/value head, token range) decodes every K and V block of its range once and serves all grp = Hq / Hkv
+// query heads of the group with it, on the matrix cores, in 16 x 16 tiles (v_mfma_f32_16x16x32_f16): a lane's four accumulator registers per tile
+// leave room for three wavefronts per SIMD, four where workgroups share a compute unit, where 32 x 32 tiles, half of whose columns no group of at
+// most 16 heads can use, left two. A unit is 32 tokens; lane l decodes chain (l / 16) % 2 of token l % 16 + 16 (l / 32).
 //   scores  S[token][head] = sum_dim K[token][dim] q[head][dim]: eight decoded values of a lane are its A operand (row
 //           l % 16, k slice l / 16).  Slices 0 and 1 belong to tokens 0..15, slices 2 and 3 to tokens 16..31; with up to
 //           eight heads, B holds the queries in columns 0..7 for the former and in columns 8..15 for the latter (zeros
@@ -992,14 +990,14 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(kWa
 //           to its private LDS buffer (neighbouring lanes first swap halves so that each writes two tokens of one
 //           dimension), reads it back as an A operand (row = dimension, eight tokens per lane) and multiplies with
 //           the FP16 probabilities; the eight 16 x 16 accumulator tiles (32 registers) live across the spans.
-// The sequence is walked in spans whose scores fit LDS; per span a wavefront takes its units twice, with the K and with the V tables.
-// The softmax is the wavefront's own: scores become FP16 probabilities, relative to the largest score that the wavefront has met, when
-// they are read as B operands (the denominator sums the rounded values), and the accumulators of a lane -- all of one head -- are
-// rescaled from span to span.  Maxima, denominators and outputs of the wavefronts meet once, at the end.  If both models' tables fit
-// they are built once, and that is the only barrier until then (8 x 8 heads in groups of 4, 16 patterns, append, attention and merge:
-// 4096 tokens 34.9 us with a softmax of the workgroup between the passes, 33.3 us so; groups of 8, 1024 tokens 19.1 -> 17.9 us); otherwise the V tables replace the K tables in every span.  With one
-// range per sequence the result is normalised and written; otherwise (maximum, denominator, unnormalised output) of the range go to the
-// caller's workspace and kv_attend_combine_kernel merges them.
+// The sequence is walked in spans whose scores fit LDS; per span a wavefront takes its units twice, with the K and with the V tables. The softmax is
+// the wavefront's own: scores become FP16 probabilities, relative to the largest score that the wavefront has met, when they are read as B operands
+// (the denominator sums the rounded values), and the accumulators of a lane -- all of one head -- are rescaled from span to span.  Maxima,
+// denominators and outputs of the wavefronts meet once, at the end.  If both models' tables fit they are built once, and that is the only barrier
+// until then (8 x 8 heads in groups of 4, 16 patterns, append, attention and merge: 4096 tokens 34.9 us with a softmax of the workgroup between the
+// passes, 33.3 us so; groups of 8, 1024 tokens 19.1 -> 17.9 us); otherwise the V tables replace the K tables in every span.  With one range per
+// sequence the result is normalised and written; otherwise (maximum, denominator, unnormalised output) of the range go to the caller's workspace and
+// kv_attend_combine_kernel merges them.
 
 // grid: (B * Hkv, n_splits).  The partial result of a split and query head is at
 // index (sequence * Hq + query head) * n_splits + split of the workspace: 128 outputs each, then (maximum, denominator) pairs.

@@ -11,7 +11,8 @@ namespace ecco {
 
 constexpr int kStride = kBlockWords + 1;  // LDS words per staged block (last one is a zero pad)
 constexpr int kUnitBlocks = 32;
-constexpr int kUnitWords = kUnitBlocks * kStride + 4;  // private payload buffer of a wavefront, and two words that a chain of whole windows may read (but does not use) behind it
+// private payload buffer of a wavefront, and behind it two words that a chain of whole windows reads, though it does not use them
+constexpr int kUnitWords = kUnitBlocks * kStride + 4;
 constexpr int kLdsWords = 160 * 1024 / 4;              // of a compute unit
 // LDS words of the decode tables: the long-code lists and the centroids are only copied for models that need them
 constexpr int decode_table_words(int S, bool lng) { return S * (kPeekEntries + kK + (lng ? kK + kK / 2 : 0)); }
