@@ -989,10 +989,13 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(kWa
 //           decoded values have to be turned: every 8 values the wavefront writes a 16 dims x 32 tokens FP16 tile
 //           to its private LDS buffer (neighbouring lanes first swap halves so that each writes two tokens of one
 //           dimension), reads it back as an A operand (row = dimension, eight tokens per lane) and multiplies with
-//           the FP16 probabilities; the eight 16 x 16 accumulator tiles (32 registers) live across the spans.
+//           the probabilities; the eight 16 x 16 accumulator tiles (32 registers) live across the spans.
 // The sequence is walked in spans whose scores fit LDS; per span a wavefront takes its units twice, with the K and with the V tables. The softmax is
-// the wavefront's own: scores become FP16 probabilities, relative to the largest score that the wavefront has met, when they are read as B operands
-// (the denominator sums the rounded values), and the accumulators of a lane -- all of one head -- are rescaled from span to span.  Maxima,
+// the wavefront's own: scores become probabilities, relative to the largest score that the wavefront has met, when they are read as B operands,
+// each as two FP16 numbers (the rounded value and the rest, 22 bits together), and the accumulators of a lane -- all of one head -- are rescaled from
+// span to span.  With one FP16 number and a denominator of the rounded values the error against 64 bits followed the number of wavefronts, each of
+// which holds its own largest probability exactly: 8 x 8 heads in groups of 4, 4096 tokens, 2.2e-5 to 3.1e-5 with 12 wavefronts, 2.2e-5 to 3.0e-5 with 16;
+// 4e-7 so, for a second product per tile: 31.7 -> 31.8 us with append and merge.  Maxima,
 // denominators and outputs of the wavefronts meet once, at the end.  If both models' tables fit they are built once, and that is the only barrier
 // until then (8 x 8 heads in groups of 4, 16 patterns, append, attention and merge: 4096 tokens 34.9 us with a softmax of the workgroup between the
 // passes, 33.3 us so; groups of 8, 1024 tokens 19.1 -> 17.9 us); otherwise the V tables replace the K tables in every span.  With one range per
@@ -1183,15 +1186,20 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
                 const Lane L = lane_setup(TV, mw, Sv);
                 const _Float16 sh16 = __builtin_bit_cast(_Float16, (unsigned short)(mw & 0xFFFFu));
                 const half2_t s2 = {sh16, sh16};
-                // B operand: probabilities of head l % 16 for tokens 8 * (l / 16) .. + 7 of the unit; 0 for the tokens past the span
-                half8_t pb;
+                // B operand: probabilities of head l % 16 for tokens 8 * (l / 16) .. + 7 of the unit; 0 for the tokens past the span.
+                // What an FP16 probability leaves of the FP32 one (`rest`) goes through a product of its own.
+                half8_t pb, rest;
                 {
                     const float4_t s[2] = {reinterpret_cast<const float4_t*>(score + u * kUnitBlocks)[0], reinterpret_cast<const float4_t*>(score + u * kUnitBlocks)[1]};
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
-                        pb[i] = n < grp ? (_Float16)__expf(s[i >> 2][i & 3] - base) : (_Float16)0.0f;
-                        run_den += (float)pb[i];
+                        const float p = n < grp ? __expf(s[i >> 2][i & 3] - base) : 0.0f;
+                        pb[i] = (_Float16)p;
+                        rest[i] = (_Float16)(p - (float)pb[i]);
+                        run_den += p;
                     }
+                    // a block without a finite scale: its infinities must meet no rest of 0 or below, which would make NaN of them
+                    if (__ballot((mw & 0x7C00u) == 0x7C00u)) rest = pb;
                 }
                 uint32_t pk[4];
                 decode_chain<kLongV, kHalf>(wbuf + tok * kStride, half ? L.second_start : 0u, L, [&](int i, uint32_t e) {
@@ -1212,6 +1220,7 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
                     wave_lds_fence();
                     const uint4 a0 = *reinterpret_cast<const uint4*>(tile + n * kTileStride + 4 * slice);
                     o[i >> 3] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a0), pb, o[i >> 3], 0, 0, 0);
+                    o[i >> 3] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a0), rest, o[i >> 3], 0, 0, 0);
                 });
             }
         }

@@ -661,6 +661,50 @@ def test_kv_attend_gqa_matches_oracle(dev, oracle, grp, n_splits):
 
 
 # eight wavefronts where twelve would take as many rounds over the units (32 tokens) of a range, twelve otherwise
+@pytest.mark.parametrize("S,Hkv,grp,T,n_splits", [
+    (16, 8, 4, 700, 1),   # 12 wavefronts
+    (16, 2, 1, 31, 1),    # less than one unit
+    (64, 2, 16, 1100, 2), # two products for the scores, several spans, a merge
+])
+def test_gqa_precision(dev, oracle, S, Hkv, grp, T, n_splits):
+    """Against 64 bits over the decoded values.  A probability is carried by two FP16 numbers (22 bits), scores are sums of 128 exact
+    products in 32 bits, off by about sqrt(128) * 2^-24 of |s| < 8, and the errors of different tokens are independent: 2^-18 of the
+    norm is four times their sum.  A single FP16 number per probability, 2^-12 off, exceeds it."""
+    B, Hq = 2, Hkv * grp
+    k, v, mk, mv = _kv_setup(dev, oracle, B, Hkv, T, S)
+    kb, km, _, _ = enc_both(dev, oracle, mk, k); vb, vm, _, _ = enc_both(dev, oracle, mv, v)
+    q = W.activation(B * Hq, 128, 116).reshape(B, Hq, 128)
+    seq = np.array([T, T - T // 5], np.int32)
+    out = E.ecco_kv_attend_gqa(mk, mv, t16(q, dev), kb, km, vb, vm, ti32(seq, dev), B, Hq, Hkv, T, n_splits=n_splits).cpu().numpy()
+    K = E.ecco_decode(mk, kb.view(-1, 64), km.view(-1)).cpu().numpy().astype(np.float64).reshape(B, Hkv, T, 128)
+    V = E.ecco_decode(mv, vb.view(-1, 64), vm.view(-1)).cpu().numpy().astype(np.float64).reshape(B, Hkv, T, 128)
+    s = q.astype(np.float64).reshape(B, Hkv, grp, 128) @ K.transpose(0, 1, 3, 2) / 128 ** 0.5
+    s[np.broadcast_to(np.arange(T) >= seq[:, None, None, None], s.shape)] = -np.inf
+    p = np.exp(s - s.max(-1, keepdims=True))
+    want = ((p / p.sum(-1, keepdims=True)) @ V).reshape(B, Hq, 128)
+    err = np.linalg.norm(out.reshape(B, Hq, 128) - want) / np.linalg.norm(want)
+    assert err < 2.0 ** -18, err
+
+
+@pytest.mark.parametrize("bits", [0x7C00, 0xFC00])
+def test_gqa_infinite_value(dev, oracle, bits):
+    """A V block with an infinite scale: the outputs are infinities of the signs that the plain kernel gives, and NaN where it does
+    (a centroid of 0); the other sequence's outputs are finite."""
+    B, H, T, at = 2, 2, 150, 37
+    k, v, mk, mv = _kv_setup(dev, oracle, B, H, T, 16)
+    kb, km, _, _ = enc_both(dev, oracle, mk, k); vb, vm, _, _ = enc_both(dev, oracle, mv, v)
+    m = vm.view(B, H, T)
+    m[0, 0, at] = (m[0, 0, at] & ~0xFFFF) | bits
+    q = t16(W.activation(B * H, 128, 117).reshape(B, H, 128), dev)
+    seq = ti32(np.array([T, T - 1], np.int32), dev)
+    plain = E.ecco_kv_attend(mk, mv, q, kb, km, vb, vm, seq, B, H, T).cpu().numpy().reshape(B, H, 128)
+    assert np.isinf(plain[0, 0]).any() and np.isfinite(plain[1]).all() and np.isfinite(plain[0, 1]).all()
+    for n_splits in (1, 2):
+        out = E.ecco_kv_attend_gqa(mk, mv, q, kb, km, vb, vm, seq, B, H, H, T, n_splits=n_splits).cpu().numpy().reshape(B, H, 128)
+        for is_kind in (np.isposinf, np.isneginf, np.isnan):
+            assert np.array_equal(is_kind(out), is_kind(plain)), (n_splits, is_kind.__name__)
+
+
 @pytest.mark.parametrize("lengths,T,grp,n_splits", [
     ([1300, 0, 1, 33, 640, 31, 1024, 7], 1300, 2, 4),    # 11 units: twelve; empty, one-token and full sequences side by side
     ([900, 899], 900, 9, 2),                              # 15 units: eight; more than eight heads: two products per unit
