@@ -993,9 +993,10 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(kWa
 // The sequence is walked in spans whose scores fit LDS; per span a wavefront takes its units twice, with the K and with the V tables. The softmax is
 // the wavefront's own: scores become probabilities, relative to the largest score that the wavefront has met, when they are read as B operands,
 // each as two FP16 numbers (the rounded value and the rest, 22 bits together), and the accumulators of a lane -- all of one head -- are rescaled from
-// span to span.  With one FP16 number and a denominator of the rounded values the error against 64 bits followed the number of wavefronts, each of
-// which holds its own largest probability exactly: 8 x 8 heads in groups of 4, 4096 tokens, 2.2e-5 to 3.1e-5 with 12 wavefronts, 2.2e-5 to 3.0e-5 with 16;
-// 4e-7 so, for a second product per tile: 31.7 -> 31.8 us with append and merge.  Maxima,
+// span to span.  Up to eight heads leave columns 8..15 of the product free for the rests, more take a second product.  (With one FP16 number and a
+// denominator of the rounded values the error against 64 bits followed the number of wavefronts, each of which holds its own largest probability
+// exactly: 8 x 8 heads in groups of 4, 4096 tokens, 2.2e-5 to 3.1e-5 with 12 wavefronts, 2.2e-5 to 3.0e-5 with 16; 4e-7 to 5e-7 so. With append and
+// merge 31.7 us either way; a second product there 31.8 us, and 1 to 3 % at short ranges.)  Maxima,
 // denominators and outputs of the wavefronts meet once, at the end.  If both models' tables fit they are built once, and that is the only barrier
 // until then (8 x 8 heads in groups of 4, 16 patterns, append, attention and merge: 4096 tokens 34.9 us with a softmax of the workgroup between the
 // passes, 33.3 us so; groups of 8, 1024 tokens 19.1 -> 17.9 us); otherwise the V tables replace the K tables in every span.  With one range per
@@ -1178,7 +1179,8 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
 #pragma unroll
                 for (int j = 0; j < 8; ++j) o[j] *= alpha;
             }
-            const float* score = scores + min(n, grp - 1) * sstride + 8 * slice;
+            const int head = kWide ? n : n & 7;
+            const float* score = scores + min(head, grp - 1) * sstride + 8 * slice;
             for (; u < units; u += kWaves) {
                 store_unit(wbuf, pre, lane);
                 const uint32_t mw = (u * kUnitBlocks + tok < span) ? pre.meta : (pre.meta & 0xFFFF0000u);
@@ -1186,20 +1188,22 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
                 const Lane L = lane_setup(TV, mw, Sv);
                 const _Float16 sh16 = __builtin_bit_cast(_Float16, (unsigned short)(mw & 0xFFFFu));
                 const half2_t s2 = {sh16, sh16};
-                // B operand: probabilities of head l % 16 for tokens 8 * (l / 16) .. + 7 of the unit; 0 for the tokens past the span.
-                // What an FP16 probability leaves of the FP32 one (`rest`) goes through a product of its own.
+                // B operand: probabilities of head l % 16 for tokens 8 * (l / 16) .. + 7 of the unit; 0 for the tokens past the span. What an
+                // FP16 probability leaves of the FP32 one is the operand of a product of its own, or with up to eight heads of columns 8..15.
+                // (A block without a finite scale: its infinities must meet no rest of 0 or below, which would make NaN of them.)
+                const bool no_rest = __ballot((mw & 0x7C00u) == 0x7C00u) != 0;
+                const float taken = no_rest || (!kWide && n < 8) ? 0.0f : 1.0f;
                 half8_t pb, rest;
                 {
                     const float4_t s[2] = {reinterpret_cast<const float4_t*>(score + u * kUnitBlocks)[0], reinterpret_cast<const float4_t*>(score + u * kUnitBlocks)[1]};
 #pragma unroll
                     for (int i = 0; i < 8; ++i) {
-                        const float p = n < grp ? __expf(s[i >> 2][i & 3] - base) : 0.0f;
+                        const float p = head < grp ? __expf(s[i >> 2][i & 3] - base) : 0.0f;
                         pb[i] = (_Float16)p;
-                        rest[i] = (_Float16)(p - (float)pb[i]);
+                        rest[i] = (_Float16)fmaf(-taken, (float)pb[i], p);
                         run_den += p;
                     }
-                    // a block without a finite scale: its infinities must meet no rest of 0 or below, which would make NaN of them
-                    if (__ballot((mw & 0x7C00u) == 0x7C00u)) rest = pb;
+                    if (!kWide) pb = rest;
                 }
                 uint32_t pk[4];
                 decode_chain<kLongV, kHalf>(wbuf + tok * kStride, half ? L.second_start : 0u, L, [&](int i, uint32_t e) {
@@ -1220,7 +1224,7 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
                     wave_lds_fence();
                     const uint4 a0 = *reinterpret_cast<const uint4*>(tile + n * kTileStride + 4 * slice);
                     o[i >> 3] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a0), pb, o[i >> 3], 0, 0, 0);
-                    o[i >> 3] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a0), rest, o[i >> 3], 0, 0, 0);
+                    if (kWide) o[i >> 3] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a0), rest, o[i >> 3], 0, 0, 0);
                 });
             }
         }
@@ -1241,6 +1245,16 @@ __global__ __launch_bounds__(kWaves * 64) void kv_attend_gqa_kernel(GqaArgs args
     const float mine = run_max == -INFINITY ? 0.0f : __expf(run_max - most);
     if (lane < 16) state[(kWaves + wave) * kGqaMaxGroup + lane] = run_den * mine;
     float* red = reinterpret_cast<float*>(k_tables);  // [wavefront][8 tiles][4 slices][16 lanes][4]
+    if (!kWide) {  // what the rests contributed
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float here = o[j][i];
+                o[j][i] = here + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, here), 0x128, 0xF, 0xF, true));  // row_ror:8
+            }
+        }
+    }
 #pragma unroll
     for (int j = 0; j < 8; ++j) *reinterpret_cast<float4_t*>(red + (wave * 8 + j) * kRedTile + slice * kRedRow + n * 4) = o[j] * mine;
     __syncthreads();
